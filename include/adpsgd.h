@@ -312,7 +312,7 @@ const char* adpsgd_last_error(void);
  * bias (fp32 [N], or NULL) is added to every row.  Strides are in elements.
  * All pointers: device.  M, N, K >= 1; groups in 1..128; lda, ldb and the group
  * strides must be multiples of 4.  tile_config: -1 = automatic choice, or one of the
- * tile configurations 0, 5, 11, 12, 13 of csrc/gemm.hip (a configuration whose
+ * tile configurations 0, 5, 11 .. 15 of csrc/gemm.hip (a configuration whose
  * alignment rules the operands do not meet falls back to one that fits).        */
 int adpsgd_gemm(int precision, int a_kmajor, int b_kmajor, int c_is_elem,
                 int M, int N, int K,

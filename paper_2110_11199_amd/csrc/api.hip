@@ -1115,8 +1115,8 @@ int adpsgd_set_tuning(adpsgd_t h, int key, int value) {
     if (!h) return fail(ADPSGD_EINVAL, "NULL handle");
     switch (key) {
         case ADPSGD_TUNE_GEMM_TILE:
-            if (value != -1 && value != 0 && value != 5 && (value < 11 || value > 13))
-                return fail(ADPSGD_EINVAL, "GEMM tile configuration must be -1, 0, 5, 11, 12 or 13");
+            if (value != -1 && value != 0 && value != 5 && (value < 11 || value > 15))
+                return fail(ADPSGD_EINVAL, "GEMM tile configuration must be -1, 0, 5 or 11 .. 15");
             h->tune_gemm_tile = value; return ADPSGD_OK;
         case ADPSGD_TUNE_REC_DIRECT:
             if (value != 0 && value != 1) return fail(ADPSGD_EINVAL, "0 or 1");

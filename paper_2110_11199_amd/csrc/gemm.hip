@@ -1,22 +1,31 @@
 // Grouped MFMA GEMM kernels: the time-batched GEMMs of the LSTM gradient
 // (input projections, output layers, weight gradients, input gradients).
 //
-// Five tile configurations are built; 11-13 bring their operands in by direct global->LDS loads (no staging
+// Seven tile configurations are built; 11-15 bring their operands in by direct global->LDS loads (no staging
 // registers, no LDS store instructions), transpose an operand that is not K-contiguous (dW = dA' X, dX = dA W)
-// on the LDS read, and run a main loop that is software-pipelined by hand (GemmDma::run_deep); they need bf16,
-// 16-byte aligned rows and K a multiple of 64:
+// on the LDS read, and run a main loop that is software-pipelined by hand (GemmDma::run_deep); they need
+// 16-byte aligned rows and whole 16-byte chunks of K where an operand is K-contiguous:
 //   12  256x256 tile on 4 waves (128x128 each, one wave per SIMD, accumulators in AGPRs), three 64-byte K
-//       stages.  Problems with a rows-contiguous operand (dW, dX).
+//       stages.  Large bf16 problems with a rows-contiguous operand (dW, dX).
 //   11  the same with two 128-byte stages: when both operands are K-contiguous (input projections) their rows
 //       are fetched in whole 128-byte lines, which 64-byte stages split in two requests (measured inside the
 //       training step: 1.40 against 1.48 ms per input projection, and the reverse, 1.32 against 1.25 ms, for dX).
 //   13  128x256 tile on 4 waves (64x128 each), three 64-byte stages, two workgroups per CU: K-contiguous
 //       operands with K < 512 or a narrow output (output layer, layer-0 input projection), whose tiles spend
 //       as long storing as computing; the second workgroup's loop runs during the first one's epilogue.
+//   14  128x128 tile on 4 waves (64x64 each), two 128-byte stages (bf16) or three 64-byte ones (fp32).
+//   15  64x64 tile on 4 waves (32x32 each), three 128-byte stages (bf16) or four 64-byte ones (fp32).
+//       14 and 15 are for problems with too few 256x256 tiles for the 256 CUs, and for fp32 operands.  A small problem
+//       is bound by the latency of its K loop (a 64x64 tile alone on its CU takes 5 ns per k in bf16, a 128x128 one 13)
+//       and by how evenly its tiles cover the CUs, not by operand bytes per flop.  Against the register-staged
+//       kernel 0, us: fp32 (matrix-pipe bound) 672x512x2048x8 217 -> 97, 2000x320x1280x6 234 -> 86, 2688x4096x1024x8
+//       1422 -> 1232 (146 TFLOP/s); bf16 336x256x1024x8 30.8 -> 8.4, 1050x720x2880x5 91 -> 38, 1050x120x3000x5 81 -> 18.
 //   5   256x256 tile on 8 waves (128x64 each) staged through registers, the transposition done between
-//       the registers and LDS.  Large bf16 problems that miss the conditions of 11-13 (ragged K, 8-byte rows).
+//       the registers and LDS.  Large bf16 problems that miss the conditions of 11-15.
 //   0   128x128 tile, 4 waves (64x64 each), 64-byte stages, staged through registers.  Small
-//       problems and fp32 operands.
+//       problems that miss them.
+// K need not be a multiple of a stage (GemmDma::run_tail): 1344x1024x9000x16, bf16, 692 us on kernel 5, 486 on 13;
+// 5120x1280x2016x8 354 -> 204.
 // A 256x256 tile needs half the operand bytes per flop of a 128x128 one.
 #include <type_traits>
 #include "gemm_core.hpp"
@@ -211,7 +220,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_kernel(GemmDesc p) {
 // Same tile bookkeeping with the direct-to-LDS main loop (16-byte aligned operands, K a multiple of
 // the stage length).
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
-__global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4 && FM * FN == 8) ? 2 : 1) void gemm_dma_kernel(GemmDesc p) {
+__global__ __launch_bounds__(64 * WM * WN, FM * FN <= 4 ? 3 : FM * FN == 8 ? 2 : 1) void gemm_dma_kernel(GemmDesc p) {
     typedef typename std::conditional<AKC, KcSrc<T>, McSrc<T>>::type ASrc;
     typedef typename std::conditional<BKC, KcSrc<T>, McSrc<T>>::type BSrc;
     typedef GemmDma<T, ASrc, BSrc, WM, WN, FM, FN, SB, NS> Core;
@@ -225,19 +234,19 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4 && FM * FN == 8) ? 2 : 
     const T* A = (const T*)p.A + gi * p.sAi + gd * p.sAd;
     const T* B = (const T*)p.B + gi * p.sBi + gd * p.sBd;
     ASrc a; BSrc b;
-    // A rows-contiguous operand is loaded in chunks of 8 rows: its row count is rounded up (its k-rows
+    // A rows-contiguous operand is loaded in 16-byte chunks of rows: its row count is rounded up (its k-rows
     // are ld >= that many elements long, so the extra rows are readable; their products are never stored).
-    if constexpr (AKC) { a.base = A + (int64_t)m0 * p.lda; a.R = p.M - m0; } else { a.base = A + m0; a.R = (p.M - m0 + 7) & ~7; }
+    constexpr int EPC = 16 / (int)sizeof(T);
+    if constexpr (AKC) { a.base = A + (int64_t)m0 * p.lda; a.R = p.M - m0; } else { a.base = A + m0; a.R = (p.M - m0 + EPC - 1) & ~(EPC - 1); }
     a.ld = p.lda;
-    if constexpr (BKC) { b.base = B + (int64_t)n0 * p.ldb; b.R = p.N - n0; } else { b.base = B + n0; b.R = (p.N - n0 + 7) & ~7; }
+    if constexpr (BKC) { b.base = B + (int64_t)n0 * p.ldb; b.R = p.N - n0; } else { b.base = B + n0; b.R = (p.N - n0 + EPC - 1) & ~(EPC - 1); }
     b.ld = p.ldb;
 
     float bias[FN];
     load_bias<Core, FN>(bias, p, n0, gi, gd);
     f32x16_t acc[FM][FN];
     zero_tile<FM, FN>(acc);
-    if constexpr (WM * WN == 4 && (FM * FN == 16 || FM * FN == 8)) Core::run_deep(acc, a, b, p.K, lds);
-    else Core::run(acc, a, b, p.K, lds);
+    Core::run_deep(acc, a, b, p.K, lds);
     if (m0 + Core::BM <= p.M && n0 + Core::BN <= p.N && p.ldc < (1 << 26)) store_tile_interior<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
     else store_tile<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
 }
@@ -287,21 +296,41 @@ static bool aligned_to(const void* p, int64_t ld, int64_t s1, int64_t s2, int es
            ((s2 * esz) % bytes == 0);
 }
 
+// Time estimate of covering the problem with bm x bn tiles, for the choice between the smaller tiles: a CU works
+// through its tiles at `rate` ns per k and tile, but a tile that has the CU to itself takes `latency` ns per k (its loads are not
+// hidden by a second workgroup's MFMAs).
+static double tile_time(const GemmDesc& d, int bm, int bn, double rate, double latency) {
+    const int64_t tiles = (int64_t)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.groupsI * d.groupsD;
+    const double rounds = (double)((tiles + 255) / 256);
+    return (rounds * rate > latency ? rounds * rate : latency) * d.K;
+}
+
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     if (d.M < 1 || d.N < 1 || d.K < 1 || d.groupsI < 1 || d.groupsI > 128 || d.groupsD < 1) return hipErrorInvalidValue;
-    if (d.tile != -1 && d.tile != 0 && d.tile != 5 && (d.tile < 11 || d.tile > 13)) return hipErrorInvalidValue;
-    // one-dimensional grid over all tiles of all groups (smallest tile 128 x 128)
-    if ((int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * d.groupsI * d.groupsD > 0x7fffffff) return hipErrorInvalidValue;
-    const int esz = d.precision ? 2 : 4;
+    if (d.tile != -1 && d.tile != 0 && d.tile != 5 && (d.tile < 11 || d.tile > 15)) return hipErrorInvalidValue;
+    // one-dimensional grid over all tiles of all groups (smallest tile 64 x 64)
+    if ((int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD > 0x7fffffff) return hipErrorInvalidValue;
+    const int esz = d.precision ? 2 : 4, epc = 16 / esz;
     const int quad = 4 * esz;    // every operand must allow loads of 4 elements
     if (!aligned_to(d.A, d.lda, d.sAi, d.sAd, esz, quad) || !aligned_to(d.B, d.ldb, d.sBi, d.sBd, esz, quad))
         return hipErrorInvalidValue;
-    if (d.precision == 0) return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
-    bool wide = true;
-    if (d.a_kc && !aligned_to(d.A, d.lda, d.sAi, d.sAd, esz, 16)) wide = false;
-    if (d.b_kc && !aligned_to(d.B, d.ldb, d.sBi, d.sBd, esz, 16)) wide = false;
-    if (!wide) return launch_layout<bf16_t, 2, 2, 2, 2, 8, 64>(d, s);
+    // Direct-to-LDS loads need 16-byte aligned rows, whole 16-byte chunks along the contiguous dimension (of K, or of
+    // rows: the k-rows must be at least round_up(rows, chunk) long), and per-lane load offsets inside a tile that fit
+    // 32 bits (row strides below 2^22 elements).
+    const bool wide_a = aligned_to(d.A, d.lda, d.sAi, d.sAd, esz, 16), wide_b = aligned_to(d.B, d.ldb, d.sBi, d.sBd, esz, 16);
+    const bool dma = d.lda < (1 << 22) && d.ldb < (1 << 22) && wide_a && wide_b &&
+                     (d.a_kc ? d.K % epc == 0 : d.lda >= (d.M + epc - 1) / epc * epc) &&
+                     (d.b_kc ? d.K % epc == 0 : d.ldb >= (d.N + epc - 1) / epc * epc);
     int v = d.tile;
+    if (d.precision == 0) {
+        // fp32 tiles are bound by the matrix pipe (256 flop per clock and CU) in either size: what decides is how evenly
+        // the tiles cover the CUs
+        if (v < 0) v = !dma ? 0 : tile_time(d, 64, 64, 14.0, 20.0) < tile_time(d, 128, 128, 53.0, 60.0) ? 15 : 14;
+        if (v == 15 && dma) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
+        if (v >= 11 && dma) return launch_dma<float, 2, 2, 2, 2, 64, 3>(d, s);
+        return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
+    }
+    if ((d.a_kc && !wide_a) || (d.b_kc && !wide_b)) return launch_layout<bf16_t, 2, 2, 2, 2, 8, 64>(d, s);
     if (v < 0) {
         // 256x256 tiles once there are enough of them to fill the 256 CUs
         const int64_t big_tiles = (int64_t)((d.M + 255) / 256) * ((d.N + 255) / 256) * d.groupsI * d.groupsD;
@@ -312,18 +341,17 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
         // which move half the operand bytes per flop.
         const bool short_k = d.K <= 1536;
         const bool ragged_m = (int64_t)(((d.M + 255) / 256) * 256 - d.M) * 10 >= d.M;
-        v = big_tiles < 128 ? 0 : (short_k || ragged_m) ? 13 : !(d.a_kc && d.b_kc) ? 12 : (d.M >= 512 && d.N >= 512) ? 11 : 13;
+        if (big_tiles < 128 && dma) {
+            const double t64 = tile_time(d, 64, 64, 3.7, 5.0), t128 = tile_time(d, 128, 128, 8.0, 13.0), t256 = tile_time(d, 128, 256, 14.5, 14.5);
+            v = t64 <= t128 && t64 <= t256 ? 15 : t128 <= t256 ? 14 : 13;
+        } else v = big_tiles < 128 ? 0 : (short_k || ragged_m) ? 13 : !(d.a_kc && d.b_kc) ? 12 : (d.M >= 512 && d.N >= 512) ? 11 : 13;
     }
-    // direct-to-LDS loads need whole stages and, for a rows-contiguous operand, whole 16-byte chunks of rows
-    // (16-byte aligned k-rows of a rows-contiguous operand must be at least round_up(rows, 8) long)
-    // (the per-lane load offsets inside a tile are 32-bit: row strides below 2^22 elements)
-    const bool dma = d.K % 64 == 0 && d.lda < (1 << 22) && d.ldb < (1 << 22) && aligned_to(d.A, d.lda, d.sAi, d.sAd, esz, 16) &&
-                     aligned_to(d.B, d.ldb, d.sBi, d.sBd, esz, 16) &&
-                     (d.a_kc || d.lda >= ((d.M + 7) & ~7)) && (d.b_kc || d.ldb >= ((d.N + 7) & ~7));
+    if (v == 15 && dma) return launch_dma<bf16_t, 2, 2, 1, 1, 128, 3>(d, s);
+    if (v == 14 && dma) return launch_dma<bf16_t, 2, 2, 2, 2, 128, 2>(d, s);
     if (v == 13 && dma) return launch_dma<bf16_t, 2, 2, 2, 4, 64, 3>(d, s);
     if (v == 12 && dma) return launch_dma<bf16_t, 2, 2, 4, 4, 64, 3>(d, s);
     if (v == 11 && dma) return launch_dma<bf16_t, 2, 2, 4, 4, 128, 2>(d, s);
-    if (v >= 5) return launch_layout<bf16_t, 2, 4, 4, 2, 16, 128>(d, s);
+    if (v >= 5 && v < 14) return launch_layout<bf16_t, 2, 4, 4, 2, 16, 128>(d, s);
     return launch_layout<bf16_t, 2, 2, 2, 2, 16, 64>(d, s);
 }
 

@@ -65,10 +65,11 @@ template <typename T> struct McSrc {  // element (r,k) at base[k*ld + r], r < R
     static constexpr bool kc = false;
     const T* base; int64_t ld; int R;
     __device__ bool full(int rows) const { return R >= rows; }
-    // 8 consecutive rows r = 8*chunk.. of k-row k (R a multiple of 8); chunks past the end repeat the last one
+    // the 16 bytes of consecutive rows r = EPC*chunk.. of k-row k (R a multiple of EPC); chunks past the end repeat the last one
     __device__ int64_t chunk_offset_clamped(int k, int chunk) const {      // elements from base
-        const int last = (R >> 3) - 1;
-        return (int64_t)k * ld + 8 * (chunk < last ? chunk : last);
+        constexpr int EPC = 16 / (int)sizeof(T);
+        const int last = R / EPC - 1;
+        return (int64_t)k * ld + EPC * (chunk < last ? chunk : last);
     }
 };
 

@@ -2,10 +2,12 @@
 // no staging registers, no LDS store instructions, NS LDS stages in flight.
 //
 // Same contract as GemmCore (gemm_core.hpp): C[m][n] = sum_k A(m,k) B(n,k) for a
-// (32*FM*WM) x (32*FN*WN) workgroup tile, K a multiple of the stage length, operand rows
-// 16-byte aligned.  Rows past the end of an operand are clamped to its last row (their
-// products land in accumulator rows/columns the caller discards), so no guard and no zero
-// fill is needed.
+// (32*FM*WM) x (32*FN*WN) workgroup tile, operand rows 16-byte aligned, K a multiple of 16
+// bytes where an operand is K-contiguous.  Rows past the end of an operand are clamped to its
+// last row (their products land in accumulator rows/columns the caller discards), so no guard
+// and no zero fill is needed.  The part of K past the last whole stage is one more stage whose
+// loads are clamped the same way along K and whose fragments are zeroed past K in registers
+// (run_tail).
 //
 // A wave-wide direct load writes lane l's 16 bytes to LDS at base + 16*l, i.e. 1 KB
 // contiguous per instruction.  A tile is therefore stored row-major WITHOUT padding
@@ -14,14 +16,15 @@
 // swz(r) = (r / (256/SB)) mod (SB/16), so that any 16 rows read at one chunk index hit 16
 // different 16-byte bank groups.
 //
-// An operand stored rows-contiguous ("mc": element (r,k) at base[k*ld + r], bf16 only) is copied as
-// it lies in memory, k-row by k-row (tile = [KT][ROWS], ROWS*2 bytes per k-row), and transposed
-// on the LDS read: ds_read_b64_tr_b16 hands lane i of a 16-lane group the four 16-bit values that
+// An operand stored rows-contiguous ("mc": element (r,k) at base[k*ld + r]) is copied as
+// it lies in memory, k-row by k-row (tile = [KT][ROWS]).  fp32: a fragment is four 4-byte reads, one per
+// k, each 32 consecutive rows wide.  bf16: the tile is transposed on the LDS read: ds_read_b64_tr_b16 hands lane i of a 16-lane group the four 16-bit values that
 // lanes 4c + i/4 (c = 0..3) of the group address at position i%4.  With lane 4c+q addressing
 // (k0+c, r0+4q..r0+4q+3), lane i receives (k0..k0+3, r0+i): four consecutive k of its own row, so
 // two such reads give the same 8-k fragment as one 16-byte read of a K-contiguous tile.  The 16-byte
 // slot s of k-row k holds chunk s ^ 4*(k mod 4) of that row: the 32 lanes served in one LDS
-// cycle (4 k-rows x 64 bytes, twice) then cover all 64 banks once.
+// cycle (4 k-rows x 64 bytes, twice) then cover all 64 banks once.  (k-rows of 64 elements, two of which
+// share the 64 banks: chunk s ^ 4*(k/2 mod 2).)
 #pragma once
 #include <type_traits>
 #include "gemm_core.hpp"
@@ -59,26 +62,34 @@ struct GemmDma {
     static constexpr int LDS_BYTES = NS * STAGE_BYTES;
     static constexpr int LA = BM * CPR / NT, LB = BN * CPR / NT;   // loads per thread per stage
     static_assert((BM * CPR) % NT == 0 && (BN * CPR) % NT == 0, "tile must divide over the workgroup");
-    static_assert((ASrc::kc && BSrc::kc) || sizeof(T) == 2, "transposing LDS reads exist for 16-bit operands only");
+    static constexpr int EPC = 16 / (int)sizeof(T);           // elements per 16-byte chunk
+
+    // slot swizzle of k-row k of a rows-contiguous tile
+    template <int ROWS> __device__ static int mc_swz(int krow) {
+        if constexpr (sizeof(T) == 4) return 0;
+        else if constexpr (ROWS % 128 == 0) return 4 * (krow & 3);
+        else { static_assert(ROWS == 64, "k-rows of 64 or a multiple of 128 elements"); return 4 * ((krow >> 1) & 1); }
+    }
 
     // Byte offsets, relative to the operand's stage base, of the L 16-byte chunks this lane loads per stage.
+    // kvalid: k of the stage that exist; what lies past them is read from the last valid chunk or k-row instead.
     template <int ROWS, int L, class Src>
-    __device__ static void lane_offsets(const Src& src, int tid, uint32_t (&off)[L]) {
+    __device__ static void lane_offsets(const Src& src, int tid, uint32_t (&off)[L], int kvalid = KT) {
 #pragma unroll
         for (int j = 0; j < L; ++j) {
             const int c = tid + j * NT;
             if constexpr (Src::kc) {
                 const int row = c / CPR;
                 const int slot = c % CPR;
-                const int chunk = slot ^ swz_<SB>(row);
+                int chunk = slot ^ swz_<SB>(row);
+                chunk = chunk < kvalid / EPC ? chunk : kvalid / EPC - 1;
                 off[j] = (uint32_t)(src.row_offset_clamped(row) * (int64_t)sizeof(T)) + (uint32_t)chunk * 16u;
             } else {
-                constexpr int CPK = ROWS / 8;                 // 16-byte chunks per k-row
-                static_assert(ROWS % 128 == 0, "the chunk swizzle needs k-rows of a multiple of 16 chunks");
+                constexpr int CPK = ROWS / EPC;               // 16-byte chunks per k-row
                 const int krow = c / CPK;
                 const int slot = c % CPK;
-                const int chunk = slot ^ (4 * (krow & 3));
-                off[j] = (uint32_t)(src.chunk_offset_clamped(krow, chunk) * (int64_t)sizeof(T));
+                const int chunk = slot ^ mc_swz<ROWS>(krow);
+                off[j] = (uint32_t)(src.chunk_offset_clamped(krow < kvalid ? krow : kvalid - 1, chunk) * (int64_t)sizeof(T));
             }
         }
     }
@@ -92,16 +103,19 @@ struct GemmDma {
         for (int j = 0; j < L; ++j) dma16_(off[j], sbase, dst0 + (uint32_t)(j * NT) * 16u);
     }
 
-    // 16-byte MFMA fragment of tile row `row0 + lane%32`, k-chunk `ch` (8 consecutive k) of the stage.
+    // 16-byte MFMA fragment of tile row `row0 + lane%32`, k-chunk `ch` (EPC consecutive k) of the stage.
     template <int ROWS, bool KC>
     __device__ static uint4 frag(const char* tile, int row0, int ch, int lane) {
         if constexpr (KC) {
             const int row = row0 + (lane & 31);
             return *(const uint4*)(tile + row * SB + ((ch ^ swz_<SB>(row)) * 16));
+        } else if constexpr (sizeof(T) == 4) {
+            const uint32_t* p = (const uint32_t*)tile + ch * 4 * ROWS + row0 + (lane & 31);
+            return make_uint4(p[0], p[ROWS], p[2 * ROWS], p[3 * ROWS]);
         } else {
             const int j = lane & 15, c = j >> 2, q = j & 3;
             const int r = row0 + (lane & 16) + 4 * q;         // first of the 4 rows this lane addresses
-            const char* p = tile + (ch * 8 + c) * (ROWS * 2) + (((r >> 3) ^ (4 * c)) * 16) + (r & 7) * 2;
+            const char* p = tile + (ch * 8 + c) * (ROWS * 2) + (((r >> 3) ^ mc_swz<ROWS>(c)) * 16) + (r & 7) * 2;
             const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p);
             const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p + 4 * (ROWS * 2)));
             const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
@@ -114,7 +128,51 @@ struct GemmDma {
         asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
     }
 
-    // K must be a multiple of KT (checked by the host).  acc must be initialised.
+    // fragment of k-chunk ch with everything from k = kvalid of the stage on set to zero
+    __device__ static uint4 zero_past(uint4 v, int ch, int kvalid) {
+        const int n = kvalid - ch * EPC;                       // valid elements of the fragment
+        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (sizeof(T) == 4) w[i] = i < n ? w[i] : 0u;
+            else w[i] &= (2 * i < n ? 0xffffu : 0u) | (2 * i + 1 < n ? 0xffff0000u : 0u);
+        }
+        return make_uint4(w[0], w[1], w[2], w[3]);
+    }
+
+    // The k past the last whole stage, after the main loop: one stage loaded with clamped addresses into the first
+    // stage buffer, both operands zeroed past K.  One load latency and one stage of work per tile, against a second
+    // launch or the register-staged kernels for every K that is not a multiple of the stage.
+    __device__ static void run_tail(f32x16_t (&acc)[FM][FN], const ASrc& a, const BSrc& b, int K, char* lds) {
+        const int k0 = K / KT * KT, rem = K - k0;
+        if (rem == 0) return;
+        const int tid = threadIdx.x;
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wave_m = wave / WN, wave_n = wave % WN;
+        uint32_t aoff[LA], boff[LB];
+        lane_offsets<BM, LA>(a, tid, aoff, rem);
+        lane_offsets<BN, LB>(b, tid, boff, rem);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();                          // every wave has its last fragments in registers
+        issue<LA>(a, aoff, k0, lds, wave);
+        issue<LB>(b, boff, k0, lds + A_BYTES, wave);
+        wait_vm<0>();
+        __builtin_amdgcn_s_barrier();
+        for (int c = 0; c * 2 * EPC < rem; ++c) {
+            const int ch = 2 * c + (lane >> 5);
+            uint4 af[FM], bfr[FN];
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm) af[fm] = zero_past(frag<BM, ASrc::kc>(lds, (wave_m * FM + fm) * 32, ch, lane), ch, rem);
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn) bfr[fn] = zero_past(frag<BN, BSrc::kc>(lds + A_BYTES, (wave_n * FN + fn) * 32, ch, lane), ch, rem);
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+                for (int fn = 0; fn < FN; ++fn) mma_chunk<T>(acc[fm][fn], af[fm], bfr[fn]);
+        }
+    }
+
+    // acc must be initialised.
     // rot (0 <= rot < K/KT) rotates the order in which the K stages are consumed: stage s reads
     // k-block (s + rot) mod nk.  Workgroups that would otherwise walk K in lockstep (same column
     // offset of every row at the same time, i.e. the same few memory channels) are given
@@ -166,6 +224,7 @@ struct GemmDma {
                     for (int fn = 0; fn < FN; ++fn) mma_chunk<T>(acc[fm][fn], af[fm], bfr[fn]);
             }
         }
+        run_tail(acc, a, b, K, lds);
     }
 
     // One fragment of k-chunk C for run_deep: fragment index F counts a0, b0, a1, b1, ... (A and B alternate
@@ -282,6 +341,7 @@ struct GemmDma {
         const int wave_m = wave / WN, wave_n = wave % WN;
         const int g = lane >> 5;
         const int nk = K / KT;
+        if (nk == 0) { run_tail(acc, a, b, K, lds); return; }
         uint32_t aoff[LA], boff[LB];
         lane_offsets<BM, LA>(a, tid, aoff);
         lane_offsets<BN, LB>(b, tid, boff);
@@ -317,6 +377,7 @@ struct GemmDma {
             buf = next_buf(buf);
         }
         deep_stage<false, false, 0>(acc, a, b, aoff, boff, lds + buf * STAGE_BYTES, lds, 0, wave, wave_m, wave_n, g, lane, af, bfr);
+        run_tail(acc, a, b, K, lds);
     }
 
     __device__ static int acc_row(int fm, int i) {

@@ -25,7 +25,7 @@ struct GemmDesc {
     void* C; int64_t ldc, sCi, sCd;
     const float* bias; int64_t sBiasI, sBiasD;
     int groupsI, groupsD;
-    int tile;                 // tile configuration (see gemm.hip): -1 automatic, or 0, 5, 11, 12, 13
+    int tile;                 // tile configuration (see gemm.hip): -1 automatic, or 0, 5, 11 .. 15
     LearnerMap lmap;
 };
 // Returns hipSuccess, or hipErrorInvalidValue when the operands do not meet the

@@ -112,3 +112,18 @@ def test_gemm_rejects_misaligned_rows():
             Bd.adpsgd_gemm(0, 1, 1, 0, 8, 8, 8, t.data_ptr(), 8, 0, t.data_ptr(), 8, 0, t.data_ptr(), 8, 0, None, 0, groups, None,
                            tile_config=bad_tile)
         assert ei.value.code == Bd.EINVAL
+
+
+@pytest.mark.parametrize("prec,tile", [(0, 14), (0, 15), (1, 11), (1, 12), (1, 13), (1, 14), (1, 15)])
+@pytest.mark.parametrize("a_k,b_k", LAYOUTS)
+@pytest.mark.parametrize("M,N,K", [(64, 128, 8), (68, 60, 72), (300, 264, 200), (132, 520, 333), (129, 65, 61), (72, 72, 1)])
+def test_gemm_k_past_the_last_whole_stage(prec, tile, a_k, b_k, M, N, K):
+    # the part of K past the last 32- or 64-element stage (alone, after one stage, after several), one element to a
+    # whole stage less one; K-contiguous operands need whole 16-byte chunks of K, the others take any K
+    epc = 8 if prec else 4
+    if a_k or b_k:
+        K = (K + epc - 1) // epc * epc
+    print("gemm K tail", prec, tile, a_k, b_k, M, N, K, flush=True)
+    lda_pad = 8 if K % 8 == 0 else 4
+    assert _run(prec, a_k, b_k, 0, M, N, K, 3, True, pad=lda_pad, tile=tile) < 2e-6
+    assert _run(prec, a_k, b_k, 1, M, N, K, 2, False, tile=tile) < (6e-3 if prec else 2e-6)
