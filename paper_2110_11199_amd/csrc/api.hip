@@ -325,7 +325,7 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->dy = (float*)w.take(L * M * DH * 4);
         h->da = w.take(L * M * G4 * e);
         h->dc = (float*)w.take(L * (size_t)h->B * DH * 4);
-        h->dbp = (float*)w.take(L * (size_t)h->T * rec_backward_batch_tiles(h->B) * G4 * 4);
+        h->dbp = (float*)w.take(L * (size_t)h->T * ((h->B + 31) / 32) * G4 * 4);
         h->row_loss = (float*)w.take(L * M * 4);
         h->loss = (float*)w.take(L * 4);
     }
@@ -576,7 +576,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         r.da = h->da; r.sDAi = M * G4;
         r.dc = h->dc; r.sDCi = (int64_t)B * DH;
         // rows of partial bias sums per learner: one per frame and batch tile (the persistent kernel writes one per frame)
-        const int64_t dbrows = persist ? (int64_t)T : (int64_t)T * rec_backward_batch_tiles(B);
+        const int64_t dbrows = persist ? (int64_t)T : (int64_t)T * rec_backward_batch_tiles(r);
         r.dbp = h->dbp; r.sDBi = dbrows * G4;
         if (persist) {
             // per (learner, direction): W_h once; per frame: da in (4 gates) and out, dY, 4 gates, c, c'

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void rec_backward_kernel(RecDesc p) {
     backward_epilogue<T, Core, FN>(p, acc, li, d, t, tp, u0, b0, lds);
 }
 
-// ---- direct-to-LDS versions (bf16, H a multiple of the stage, 16-byte aligned rows) -----
+// ---- direct-to-LDS versions (16-byte aligned rows, H a multiple of 16 bytes) -----
 
 // All workgroups of a launch start together and stream their W_h rows (a power-of-two pitch apart)
 // at the same pace; walking K from the same offset they would all touch the same column block of
@@ -259,8 +259,8 @@ __global__ __launch_bounds__(256) void rec_backward_kernel(RecDesc p) {
 // Forward: every tile its own rotation (its shared operand h is small and stays in L2).  Backward:
 // one rotation per (learner, direction), so that the tiles of a group still read the same block of
 // their shared operand da (1 MB per group) at the same time and fetch it from HBM once.
-__device__ inline int stage_rotation_fwd(int nk) { return (int)((blockIdx.y * 5 + blockIdx.x * 3) % nk); }
-__device__ inline int stage_rotation_bwd(int nk) { return (int)((blockIdx.x * 5) % nk); }
+__device__ inline int stage_rotation_fwd(int nk) { return nk > 1 ? (int)((blockIdx.y * 5 + blockIdx.x * 3) % nk) : 0; }
+__device__ inline int stage_rotation_bwd(int nk) { return nk > 1 ? (int)((blockIdx.x * 5) % nk) : 0; }
 
 template <typename T, int WM, int WN, int SB, int NS>
 __global__ __launch_bounds__(256) void rec_forward_dma_kernel(RecDesc p) {
@@ -345,56 +345,95 @@ static hipError_t bwd_t(const RecDesc& d, hipStream_t s) {
     return hipGetLastError();
 }
 
-// rows of the batch per backward tile: 128, or 32 for batches up to 64 (the same choice in every per-frame kernel variant)
-int rec_backward_batch_tiles(int B) { return B > 64 ? (B + 127) / 128 : (B + 31) / 32; }
-
 static bool rec_ok(const RecDesc& d) {
     return d.L >= 1 && d.L <= 128 && d.D >= 1 && d.D <= 2 && d.B >= 1 && d.H >= 4 && d.H % 4 == 0 && d.T >= 1 &&
            d.step >= 0 && d.step < d.T;
 }
 
-static bool dma_ok(const RecDesc& d) {
-    // whole stages, and 16-byte aligned rows of every operand the direct loads touch
-    return d.direct && d.precision == 1 && d.H % 64 == 0 && d.B > 32 && (uintptr_t)d.wh % 16 == 0 && d.sWi % 8 == 0 &&
-           d.sWd % 8 == 0 && (uintptr_t)d.y % 16 == 0 && d.sYi % 8 == 0 && (uintptr_t)d.da % 16 == 0 && d.sDAi % 8 == 0;
+// 16-byte aligned rows of every operand that is loaded in 16-byte pieces
+static bool rec_aligned(const RecDesc& d) {
+    const int epc = d.precision ? 8 : 4;
+    return d.H % epc == 0 && (uintptr_t)d.wh % 16 == 0 && d.sWi % epc == 0 && d.sWd % epc == 0 && (uintptr_t)d.y % 16 == 0 &&
+           d.sYi % epc == 0 && (uintptr_t)d.da % 16 == 0 && d.sDAi % epc == 0;
+}
+
+// Which kernels a step runs on.
+//   kSplit   32 x 32 tiles, contraction split over the waves (lstm_small.hip): as long as its workgroups fit the chip in
+//            one round (two in fp32, whose other tiles are no faster), a step is bound by the latency of the K walk and this
+//            one is the shortest.  us per frame (forward / backward), split against direct: fp32 6 x 320 cells, batch
+//            64: 16.3 / 16.9 against 29.7 / 32.7; 16 x 256, 128 (512 workgroups): 23.4 / 25.9 against 25.9 / 29.4; bf16 10 x
+//            360, 50: 8.4 / 11.4 against 15.0 / 17.4; and on the other side bf16 16 x 512, 64 (512 workgroups) 20.0 / 21.6
+//            against 15.5 / 18.9, fp32 32 x 512, 64 (1024) 78 / 94 against 48 / 54.
+//   kDirect  the direct-to-LDS kernels.
+//   kStaged  register-staged kernels: rows that are not 16-byte aligned, or forced (tuning).  fp32 6 x 320, 64: 31.0 /
+//            91.6; 32 x 1024, 128: 317 / 700 against 277 / 299 direct.
+enum RecKind { kStaged, kDirect, kSplit };
+
+static RecKind rec_kind(const RecDesc& d) {
+    if (!d.direct || !rec_aligned(d)) return kStaged;
+    const int64_t split_wgs = (int64_t)d.L * d.D * ((d.H + 31) / 32) * ((d.B + 31) / 32);
+    return split_wgs <= (d.precision ? 256 : 512) ? kSplit : kDirect;
+}
+
+// Rows of a backward direct tile: 128 where that leaves three quarters of the chip a workgroup, else 32 (every batch tile
+// reads its W_h slice again, but a launch that fills the chip matters more).  32 against 128 rows, us per frame:
+// bf16 16 x 640 cells, batch 96 (80 workgroups of 128 rows): 23.8 against 38.9; fp32 32 x 512, 96 (128): 76 against 148; bf16
+// 32 x 512, 128 (128): 35.6 against 44.4; 32 x 1024, 128 (256): 184 against 91, fp32 341 against 299.
+static bool wide_backward_tile(const RecDesc& d) {
+    return d.B > 64 && (int64_t)d.L * d.D * ((d.H + 127) / 128) * ((d.B + 127) / 128) >= 192;
+}
+
+int rec_backward_batch_tiles(const RecDesc& d) {
+    const RecKind kind = rec_kind(d);
+    const bool wide = kind == kStaged ? d.B > 64 : kind == kDirect && wide_backward_tile(d);
+    return wide ? (d.B + 127) / 128 : (d.B + 31) / 32;
+}
+
+template <typename T> static void fwd_direct_t(const RecDesc& d, hipStream_t s) {
+    const unsigned groups = (unsigned)(d.L * d.D);
+    if (d.B > 64) {
+        // two 32 KB stages (whole 128-byte lines per row and stage): 64 KB of LDS, two workgroups per CU
+        dim3 grid(groups, (d.H + 31) / 32, (d.B + 127) / 128);
+        hipLaunchKernelGGL((rec_forward_dma_kernel<T, 4, 1, 128, 2>), grid, dim3(256), 0, s, d);
+    } else {
+        dim3 grid(groups, (d.H + 63) / 64, (d.B + 63) / 64);
+        hipLaunchKernelGGL((rec_forward_dma_kernel<T, 2, 2, 128, 3>), grid, dim3(256), 0, s, d);
+    }
+}
+template <typename T> static void bwd_direct_t(const RecDesc& d, hipStream_t s) {
+    const unsigned groups = (unsigned)(d.L * d.D);
+    if (wide_backward_tile(d)) {
+        dim3 grid(groups, (d.H + 127) / 128, (d.B + 127) / 128);
+        hipLaunchKernelGGL((rec_backward_dma_kernel<T, 4, 2, 2, 128, 4>), grid, dim3(512), 0, s, d);
+    } else {
+        dim3 grid(groups, (d.H + 127) / 128, (d.B + 31) / 32);
+        hipLaunchKernelGGL((rec_backward_dma_kernel<T, 1, 4, 1, 128, 4>), grid, dim3(256), 0, s, d);
+    }
 }
 
 hipError_t launch_rec_forward(const RecDesc& d, hipStream_t s) {
     if (!rec_ok(d)) return hipErrorInvalidValue;
-    if (rec_small_supported(d)) return launch_rec_small(d, false, s);
-    if (d.precision == 0) return fwd_t<float, 16>(d, s);
-    if (dma_ok(d)) {
-        const unsigned groups = (unsigned)(d.L * d.D);
-        if (d.B > 64) {
-            dim3 grid(groups, (d.H + 31) / 32, (d.B + 127) / 128);
-            // two 32 KB stages (whole 128-byte lines per row and stage): 64 KB of LDS, two workgroups per CU
-            hipLaunchKernelGGL((rec_forward_dma_kernel<bf16_t, 4, 1, 128, 2>), grid, dim3(256), 0, s, d);
-        } else {
-            dim3 grid(groups, (d.H + 63) / 64, (d.B + 63) / 64);
-            hipLaunchKernelGGL((rec_forward_dma_kernel<bf16_t, 2, 2, 128, 3>), grid, dim3(256), 0, s, d);
-        }
+    const RecKind kind = rec_kind(d);
+    if (kind == kSplit) return launch_rec_split(d, false, s);
+    if (kind == kDirect) {
+        if (d.precision == 0) fwd_direct_t<float>(d, s);
+        else fwd_direct_t<bf16_t>(d, s);
         return hipGetLastError();
     }
+    if (d.precision == 0) return fwd_t<float, 16>(d, s);
     return d.H % 8 == 0 ? fwd_t<bf16_t, 16>(d, s) : fwd_t<bf16_t, 8>(d, s);
 }
 
 hipError_t launch_rec_backward(const RecDesc& d, hipStream_t s) {
     if (!rec_ok(d)) return hipErrorInvalidValue;
-    if (rec_small_supported(d)) return launch_rec_small(d, true, s);
-    if (d.precision == 0) return bwd_t<float, 16>(d, s);
-    if (dma_ok(d)) {
-        const unsigned groups = (unsigned)(d.L * d.D);
-        if (d.B > 64) {
-            // (64-row tiles, twice the workgroups, read every W_h slice twice: 16.0 against 11.5 ms per iteration at batch 128)
-            dim3 grid(groups, (d.H + 127) / 128, (d.B + 127) / 128);
-            hipLaunchKernelGGL((rec_backward_dma_kernel<bf16_t, 4, 2, 2, 128, 4>), grid, dim3(512), 0, s, d);
-        } else {
-            // 32-row tiles: twice the workgroups of 64-row ones (the 16 x 512-unit model: 256 instead of 128 on 256 CUs)
-            dim3 grid(groups, (d.H + 127) / 128, (d.B + 31) / 32);
-            hipLaunchKernelGGL((rec_backward_dma_kernel<bf16_t, 1, 4, 1, 128, 4>), grid, dim3(256), 0, s, d);
-        }
+    const RecKind kind = rec_kind(d);
+    if (kind == kSplit) return launch_rec_split(d, true, s);
+    if (kind == kDirect) {
+        if (d.precision == 0) bwd_direct_t<float>(d, s);
+        else bwd_direct_t<bf16_t>(d, s);
         return hipGetLastError();
     }
+    if (d.precision == 0) return bwd_t<float, 16>(d, s);
     return d.H % 8 == 0 ? bwd_t<bf16_t, 16>(d, s) : bwd_t<bf16_t, 8>(d, s);
 }
 

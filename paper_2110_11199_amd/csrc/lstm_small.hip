@@ -1,10 +1,10 @@
-// Per-time-step LSTM kernels for small batches (at most 32 segments per learner).
+// Per-time-step LSTM kernels with a split contraction, for steps that make few workgroups.
 //
 // Same operations as lstm.hip (one launch = one frame of one layer for all learners and directions,
 // gate non-linearities / cell update / cell backward fused behind the recurrent product), but laid
-// out for launches that are bound by latency, not by bytes: with a batch of 32 or fewer rows the
-// 32-row tiles of lstm.hip make only L*D*H/128 workgroups (32 on 256 compute units for 8 learners of
-// 256 units), and every wave walks the whole contraction in 16 dependent load -> LDS -> MFMA stages.
+// out for launches that are bound by latency, not by bytes: small models and small batches, where the tiles
+// of lstm.hip make a few dozen workgroups (32 on 256 compute units for 8 learners of 256 units and a
+// batch of 32), and every wave walks the whole contraction in 16 dependent load -> LDS -> MFMA stages.
 //
 // Here a workgroup of 8 waves owns a 32 x 32 (batch rows x hidden units) tile and SPLITS THE
 // CONTRACTION over its waves: wave w takes the k-chunks w, w+8, w+16, ...  Every wave loads its MFMA
@@ -250,18 +250,7 @@ __global__ __launch_bounds__(64 * kKS) void rec_backward_small_kernel(RecDesc p)
 
 }  // namespace
 
-// At most 32 batch rows (one row tile, so the partial bias sums keep one row per frame as
-// rec_backward_batch_tiles says), whole 16-byte fragments, 16-byte aligned operand rows.
-bool rec_small_supported(const RecDesc& d) {
-    const int el = d.precision ? 8 : 4;
-    const int64_t m = el;
-    return d.direct && d.B >= 1 && d.B <= 32 && d.H % el == 0 && d.L >= 1 && d.L <= 128 && d.D >= 1 && d.D <= 2 &&
-           (uintptr_t)d.wh % 16 == 0 && d.sWi % m == 0 && d.sWd % m == 0 && (uintptr_t)d.y % 16 == 0 && d.sYi % m == 0 &&
-           (d.da == nullptr || ((uintptr_t)d.da % 16 == 0 && d.sDAi % m == 0));
-}
-
-hipError_t launch_rec_small(const RecDesc& d, bool backward, hipStream_t s) {
-    if (!rec_small_supported(d) || d.step < 0 || d.step >= d.T) return hipErrorInvalidValue;
+hipError_t launch_rec_split(const RecDesc& d, bool backward, hipStream_t s) {
     const dim3 grid((unsigned)(d.L * d.D), (unsigned)((d.H + 31) / 32), (unsigned)((d.B + 31) / 32));
     const dim3 block(64 * kKS);
     if (d.precision == 0) {

@@ -65,9 +65,29 @@ SHAPES = [
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_gradient_matches_oracle(shape, prec):
+    _check_gradient(shape, 2, prec)
+
+
+# Enough learners for the direct-to-LDS step kernels (more split-contraction workgroups than the chip takes at once), at
+# hidden sizes that are no multiple of their K stage: below one stage, one stage and a remainder, several.
+DIRECT_SHAPES = [
+    (Shape(8, 40, 1, 1, 0, 12, 130, 3), 26),      # 130 rows: five 32-row backward tiles, two 128-row forward tiles
+    (Shape(8, 72, 1, 1, 0, 12, 70, 3), 30),       # 70 rows: 32-row backward tiles, ragged
+    (Shape(8, 40, 1, 1, 0, 12, 70, 3), 97),       # the 128-row backward tile, partly filled
+    (Shape(8, 136, 1, 0, 0, 12, 40, 3), 55),      # one direction, batch 40: the 64-row forward tile
+    (Shape(8, 104, 1, 1, 0, 12, 20, 2), 66),      # a batch below 32 rows with many learners
+]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("shape,L", DIRECT_SHAPES)
+def test_gradient_on_the_direct_step_kernels(shape, L, prec):
+    _check_gradient(shape, L, prec)
+
+
+def _check_gradient(shape, L, prec):
     import torch
-    print("lstm grad", shape, prec, flush=True)
-    L = 2
+    print("lstm grad", shape, L, prec, flush=True)
     P = lstm.param_count(shape)
     w0 = synth.initial_model(1, P, 0.2)
     eng = _engine(shape, L, S.FIXED_RING, prec)
