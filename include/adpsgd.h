@@ -344,9 +344,10 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
  *                                batches over 32; contraction split over the waves for batches up to 32) allowed, or
  *                                the general register-staged kernels everywhere
  *   ADPSGD_TUNE_REC_FWD_GROUPS   learner groups the forward recurrence is run in, 0 = automatic
- *   ADPSGD_TUNE_REC_PERSISTENT   persistent recurrent kernels (all frames of a layer in one launch, W_h held in
- *                                registers; bf16 operands, hidden 128/256/512/1024, batch <= 128): 1 on where the
- *                                shape allows, 0 off, -1 (default) automatic
+ *   ADPSGD_TUNE_REC_PERSISTENT   all frames of a layer in one launch with W_h held in registers: -1 (default) where the whole
+ *                                W_h of a (learner, direction) fits one compute unit (hidden up to 128); 0 never; 1 also
+ *                                the kernels that spread it over several compute units, which wait for each other (bf16
+ *                                operands, hidden 128/256/512/1024, batch <= 128)
  *   ADPSGD_TUNE_REC_WAIT_US      bound, in microseconds, of one wait between the workgroups of a persistent
  *                                kernel (default 2 000 000); when it runs out every workgroup returns and the
  *                                handle's sticky error becomes ADPSGD_EHIP

@@ -325,7 +325,8 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->dy = (float*)w.take(L * M * DH * 4);
         h->da = w.take(L * M * G4 * e);
         h->dc = (float*)w.take(L * (size_t)h->B * DH * 4);
-        h->dbp = (float*)w.take(L * (size_t)h->T * ((h->B + 31) / 32) * G4 * 4);
+        const size_t dbrows = (size_t)h->T * ((h->B + 31) / 32), dbtiles = (size_t)(h->B + 15) / 16;
+        h->dbp = (float*)w.take(L * (dbrows > dbtiles ? dbrows : dbtiles) * G4 * 4);
         h->row_loss = (float*)w.take(L * M * 4);
         h->loss = (float*)w.take(L * 4);
     }
@@ -445,6 +446,17 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     // a GEMM over the active learners, one group per learner (and direction)
     auto G = [&]() { GemmDesc g{}; g.precision = prec; g.groupsI = n; g.groupsD = 1; g.lmap = act; return g; };
 
+    // Algorithmic work of the recurrence of one layer (learners n): products, and bytes: W_h per (learner, direction), once
+    // where it stays on chip and else once per frame; per frame: pre-activations in, gates, c and h out, h (and c) in; and
+    // backward da in (4 gates) and out, dY, 4 gates, c, c' (dc in and out)
+    auto rec_flops = [&](int n) { return 2.0 * B * H * 4 * H * (T - 1) * n * D; };
+    auto rec_bytes_fwd = [&](int n, bool once) {
+        return (double)n * D * ((once ? 1.0 : T) * 4.0 * H * H * esz + (double)T * B * H * (2 * esz + 16 + 16 + (once ? 4 : 8)));
+    };
+    auto rec_bytes_bwd = [&](int n, bool once) {
+        return (double)n * D * ((once ? 1.0 : T) * 4.0 * H * H * esz + (double)T * B * H * (8 * esz + 4 + 16 + 8 + (once ? 0 : 8)));
+    };
+
     GemmDesc g;
     // ---- forward ----
     for (int l = 0; l < h->layers; ++l) {
@@ -472,15 +484,16 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         // few workgroups per launch and are slower than one).
         const int parts = rec_forward_parts(h, n);
         if (persist) {
-            // per (learner, direction): W_h once; per frame: pre-activations in, gates, c and h out, h in
-            if (int rc = mark(h, 2, persist_launches, 2.0 * B * H * 4 * H * (T - 1) * n * D,
-                              (double)n * D * (4.0 * H * H * esz + (double)T * B * H * (2 * esz + 16 + 16 + 4)))) return rc;
+            if (int rc = mark(h, 2, persist_launches, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
             if (int rc = run_persistent(r, l, false)) return rc;
             continue;
         }
-        // per frame and (learner, direction): W_h once, h in and out, 4 gates in and out (fp32), c in and out
-        if (int rc = mark(h, 2, T * parts, 2.0 * B * H * 4 * H * (T - 1) * n * D,
-                          (double)T * n * D * (4.0 * H * H * esz + (double)B * H * (2 * esz + 8 * 4 + 2 * 4)))) return rc;
+        if (h->tune_rec_persist != 0 && rec_resident_supported(r)) {
+            if (int rc = mark(h, 2, 1, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
+            HIPCHK(launch_rec_resident(r, false, s), "resident recurrent forward");
+            continue;
+        }
+        if (int rc = mark(h, 2, T * parts, rec_flops(n), rec_bytes_fwd(n, false))) return rc;
         for (int part = 0; part < parts; ++part) {
             const int per = n / parts, l0 = part * per;
             RecDesc q = r;
@@ -575,18 +588,19 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         r.dy = h->dy; r.sDYi = M * DH;
         r.da = h->da; r.sDAi = M * G4;
         r.dc = h->dc; r.sDCi = (int64_t)B * DH;
-        // rows of partial bias sums per learner: one per frame and batch tile (the persistent kernel writes one per frame)
-        const int64_t dbrows = persist ? (int64_t)T : (int64_t)T * rec_backward_batch_tiles(r);
+        const bool resident = !persist && h->tune_rec_persist != 0 && rec_resident_supported(r);
+        // rows of partial bias sums per learner: one per frame and batch tile (the persistent kernel writes one per frame,
+        // the resident one one per batch tile)
+        const int64_t dbrows = persist ? (int64_t)T : resident ? rec_resident_batch_tiles(r) : (int64_t)T * rec_backward_batch_tiles(r);
         r.dbp = h->dbp; r.sDBi = dbrows * G4;
         if (persist) {
-            // per (learner, direction): W_h once; per frame: da in (4 gates) and out, dY, 4 gates, c, c'
-            if (int rc = mark(h, 3, persist_launches, 2.0 * B * H * 4 * H * (T - 1) * n * D,
-                              (double)n * D * (4.0 * H * H * esz + (double)T * B * H * (8 * esz + 4 + 16 + 8)))) return rc;
+            if (int rc = mark(h, 3, persist_launches, rec_flops(n), rec_bytes_bwd(n, true))) return rc;
             if (int rc = run_persistent(r, l, true)) return rc;
+        } else if (resident) {
+            if (int rc = mark(h, 3, 1, rec_flops(n), rec_bytes_bwd(n, true))) return rc;
+            HIPCHK(launch_rec_resident(r, true, s), "resident recurrent backward");
         } else {
-            // per frame and (learner, direction): W_h once, da in (4 gates) and out, dY, 4 gates, c, c', dc in and out
-            if (int rc = mark(h, 3, T, 2.0 * B * H * 4 * H * (T - 1) * n * D,
-                              (double)T * n * D * (4.0 * H * H * esz + (double)B * H * (8 * esz + 4 + 16 + 8 + 8)))) return rc;
+            if (int rc = mark(h, 3, T, rec_flops(n), rec_bytes_bwd(n, false))) return rc;
             for (int t = 0; t < T; ++t) {
                 r.step = t;
                 HIPCHK(launch_rec_backward(r, s), "recurrent backward step");

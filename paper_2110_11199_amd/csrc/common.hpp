@@ -39,6 +39,24 @@ __device__ inline float exp_fast_(float a) { return __builtin_amdgcn_exp2f(a * 1
 __device__ inline float sigmoidf_(float a) { return __builtin_amdgcn_rcpf(1.0f + exp_fast_(-a)); }
 __device__ inline float tanhf_(float a) { return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + exp_fast_(2.0f * a)); }
 
+// Buffer accesses: (uniform descriptor) + (per-lane byte offset voff) + (uniform byte offset soff).  A lane whose voff lies
+// outside the descriptor's range reads 0 and its store is dropped, so that guards cost no branches: kOutOfRange is such an
+// offset for every region below 2 GiB (voff + soff does not wrap).
+typedef __amdgpu_buffer_rsrc_t buf_t;
+constexpr uint32_t kOutOfRange = 0x80000000u;
+__device__ inline buf_t make_buf_(const void* base_uniform, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base_uniform, 0, (int)bytes, 0x00027000);
+}
+__device__ inline float buf_load_(buf_t b, uint32_t voff, uint32_t soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)voff, (int)soff, 0));
+}
+__device__ inline void buf_store_(float v, buf_t b, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, (int)voff, (int)soff, 0);
+}
+__device__ inline void buf_store_(bf16_t v, buf_t b, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b16(v, b, (int)voff, (int)soff, 0);
+}
+
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 }  // namespace adpsgd

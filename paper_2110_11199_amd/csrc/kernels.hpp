@@ -111,6 +111,16 @@ hipError_t launch_rec_backward(const RecDesc& d, hipStream_t s);
 // (lstm_small.hip); needs 16-byte aligned operand rows and H a multiple of 16 bytes.
 hipError_t launch_rec_split(const RecDesc& d, bool backward, hipStream_t s);
 
+// Whether every operand row that is loaded in 16-byte pieces is 16-byte aligned and a whole number of them.
+bool rec_aligned(const RecDesc& d);
+
+// All T frames of one layer in one launch, W_h held in registers, a workgroup per (learner, direction) and 16 batch rows
+// (lstm_resident.hip; hidden sizes up to 128).  d.step is not used; the backward pass writes rec_resident_batch_tiles(d)
+// rows of dbp for all frames together.
+bool rec_resident_supported(const RecDesc& d);
+int rec_resident_batch_tiles(const RecDesc& d);
+hipError_t launch_rec_resident(const RecDesc& d, bool backward, hipStream_t s);
+
 // Bits of the device-side status word of a handle (0 = fine).
 constexpr uint32_t kStatusBadLabel = 1u;       // a label outside [0, classes) was met (and clamped)
 constexpr uint32_t kStatusWaitExpired = 2u;    // a bounded wait between workgroups ran out

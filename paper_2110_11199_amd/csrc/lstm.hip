@@ -350,8 +350,7 @@ static bool rec_ok(const RecDesc& d) {
            d.step >= 0 && d.step < d.T;
 }
 
-// 16-byte aligned rows of every operand that is loaded in 16-byte pieces
-static bool rec_aligned(const RecDesc& d) {
+bool rec_aligned(const RecDesc& d) {
     const int epc = d.precision ? 8 : 4;
     return d.H % epc == 0 && (uintptr_t)d.wh % 16 == 0 && d.sWi % epc == 0 && d.sWd % epc == 0 && (uintptr_t)d.y % 16 == 0 &&
            d.sYi % epc == 0 && (uintptr_t)d.da % 16 == 0 && d.sDAi % epc == 0;

@@ -82,10 +82,27 @@ DIRECT_SHAPES = [
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("shape,L", DIRECT_SHAPES)
 def test_gradient_on_the_direct_step_kernels(shape, L, prec):
-    _check_gradient(shape, L, prec)
+    from paper_2110_11199_amd import binding as Bd
+    _check_gradient(shape, L, prec, tune=[(Bd.TUNE_REC_PERSISTENT, 0)])
 
 
-def _check_gradient(shape, L, prec):
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[4], SHAPES[7], SHAPES[10], SHAPES[11]])
+def test_gradient_frame_by_frame(shape, prec):
+    # hidden sizes up to 128 run all frames in one launch unless told otherwise: here the kernels that take one frame each
+    from paper_2110_11199_amd import binding as Bd
+    _check_gradient(shape, 2, prec, tune=[(Bd.TUNE_REC_PERSISTENT, 0)])
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("hidden", [16, 48, 100, 128])
+@pytest.mark.parametrize("batch,frames", [(1, 2), (16, 5), (17, 1)])
+def test_gradient_with_all_frames_on_one_compute_unit(hidden, batch, frames, prec):
+    # one wave to eight, each register size; one row, a whole tile and one row more; an even, an odd and a single frame
+    _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
+
+
+def _check_gradient(shape, L, prec, tune=()):
     import torch
     print("lstm grad", shape, L, prec, flush=True)
     P = lstm.param_count(shape)
@@ -94,6 +111,8 @@ def _check_gradient(shape, L, prec):
     assert eng.P == P
     from paper_2110_11199_amd import binding as Bd
     assert [(o, r, c) for _, o, r, c in lstm.layout(shape)[0]] == Bd.adpsgd_layout(eng.h)
+    for key, value in tune:
+        eng.tune(key, value)
     eng.set_params(-1, torch.from_numpy(w0).cuda())
     b = _batches(shape, L, 0)
     eng.step(_to_dev(b), 0.0)
