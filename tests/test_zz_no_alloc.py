@@ -45,6 +45,19 @@ def test_static_scratch_consensus_matches_the_handle_based_one_twice_in_a_row():
         assert abs(got - oracle) <= 1e-11 * max(oracle, 1e-30)
 
 
+@pytest.mark.parametrize("L,P", [(2, 3), (5, 256), (16, 257), (17, 1022), (32, 4099), (33, 513), (128, 1026)])
+def test_consensus_at_the_edges_of_its_positions_and_learner_counts(L, P):
+    # elements past the last whole float4, learners past the last whole round of the four waves; the learners of the
+    # static call lie P elements apart (16-byte aligned or not), those of the handle 64-float aligned: same bits
+    from oracle import adpsgd as A
+    print("consensus", L, P, flush=True)
+    got, ref, x = _both(L, P, L)
+    assert got == ref
+    # both sides sum in fp64, in another order: a few hundred roundings of 1.1e-16
+    oracle = A.consensus_distance(x)
+    assert abs(got - oracle) <= 1e-12 * oracle
+
+
 def test_static_scratch_consensus_rejects_what_it_cannot_take():
     import torch
     from paper_2110_11199_amd import binding as Bd
