@@ -766,8 +766,12 @@ static int step_impl(adpsgd_t h, const void* const* batch_ptrs, float lr, const 
     u.tri_segment = h->tune_tri_segment;
     u.sync_segment = h->tune_sync_segment;
     u.pair_split = h->tune_pair_split;
-    {   // two-kernel global mean: by default on models large enough for the extra launches not to matter
-        int64_t chunk = h->tune_mean_chunk >= 0 ? h->tune_mean_chunk : (h->P >= (4 << 20) ? kMeanChunkDefault : 0);
+    {   // Two-kernel global mean: by default with 12 learners or more (streams per thread of the single kernel) where the extra
+        // launch does not matter, or where the single kernel's few threads walk all learners one after another.  us, one kernel
+        // / two: 16 x 100k 14.4 / 9.5, x 400k 20.7 / 24.3, x 1.25M 43 / 47, x 3M 99.8 / 98.0, x 7.7M 262 / 259; 12 x 100k
+        // 10.6 / 9.5, x 7.7M 196 / 197; 5 x 100k 5.2 / 8.7, x 7.7M 74 / 89.
+        const bool two = L >= 12 && (h->P >= 3000000 || h->P < (1 << 18));
+        int64_t chunk = h->tune_mean_chunk >= 0 ? h->tune_mean_chunk : (two ? kMeanChunkDefault : 0);
         if (chunk > h->mean_cap) chunk = h->mean_cap;
         u.mean_buf = chunk > 0 ? h->mean_buf : nullptr;
         u.mean_elems = chunk;

@@ -234,6 +234,7 @@ __global__ __launch_bounds__(1024) void sync_seg_update_kernel(AllArgs p) {
     const int64_t e = (int64_t)blockIdx.x * nx + tx;
     const bool ok = e < (p.P >> 2);
     const int j0 = sy * SEG;
+    if (blockIdx.x == 0 && sy == 0 && tx < (p.P & 3)) sync_scalar_(p, ((p.P >> 2) << 2) + tx);     // the P % 4 last elements
     float4 u[SEG];
 #pragma unroll
     for (int j = 0; j < SEG; ++j)
@@ -260,11 +261,6 @@ __global__ __launch_bounds__(1024) void sync_seg_update_kernel(AllArgs p) {
     }
 }
 
-// the P % 4 last elements of every learner of the synchronous baseline (one thread each)
-__global__ void sync_tail_kernel(AllArgs p) {
-    if (threadIdx.x < (p.P & 3)) sync_scalar_(p, ((p.P >> 2) << 2) + threadIdx.x);
-}
-
 template <int SEG>
 static void launch_sync_seg(const AllArgs& a, hipStream_t s) {
     const int ns = (a.L + SEG - 1) / SEG;
@@ -272,7 +268,6 @@ static void launch_sync_seg(const AllArgs& a, hipStream_t s) {
     while (nx * ns > 512 && nx > 8) nx >>= 1;
     const int64_t n4 = a.P >> 2;
     hipLaunchKernelGGL(sync_seg_update_kernel<SEG>, dim3((unsigned)((n4 + nx - 1) / nx)), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
-    if (a.P & 3) hipLaunchKernelGGL(sync_tail_kernel, dim3(1), dim3(64), 0, s, a);
 }
 
 __device__ inline void all_scalar_(const AllArgs& p, int64_t t) {
@@ -338,10 +333,13 @@ struct AllSplitArgs {
     AllArgs a;
     float* mean;            // [chunk] fp32
     int64_t e0, n4c;        // chunk start and length in float4 positions
+    int tail;               // last chunk: the P % 4 last elements too
 };
 
 __global__ __launch_bounds__(256) void all_mean_kernel(AllSplitArgs q) {
     const AllArgs& p = q.a;
+    // the P % 4 last elements of every learner, whole, on a workgroup beside the others (a launch of their own took 15 us)
+    if (blockIdx.x == 0 && q.tail && threadIdx.x < (p.P & 3)) all_scalar_(p, ((p.P >> 2) << 2) + threadIdx.x);
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= q.n4c) return;
     const int64_t e = q.e0 + c;
@@ -369,11 +367,6 @@ __global__ __launch_bounds__(256) void all_apply_kernel(AllSplitArgs q) {
     if (p.shadow && !p.emit_input) emit4_(p.shadow + i * p.stride, e, r);
 }
 
-// the P % 4 last elements of every learner (one thread each)
-__global__ void all_tail_kernel(AllArgs p) {
-    if (threadIdx.x < (p.P & 3)) all_scalar_(p, ((p.P >> 2) << 2) + threadIdx.x);
-}
-
 // ---- ring-neighbour mixing with weights 1/3 (the circulant operator T^f of Eq. 9, and T^r = P' T^f P) -------
 // One thread owns an element index of all learners and walks the ring order with the previous, current and
 // next model value in registers: every model is read once (the last one of the order twice), so the update
@@ -381,8 +374,8 @@ __global__ void all_tail_kernel(AllArgs p) {
 struct TriArgs {
     const float* src; float* dst; int64_t stride; int64_t P; float lr; float third; int L;
     bf16_t* shadow; int emit_input;
-    const float* g[128];
-    int16_t order[128];
+    const float* g[128];        // gradients in ring order
+    int32_t order[128];         // learners in ring order (whole words: a scalar load each, 16-bit entries take vector loads)
 };
 
 __device__ inline float tri_mean_(float l, float c, float r, float third) { return __fmul_rn(__fadd_rn(__fadd_rn(l, c), r), third); }
@@ -393,12 +386,16 @@ __device__ inline void tri_scalar_(const TriArgs& p, int64_t t) {
     for (int q = 0; q < p.L; ++q) {
         const int i = p.order[q];
         const float next = q + 1 < p.L ? p.src[p.order[q + 1] * p.stride + t] : first;
-        const float r = sgd_(tri_mean_(prev, cur, next, p.third), p.lr, p.g[i][t]);
+        const float r = sgd_(tri_mean_(prev, cur, next, p.third), p.lr, p.g[q][t]);
         p.dst[i * p.stride + t] = r;
         if (p.shadow) p.shadow[i * p.stride + t] = f32_to_bf16(p.emit_input ? cur : r);
         prev = cur; cur = next;
     }
 }
+
+// Ring positions whose loads go out together: no load passes a store (the result may replace a model), so that a walk
+// position by position waits once for each.  12 x 1.25M with whole-word orders: 37 -> 34 us, 16 x 100k: 17.7 -> 8.8.
+constexpr int kTriBlock = 4;
 
 template <bool VEC>
 __global__ __launch_bounds__(256) void tri_update_kernel(TriArgs p) {
@@ -408,17 +405,26 @@ __global__ __launch_bounds__(256) void tri_update_kernel(TriArgs p) {
         if (e < n4) {
             const float4 first = ldnt_(p.src + p.order[0] * p.stride, e);
             float4 prev = ldnt_(p.src + p.order[p.L - 1] * p.stride, e), cur = first;
-            for (int q = 0; q < p.L; ++q) {
-                const int i = p.order[q];
-                float4 next = first;
-                if (q + 1 < p.L) next = ldnt_(p.src + p.order[q + 1] * p.stride, e);
-                const float4 g = ldnt_(p.g[i], e);
-                const float4 m = make_float4(tri_mean_(prev.x, cur.x, next.x, p.third), tri_mean_(prev.y, cur.y, next.y, p.third),
-                                             tri_mean_(prev.z, cur.z, next.z, p.third), tri_mean_(prev.w, cur.w, next.w, p.third));
-                const float4 r = pair_new_(m, p.lr, g);
-                stnt_(p.dst + i * p.stride, e, r);
-                if (p.shadow) emit4_(p.shadow + i * p.stride, e, p.emit_input ? cur : r);
-                prev = cur; cur = next;
+            for (int q0 = 0; q0 < p.L; q0 += kTriBlock) {
+                float4 next[kTriBlock], g[kTriBlock];
+#pragma unroll
+                for (int j = 0; j < kTriBlock; ++j) {
+                    if (q0 + j >= p.L) break;
+                    g[j] = ldnt_(p.g[q0 + j], e);
+                    next[j] = first;
+                    if (q0 + j + 1 < p.L) next[j] = ldnt_(p.src + p.order[q0 + j + 1] * p.stride, e);
+                }
+#pragma unroll
+                for (int j = 0; j < kTriBlock; ++j) {
+                    if (q0 + j >= p.L) break;
+                    const int i = p.order[q0 + j];
+                    const float4 m = make_float4(tri_mean_(prev.x, cur.x, next[j].x, p.third), tri_mean_(prev.y, cur.y, next[j].y, p.third),
+                                                 tri_mean_(prev.z, cur.z, next[j].z, p.third), tri_mean_(prev.w, cur.w, next[j].w, p.third));
+                    const float4 r = pair_new_(m, p.lr, g[j]);
+                    stnt_(p.dst + i * p.stride, e, r);
+                    if (p.shadow) emit4_(p.shadow + i * p.stride, e, p.emit_input ? cur : r);
+                    prev = cur; cur = next[j];
+                }
             }
         }
         if (blockIdx.x == 0 && threadIdx.x < (p.P & 3)) tri_scalar_(p, (n4 << 2) + threadIdx.x);
@@ -441,6 +447,8 @@ __global__ __launch_bounds__(1024) void tri_seg_update_kernel(TriArgs p) {
     const int64_t e = (int64_t)blockIdx.x * nx + tx;
     const bool ok = e < (p.P >> 2);
     const int q0 = sy * SEG;
+    // the P % 4 last elements of every learner: one thread each walks the whole ring
+    if (blockIdx.x == 0 && sy == 0 && tx < (p.P & 3)) tri_scalar_(p, ((p.P >> 2) << 2) + tx);
     float4 x[SEG], g[SEG];
     float4 lastv = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -448,7 +456,7 @@ __global__ __launch_bounds__(1024) void tri_seg_update_kernel(TriArgs p) {
         if (ok && q0 + j < p.L) {
             const int i = p.order[q0 + j];
             x[j] = ldnt_(p.src + i * p.stride, e);
-            g[j] = ldnt_(p.g[i], e);
+            g[j] = ldnt_(p.g[q0 + j], e);
             lastv = x[j];
         }
     }
@@ -473,11 +481,6 @@ __global__ __launch_bounds__(1024) void tri_seg_update_kernel(TriArgs p) {
     }
 }
 
-// the P % 4 last elements of every learner (one thread each walks the whole ring)
-__global__ void tri_tail_kernel(TriArgs p) {
-    if (threadIdx.x < (p.P & 3)) tri_scalar_(p, ((p.P >> 2) << 2) + threadIdx.x);
-}
-
 template <int SEG>
 static void launch_tri_seg(const TriArgs& a, hipStream_t s) {
     const int ns = (a.L + SEG - 1) / SEG;                        // at most 128 segments (L <= 128)
@@ -485,7 +488,6 @@ static void launch_tri_seg(const TriArgs& a, hipStream_t s) {
     while (nx * ns > 512 && nx > 8) nx >>= 1;
     const int64_t n4 = a.P >> 2;
     hipLaunchKernelGGL(tri_seg_update_kernel<SEG>, dim3((unsigned)((n4 + nx - 1) / nx)), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
-    if (a.P & 3) hipLaunchKernelGGL(tri_tail_kernel, dim3(1), dim3(64), 0, s, a);
 }
 
 // ---- hybrid mixing (Section V: synchronous super-learners joined by the asynchronous ring) -----------
@@ -670,24 +672,30 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
         }
         if (vec && !d.update_first && d.mean_buf && d.mean_elems >= 1024 && d.L >= 4 && (d.P >> 2) > 0 &&
             (uintptr_t)d.mean_buf % 16 == 0) {
-            const int64_t n4 = d.P >> 2, chunk4 = d.mean_elems >> 2;
+            // Equal chunks (a short last one leaves the chip idle at its end), and a grid of whole rounds of the 8 XCDs: the
+            // workgroups of one position then run on one XCD for every learner and find its mean in that L2.
+            const int64_t n4 = d.P >> 2, chunks = (n4 + (d.mean_elems >> 2) - 1) / (d.mean_elems >> 2);
+            const int64_t chunk4 = (n4 + chunks - 1) / chunks;
             AllSplitArgs q;
             q.a = a; q.mean = d.mean_buf;
             for (int64_t e0 = 0; e0 < n4; e0 += chunk4) {
                 q.e0 = e0; q.n4c = n4 - e0 < chunk4 ? n4 - e0 : chunk4;
+                q.tail = e0 + chunk4 >= n4;
                 // (workgroups of 64 or 128 threads instead of 256 change nothing here: 5.8 - 6.0 TB/s in all nine combinations;
                 // a mean kernel with one (position, learner) per thread and the sum through LDS is slower: 5.1 - 5.8)
-                const unsigned blocks = (unsigned)((q.n4c + 255) / 256);
+                const unsigned blocks = (unsigned)(((q.n4c + 255) / 256 + 7) / 8 * 8);
                 hipLaunchKernelGGL(all_mean_kernel, dim3(blocks), dim3(256), 0, s, q);
                 hipLaunchKernelGGL(all_apply_kernel, dim3(blocks, (unsigned)d.L), dim3(256), 0, s, q);
             }
-            if (d.P & 3) hipLaunchKernelGGL(all_tail_kernel, dim3(1), dim3(64), 0, s, a);
         } else if (vec) {
             const int64_t n4 = d.P >> 2;
             const unsigned blocks = (unsigned)((n4 > 0 ? n4 : 1) + 255) / 256;
-            // two learners per thread are the measured best on large models (64 x 135M: 5.16 -> 5.48 TB/s, 16 x 145M:
-            // 5.49 -> 5.99; four 5.40 / 5.75, eight 5.34 / 5.67)
-            const int seg = d.sync_segment < 0 ? ((d.P >= (4 << 20) && d.L >= 4) ? 2 : 0) : d.sync_segment;
+            // Two learners per thread are the measured best on large models (64 x 135M: 5.16 -> 5.48 TB/s, 16 x 145M:
+            // 5.49 -> 5.99; four 5.40 / 5.75, eight 5.34 / 5.67) and on small ones, where few threads walk all learners one
+            // after another (us, one walk -> two learners: 16 x 100k 10.4 -> 6.2, x 400k 16.2 -> 14.5, x 800k 23.3 -> 28.1;
+            // 8 x 400k 8.9 -> 7.2; 5 x 400k 6.3 -> 6.4).
+            const bool large = d.P >= (4 << 20) && d.L >= 4, small = d.P >= (1 << 16) && d.P < (1 << 19) && d.L >= 8;
+            const int seg = d.sync_segment >= 0 ? d.sync_segment : (large || small ? 2 : 0);
             if (d.update_first && n4 > 0 && seg >= 2 && d.L > seg) {
                 if (seg >= 8) launch_sync_seg<8>(a, s);
                 else if (seg >= 4) launch_sync_seg<4>(a, s);
@@ -706,17 +714,21 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
         a.src = d.src; a.dst = d.dst; a.stride = d.stride; a.P = d.P; a.lr = d.lr; a.L = d.L;
         a.third = 1.0f / 3.0f;
         a.shadow = d.shadow; a.emit_input = d.emit_input;
-        for (int i = 0; i < 128; ++i) { a.g[i] = i < d.L ? d.g[i] : nullptr; a.order[i] = i < d.L ? d.order[i] : 0; }
         // the order must be a permutation of 0..L-1 (an index out of range would address another learner's memory)
         bool seen[128] = {false};
         for (int i = 0; i < d.L; ++i) {
             if (d.order[i] < 0 || d.order[i] >= d.L || seen[d.order[i]]) return hipErrorInvalidValue;
             seen[d.order[i]] = true;
         }
-        // Two ring positions per thread are the measured best on large models (64 x 135M: 5.0 -> 5.4-5.5 TB/s, 16 x 145M:
-        // 5.5 -> 6.1; one position 5.2 / 5.8, four 5.4 / 5.0, eight 4.9 / 3.3); on small ones the single walk's fewer,
-        // larger workgroups are as fast or faster.
-        const int seg = d.tri_segment < 0 ? ((d.P >= (4 << 20) && d.L >= 4) ? 2 : 0) : d.tri_segment;
+        for (int q = 0; q < 128; ++q) { a.order[q] = q < d.L ? d.order[q] : 0; a.g[q] = q < d.L ? d.g[d.order[q]] : nullptr; }
+        // Segments against the single walk, us for segments of none / 1 / 2: the walk has the fewest loads, but a thread walks
+        // 2 L streams (long rings of large models) and takes all learners' time (small models, a few workgroups per compute
+        // unit).  L = 16: 100k 8.8 / 6.6 / 6.6, 800k 30.4 / 26.6 / 28.4, 1.25M 44 / 43 / 44, 3M 104 / 105 / 100, 7.7M 276 / 258 / 244,
+        // 145M 5.5 / 5.8 / 6.1 TB/s (four positions 5.0); L = 8: 100k 5.6 / 5.6 / 5.5, 800k 14.6 / 13.7 / 16.1, 7.7M 132 / 122 / 140;
+        // L = 5: 400k 6.5 / 6.3 / 7.5, 7.7M 81 / 86 / 117.
+        const int seg = d.tri_segment >= 0 ? d.tri_segment
+                        : d.P >= (4 << 20) ? (d.L >= 12 ? 2 : 0)
+                        : (d.P < (1 << 20) && d.L >= 8 ? 1 : 0);
         if (vec && (d.P >> 2) > 0 && seg >= 1 && d.L > seg) {
             if (seg == 1) launch_tri_seg<1>(a, s);
             else if (seg >= 8) launch_tri_seg<8>(a, s);
