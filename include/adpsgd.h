@@ -345,9 +345,10 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
  *                                the general register-staged kernels everywhere
  *   ADPSGD_TUNE_REC_FWD_GROUPS   learner groups the forward recurrence is run in, 0 = automatic
  *   ADPSGD_TUNE_REC_PERSISTENT   all frames of a layer in one launch with W_h held in registers: -1 (default) where the whole
- *                                W_h of a (learner, direction) fits one compute unit (hidden up to 128); 0 never; 1 also
- *                                the kernels that spread it over several compute units, which wait for each other (bf16
- *                                operands, hidden 128/256/512/1024, batch <= 128)
+ *                                W_h of a (learner, direction) fits one compute unit (hidden up to 128) or a group of up to
+ *                                16 (hidden up to 512 in fp32, 640 with bf16 operands; not for the largest batches), whose
+ *                                workgroups wait for each other; 0 never; 1 the kernels that hold it on a whole round of
+ *                                the chip at once (bf16 operands, hidden 128/256/512/1024, batch <= 128)
  *   ADPSGD_TUNE_REC_WAIT_US      bound, in microseconds, of one wait between the workgroups of a persistent
  *                                kernel (default 2 000 000); when it runs out every workgroup returns and the
  *                                handle's sticky error becomes ADPSGD_EHIP

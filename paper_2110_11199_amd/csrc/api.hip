@@ -1,5 +1,6 @@
 // C ABI of the ADPSGD library: configuration checks, workspace carving, the
 // host-side integer schedule and the orchestration of one iteration.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -148,6 +149,9 @@ struct adpsgd_handle {
     float* cbuf;       // [layers][L][D][M][H]
     void* z; void* dz; float* logits; void* dlogits; float* dy; void* da; float* dc;
     float* row_loss; float* loss;
+    // recurrences over clusters of workgroups: iteration counter and [layers][2 passes] tickets behind it; exchange words
+    uint32_t* epoch = nullptr;
+    uint64_t* exchange = nullptr; size_t exchange_bytes = 0;
 };
 
 // A recorded sequence of iterations of one handle (adpsgd_capture_end), replayed by adpsgd_graph_replay.
@@ -193,6 +197,12 @@ bool use_persistent(const adpsgd_handle* h) {
     if (!rec_persist_supported(r, h->cu_count)) return false;
     if (h->tune_rec_persist == 1) return true;
     return false;       // automatic: off
+}
+
+// Whether the recurrences of `n` learners run on clusters of workgroups, W_h on their registers.
+bool use_cluster(const adpsgd_handle* h, const RecDesc& r, bool backward) {
+    return h->tune_rec_persist != 0 && h->exchange_bytes > 0 && rec_cluster_supported(r, backward, h->cu_count) &&
+           (size_t)rec_cluster_exchange_words(r, backward) * 8 <= h->exchange_bytes;
 }
 
 // Turns the status bits a kernel has raised (as last copied to the host) into an error.
@@ -329,6 +339,16 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->dbp = (float*)w.take(L * (dbrows > dbtiles ? dbrows : dbtiles) * G4 * 4);
         h->row_loss = (float*)w.take(L * M * 4);
         h->loss = (float*)w.take(L * 4);
+        RecDesc r{};
+        r.precision = h->prec; r.L = h->L; r.D = h->D; r.B = h->B; r.H = h->H; r.T = h->T; r.direct = 1;
+        int64_t words = 0;                                 // (the alignment of the tensors follows from the layout)
+        for (bool backward : {false, true})
+            if (rec_cluster_supported(r, backward, 1 << 20)) words = std::max(words, rec_cluster_exchange_words(r, backward));
+        h->exchange_bytes = (size_t)words * 8;
+        if (words > 0) {
+            h->epoch = (uint32_t*)w.take((1 + (size_t)h->layers * 2) * 4);
+            h->exchange = (uint64_t*)w.take(h->exchange_bytes);
+        }
     }
     return w.used;
 }
@@ -434,6 +454,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     StageDesc st;
     st.L = n; st.lmap = act; st.precision = prec; st.rows = M; st.I = h->I; st.ldx = h->ldx;
     st.x0 = h->x0; st.sX0 = M * h->ldx; st.y = h->labels; st.sY = M;
+    st.epoch = h->epoch; st.tickets = h->layers * 2;
     for (int i = 0; i < 128; ++i) {
         st.feats[i] = i < L ? (const float*)batch_ptrs[2 * i] : nullptr;
         st.labels[i] = i < L ? (const int32_t*)batch_ptrs[2 * i + 1] : nullptr;
@@ -455,6 +476,15 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     };
     auto rec_bytes_bwd = [&](int n, bool once) {
         return (double)n * D * ((once ? 1.0 : T) * 4.0 * H * H * esz + (double)T * B * H * (8 * esz + 4 + 16 + 8 + (once ? 0 : 8)));
+    };
+
+    auto cluster_desc = [&](const RecDesc& r, int l, bool backward) {
+        ClusterDesc c;
+        c.r = r;
+        c.launches = 2 * h->layers; c.launch = 2 * l + (backward ? 1 : 0);
+        c.exchange = h->exchange; c.epoch = h->epoch; c.ticket = h->epoch + 1 + c.launch; c.status = h->status;
+        c.wait_ticks = (unsigned long long)h->tune_wait_us * 100ull;
+        return c;
     };
 
     GemmDesc g;
@@ -491,6 +521,11 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         if (h->tune_rec_persist != 0 && rec_resident_supported(r)) {
             if (int rc = mark(h, 2, 1, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
             HIPCHK(launch_rec_resident(r, false, s), "resident recurrent forward");
+            continue;
+        }
+        if (use_cluster(h, r, false)) {
+            if (int rc = mark(h, 2, 1, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
+            HIPCHK(launch_rec_cluster(cluster_desc(r, l, false), false, h->cu_count, s), "recurrent forward (clusters)");
             continue;
         }
         if (int rc = mark(h, 2, T * parts, rec_flops(n), rec_bytes_fwd(n, false))) return rc;
@@ -589,9 +624,11 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         r.da = h->da; r.sDAi = M * G4;
         r.dc = h->dc; r.sDCi = (int64_t)B * DH;
         const bool resident = !persist && h->tune_rec_persist != 0 && rec_resident_supported(r);
+        const bool cluster = !persist && !resident && use_cluster(h, r, true);
         // rows of partial bias sums per learner: one per frame and batch tile (the persistent kernel writes one per frame,
         // the resident one one per batch tile)
-        const int64_t dbrows = persist ? (int64_t)T : resident ? rec_resident_batch_tiles(r) : (int64_t)T * rec_backward_batch_tiles(r);
+        const int64_t dbrows = persist ? (int64_t)T : resident ? rec_resident_batch_tiles(r) : cluster ? rec_cluster_batch_tiles(r)
+                                       : (int64_t)T * rec_backward_batch_tiles(r);
         r.dbp = h->dbp; r.sDBi = dbrows * G4;
         if (persist) {
             if (int rc = mark(h, 3, persist_launches, rec_flops(n), rec_bytes_bwd(n, true))) return rc;
@@ -599,6 +636,9 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         } else if (resident) {
             if (int rc = mark(h, 3, 1, rec_flops(n), rec_bytes_bwd(n, true))) return rc;
             HIPCHK(launch_rec_resident(r, true, s), "resident recurrent backward");
+        } else if (cluster) {
+            if (int rc = mark(h, 3, 1, rec_flops(n), rec_bytes_bwd(n, true))) return rc;
+            HIPCHK(launch_rec_cluster(cluster_desc(r, l, true), true, h->cu_count, s), "recurrent backward (clusters)");
         } else {
             if (int rc = mark(h, 3, T, rec_flops(n), rec_bytes_bwd(n, false))) return rc;
             for (int t = 0; t < T; ++t) {
@@ -681,6 +721,14 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
             h->cu_count = cus;
+        // a stream may be restricted to part of them (groups of workgroups that wait for each other must fit)
+        uint32_t mask[32] = {0};
+        if (h->cu_count > 0 && hipExtStreamGetCUMask(h->stream, 32, mask) == hipSuccess) {
+            int n = 0;
+            for (uint32_t m : mask) n += __builtin_popcount(m);
+            if (n > 0 && n < h->cu_count) h->cu_count = n;
+        }
+        (void)hipGetLastError();
     }
     hipStream_t s = h->stream;
     const size_t slab = (size_t)h->L * h->Ppad * 4;
@@ -693,6 +741,8 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     if (e == hipSuccess) e = hipMemsetAsync(h->params[0], 0, slab, s);
     if (e == hipSuccess && h->tau == 1) e = hipMemsetAsync(h->params[1], 0, slab, s);
     if (e == hipSuccess && !h->flat) e = hipMemsetAsync(h->grads, 0, slab, s);
+    if (e == hipSuccess && h->epoch) e = hipMemsetAsync(h->epoch, 0, (1 + (size_t)h->layers * 2) * 4, s);
+    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes, s);   // no word carries a tag in use
     if (e != hipSuccess) { (void)hipHostFree(mirror); delete h; return hipfail(e, "clear models"); }
     if (cfg->init_scale > 0.f) {
         // same w_0 on every learner (Algorithm 1, input)

@@ -50,6 +50,16 @@ __device__ inline buf_t make_buf_(const void* base_uniform, int64_t bytes) {
 __device__ inline float buf_load_(buf_t b, uint32_t voff, uint32_t soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)voff, (int)soff, 0));
 }
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+__device__ inline uint4 buf_load16_(buf_t b, uint32_t voff, uint32_t soff) {
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(b, (int)voff, (int)soff, 0);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+__device__ inline uint2 buf_load8_(buf_t b, uint32_t voff, uint32_t soff) {
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(b, (int)voff, (int)soff, 0);
+    return make_uint2(v.x, v.y);
+}
 __device__ inline void buf_store_(float v, buf_t b, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, (int)voff, (int)soff, 0);
 }

@@ -77,6 +77,8 @@ struct StageDesc {             // copy / cast the minibatches into the workspace
     const int32_t* labels[128];
     void* x0; int64_t sX0;     // [L][rows][ldx] operand type
     int32_t* y; int64_t sY;    // [L][rows]
+    uint32_t* epoch;           // incremented once (may be NULL), and the `tickets` words behind it are cleared
+    int tickets;
 };
 hipError_t launch_stage(const StageDesc& d, hipStream_t s);
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s);
@@ -124,6 +126,23 @@ hipError_t launch_rec_resident(const RecDesc& d, bool backward, hipStream_t s);
 // Bits of the device-side status word of a handle (0 = fine).
 constexpr uint32_t kStatusBadLabel = 1u;       // a label outside [0, classes) was met (and clamped)
 constexpr uint32_t kStatusWaitExpired = 2u;    // a bounded wait between workgroups ran out
+
+// All T frames of one layer in one launch, W_h spread over clusters of workgroups that exchange h (partial sums of dh) through
+// `exchange` (lstm_cluster.hip).  r.step is not used; the backward pass writes rec_cluster_batch_tiles(r) rows of dbp for all
+// frames together.
+struct ClusterDesc {
+    RecDesc r;
+    uint64_t* exchange;                  // rec_cluster_exchange_words(r, backward) words, zero before the handle's first launch
+    uint32_t* ticket;                    // zero before the launch
+    const uint32_t* epoch;               // differs from iteration to iteration, 0 in none
+    int launch, launches;                // this launch among those of an iteration
+    uint32_t* status;                    // kStatusWaitExpired is or-ed in
+    unsigned long long wait_ticks;
+};
+bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count);
+int rec_cluster_batch_tiles(const RecDesc& d);
+int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward);
+hipError_t launch_rec_cluster(const ClusterDesc& p, bool backward, int cu_count, hipStream_t s);
 
 // All T frames of one layer for ngl (learner, direction) pairs in one launch, W_h held in registers
 // (lstm_persist.hip).  r: the tensors of the layer (r.L, r.lmap, r.step and r.direct are not used);

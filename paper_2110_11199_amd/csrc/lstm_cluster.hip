@@ -1,0 +1,515 @@
+// Recurrent LSTM kernels that keep W_h on the registers of a few compute units: all T frames of one layer in one launch, for
+// hidden sizes above what one compute unit holds (lstm_resident.hip).
+//
+// Frame by frame such a layer costs a launch, W_h from the caches and a latency-bound product per frame: 8-20 us, of which the
+// products are 1-4; here 3.4-8 (both sides at the rule below).  Iterations: fp32 8 x 2 x 256 cells 1722 -> 1090 us, 6 x 320 2984 -> 1644,
+// bf16 5 x 2 x 360 1396 -> 934.  What is left of a frame: the exchange (about 1.5 us), fp32 products of one wave per SIMD, the cells.  Here a CLUSTER of S workgroups takes RB batch rows of one (learner, direction) through all frames
+// (batch rows do not depend on each other: as many clusters as row blocks).  Workgroup m of a cluster owns U hidden units and holds
+// their part of W_h as MFMA fragments in registers (a wave per SIMD, up to 320 of its 512 registers); the cell state (dL/dc)
+// stays in registers too.  What a frame needs of the other workgroups goes through memory:
+//   forward   h_{t'} of all units (H values per row, in the operand type) - every workgroup reads all of it into LDS;
+//   backward  dh = da W_h is split over its CONTRACTION: workgroup m multiplies the da of its own units (LDS) with their rows of
+//             W_h and hands every workgroup the partial sums of its units (fp32).  Splitting over the result instead would
+//             have every workgroup read all of da, four times H values per row.
+//
+// Exchange.  A 32-bit payload and a 32-bit tag travel in one aligned 64-bit word, stored and loaded with single relaxed atomics
+// at device scope: a word is there or it is not, so there are no fences, no write-backs and no counters, and a frame costs one
+// store-to-load latency.  The tag counts frames over launches AND iterations (a device word that the staging kernel of
+// every iteration increments, so that a replayed recording gets new tags as well), so nothing is cleared between uses;
+// the buffer is zeroed when the handle is made and 0 is no tag in use.  Two slots by the parity of the frame suffice: whoever
+// writes frame s has received all of frame s-1, whose senders had read frame s-2.
+//
+// Progress.  Workgroups take their place (cluster, member) from a ticket counter when they START, so a cluster consists of
+// workgroups that run: a complete cluster needs nobody else, and an incomplete one holds at most S-1 compute units until the
+// clusters before it are done, whatever else shares the device and in whatever order workgroups are dispatched.  The grid may
+// exceed the chip.  Every wait is bounded all the same (wait_ticks of the 100 MHz clock, or another workgroup's expiry):
+// the workgroup raises kStatusWaitExpired and returns.
+//
+// MFMA operand mapping (16x16 tiles) as in lstm_resident.hip.
+#include "gemm_core.hpp"
+#include "kernels.hpp"
+#include "rec_tiles.hpp"
+
+namespace adpsgd {
+namespace {
+
+// S workgroups of 4 waves per cluster.  bf16: a wave holds the four gates of 16 units, U = 64.  fp32, whose products are 16
+// times slower: two waves share 16 units, each with half of the contraction, U = 32.
+template <typename T, int S_> struct Cl {
+    static constexpr int S = S_, KS = sizeof(T) == 4 ? 2 : 1, NU = 4 / KS, U = 16 * NU, KP = S * U;   // KP: padded H
+    static constexpr int EL = 16 / (int)sizeof(T), KC = 4 * EL, NCH = KP / KC, CW = NCH / KS;           // k-chunks: all, of a wave
+    static constexpr int RB = 16;                          // batch rows of a cluster
+    static constexpr int VW = 4 / (int)sizeof(T), RW = KP / VW;                 // values per exchange word, words per row of h
+    static constexpr int FWD_ROW = KP * (int)sizeof(T) + 16, BWD_ROW = 4 * U * (int)sizeof(T) + 16;     // bytes of an LDS row
+    static constexpr int W_ROW = KP + 4;                   // words of a row of staged W_h: rows 4 apart lie 16 banks apart
+    static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
+    static constexpr int PPT = RB * U / 256;                                    // backward: (row, unit) positions of a thread
+    static constexpr int64_t FWD_SLOT = (int64_t)RB * RW, BWD_SLOT = (int64_t)S * RB * KP;              // exchange words
+    static_assert(NCH % KS == 0 && KP % 64 == 0, "tiling");
+};
+
+// An exchange word is addressed by a wave-uniform base and one byte offset of the lane; the base passes through an empty asm in
+// every frame, so that the compiler forms the addresses from it there instead of keeping one per word across the frames.
+typedef __attribute__((address_space(1))) uint64_t word_t;
+typedef __attribute__((address_space(1))) char byte_t;
+__device__ inline word_t* per_frame_(word_t* p) { asm volatile("" : "+s"(p)); return p; }
+__device__ inline void put_(word_t* base, uint32_t lane_bytes, uint32_t v, uint32_t tag) {
+    __hip_atomic_store((word_t*)((byte_t*)base + lane_bytes), (uint64_t)v | ((uint64_t)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Words base + off(0) .. base + off(N-1) of this lane, once all of them carry the tag; false when the wait ran out.  (Every branch
+// is wave-uniform for the compiler too: a divergent one has it copy the resident fragments around the loop.)
+template <int N, class Off>
+__device__ inline bool get_(const ClusterDesc& p, const word_t* base, Off off, uint32_t lane_bytes, uint32_t tag, uint32_t (&v)[N]) {
+    uint64_t t0 = 0;
+#pragma unroll 1
+    for (uint32_t tries = 0;; ++tries) {
+        uint64_t x[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = __hip_atomic_load((const word_t*)((const byte_t*)(base + off(i)) + lane_bytes), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t differ = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) { differ |= (uint32_t)(x[i] >> 32) ^ tag; v[i] = (uint32_t)x[i]; }
+        if (__ballot(differ != 0) == 0) return true;
+        if ((tries & 15) == 15) {
+            const uint64_t now = wall_clock64();
+            if (t0 == 0) t0 = now;
+            const uint32_t st = __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            if (now - t0 >= p.wait_ticks || (st & kStatusWaitExpired)) {
+                __hip_atomic_fetch_or(p.status, kStatusWaitExpired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return false;
+            }
+        }
+    }
+}
+
+// Place of this workgroup, and the tag of the launch's frame 0.
+struct Place { int li, d, b0, blk, m, cluster; uint32_t tag0; };
+template <class C> __device__ inline bool place_(const ClusterDesc& p, Place& w) {
+    __shared__ uint32_t sh[2];
+    if (threadIdx.x == 0) {
+        sh[0] = __hip_atomic_fetch_add(p.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh[1] = *p.epoch;
+    }
+    __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane((int)sh[0]);
+    const int blocks = (p.r.B + 15) / 16, cluster = t / C::S, pair = cluster / blocks;
+    if (pair >= p.r.L * p.r.D) return false;
+    w.m = t % C::S; w.cluster = cluster; w.blk = cluster % blocks; w.b0 = w.blk * C::RB;
+    w.li = __builtin_amdgcn_readfirstlane(p.r.lmap.idx[pair / p.r.D]); w.d = pair % p.r.D;
+    w.tag0 = ((uint32_t)__builtin_amdgcn_readfirstlane((int)sh[1]) * (uint32_t)p.launches + (uint32_t)p.launch) * (uint32_t)p.r.T + 1u;
+    return true;
+}
+
+}  // namespace
+
+// ---- forward ------------------------------------------------------------------------------------
+//   a = W_x x_t + b + W_h h_{t'}     i,f,o = sigmoid(a), g = tanh(a)     c_t = f c_{t'} + i g     h_t = o tanh(c_t)
+template <typename T, int S>
+__global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc cd) {
+    typedef Cl<T, S> C;
+    constexpr int KS = C::KS, PR = 4 / KS;                 // rows of a 16-row tile that a lane finishes
+    __shared__ __attribute__((aligned(16))) char lds[2 * C::RB * C::FWD_ROW];
+    __shared__ float red[KS == 2 ? 4 * 8 * 64 : 1];
+    __shared__ int expired;
+    const RecDesc& p = cd.r;
+    Place w;
+    if (threadIdx.x == 0) expired = 0;
+    if (!place_<C>(cd, w)) return;
+    const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
+    const int kh = wave / C::NU;                           // which part of the contraction
+    const int u = w.m * C::U + (wave % C::NU) * 16 + r;
+    const bool ok_u = u < H;
+    const uint32_t DH = (uint32_t)(D * H), G4 = DH * 4;
+    const buf_t gates = make_buf_(p.gates + w.li * p.sGi, (int64_t)Tn * B * G4 * 4);
+    const buf_t cbuf = make_buf_(p.c + w.li * p.sCi + (int64_t)d * Tn * B * H, (int64_t)Tn * B * H * 4);
+    const buf_t y = make_buf_((const T*)p.y + w.li * p.sYi, (int64_t)Tn * B * DH * sizeof(T));
+    word_t* const xch = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::FWD_SLOT;
+
+    uint4 wf[4][C::CW];
+    {
+        const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
+#pragma unroll
+        for (int c = 0; c < C::CW; ++c) {
+            const int k0 = (kh * C::CW + c) * C::KC;       // H is a multiple of EL: a fragment is whole or absent
+            const uint32_t vw = ok_u && k0 + g * C::EL < H ? (uint32_t)(u * H + g * C::EL) * (uint32_t)sizeof(T) : kOutOfRange;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wf[q][c] = buf_load16_(wh, vw, (uint32_t)(q * H * H + k0) * (uint32_t)sizeof(T));
+        }
+    }
+    // rows this lane finishes: row0 + i, i < PR
+    const int row0 = 4 * g + (KS == 2 ? 2 * kh : 0);
+    uint32_t vg[PR], vc[PR], vy[PR / C::VW];
+#pragma unroll
+    for (int i = 0; i < PR; ++i) {
+        const uint32_t row = w.b0 + row0 + i;
+        const bool ok = ok_u && (int)row < B;
+        vg[i] = ok ? (row * G4 + d * 4 * H + u) * 4u : kOutOfRange;
+        vc[i] = ok ? (row * H + u) * 4u : kOutOfRange;
+    }
+    // 4 bytes of h: one value, or (bf16) the values of two units, the even lane of the pair for the first of two rows
+#pragma unroll
+    for (int i = 0; i < PR / C::VW; ++i) {
+        const uint32_t row = w.b0 + row0 + i * C::VW + (C::VW == 2 ? (r & 1) : 0);
+        vy[i] = ok_u && (int)row < B ? (row * DH + d * H + (u & ~(C::VW - 1))) * (uint32_t)sizeof(T) : kOutOfRange;
+    }
+    float pre[4][PR];
+    auto load_pre = [&](int s) {
+        const uint32_t m = (uint32_t)(d == 0 ? s : Tn - 1 - s) * B;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < PR; ++i) pre[q][i] = buf_load_(gates, vg[i], (m * G4 + q * H) * 4u);
+    };
+    float cs[PR];
+#pragma unroll
+    for (int i = 0; i < PR; ++i) cs[i] = 0.f;
+    load_pre(0);
+#pragma unroll 1
+    for (int s = 0; s < Tn; ++s) {
+        const uint32_t m = (uint32_t)(d == 0 ? s : Tn - 1 - s) * B;
+        f32x4_t acc[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (KS == 1) acc[q] = f32x4_t{pre[q][0], pre[q][1], pre[q][2], pre[q][3]};
+            else acc[q] = kh == 0 ? f32x4_t{pre[q][0], pre[q][1], 0.f, 0.f} : f32x4_t{0.f, 0.f, pre[q][0], pre[q][1]};
+        }
+        if (s > 0) {
+            // h of the frame before, all units, into LDS: 16 threads to a row, words tid % 16 + 16 i
+            constexpr int N = C::RW / 16;
+            char* const hl = lds + (s & 1) * (C::RB * C::FWD_ROW);
+            const word_t* const slot = per_frame_(xch + (s & 1) * C::FWD_SLOT);
+            uint32_t v[N];
+            const bool ok = get_<N>(cd, slot, [](int i) { return 16 * i; }, (uint32_t)((tid >> 4) * C::RW + (tid & 15)) * 8u, w.tag0 + s, v);
+#pragma unroll
+            for (int i = 0; i < N; ++i) *(uint32_t*)(hl + (tid >> 4) * C::FWD_ROW + (tid & 15) * 4 + i * 64) = v[i];
+            if (!ok) expired = 1;
+            load_pre(s + 1 < Tn ? s + 1 : s);              // (after the exchange: its loads return in order behind these)
+            lds_barrier_();
+            if (__builtin_amdgcn_readfirstlane(expired)) return;
+            const char* hrow = hl + r * C::FWD_ROW + kh * (C::CW * 64) + g * 16;
+#pragma unroll
+            for (int c = 0; c < C::CW; ++c) {
+                const uint4 a = *(const uint4*)(hrow + c * 64);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, wf[q][c]);
+            }
+            if constexpr (KS == 2) {                       // swap the halves: each wave finishes two of the four rows
+                float* mine = red + (wave * 8) * 64 + lane;
+                const float* other = red + ((wave ^ C::NU) * 8) * 64 + lane;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    mine[(2 * q) * 64] = kh == 0 ? acc[q][2] : acc[q][0];
+                    mine[(2 * q + 1) * 64] = kh == 0 ? acc[q][3] : acc[q][1];
+                }
+                lds_barrier_();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[q][0] = (kh == 0 ? acc[q][0] : acc[q][2]) + other[(2 * q) * 64];
+                    acc[q][1] = (kh == 0 ? acc[q][1] : acc[q][3]) + other[(2 * q + 1) * 64];
+                }
+            }
+        } else {
+            if constexpr (KS == 2) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { acc[q][0] = pre[q][0]; acc[q][1] = pre[q][1]; }
+            }
+            load_pre(Tn > 1 ? 1 : 0);
+        }
+        float h[PR];
+#pragma unroll
+        for (int i = 0; i < PR; ++i) {                     // the gates replace the pre-activations
+            acc[0][i] = sigmoidf_(acc[0][i]); acc[1][i] = sigmoidf_(acc[1][i]);
+            acc[2][i] = tanhf_(acc[2][i]); acc[3][i] = sigmoidf_(acc[3][i]);
+            cs[i] = acc[1][i] * cs[i] + acc[0][i] * acc[2][i];
+            h[i] = acc[3][i] * tanhf_(cs[i]);
+        }
+        // h first: the other workgroups wait for it (rows past the batch and units past H too: they are read, as zeros or unused)
+        word_t* const out = per_frame_(xch + ((s + 1) & 1) * C::FWD_SLOT);
+        const uint32_t out_lane = (uint32_t)((row0 + (C::VW == 2 ? r & 1 : 0)) * C::RW + u / C::VW) * 8u;
+        uint32_t hw[PR / C::VW];
+#pragma unroll
+        for (int i = 0; i < PR / C::VW; ++i) {
+            if constexpr (C::VW == 2) {                    // swap with the neighbouring unit: two units of one row to a word
+                const uint32_t own = pack_bf16(h[2 * i], h[2 * i + 1]);
+                const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+                hw[i] = (r & 1) ? (nb >> 16) | (own & 0xffff0000u) : (own & 0xffffu) | (nb << 16);
+            } else {
+                hw[i] = __builtin_bit_cast(uint32_t, h[i]);
+            }
+            if (s + 1 < Tn) put_(out + i * C::VW * C::RW, out_lane, hw[i], w.tag0 + s + 1);
+        }
+#pragma unroll
+        for (int i = 0; i < PR / C::VW; ++i) buf_store_(__builtin_bit_cast(float, hw[i]), y, vy[i], m * DH * (uint32_t)sizeof(T));
+#pragma unroll
+        for (int i = 0; i < PR; ++i) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) buf_store_(acc[q][i], gates, vg[i], (m * G4 + q * H) * 4u);
+            buf_store_(cs[i], cbuf, vc[i], m * H * 4u);
+        }
+    }
+}
+
+// ---- backward -----------------------------------------------------------------------------------
+//   dh_t = dY_t + da_{t''} W_h  (t'' = the frame handled before)
+//   do = dh tanh(c_t)            dc = dc_rec + dh o (1 - tanh^2 c_t)
+//   di = dc g, dg = dc i, df = dc c_{t'}, dc_rec <- dc f
+//   da = (di i(1-i), df f(1-f), dg (1-g^2), do o(1-o))
+// A thread finishes one unit of the workgroup, rows tid / U + i * 256 / U; it adds the partial sums of its positions in the order
+// of the members.  The column sums of da (bias gradients) run over all frames in registers: one row per row block.
+template <typename T, int S>
+__global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDesc cd) {
+    typedef Cl<T, S> C;
+    constexpr int U = C::U, PPT = C::PPT, RSTEP = 256 / U;
+    constexpr int OP_BYTES = 2 * C::RB * C::BWD_ROW, W_BYTES = 2 * 16 * C::W_ROW * 4;
+    __shared__ __attribute__((aligned(16))) char lds[OP_BYTES > W_BYTES ? OP_BYTES : W_BYTES];
+    __shared__ float bred[4][256];
+    __shared__ int expired;
+    const RecDesc& p = cd.r;
+    Place w;
+    if (threadIdx.x == 0) expired = 0;
+    if (!place_<C>(cd, w)) return;
+    const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
+    const uint32_t DH = (uint32_t)(D * H), G4 = DH * 4;
+    const buf_t gates = make_buf_(p.gates + w.li * p.sGi, (int64_t)Tn * B * G4 * 4);
+    const buf_t cbuf = make_buf_(p.c + w.li * p.sCi + (int64_t)d * Tn * B * H, (int64_t)Tn * B * H * 4);
+    const buf_t dy = make_buf_(p.dy + w.li * p.sDYi, (int64_t)Tn * B * DH * 4);
+    const buf_t da = make_buf_((const T*)p.da + w.li * p.sDAi, (int64_t)Tn * B * G4 * sizeof(T));
+    word_t* const xch = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT;
+
+    // cell part: this thread's unit and rows
+    const int uu = tid % U, cu = w.m * U + uu;
+    const bool ok_c = cu < H;
+    uint32_t vg[PPT], vc[PPT], vy[PPT];
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) {
+        const uint32_t row = w.b0 + tid / U + i * RSTEP;
+        const bool ok = ok_c && (int)row < B;
+        vg[i] = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange;
+        vc[i] = ok ? (row * H + cu) * 4u : kOutOfRange;
+        vy[i] = ok ? (row * DH + d * H + cu) * 4u : kOutOfRange;
+    }
+    float in_dy[PPT], in_c[PPT], in_g[PPT][4];             // inputs of the next frame to be finished
+    auto load_in = [&](int s) {
+        const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;                    // reverse of the forward order
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) {
+            in_dy[i] = buf_load_(dy, vy[i], m * DH * 4u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) in_g[i][q] = buf_load_(gates, vg[i], (m * G4 + q * H) * 4u);
+        }
+    };
+    auto load_c = [&](int s, float (&c)[PPT]) {            // s = T: the cell state before the first frame is 0
+        const bool end = s >= Tn;
+        const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - (end ? Tn - 1 : s) : (end ? Tn - 1 : s)) * B;
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) c[i] = buf_load_(cbuf, end ? kOutOfRange : vc[i], m * H * 4u);
+    };
+    float c_prev[PPT];
+    load_c(0, in_c);
+    load_in(0);
+    load_c(1, c_prev);
+
+    // product part: columns n of W_h (tiles wave, wave + 4, ...), rows: the four gates of this workgroup's units
+    // Rows of W_h come in as they lie, a k-chunk (16 words of a column's fragments deep) at a time, two chunks ahead, and the
+    // fragments are read from LDS: column by column from memory they took 384 two-byte loads a lane (bf16 x 360: 60 us).
+    uint4 wf[C::NT][C::BCH];
+    {
+        constexpr int EPW = 4 / (int)sizeof(T);            // rows of W_h to a word
+        const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
+        uint4 st[3][C::NT];                                // words tid + 256 j of the chunk's 16 x KP / 4 quadruples
+        auto load = [&](int c, uint4 (&v)[C::NT]) {
+            const int q = c * C::KC / U, unit0 = w.m * U + c * C::KC % U;              // a chunk lies in one gate
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j) {
+                const int x = tid + 256 * j, k = unit0 + x / (C::KP / 4) * EPW, n = x % (C::KP / 4) * 4;
+                const uint32_t at = k < H && n < H ? (uint32_t)((q * H + k) * H + n) * (uint32_t)sizeof(T) : kOutOfRange;   // (H: a multiple of EL)
+                if constexpr (EPW == 1) {
+                    v[j] = buf_load16_(wh, at, 0u);
+                } else {
+                    const uint2 lo = buf_load8_(wh, at, 0u), hi = buf_load8_(wh, at, (uint32_t)H * 2u);
+                    v[j] = make_uint4(__builtin_amdgcn_perm(hi.x, lo.x, 0x05040100u), __builtin_amdgcn_perm(hi.x, lo.x, 0x07060302u),
+                                      __builtin_amdgcn_perm(hi.y, lo.y, 0x05040100u), __builtin_amdgcn_perm(hi.y, lo.y, 0x07060302u));
+                }
+            }
+        };
+        load(0, st[0]);
+        load(1, st[1]);
+#pragma unroll
+        for (int c = 0; c < C::BCH; ++c) {
+            uint32_t* const buf = (uint32_t*)lds + (c & 1) * (16 * C::W_ROW);
+            if (c + 2 < C::BCH) load(c + 2, st[(c + 2) % 3]);
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j) {
+                const int x = tid + 256 * j;
+                *(uint4*)(buf + x / (C::KP / 4) * C::W_ROW + x % (C::KP / 4) * 4) = st[c % 3][j];
+            }
+            lds_barrier_();
+            const uint32_t* col = buf + 4 * g * C::W_ROW + wave * 16 + r;
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j)
+                wf[j][c] = make_uint4(col[64 * j], col[64 * j + C::W_ROW], col[64 * j + 2 * C::W_ROW], col[64 * j + 3 * C::W_ROW]);
+        }
+        lds_barrier_();                                    // the operand of the products goes into the same LDS
+    }
+    float dcr[PPT], bs[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) dcr[i] = 0.f;
+
+#pragma unroll 1
+    for (int s = 0; s < Tn; ++s) {
+        const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;
+        float dh[PPT];
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) dh[i] = 0.f;
+        if (s > 0) {
+            // partial sums for this workgroup's units: words [member][row][unit]
+            const word_t* const slot = per_frame_(xch + (s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U);
+            constexpr int PB = PPT * S <= 32 ? PPT : 2;          // positions gathered together
+            static_assert(PPT % PB == 0, "gather blocks");
+            bool ok = true;
+#pragma unroll
+            for (int i0 = 0; i0 < PPT; i0 += PB) {
+                uint32_t v[PB * S];
+                ok &= get_<PB * S>(cd, slot, [&](int j) { return (j % S) * C::RB * U + 256 * (i0 + j / S); }, (uint32_t)tid * 8u, w.tag0 + s, v);
+#pragma unroll
+                for (int i = 0; i < PB; ++i)
+#pragma unroll
+                    for (int j = 0; j < S; ++j) dh[i0 + i] += __builtin_bit_cast(float, v[i * S + j]);
+            }
+            if (!ok) expired = 1;
+        }
+        char* const al = lds + (s & 1) * (C::RB * C::BWD_ROW);
+        float a4[PPT][4];
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) {
+            // rows past the batch and units past H: all gates were read as 0, so all four results are 0
+            const float dhv = in_dy[i] + dh[i], ig = in_g[i][0], fg = in_g[i][1], gg = in_g[i][2], og = in_g[i][3];
+            const float tc = tanhf_(in_c[i]);
+            const float dov = dhv * tc;
+            const float dcv = dcr[i] + dhv * og * (1.f - tc * tc);
+            const float di = dcv * gg, dg = dcv * ig, df = dcv * c_prev[i];
+            dcr[i] = dcv * fg;
+            a4[i][0] = di * ig * (1.f - ig); a4[i][1] = df * fg * (1.f - fg);
+            a4[i][2] = dg * (1.f - gg * gg); a4[i][3] = dov * og * (1.f - og);
+            T* arow = (T*)(al + (tid / U + i * RSTEP) * C::BWD_ROW) + uu;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { bs[q] += a4[i][q]; arow[q * U] = Elem<T>::from(a4[i][q]); }
+            in_c[i] = c_prev[i];
+        }
+        if (s + 1 < Tn) {
+            load_in(s + 1);
+            load_c(s + 2, c_prev);
+            lds_barrier_();
+            if (__builtin_amdgcn_readfirstlane(expired)) return;
+            f32x4_t acc[C::NT];
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            const char* arow = al + r * C::BWD_ROW + g * 16;
+#pragma unroll
+            for (int c = 0; c < C::BCH; ++c) {
+                const uint4 a = *(const uint4*)(arow + c * 64);
+#pragma unroll
+                for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a, wf[j][c]);
+            }
+            word_t* const out = per_frame_(xch + ((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U);
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j) {
+                const int n0 = (wave + 4 * j) * 16;        // (a tile lies in one workgroup's units: U is a multiple of 16)
+                word_t* const to = out + ((n0 / U) * S * C::RB * U + n0 % U);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    put_(to + i * U, (uint32_t)(4 * g * U + r) * 8u, __builtin_bit_cast(uint32_t, (float)acc[j][i]), w.tag0 + s + 1);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) {
+            const uint32_t va = vg[i] == kOutOfRange ? kOutOfRange : vg[i] / (4u / (uint32_t)sizeof(T));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) buf_store_(Elem<T>::from(a4[i][q]), da, va, (m * G4 + q * H) * (uint32_t)sizeof(T));
+        }
+    }
+    // column sums over the threads of a unit, in order
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bred[q][tid] = bs[q];
+    __syncthreads();
+    if (tid < U && ok_c) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v = bred[q][tid];
+#pragma unroll
+            for (int k = 1; k < RSTEP; ++k) v += bred[q][tid + k * U];
+            p.dbp[w.li * p.sDBi + (int64_t)w.blk * G4 + (int64_t)d * 4 * H + (int64_t)q * H + cu] = v;
+        }
+    }
+}
+
+// ---- rule and launchers -----------------------------------------------------------------------------
+namespace {
+
+// Members of a cluster: enough to hold W_h, in the sizes that are built; U units each.
+int cluster_members(const RecDesc& d) {
+    const int U = d.precision ? 64 : 32, need = (d.H + U - 1) / U;
+    if (d.precision) return need <= 4 ? 4 : need <= 6 ? 6 : need <= 8 ? 8 : need <= 10 ? 10 : 0;
+    return need <= 8 ? 8 : need <= 10 ? 10 : need <= 12 ? 12 : need <= 16 ? 16 : 0;
+}
+int cluster_blocks(const RecDesc& d) { return (d.B + 15) / 16; }
+
+template <typename T, int S> void launch_cluster_t(const ClusterDesc& p, bool backward, hipStream_t s) {
+    const unsigned grid = (unsigned)(p.r.L * p.r.D * cluster_blocks(p.r) * S);
+    if (backward) hipLaunchKernelGGL((rec_backward_cluster_kernel<T, S>), dim3(grid), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((rec_forward_cluster_kernel<T, S>), dim3(grid), dim3(256), 0, s, p);
+}
+
+}  // namespace
+
+// Where the clusters run, by their workgroups: a workgroup takes a compute unit (a SIMD's whole register file per wave; in fp32 up to
+// 320 cells two share one), the rest of a larger grid waits, and the frame-by-frame kernels win once they stream W_h for enough
+// rows at a time.  us per frame, frame by frame against clusters (workgroups):
+//   fp32 forward  16 x 256 cells, batch 32 (256) 11.9 / 4.5; 16 x 320, 128 (1280) 29.1 / 25.3; 32 x 256, 128 (2048) 28.1 / 29.6
+//   fp32 backward 16 x 256, 32 (256) 12.8 / 5.6; 16 x 512, 64 (1024) 47 / 41; 32 x 320, 64 (1280) 34 / 33; 32 x 256, 128 (2048) 33 / 41
+//   bf16 forward  10 x 360, 50 (240) 8.2 / 3.4; 32 x 512, 64 (1024) 21.3 / 16.1, 128 (2048) 28.5 / 31.0; 16 x 640, 64 (640) 17.3 / 13.4,
+//                 96 (960; between the other kernels of an iteration) 20.6 / 22; 16 x 256, 128 (512) 12.1 / 7.7; 32 x 256, 128 (1024) 14.3 / 15.1
+//   bf16 backward 10 x 360, 50 (240) 11.5 / 5.9; 16 x 256, 128 (512) 13.9 / 10.0; 32 x 256, 128 (1024) 17.0 / 18.6; 32 x 512, 32 (512)
+//                 18.9 / 16.4, 64 (1024) 23 / 56 (the exchange of fp32 sums); 16 x 640, 16 (160) 18.2 / 9.5, 32 (320) 20.0 / 20.8
+// More rows to a cluster (two and four tiles) shorten nothing: 32 x 512, 64: 16 -> 15 and 18; the exchange grows with the rows.
+bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count) {
+    if (!d.direct || d.T < 2 || d.H <= 128 || !rec_aligned(d) || d.L < 1 || d.L > 128 || d.D < 1 || d.D > 2 || d.B < 1) return false;
+    if ((int64_t)d.T * d.B * d.D * d.H * 16 >= (int64_t)kOutOfRange) return false;     // buffer offsets
+    const int S = cluster_members(d);
+    if (S == 0 || cu_count < 4 * S) return false;
+    const int64_t workgroups = (int64_t)d.L * d.D * cluster_blocks(d) * S;
+    if (d.precision) return workgroups <= (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640);
+    return workgroups <= (backward ? 1024 : 1280);
+}
+
+int rec_cluster_batch_tiles(const RecDesc& d) { return cluster_blocks(d); }
+
+int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward) {
+    const int64_t S = cluster_members(d), KP = S * (d.precision ? 64 : 32), row = backward ? S * KP : d.precision ? KP / 2 : KP;
+    return (int64_t)d.L * d.D * cluster_blocks(d) * 2 * 16 * row;
+}
+
+hipError_t launch_rec_cluster(const ClusterDesc& p, bool backward, int cu_count, hipStream_t s) {
+    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || !p.ticket || !p.epoch || !p.status) return hipErrorInvalidValue;
+    const int S = cluster_members(p.r);
+    if (p.r.precision) {
+        switch (S) {
+            case 4: launch_cluster_t<bf16_t, 4>(p, backward, s); break;
+            case 6: launch_cluster_t<bf16_t, 6>(p, backward, s); break;
+            case 8: launch_cluster_t<bf16_t, 8>(p, backward, s); break;
+            default: launch_cluster_t<bf16_t, 10>(p, backward, s); break;
+        }
+    } else {
+        switch (S) {
+            case 8: launch_cluster_t<float, 8>(p, backward, s); break;
+            case 10: launch_cluster_t<float, 10>(p, backward, s); break;
+            case 12: launch_cluster_t<float, 12>(p, backward, s); break;
+            default: launch_cluster_t<float, 16>(p, backward, s); break;
+        }
+    }
+    return hipGetLastError();
+}
+
+}  // namespace adpsgd

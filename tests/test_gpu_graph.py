@@ -95,6 +95,42 @@ def test_replayed_iterations_equal_direct_ones_on_every_replay(pattern, prec):
     eng.close(); ref.close()
 
 
+@pytest.mark.parametrize("prec,hidden", [(0, 256), (1, 200)])
+def test_recurrences_on_clusters_replayed_beside_another_handle(prec, hidden):
+    # two handles of which one is recorded and replayed, their work in flight on two streams at the same time; a third, alone,
+    # makes the same iterations
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("graph replay, clusters", prec, hidden, flush=True)
+    L, lr, shape = 4, 0.1, Shape(24, hidden, 2, 1, 0, 40, 40, 6)
+    w0 = torch.from_numpy(synth.initial_model(5, lstm.param_count(shape), 0.1)).cuda()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    eng, other, ref = _engine(shape, L, S.D1D, prec, s1), _engine(shape, L, S.D1D, prec, s2), _engine(shape, L, S.D1D, prec, s2)
+    dev = [[(torch.from_numpy(f).cuda(), torch.from_numpy(y).cuda()) for f, y in _batch(shape, L, k)] for k in range(2)]
+    torch.cuda.synchronize()
+    for e in (eng, other, ref):
+        e.set_params(-1, w0)
+        e.step(dev[0], lr); e.step(dev[1], lr)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s1):
+        eng.capture_begin()
+        eng.step(dev[0], lr); eng.step(dev[1], lr)
+        graph = eng.capture_end()
+    for _ in range(4):
+        Bd.adpsgd_graph_replay(graph)
+        other.step(dev[0], lr); other.step(dev[1], lr)
+    torch.cuda.synchronize()
+    for _ in range(4):
+        ref.step(dev[0], lr); ref.step(dev[1], lr)
+    torch.cuda.synchronize()
+    for i in range(L):
+        want = _bits(ref.params(i))
+        assert (_bits(eng.params(i)) == want).all() and (_bits(other.params(i)) == want).all(), i
+    Bd.adpsgd_graph_destroy(graph)
+    for e in (eng, other, ref):
+        e.close()
+
+
 def test_replay_of_the_model_free_update_is_bit_exact_against_the_oracle():
     import torch
     from paper_2110_11199_amd import binding as Bd

@@ -102,6 +102,13 @@ def test_gradient_with_all_frames_on_one_compute_unit(hidden, batch, frames, pre
     _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
 
 
+@pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 256), (0, 260), (0, 384), (0, 512), (1, 136), (1, 256), (1, 360), (1, 512), (1, 640)])
+@pytest.mark.parametrize("batch,frames", [(1, 2), (17, 5), (32, 3)])
+def test_gradient_with_all_frames_on_clusters_of_compute_units(prec, hidden, batch, frames):
+    # every cluster size, whole and with units past the hidden size; one row, one row more than a block, whole blocks
+    _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
+
+
 def _check_gradient(shape, L, prec, tune=()):
     import torch
     print("lstm grad", shape, L, prec, flush=True)
@@ -403,4 +410,20 @@ def test_persistent_kernel_wait_runs_out_and_is_reported():
     with pytest.raises(Bd.AdpsgdError) as ei:
         e.step(_to_dev(_batches(shape, 2, 1)), 0.1)
     assert ei.value.code == Bd.EHIP
+    e.close()
+
+
+def test_cluster_wait_runs_out_and_is_reported():
+    # 26 clusters of 10 workgroups on 256 compute units: the last one waits until another is done, and a wait bound of 0
+    # microseconds gives up; every workgroup returns and the handle reports it
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    shape = Shape(8, 640, 1, 1, 0, 8, 48, 8)
+    e = _engine(shape, 8, S.FIXED_RING, 1)
+    e.tune(Bd.TUNE_REC_WAIT_US, 0)
+    e.set_params(-1, torch.from_numpy(synth.initial_model(0, e.P, 0.1)).cuda())
+    e.step(_to_dev(_batches(shape, 8, 0)), 0.1)
+    with pytest.raises(Bd.AdpsgdError) as ei:
+        e.status()
+    assert ei.value.code == Bd.EHIP and "wait" in str(ei.value)
     e.close()
