@@ -205,9 +205,9 @@ bool use_cluster(const adpsgd_handle* h, const RecDesc& r, bool backward) {
            (size_t)rec_cluster_exchange_words(r, backward) * 8 <= h->exchange_bytes;
 }
 
-// Turns the status bits a kernel has raised (as last copied to the host) into an error.
+// Turns the status bits that kernels have raised into an error.
 int status_error(const adpsgd_handle* h) {
-    const uint32_t st = h->status_host ? *h->status_host : 0u;
+    const uint32_t st = h->status_host ? (h->status_host[0] ? kStatusBadLabel : 0u) | (h->status_host[1] ? kStatusWaitExpired : 0u) : 0u;
     if (st & kStatusWaitExpired)
         return fail(ADPSGD_EHIP, "a bounded wait between the workgroups of a persistent recurrent kernel ran out in an earlier "
                                  "step; the results of this handle are not valid");
@@ -564,12 +564,11 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     if (int rc = gemm(h, g, "output GEMM")) return rc;
 
     SoftmaxDesc sm{};
-    sm.precision = prec; sm.L = n; sm.lmap = act; sm.L_all = L; sm.rows = M; sm.C = C;
-    for (int i = 0; i < 4; ++i) sm.active_bits[i] = bits[i];
+    sm.precision = prec; sm.L = n; sm.lmap = act; sm.rows = M; sm.C = C;
     sm.status = h->status;
     sm.logits = h->logits; sm.sLi = M * C; sm.y = h->labels; sm.sYi = M;
-    sm.dlogits = h->dlogits; sm.sDi = M * C; sm.row_loss = h->row_loss; sm.loss = h->loss;
-    if (int rc = mark(h, 4, 2)) return rc;
+    sm.dlogits = h->dlogits; sm.sDi = M * C; sm.row_loss = h->row_loss;
+    if (int rc = mark(h, 4, 1)) return rc;
     HIPCHK(launch_softmax_ce(sm, s), "softmax cross-entropy");
 
     // ---- backward: output layer(s) ----
@@ -582,7 +581,13 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     g.C = Gr(h->ix_wo); g.ldc = F; g.sCi = Pp;
     if (int rc = gemm(h, g, "dW_o GEMM")) return rc;
     if (int rc = mark(h, 5, 1)) return rc;
-    HIPCHK(launch_colsum(prec, h->dlogits, C, M * C, M, C, Gr(h->ix_bo), Pp, n, act, s), "db_o");
+    ColsumDesc cs{};
+    cs.precision = prec; cs.L = n; cs.lmap = act; cs.rows = M; cs.sOi = Pp;
+    cs.in = h->dlogits; cs.ld = C; cs.sIi = M * C; cs.N = C; cs.out = Gr(h->ix_bo);
+    cs.loss = h->loss; cs.row_loss = h->row_loss; cs.L_all = L;
+    for (int i = 0; i < 4; ++i) cs.active_bits[i] = bits[i];
+    HIPCHK(launch_colsum(cs, s), "db_o and losses");
+    cs.loss = nullptr;
     // d(z) = dlogits W_o
     g = G();
     g.a_kc = 1; g.b_kc = 0; g.c_elem = h->Bn ? 1 : 0;
@@ -600,7 +605,8 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         g.C = Gr(h->ix_wp); g.ldc = DH; g.sCi = Pp;
         if (int rc = gemm(h, g, "dW_p GEMM")) return rc;
         if (int rc = mark(h, 5, 1)) return rc;
-        HIPCHK(launch_colsum(prec, h->dz, h->Bn, M * h->Bn, M, h->Bn, Gr(h->ix_bp), Pp, n, act, s), "db_p");
+        cs.in = h->dz; cs.ld = h->Bn; cs.sIi = M * h->Bn; cs.N = h->Bn; cs.out = Gr(h->ix_bp);
+        HIPCHK(launch_colsum(cs, s), "db_p");
         g = G();
         g.a_kc = 1; g.b_kc = 0; g.c_elem = 0;
         g.M = (int)M; g.N = (int)DH; g.K = h->Bn;
@@ -629,7 +635,8 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         // the resident one one per batch tile)
         const int64_t dbrows = persist ? (int64_t)T : resident ? rec_resident_batch_tiles(r) : cluster ? rec_cluster_batch_tiles(r)
                                        : (int64_t)T * rec_backward_batch_tiles(r);
-        r.dbp = h->dbp; r.sDBi = dbrows * G4;
+        const bool db_direct = dbrows == 1;                // a single row of partial sums is the bias gradient
+        r.dbp = db_direct ? Gr(h->ix_b[l]) : h->dbp; r.sDBi = db_direct ? Pp : dbrows * G4;
         if (persist) {
             if (int rc = mark(h, 3, persist_launches, rec_flops(n), rec_bytes_bwd(n, true))) return rc;
             if (int rc = run_persistent(r, l, true)) return rc;
@@ -673,8 +680,12 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
             HIPCHK(launch_zero(Gr(h->ix_wh[l]), Pp, G4 * H, n, act, s), "zero dW_h");
         }
         // db = sum over the frames (and batch tiles) of the column sums the backward steps left behind
-        if (int rc = mark(h, 5, 1)) return rc;
-        HIPCHK(launch_colsum(0, h->dbp, G4, dbrows * G4, dbrows, (int)G4, Gr(h->ix_b[l]), Pp, n, act, s), "db");
+        if (!db_direct) {
+            if (int rc = mark(h, 5, 1)) return rc;
+            ColsumDesc cd = cs;
+            cd.precision = 0; cd.in = h->dbp; cd.ld = G4; cd.sIi = dbrows * G4; cd.rows = dbrows; cd.N = (int)G4; cd.out = Gr(h->ix_b[l]);
+            HIPCHK(launch_colsum(cd, s), "db");
+        }
         if (l > 0) {
             // dY_{l-1} = da W_x  (sum over both directions: K = D*4H)
             g = G();
@@ -736,8 +747,11 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     hipError_t e = hipHostMalloc(&mirror, 64, hipHostMallocDefault);
     if (e != hipSuccess) { delete h; return hipfail(e, "pinned status word"); }
     h->status_host = (volatile uint32_t*)mirror;
-    *h->status_host = 0u;
+    h->status_host[0] = h->status_host[1] = 0u;
     e = hipMemsetAsync(h->status, 0, 256, s);
+    void* mirror_dev = nullptr;
+    if (e == hipSuccess) e = hipHostGetDevicePointer(&mirror_dev, mirror, 0);
+    if (e == hipSuccess) e = hipMemcpyAsync(h->status + 2, &mirror_dev, sizeof(mirror_dev), hipMemcpyHostToDevice, s);   // (ends before this function does)
     if (e == hipSuccess) e = hipMemsetAsync(h->params[0], 0, slab, s);
     if (e == hipSuccess && h->tau == 1) e = hipMemsetAsync(h->params[1], 0, slab, s);
     if (e == hipSuccess && !h->flat) e = hipMemsetAsync(h->grads, 0, slab, s);
@@ -846,8 +860,6 @@ static int step_impl(adpsgd_t h, const void* const* batch_ptrs, float lr, const 
     }
     HIPCHK(launch_update(u, h->stream), "mix + update");
     if (int rc = mark(h, -1)) return rc;
-    if (!h->flat)    // what the kernels of this step have reported reaches the host with the stream, without a wait
-        HIPCHK(hipMemcpyAsync((void*)h->status_host, h->status, 4, hipMemcpyDeviceToHost, h->stream), "status copy");
     if (h->tau == 1) h->cur = 1 - h->cur;
     if (u.shadow) h->shadow_valid = true;
     h->k += 1;
@@ -1006,7 +1018,6 @@ int adpsgd_delay(uint64_t microseconds, void* hip_stream) {
 int adpsgd_status(adpsgd_t h) {
     if (!h) return fail(ADPSGD_EINVAL, "NULL handle");
     if (h->capturing) return fail(ADPSGD_EINVAL, "not while iterations are being recorded (adpsgd_capture_begin)");
-    if (!h->flat) HIPCHK(hipMemcpyAsync((void*)h->status_host, h->status, 4, hipMemcpyDeviceToHost, h->stream), "status copy");
     HIPCHK(hipStreamSynchronize(h->stream), "stream sync");
     return status_error(h);
 }

@@ -99,7 +99,7 @@ __device__ inline void lse_merge_(float& m, float& s, float m2, float s2) {
 __device__ inline int checked_label_(const SoftmaxDesc& p, int li, int64_t row) {
     const int y = p.y[li * p.sYi + row];
     if (y >= 0 && y < p.C) return y;
-    if (threadIdx.x == 0 && p.status) atomicOr(p.status, kStatusBadLabel);
+    if (threadIdx.x == 0 && p.status) raise_status_(p.status, kStatusBadLabel);
     return y < 0 ? 0 : p.C - 1;
 }
 
@@ -134,25 +134,6 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(SoftmaxDesc p) {
         dz[c] = Elem<T>::from(pr * scale);
     }
     if (threadIdx.x == 0) p.row_loss[li * p.rows + row] = -((z[y] - m) - logf(s));
-}
-
-// One workgroup per learner of the handle; a learner that took no part in the iteration reports 0.
-__global__ __launch_bounds__(256) void loss_reduce_kernel(const float* row_loss, int64_t rows, float* loss, SoftmaxDesc p) {
-    const int li = blockIdx.x;
-    if (!((p.active_bits[li >> 5] >> (li & 31)) & 1u)) {
-        if (threadIdx.x == 0) loss[li] = 0.f;
-        return;
-    }
-    float s = 0.f;
-    for (int64_t r = threadIdx.x; r < rows; r += 256) s += row_loss[li * rows + r];
-    __shared__ float sh[256];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) sh[threadIdx.x] += sh[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss[li] = sh[0] / (float)rows;
 }
 
 // Single-pass version: the whole row of logits lives in registers (NV float4 per thread, C <= 4*NT*NV),
@@ -243,50 +224,107 @@ static void launch_softmax_t(const SoftmaxDesc& d, hipStream_t s) {
 }
 
 hipError_t launch_softmax_ce(const SoftmaxDesc& d, hipStream_t s) {
-    if (d.L < 1 || d.L > d.L_all || d.L_all > 128) return hipErrorInvalidValue;
+    if (d.L < 1 || d.L > 128) return hipErrorInvalidValue;
     if (d.precision == 0) launch_softmax_t<float>(d, s);
     else launch_softmax_t<bf16_t>(d, s);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3((unsigned)d.L_all), dim3(256), 0, s, d.row_loss, d.rows, d.loss, d);
     return hipGetLastError();
 }
 
 // ---- column sums -----------------------------------------------------------------
-// Workgroup = 64 columns x 4 row slices; fixed summation order (deterministic).
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T* in, int64_t ld, int64_t sIi, int64_t rows, int N,
-                                                     float* out, int64_t sOi, LearnerMap lmap) {
-    const int li = lmap.idx[blockIdx.y];
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int slice = threadIdx.x >> 6;
-    const T* src = in + li * sIi;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    if (col < N) {
-        int64_t r = slice;
-        for (; r + 12 < rows; r += 16) {
-            s0 += Elem<T>::to(__builtin_nontemporal_load(src + r * ld + col));
-            s1 += Elem<T>::to(__builtin_nontemporal_load(src + (r + 4) * ld + col));
-            s2 += Elem<T>::to(__builtin_nontemporal_load(src + (r + 8) * ld + col));
-            s3 += Elem<T>::to(__builtin_nontemporal_load(src + (r + 12) * ld + col));
-        }
-        for (; r < rows; r += 4) s0 += Elem<T>::to(src[r * ld + col]);
+// Workgroup = 128 columns, four to a thread, x SL row slices; a slice's sums of four rows at a time and the slices are added in a
+// fixed order (deterministic).  Bound by the read of the input once enough of it is in flight: with 64 columns x 4 slices, one
+// column to a thread, 1050 rows took 33 us at any width (bf16 5 x 1050 x 120: 33 -> 5 us, x 3000: 35 -> 9).
+// The workgroups behind the columns add the row losses of a learner, if asked for; a learner that took no part reports 0.
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+    __device__ static float4 load(const float* p) {
+        const vf4_t v = __builtin_nontemporal_load((const vf4_t*)p);
+        return make_float4(v.x, v.y, v.z, v.w);
     }
-    __shared__ float sh[4][64];
-    sh[slice][threadIdx.x & 63] = (s0 + s1) + (s2 + s3);
+};
+template <> struct Quad<bf16_t> {
+    __device__ static float4 load(const bf16_t* p) {
+        const vu2_t v = __builtin_nontemporal_load((const vu2_t*)p);
+        return make_float4(__builtin_bit_cast(float, v.x << 16), __builtin_bit_cast(float, v.x & 0xffff0000u),
+                           __builtin_bit_cast(float, v.y << 16), __builtin_bit_cast(float, v.y & 0xffff0000u));
+    }
+};
+__device__ inline float4 add4_(const float4& a, const float4& b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+
+template <typename T, int SL>
+__global__ __launch_bounds__(32 * SL) void colsum_kernel(ColsumDesc p) {
+    __shared__ float4 sh[SL][32];
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x * 128 >= p.N) {                    // row losses: blockIdx.x runs to L_all past the columns, y = 0
+        const int li = blockIdx.x - (p.N + 127) / 128;
+        if (blockIdx.y != 0) return;
+        if (!((p.active_bits[li >> 5] >> (li & 31)) & 1u)) {
+            if (tid == 0) p.loss[li] = 0.f;
+            return;
+        }
+        float s = 0.f;
+        for (int64_t r = tid; r < p.rows; r += 32 * SL) s += p.row_loss[li * p.rows + r];
+        float* f = (float*)sh;
+        f[tid] = s;
+        __syncthreads();
+        for (int off = 16 * SL; off > 0; off >>= 1) {
+            if (tid < off) f[tid] += f[tid + off];
+            __syncthreads();
+        }
+        if (tid == 0) p.loss[li] = f[0] / (float)p.rows;
+        return;
+    }
+    const int li = p.lmap.idx[blockIdx.y], tx = tid & 31, slice = tid >> 5;
+    const int col = blockIdx.x * 128 + 4 * tx;
+    const T* src = (const T*)p.in + li * p.sIi + col;
+    float4 s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (col < p.N) {
+        int64_t r = slice;
+        for (; r + 7 * SL < p.rows; r += 8 * SL) {
+            float4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = Quad<T>::load(src + (r + j * SL) * p.ld);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[j & 3] = add4_(s[j & 3], v[j]);
+        }
+        for (; r + 3 * SL < p.rows; r += 4 * SL) {
+            float4 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = Quad<T>::load(src + (r + j * SL) * p.ld);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[j] = add4_(s[j], v[j]);
+        }
+        for (; r < p.rows; r += SL) s[0] = add4_(s[0], Quad<T>::load(src + r * p.ld));
+    }
+    sh[slice][tx] = add4_(add4_(s[0], s[1]), add4_(s[2], s[3]));
     __syncthreads();
-    if (slice == 0 && col < N)
-        out[li * sOi + col] = (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
+    if (slice < 4) {                                       // a quarter of the slices each, then the quarters
+        float4 t = sh[slice * (SL / 4)][tx];
+#pragma unroll
+        for (int j = 1; j < SL / 4; ++j) t = add4_(t, sh[slice * (SL / 4) + j][tx]);
+        s[0] = t;
+    }
+    __syncthreads();
+    if (slice < 4) sh[slice][tx] = s[0];
+    __syncthreads();
+    if (slice == 0 && col < p.N) *(float4*)(p.out + li * p.sOi + col) = add4_(add4_(sh[0][tx], sh[1][tx]), add4_(sh[2][tx], sh[3][tx]));
 }
 
-hipError_t launch_colsum(int precision, const void* in, int64_t ld, int64_t sIi, int64_t rows, int N,
-                         float* out, int64_t sOi, int L, const LearnerMap& lmap, hipStream_t s) {
-    if (L < 1 || L > 128) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)L);
-    if (precision == 0)
-        hipLaunchKernelGGL(colsum_kernel<float>, grid, dim3(256), 0, s, (const float*)in, ld, sIi, rows, N, out, sOi, lmap);
-    else
-        hipLaunchKernelGGL(colsum_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)in, ld, sIi, rows, N, out, sOi, lmap);
+template <typename T> static void launch_colsum_t(const ColsumDesc& d, hipStream_t s) {
+    const dim3 grid((unsigned)((d.N + 127) / 128 + (d.loss ? d.L_all : 0)), (unsigned)d.L);
+    if (d.rows >= 128) hipLaunchKernelGGL((colsum_kernel<T, 32>), grid, dim3(1024), 0, s, d);
+    else hipLaunchKernelGGL((colsum_kernel<T, 8>), grid, dim3(256), 0, s, d);
+}
+
+hipError_t launch_colsum(const ColsumDesc& d, hipStream_t s) {
+    // four columns at a time (every width and offset of the layout is a multiple of 4)
+    const int quad = d.precision ? 8 : 16;
+    if (d.L < 1 || d.L > 128 || d.L_all > 128 || d.N % 4 || d.ld % 4 || d.sIi % 4 || d.sOi % 4 || (uintptr_t)d.in % quad || (uintptr_t)d.out % 16)
+        return hipErrorInvalidValue;
+    if (d.precision == 0) launch_colsum_t<float>(d, s);
+    else launch_colsum_t<bf16_t>(d, s);
     return hipGetLastError();
 }
 

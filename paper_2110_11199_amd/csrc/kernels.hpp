@@ -123,9 +123,15 @@ bool rec_resident_supported(const RecDesc& d);
 int rec_resident_batch_tiles(const RecDesc& d);
 hipError_t launch_rec_resident(const RecDesc& d, bool backward, hipStream_t s);
 
-// Bits of the device-side status word of a handle (0 = fine).
+// Bits of the device-side status word of a handle (0 = fine).  Words 2 and 3 behind it hold the address of pinned host memory,
+// a word per bit, where a kernel that raises a bit leaves a 1: no copy in the stream while all is well.
 constexpr uint32_t kStatusBadLabel = 1u;       // a label outside [0, classes) was met (and clamped)
 constexpr uint32_t kStatusWaitExpired = 2u;    // a bounded wait between workgroups ran out
+__device__ inline void raise_status_(uint32_t* status, uint32_t bit) {
+    __hip_atomic_fetch_or(status, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t* host = *(uint32_t**)(status + 2);
+    __hip_atomic_store(host + (bit >> 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // All T frames of one layer in one launch, W_h spread over clusters of workgroups that exchange h (partial sums of dh) through
 // `exchange` (lstm_cluster.hip).  r.step is not used; the backward pass writes rec_cluster_batch_tiles(r) rows of dbp for all
@@ -170,21 +176,26 @@ hipError_t launch_stream_probe(int reads, int writes_f32, int writes_bf16, void*
 struct SoftmaxDesc {
     int precision, L;          // L: learners of this launch (entries of lmap)
     LearnerMap lmap;
-    int L_all;                 // all learners of the handle (loss[] has this many entries)
-    uint32_t active_bits[4];   // bit i: learner i takes part; the loss of the others is reported as 0
     uint32_t* status;          // device status word: kStatusBadLabel is or-ed in
     int64_t rows; int C;
     const float* logits; int64_t sLi;    // [L][rows][C]
     const int32_t* y; int64_t sYi;
     void* dlogits; int64_t sDi;          // [L][rows][C] operand type: (softmax - onehot)/rows
     float* row_loss;                     // [L][rows]
-    float* loss;                         // [L]
 };
 hipError_t launch_softmax_ce(const SoftmaxDesc& d, hipStream_t s);
 
 // out[z][n] = sum_m in[z][m][n]   (bias gradients), z = lmap.idx[0..L)
-hipError_t launch_colsum(int precision, const void* in, int64_t ld, int64_t sIi, int64_t rows, int N,
-                         float* out, int64_t sOi, int L, const LearnerMap& lmap, hipStream_t s);
+struct ColsumDesc {
+    int precision, L;
+    LearnerMap lmap;
+    const void* in; int64_t ld, sIi;     // operand type
+    int64_t rows; int N;
+    float* out; int64_t sOi;
+    // with loss != NULL also loss[i] = mean of row_loss[i][0..rows) for the learners whose bit is set, 0 for the other L_all
+    float* loss; const float* row_loss; int L_all; uint32_t active_bits[4];
+};
+hipError_t launch_colsum(const ColsumDesc& d, hipStream_t s);
 // dst[z][0..n) = 0 for z = lmap.idx[0..L)  (a fill kernel, not a memset node: safe under stream capture)
 hipError_t launch_zero(float* dst, int64_t sDi, int64_t n, int L, const LearnerMap& lmap, hipStream_t s);
 

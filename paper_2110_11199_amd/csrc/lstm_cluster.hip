@@ -69,13 +69,14 @@ __device__ inline bool get_(const ClusterDesc& p, const word_t* base, Off off, u
         uint32_t differ = 0;
 #pragma unroll
         for (int i = 0; i < N; ++i) { differ |= (uint32_t)(x[i] >> 32) ^ tag; v[i] = (uint32_t)x[i]; }
-        if (__ballot(differ != 0) == 0) return true;
-        if ((tries & 15) == 15) {
+        // (a bound of 0 gives up at the first exchange, whether the words are there or not)
+        if (__ballot(differ != 0) == 0 && p.wait_ticks != 0) return true;
+        if ((tries & 15) == 15 || p.wait_ticks == 0) {
             const uint64_t now = wall_clock64();
             if (t0 == 0) t0 = now;
             const uint32_t st = __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             if (now - t0 >= p.wait_ticks || (st & kStatusWaitExpired)) {
-                __hip_atomic_fetch_or(p.status, kStatusWaitExpired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                raise_status_(p.status, kStatusWaitExpired);
                 return false;
             }
         }

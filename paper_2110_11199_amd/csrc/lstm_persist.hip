@@ -43,10 +43,11 @@ __device__ inline bool wait_for_(const PersistDesc& p, uint32_t* cnt, uint32_t t
     if (threadIdx.x == 0) {
         int ok = 1;
         const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        // (a bound of 0 gives up at the first wait, whether the others have arrived or not)
+        while (p.wait_ticks == 0 || __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
             if ((__hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStatusWaitExpired) ||
-                wall_clock64() - t0 > p.wait_ticks) {
-                __hip_atomic_fetch_or(p.status, kStatusWaitExpired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                wall_clock64() - t0 >= p.wait_ticks) {
+                raise_status_(p.status, kStatusWaitExpired);
                 ok = 0;
                 break;
             }

@@ -414,15 +414,14 @@ def test_persistent_kernel_wait_runs_out_and_is_reported():
 
 
 def test_cluster_wait_runs_out_and_is_reported():
-    # 26 clusters of 10 workgroups on 256 compute units: the last one waits until another is done, and a wait bound of 0
-    # microseconds gives up; every workgroup returns and the handle reports it
+    # a wait bound of 0 microseconds gives up at the first exchange; every workgroup returns and the handle reports it
     import torch
     from paper_2110_11199_amd import binding as Bd
-    shape = Shape(8, 640, 1, 1, 0, 8, 48, 8)
-    e = _engine(shape, 8, S.FIXED_RING, 1)
+    shape = Shape(8, 256, 1, 1, 0, 8, 20, 4)
+    e = _engine(shape, 2, S.FIXED_RING, 1)
     e.tune(Bd.TUNE_REC_WAIT_US, 0)
     e.set_params(-1, torch.from_numpy(synth.initial_model(0, e.P, 0.1)).cuda())
-    e.step(_to_dev(_batches(shape, 8, 0)), 0.1)
+    e.step(_to_dev(_batches(shape, 2, 0)), 0.1)
     with pytest.raises(Bd.AdpsgdError) as ei:
         e.status()
     assert ei.value.code == Bd.EHIP and "wait" in str(ei.value)
