@@ -335,7 +335,7 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->dy = (float*)w.take(L * M * DH * 4);
         h->da = w.take(L * M * G4 * e);
         h->dc = (float*)w.take(L * (size_t)h->B * DH * 4);
-        const size_t dbrows = (size_t)h->T * ((h->B + 31) / 32), dbtiles = (size_t)(h->B + 15) / 16;
+        const size_t dbrows = (size_t)h->T * ((h->B + 31) / 32), dbtiles = (size_t)(h->B + 3) / 4;
         h->dbp = (float*)w.take(L * (dbrows > dbtiles ? dbrows : dbtiles) * G4 * 4);
         h->row_loss = (float*)w.take(L * M * 4);
         h->loss = (float*)w.take(L * 4);

@@ -60,6 +60,9 @@ __device__ inline uint2 buf_load8_(buf_t b, uint32_t voff, uint32_t soff) {
     const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(b, (int)voff, (int)soff, 0);
     return make_uint2(v.x, v.y);
 }
+__device__ inline uint32_t buf_load2_(buf_t b, uint32_t voff, uint32_t soff) {
+    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(b, (int)voff, (int)soff, 0);
+}
 __device__ inline void buf_store_(float v, buf_t b, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, (int)voff, (int)soff, 0);
 }

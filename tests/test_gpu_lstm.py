@@ -102,6 +102,13 @@ def test_gradient_with_all_frames_on_one_compute_unit(hidden, batch, frames, pre
     _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("hidden", [16, 72, 128])
+def test_gradient_with_all_frames_on_one_compute_unit_sixteen_rows_at_a_time(hidden, prec):
+    # more blocks of four rows than three per compute unit: the kernels that take 16, the last block ragged
+    _check_gradient(Shape(12, hidden, 1, 1, 0, 8, 77, 3), 20, prec)
+
+
 @pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 256), (0, 260), (0, 384), (0, 512), (1, 136), (1, 256), (1, 360), (1, 512), (1, 640)])
 @pytest.mark.parametrize("batch,frames", [(1, 2), (17, 5), (32, 3)])
 def test_gradient_with_all_frames_on_clusters_of_compute_units(prec, hidden, batch, frames):
