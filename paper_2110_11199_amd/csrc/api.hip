@@ -120,7 +120,7 @@ struct adpsgd_handle {
     // copy at the end of every step
     uint32_t* status = nullptr;
     volatile uint32_t* status_host = nullptr;
-    int L, D, H, T, B, I, C, Bn, layers, F, ldx;
+    int L, D, H, T, B, I, C, Bn, layers, F, ldx, ldd;
     int mix, tau, prec, esz;
     bool flat;
     int64_t P, Ppad, M;
@@ -282,7 +282,7 @@ size_t plan(adpsgd_handle* h, void* base) {
     h->ix_wp = h->ix_bp = h->ix_wo = h->ix_bo = -1;
     if (h->flat) {
         h->P = s.flat_params;
-        h->D = h->H = h->T = h->B = h->I = h->C = h->Bn = h->layers = h->F = h->ldx = 0; h->M = 0;
+        h->D = h->H = h->T = h->B = h->I = h->C = h->Bn = h->layers = h->F = h->ldx = h->ldd = 0; h->M = 0;
     } else {
         h->D = s.bidirectional ? 2 : 1; h->H = s.hidden; h->T = s.frames; h->B = s.batch; h->I = s.input_dim;
         h->C = s.classes; h->Bn = s.bottleneck; h->layers = s.layers; h->M = (int64_t)h->T * h->B;
@@ -331,7 +331,8 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->z = h->Bn ? w.take(L * M * h->Bn * e) : nullptr;
         h->dz = h->Bn ? w.take(L * M * h->Bn * e) : nullptr;
         h->logits = (float*)w.take(L * M * h->C * 4);
-        h->dlogits = w.take(L * M * h->C * e);
+        h->ldd = (int)round_up(h->C, 16 / (int)e);         // 16-byte rows (the classes are a multiple of 4)
+        h->dlogits = w.take(L * M * h->ldd * e);
         h->dy = (float*)w.take(L * M * DH * 4);
         h->da = w.take(L * M * G4 * e);
         h->dc = (float*)w.take(L * (size_t)h->B * DH * 4);
@@ -567,7 +568,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     sm.precision = prec; sm.L = n; sm.lmap = act; sm.rows = M; sm.C = C;
     sm.status = h->status;
     sm.logits = h->logits; sm.sLi = M * C; sm.y = h->labels; sm.sYi = M;
-    sm.dlogits = h->dlogits; sm.sDi = M * C; sm.row_loss = h->row_loss;
+    sm.dlogits = h->dlogits; sm.ldd = h->ldd; sm.sDi = M * h->ldd; sm.row_loss = h->row_loss;
     if (int rc = mark(h, 4, 1)) return rc;
     HIPCHK(launch_softmax_ce(sm, s), "softmax cross-entropy");
 
@@ -576,14 +577,14 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     g = G();
     g.a_kc = 0; g.b_kc = 0; g.c_elem = 0;
     g.M = C; g.N = F; g.K = (int)M;
-    g.A = h->dlogits; g.lda = C; g.sAi = M * C;
+    g.A = h->dlogits; g.lda = h->ldd; g.sAi = M * h->ldd;
     g.B = zin; g.ldb = ldz; g.sBi = M * ldz;
     g.C = Gr(h->ix_wo); g.ldc = F; g.sCi = Pp;
     if (int rc = gemm(h, g, "dW_o GEMM")) return rc;
     if (int rc = mark(h, 5, 1)) return rc;
     ColsumDesc cs{};
     cs.precision = prec; cs.L = n; cs.lmap = act; cs.rows = M; cs.sOi = Pp;
-    cs.in = h->dlogits; cs.ld = C; cs.sIi = M * C; cs.N = C; cs.out = Gr(h->ix_bo);
+    cs.in = h->dlogits; cs.ld = h->ldd; cs.sIi = M * h->ldd; cs.N = C; cs.out = Gr(h->ix_bo);
     cs.loss = h->loss; cs.row_loss = h->row_loss; cs.L_all = L;
     for (int i = 0; i < 4; ++i) cs.active_bits[i] = bits[i];
     HIPCHK(launch_colsum(cs, s), "db_o and losses");
@@ -591,8 +592,8 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     // d(z) = dlogits W_o
     g = G();
     g.a_kc = 1; g.b_kc = 0; g.c_elem = h->Bn ? 1 : 0;
-    g.M = (int)M; g.N = F; g.K = C;
-    g.A = h->dlogits; g.lda = C; g.sAi = M * C;
+    g.M = (int)M; g.N = F; g.K = C; g.k_padded = 1;
+    g.A = h->dlogits; g.lda = h->ldd; g.sAi = M * h->ldd;
     g.B = W(h->ix_wo); g.ldb = F; g.sBi = Pp;
     g.C = h->Bn ? h->dz : (void*)h->dy; g.ldc = F; g.sCi = M * F;
     if (int rc = gemm(h, g, "dz GEMM")) return rc;

@@ -82,7 +82,8 @@ struct GemmDma {
                 const int row = c / CPR;
                 const int slot = c % CPR;
                 int chunk = slot ^ swz_<SB>(row);
-                chunk = chunk < kvalid / EPC ? chunk : kvalid / EPC - 1;
+                const int chunks = (kvalid + EPC - 1) / EPC;   // (the last one may be partly padding)
+                chunk = chunk < chunks ? chunk : chunks - 1;
                 off[j] = (uint32_t)(src.row_offset_clamped(row) * (int64_t)sizeof(T)) + (uint32_t)chunk * 16u;
             } else {
                 constexpr int CPK = ROWS / EPC;               // 16-byte chunks per k-row

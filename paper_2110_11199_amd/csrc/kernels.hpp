@@ -25,6 +25,7 @@ struct GemmDesc {
     void* C; int64_t ldc, sCi, sCd;
     const float* bias; int64_t sBiasI, sBiasD;
     int groupsI, groupsD;
+    int k_padded;             // rows of K-contiguous operands are readable up to the next multiple of 16 bytes past K
     int tile;                 // tile configuration (see gemm.hip): -1 automatic, or 0, 5, 11 .. 15
     LearnerMap lmap;
 };
@@ -180,7 +181,7 @@ struct SoftmaxDesc {
     int64_t rows; int C;
     const float* logits; int64_t sLi;    // [L][rows][C]
     const int32_t* y; int64_t sYi;
-    void* dlogits; int64_t sDi;          // [L][rows][C] operand type: (softmax - onehot)/rows
+    void* dlogits; int64_t ldd, sDi;     // [L][rows][C] operand type, rows ldd apart: (softmax - onehot)/rows
     float* row_loss;                     // [L][rows]
 };
 hipError_t launch_softmax_ce(const SoftmaxDesc& d, hipStream_t s);
