@@ -116,6 +116,9 @@ hipError_t launch_rec_split(const RecDesc& d, bool backward, hipStream_t s);
 
 // Whether every operand row that is loaded in 16-byte pieces is 16-byte aligned and a whole number of them.
 bool rec_aligned(const RecDesc& d);
+// Whether the rows of W_h are whole, aligned groups of four values: what the buffer loads of the kernels that hold W_h in
+// registers need (a 16-byte buffer load asks for 4-byte alignment only).
+bool rec_quad_aligned(const RecDesc& d);
 
 // All T frames of one layer in one launch, W_h held in registers, a workgroup per (learner, direction) and 16 batch rows
 // (lstm_resident.hip; hidden sizes up to 128).  d.step is not used; the backward pass writes rec_resident_batch_tiles(d)

@@ -356,6 +356,11 @@ bool rec_aligned(const RecDesc& d) {
            d.sYi % epc == 0 && (uintptr_t)d.da % 16 == 0 && d.sDAi % epc == 0;
 }
 
+bool rec_quad_aligned(const RecDesc& d) {
+    const int quad = d.precision ? 8 : 16;
+    return d.H % 4 == 0 && (uintptr_t)d.wh % quad == 0 && d.sWi % 4 == 0 && d.sWd % 4 == 0;
+}
+
 // Which kernels a step runs on.
 //   kSplit   32 x 32 tiles, contraction split over the waves (lstm_small.hip): as long as its workgroups fit the chip in
 //            one round (two in fp32, whose other tiles are no faster), a step is bound by the latency of the K walk and this

@@ -132,10 +132,14 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
         const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
 #pragma unroll
         for (int c = 0; c < C::CW; ++c) {
-            const int k0 = (kh * C::CW + c) * C::KC;       // H is a multiple of EL: a fragment is whole or absent
-            const uint32_t vw = ok_u && k0 + g * C::EL < H ? (uint32_t)(u * H + g * C::EL) * (uint32_t)sizeof(T) : kOutOfRange;
+            const int k0 = (kh * C::CW + c) * C::KC;       // H is a multiple of 4
+            const int k = k0 + g * C::EL;
+            const uint32_t vw = ok_u && k < H ? (uint32_t)(u * H + g * C::EL) * (uint32_t)sizeof(T) : kOutOfRange;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) wf[q][c] = buf_load16_(wh, vw, (uint32_t)(q * H * H + k0) * (uint32_t)sizeof(T));
+            for (int q = 0; q < 4; ++q) {
+                wf[q][c] = buf_load16_(wh, vw, (uint32_t)(q * H * H + k0) * (uint32_t)sizeof(T));
+                if (k + C::EL > H) wf[q][c].z = wf[q][c].w = 0u;         // bf16, H = 4 mod 8: half a fragment
+            }
         }
     }
     // rows this lane finishes: row0 + i, i < PR
@@ -325,7 +329,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
             for (int j = 0; j < C::NT; ++j) {
                 const int x = tid + 256 * j, k = unit0 + x / (C::KP / 4) * EPW, n = x % (C::KP / 4) * 4;
-                const uint32_t at = k < H && n < H ? (uint32_t)((q * H + k) * H + n) * (uint32_t)sizeof(T) : kOutOfRange;   // (H: a multiple of EL)
+                const uint32_t at = k < H && n < H ? (uint32_t)((q * H + k) * H + n) * (uint32_t)sizeof(T) : kOutOfRange;   // (H: a multiple of 4)
                 if constexpr (EPW == 1) {
                     v[j] = buf_load16_(wh, at, 0u);
                 } else {
@@ -474,13 +478,16 @@ template <typename T, int S> void launch_cluster_t(const ClusterDesc& p, bool ba
 //                 96 (960; between the other kernels of an iteration) 20.6 / 22; 16 x 256, 128 (512) 12.1 / 7.7; 32 x 256, 128 (1024) 14.3 / 15.1
 //   bf16 backward 10 x 360, 50 (240) 11.5 / 5.9; 16 x 256, 128 (512) 13.9 / 10.0; 32 x 256, 128 (1024) 17.0 / 18.6; 32 x 512, 32 (512)
 //                 18.9 / 16.4, 64 (1024) 23 / 56 (the exchange of fp32 sums); 16 x 640, 16 (160) 18.2 / 9.5, 32 (320) 20.0 / 20.8
+// bf16 hidden sizes that are 4 mod 8, which frame by frame run on the register-staged kernels, take the clusters throughout: 16 x 300,
+// 32 (192) 19.5 / 30.3 against 3.5 / 5.3; 16 x 508, 128 (1024) 29 / 70 against 17 / 32; 32 x 636, 128 (2560) 77 / 119 against 51 / 134.
 // More rows to a cluster (two and four tiles) shorten nothing: 32 x 512, 64: 16 -> 15 and 18; the exchange grows with the rows.
 bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count) {
-    if (!d.direct || d.T < 2 || d.H <= 128 || !rec_aligned(d) || d.L < 1 || d.L > 128 || d.D < 1 || d.D > 2 || d.B < 1) return false;
+    if (!d.direct || d.T < 2 || d.H <= 128 || !rec_quad_aligned(d) || d.L < 1 || d.L > 128 || d.D < 1 || d.D > 2 || d.B < 1) return false;
     if ((int64_t)d.T * d.B * d.D * d.H * 16 >= (int64_t)kOutOfRange) return false;     // buffer offsets
     const int S = cluster_members(d);
     if (S == 0 || cu_count < 4 * S) return false;
     const int64_t workgroups = (int64_t)d.L * d.D * cluster_blocks(d) * S;
+    if (!rec_aligned(d)) return workgroups <= 4096;        // measured up to 3200
     if (d.precision) return workgroups <= (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640);
     return workgroups <= (backward ? 1024 : 1280);
 }

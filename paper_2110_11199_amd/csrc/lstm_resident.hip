@@ -288,8 +288,9 @@ __global__ __launch_bounds__(512) void rec_forward_row4_kernel(RecDesc p) {
         const uint32_t row = ok_u ? (uint32_t)((g * H + u) * H) * (uint32_t)sizeof(T) : kOutOfRange;
         constexpr int EL = 16 / (int)sizeof(T);
 #pragma unroll
-        for (int k = 0; k < KP; k += EL) {                 // H is a multiple of EL
-            const uint4 v = buf_load16_(wh, k < H ? row : kOutOfRange, (uint32_t)(k * (int)sizeof(T)));
+        for (int k = 0; k < KP; k += EL) {                 // H is a multiple of 4
+            uint4 v = buf_load16_(wh, k < H ? row : kOutOfRange, (uint32_t)(k * (int)sizeof(T)));
+            if (k + EL > H) v.z = v.w = 0u;                // bf16, H = 4 mod 8: half a chunk
             if constexpr (C::F32) {
                 wf[k] = __builtin_bit_cast(float, v.x); wf[k + 1] = __builtin_bit_cast(float, v.y);
                 wf[k + 2] = __builtin_bit_cast(float, v.z); wf[k + 3] = __builtin_bit_cast(float, v.w);
@@ -496,7 +497,8 @@ bool row4_blocks(const RecDesc& d) { return (int64_t)d.L * d.D * ((d.B + 3) / 4)
 
 bool rec_resident_supported(const RecDesc& d) {
     // (every tensor of a learner below 2 GiB: the buffer offsets of the kernels)
-    return d.direct && d.H <= 128 && rec_aligned(d) && (int64_t)d.T * d.B * d.D * d.H * 16 < (int64_t)kOutOfRange && d.L >= 1 && d.L <= 128 && d.D >= 1 && d.D <= 2 && d.B >= 1 && d.T >= 1;
+    if (!rec_aligned(d) && !(rec_quad_aligned(d) && row4_blocks(d))) return false;
+    return d.direct && d.H <= 128 && (int64_t)d.T * d.B * d.D * d.H * 16 < (int64_t)kOutOfRange && d.L >= 1 && d.L <= 128 && d.D >= 1 && d.D <= 2 && d.B >= 1 && d.T >= 1;
 }
 
 int rec_resident_batch_tiles(const RecDesc& d) { const int rows = row4_blocks(d) ? 4 : kRows; return (d.B + rows - 1) / rows; }

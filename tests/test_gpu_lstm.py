@@ -109,7 +109,7 @@ def test_gradient_with_all_frames_on_one_compute_unit_sixteen_rows_at_a_time(hid
     _check_gradient(Shape(12, hidden, 1, 1, 0, 8, 77, 3), 20, prec)
 
 
-@pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 256), (0, 260), (0, 384), (0, 512), (1, 136), (1, 256), (1, 360), (1, 512), (1, 640)])
+@pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 256), (0, 260), (0, 384), (0, 512), (1, 132), (1, 136), (1, 256), (1, 300), (1, 360), (1, 508), (1, 512), (1, 640)])
 @pytest.mark.parametrize("batch,frames", [(1, 2), (17, 5), (32, 3)])
 def test_gradient_with_all_frames_on_clusters_of_compute_units(prec, hidden, batch, frames):
     # every cluster size, whole and with units past the hidden size; one row, one row more than a block, whole blocks
