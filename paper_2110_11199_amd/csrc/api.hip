@@ -380,14 +380,25 @@ void prof_reset(adpsgd_handle* h) {
 
 // k_alg: the contraction length the flop and byte counts are taken for (0: d.K; smaller than d.K when
 // the operands carry zero padding along K)
-int gemm(adpsgd_handle* h, const GemmDesc& d, const char* what, int k_alg = 0) {
+int mark_gemm(adpsgd_handle* h, const GemmDesc& d, int launches, int k_alg) {
     const double esz = d.precision ? 2.0 : 4.0, g = (double)d.groupsI * d.groupsD;
     const double K = k_alg > 0 ? k_alg : d.K;
-    if (int rc = mark(h, 1, 1, 2.0 * d.M * d.N * K * g,
-                      g * (((double)d.M + d.N) * K * esz + (double)d.M * d.N * (d.c_elem ? esz : 4.0)))) return rc;
+    return mark(h, 1, launches, 2.0 * d.M * d.N * K * g,
+                g * (((double)d.M + d.N) * K * esz + (double)d.M * d.N * (d.c_elem ? esz : 4.0)));
+}
+int gemm(adpsgd_handle* h, const GemmDesc& d, const char* what, int k_alg = 0) {
+    if (int rc = mark_gemm(h, d, 1, k_alg)) return rc;
     GemmDesc q = d;
     q.tile = h->tune_gemm_tile;
     HIPCHK(launch_gemm(q, h->stream), what);
+    return ADPSGD_OK;
+}
+
+int gemm_pair(adpsgd_handle* h, GemmDesc a, GemmDesc b, const char* what) {
+    if (int rc = mark_gemm(h, a, 1, 0)) return rc;
+    if (int rc = mark_gemm(h, b, 1, 0)) return rc;
+    a.tile = b.tile = h->tune_gemm_tile;
+    HIPCHK(launch_gemm_pair(a, b, h->stream), what);
     return ADPSGD_OK;
 }
 
@@ -661,7 +672,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         g.A = h->da; g.lda = G4; g.sAi = M * G4;
         g.B = in; g.ldb = ldin; g.sBi = M * ldin;
         g.C = Gr(h->ix_wx[l]); g.ldc = Il; g.sCi = Pp;
-        if (int rc = gemm(h, g, "dW_x GEMM")) return rc;
+        const GemmDesc gx = g;
         // dW_h[d] = da_d' h_{t'}: frames with a predecessor only (T-1 of them)
         if (T > 1) {
             g = G();
@@ -674,8 +685,9 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
             g.B = Y(l); g.ldb = DH; g.sBi = M * DH; g.sBd = (int64_t)B * DH + H;
             g.C = Gr(h->ix_wh[l]); g.ldc = H; g.sCi = Pp; g.sCd = (int64_t)4 * H * H;
             g.groupsD = D;
-            if (int rc = gemm(h, g, "dW_h GEMM")) return rc;
+            if (int rc = gemm_pair(h, gx, g, "dW_x and dW_h GEMMs")) return rc;
         } else {
+            if (int rc = gemm(h, gx, "dW_x GEMM")) return rc;
             // a single frame has no predecessor: dW_h = 0 (a fill kernel, so that the step holds no memset node)
             if (int rc = mark(h, 5, 1)) return rc;
             HIPCHK(launch_zero(Gr(h->ix_wh[l]), Pp, G4 * H, n, act, s), "zero dW_h");

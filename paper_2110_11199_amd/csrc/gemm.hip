@@ -221,15 +221,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_kernel(GemmDesc p) {
 // Same tile bookkeeping with the direct-to-LDS main loop (16-byte aligned operands, K a multiple of
 // the stage length).
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
-__global__ __launch_bounds__(64 * WM * WN, FM * FN <= 4 ? 3 : FM * FN == 8 ? 2 : 1) void gemm_dma_kernel(GemmDesc p) {
+__device__ __forceinline__ void dma_tile(const GemmDesc& p, int bid, int total, char* lds) {
     typedef typename std::conditional<AKC, KcSrc<T>, McSrc<T>>::type ASrc;
     typedef typename std::conditional<BKC, KcSrc<T>, McSrc<T>>::type BSrc;
     typedef GemmDma<T, ASrc, BSrc, WM, WN, FM, FN, SB, NS> Core;
-    __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
 
     const int tiles_m = (p.M + Core::BM - 1) / Core::BM, tiles_n = (p.N + Core::BN - 1) / Core::BN;
     int grp, tm, tn;
-    map_tile(blockIdx.x, gridDim.x, tiles_m, tiles_n, grp, tm, tn);
+    map_tile(bid, total, tiles_m, tiles_n, grp, tm, tn);
     const int gi = p.lmap.idx[grp / p.groupsD], gd = grp % p.groupsD;
     const int m0 = tm * Core::BM, n0 = tn * Core::BN;
     const T* A = (const T*)p.A + gi * p.sAi + gd * p.sAd;
@@ -250,6 +249,26 @@ __global__ __launch_bounds__(64 * WM * WN, FM * FN <= 4 ? 3 : FM * FN == 8 ? 2 :
     Core::run_deep(acc, a, b, p.K, lds);
     if (m0 + Core::BM <= p.M && n0 + Core::BN <= p.N && p.ldc < (1 << 26)) store_tile_interior<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
     else store_tile<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
+}
+
+template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
+__global__ __launch_bounds__(64 * WM * WN, FM * FN <= 4 ? 3 : FM * FN == 8 ? 2 : 1) void gemm_dma_kernel(GemmDesc p) {
+    typedef GemmDma<T, KcSrc<T>, KcSrc<T>, WM, WN, FM, FN, SB, NS> Core;
+    __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
+    dma_tile<T, AKC, BKC, WM, WN, FM, FN, SB, NS>(p, blockIdx.x, gridDim.x, lds);
+}
+
+// Two independent problems of one layout in one launch (the two weight gradients of a layer): small problems pay for a launch
+// each (4.5 us) and for a last round that leaves part of the chip idle (6 x 1280 x 320 x 1280 and x 1216, fp32: 600 tiles of 64 x
+// 64 each, three rounds of the chip and three, together five).
+struct GemmPair { GemmDesc d[2]; int tiles0; };
+template <typename T, int SB, int NS>
+__global__ __launch_bounds__(256, 3) void gemm_dma_pair_kernel(GemmPair p) {
+    typedef GemmDma<T, KcSrc<T>, KcSrc<T>, 2, 2, 1, 1, SB, NS> Core;
+    __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
+    const int which = (int)blockIdx.x >= p.tiles0;
+    dma_tile<T, false, false, 2, 2, 1, 1, SB, NS>(p.d[which], which ? blockIdx.x - p.tiles0 : blockIdx.x,
+                                                  which ? gridDim.x - p.tiles0 : p.tiles0, lds);
 }
 
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int VB, int SB>
@@ -306,32 +325,30 @@ static double tile_time(const GemmDesc& d, int bm, int bn, double rate, double l
     return (rounds * rate > latency ? rounds * rate : latency) * d.K;
 }
 
-hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
-    if (d.M < 1 || d.N < 1 || d.K < 1 || d.groupsI < 1 || d.groupsI > 128 || d.groupsD < 1) return hipErrorInvalidValue;
-    if (d.tile != -1 && d.tile != 0 && d.tile != 5 && (d.tile < 11 || d.tile > 15)) return hipErrorInvalidValue;
+// The tile configuration of a problem (-1: not a valid problem), and whether its operands meet the rules of the direct loads.
+static int pick_tile(const GemmDesc& d, bool& dma) {
+    if (d.M < 1 || d.N < 1 || d.K < 1 || d.groupsI < 1 || d.groupsI > 128 || d.groupsD < 1) return -1;
+    if (d.tile != -1 && d.tile != 0 && d.tile != 5 && (d.tile < 11 || d.tile > 15)) return -1;
     // one-dimensional grid over all tiles of all groups (smallest tile 64 x 64)
-    if ((int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD > 0x7fffffff) return hipErrorInvalidValue;
+    if ((int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD > 0x7fffffff) return -1;
     const int esz = d.precision ? 2 : 4, epc = 16 / esz;
     const int quad = 4 * esz;    // every operand must allow loads of 4 elements
     if (!aligned_to(d.A, d.lda, d.sAi, d.sAd, esz, quad) || !aligned_to(d.B, d.ldb, d.sBi, d.sBd, esz, quad))
-        return hipErrorInvalidValue;
+        return -1;
     // Direct-to-LDS loads need 16-byte aligned rows, whole 16-byte chunks along the contiguous dimension (of K, or of
     // rows: the k-rows must be at least round_up(rows, chunk) long), and per-lane load offsets inside a tile that fit
     // 32 bits (row strides below 2^22 elements).
     const bool wide_a = aligned_to(d.A, d.lda, d.sAi, d.sAd, esz, 16), wide_b = aligned_to(d.B, d.ldb, d.sBi, d.sBd, esz, 16);
-    const bool dma = d.lda < (1 << 22) && d.ldb < (1 << 22) && wide_a && wide_b &&
-                     (d.a_kc ? d.K % epc == 0 || d.k_padded : d.lda >= (d.M + epc - 1) / epc * epc) &&
-                     (d.b_kc ? d.K % epc == 0 || d.k_padded : d.ldb >= (d.N + epc - 1) / epc * epc);
+    dma = d.lda < (1 << 22) && d.ldb < (1 << 22) && wide_a && wide_b &&
+          (d.a_kc ? d.K % epc == 0 || d.k_padded : d.lda >= (d.M + epc - 1) / epc * epc) &&
+          (d.b_kc ? d.K % epc == 0 || d.k_padded : d.ldb >= (d.N + epc - 1) / epc * epc);
     int v = d.tile;
     if (d.precision == 0) {
         // fp32 tiles are bound by the matrix pipe (256 flop per clock and CU) in either size: what decides is how evenly
         // the tiles cover the CUs
         if (v < 0) v = !dma ? 0 : tile_time(d, 64, 64, 14.0, 20.0) < tile_time(d, 128, 128, 53.0, 60.0) ? 15 : 14;
-        if (v == 15 && dma) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
-        if (v >= 11 && dma) return launch_dma<float, 2, 2, 2, 2, 64, 3>(d, s);
-        return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
+        return v;
     }
-    if ((d.a_kc && !wide_a) || (d.b_kc && !wide_b)) return launch_layout<bf16_t, 2, 2, 2, 2, 8, 64>(d, s);
     if (v < 0) {
         // 256x256 tiles once there are enough of them to fill the 256 CUs
         const int64_t big_tiles = (int64_t)((d.M + 255) / 256) * ((d.N + 255) / 256) * d.groupsI * d.groupsD;
@@ -347,6 +364,20 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
             v = t64 <= t128 && t64 <= t256 ? 15 : t128 <= t256 ? 14 : 13;
         } else v = big_tiles < 128 ? 0 : (short_k || ragged_m) ? 13 : !(d.a_kc && d.b_kc) ? 12 : (d.M >= 512 && d.N >= 512) ? 11 : 13;
     }
+    return v;
+}
+
+hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
+    bool dma = false;
+    const int v = pick_tile(d, dma);
+    if (v < 0) return hipErrorInvalidValue;
+    if (d.precision == 0) {
+        if (v == 15 && dma) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
+        if (v >= 11 && dma) return launch_dma<float, 2, 2, 2, 2, 64, 3>(d, s);
+        return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
+    }
+    const bool wide_a = aligned_to(d.A, d.lda, d.sAi, d.sAd, 2, 16), wide_b = aligned_to(d.B, d.ldb, d.sBi, d.sBd, 2, 16);
+    if ((d.a_kc && !wide_a) || (d.b_kc && !wide_b)) return launch_layout<bf16_t, 2, 2, 2, 2, 8, 64>(d, s);
     if (v == 15 && dma) return launch_dma<bf16_t, 2, 2, 1, 1, 128, 3>(d, s);
     if (v == 14 && dma) return launch_dma<bf16_t, 2, 2, 2, 2, 128, 2>(d, s);
     if (v == 13 && dma) return launch_dma<bf16_t, 2, 2, 2, 4, 64, 3>(d, s);
@@ -354,6 +385,22 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     if (v == 11 && dma) return launch_dma<bf16_t, 2, 2, 4, 4, 128, 2>(d, s);
     if (v >= 5 && v < 14) return launch_layout<bf16_t, 2, 4, 4, 2, 16, 128>(d, s);
     return launch_layout<bf16_t, 2, 2, 2, 2, 16, 64>(d, s);
+}
+
+hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
+    bool dma_a = false, dma_b = false;
+    const int va = pick_tile(a, dma_a), vb = pick_tile(b, dma_b);
+    auto tiles = [](const GemmDesc& d) { return (int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD; };
+    if (va != 15 || vb != 15 || !dma_a || !dma_b || a.precision != b.precision || a.a_kc || a.b_kc || b.a_kc || b.b_kc ||
+        tiles(a) + tiles(b) > 0x7fffffff) {
+        const hipError_t e = launch_gemm(a, s);
+        return e != hipSuccess ? e : launch_gemm(b, s);
+    }
+    GemmPair p{{a, b}, (int)tiles(a)};
+    const dim3 grid((unsigned)(tiles(a) + tiles(b)));
+    if (a.precision == 0) hipLaunchKernelGGL((gemm_dma_pair_kernel<float, 64, 4>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((gemm_dma_pair_kernel<bf16_t, 128, 3>), grid, dim3(256), 0, s, p);
+    return hipGetLastError();
 }
 
 }  // namespace adpsgd
