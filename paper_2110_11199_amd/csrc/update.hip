@@ -675,7 +675,7 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
             // Equal chunks (a short last one leaves the chip idle at its end), and a grid of whole rounds of the 8 XCDs: the
             // workgroups of one position then run on one XCD for every learner and find its mean in that L2.
             const int64_t n4 = d.P >> 2, chunks = (n4 + (d.mean_elems >> 2) - 1) / (d.mean_elems >> 2);
-            const int64_t chunk4 = (n4 + chunks - 1) / chunks;
+            const int64_t chunk4 = round_up((n4 + chunks - 1) / chunks, 256);     // whole workgroups: every chunk starts on a line
             AllSplitArgs q;
             q.a = a; q.mean = d.mean_buf;
             for (int64_t e0 = 0; e0 < n4; e0 += chunk4) {
