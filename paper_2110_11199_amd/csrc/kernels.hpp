@@ -110,6 +110,9 @@ struct RecDesc {               // one time step of one layer, all learners and d
 };
 // Rows of dbp per frame that launch_rec_backward writes for this layer (its batch tiles); at most ceil(B / 32).
 int rec_backward_batch_tiles(const RecDesc& d);
+// Which kernels the steps of a layer whose tensors meet rec_aligned run on (pairs: learners x directions): 0 register-staged,
+// 1 direct-to-LDS, 2 contraction split over the waves.
+int rec_step_kind(int precision, int pairs, int H, int B);
 hipError_t launch_rec_forward(const RecDesc& d, hipStream_t s);
 hipError_t launch_rec_backward(const RecDesc& d, hipStream_t s);
 // The same step with the contraction split over the waves of a workgroup and the operands read straight into registers

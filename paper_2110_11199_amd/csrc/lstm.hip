@@ -371,12 +371,19 @@ bool rec_quad_aligned(const RecDesc& d) {
 //   kDirect  the direct-to-LDS kernels.
 //   kStaged  register-staged kernels: rows that are not 16-byte aligned, or forced (tuning).  fp32 6 x 320, 64: 31.0 /
 //            91.6; 32 x 1024, 128: 317 / 700 against 277 / 299 direct.
+//            The direct kernels address W_h of a (learner, direction) by a lane's 32-bit byte offset from its start: a matrix of
+//            more than 4 GB (H > 16384 in fp32, 23170 with bf16 operands) is kStaged too, whose addresses have 64 bits.
 enum RecKind { kStaged, kDirect, kSplit };
+
+int rec_step_kind(int precision, int pairs, int H, int B) {
+    const int64_t split_wgs = (int64_t)pairs * ((H + 31) / 32) * ((B + 31) / 32);
+    if (split_wgs <= (precision ? 256 : 512)) return kSplit;
+    return (int64_t)4 * H * H * (precision ? 2 : 4) <= (int64_t)1 << 32 ? kDirect : kStaged;
+}
 
 static RecKind rec_kind(const RecDesc& d) {
     if (!d.direct || !rec_aligned(d)) return kStaged;
-    const int64_t split_wgs = (int64_t)d.L * d.D * ((d.H + 31) / 32) * ((d.B + 31) / 32);
-    return split_wgs <= (d.precision ? 256 : 512) ? kSplit : kDirect;
+    return (RecKind)rec_step_kind(d.precision, d.L * d.D, d.H, d.B);
 }
 
 // Rows of a backward direct tile: 128 where that leaves three quarters of the chip a workgroup, else 32 (every batch tile
