@@ -349,15 +349,21 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
  *                                16 (hidden up to 512 in fp32, 640 with bf16 operands; not for the largest batches), whose
  *                                workgroups wait for each other; 0 never; 1 the kernels that hold it on a whole round of
  *                                the chip at once (bf16 operands, hidden 128/256/512/1024, batch <= 128)
- *   ADPSGD_TUNE_REC_WAIT_US      bound, in microseconds, of one wait between the workgroups of a persistent
- *                                kernel (default 2 000 000); when it runs out every workgroup returns and the
+ *   ADPSGD_TUNE_REC_WAIT_US      bound, in microseconds, of one wait between workgroups that exchange data (groups of up to 16
+ *                                of them: REC_PERSISTENT -1, all of which have started by then; a whole round of the
+ *                                chip: 1; default 2 000 000); when it runs out every workgroup returns and the
  *                                handle's sticky error becomes ADPSGD_EHIP
+ *   ADPSGD_TUNE_REC_JOIN_US      how long, in microseconds, a group of up to 16 workgroups waits for those that have not started
+ *                                (other work may hold the device) before one of those that wait does the group's work
+ *                                alone: same results bit for bit, several times slower.  -1 (default): 1000 per
+ *                                frame of the segment; 0: always alone
  * Takes effect from the next adpsgd_step of that handle; other handles are not touched. */
 #define ADPSGD_TUNE_GEMM_TILE       0
 #define ADPSGD_TUNE_REC_DIRECT      1
 #define ADPSGD_TUNE_REC_FWD_GROUPS  2
 #define ADPSGD_TUNE_REC_PERSISTENT  3
 #define ADPSGD_TUNE_REC_WAIT_US     4
+#define ADPSGD_TUNE_REC_JOIN_US     9
 #define ADPSGD_TUNE_MEAN_CHUNK      5   /* global-mean update: elements per chunk of its two-kernel form (a multiple of
                                            1024, at most 16777216), 0 = the single-kernel form, -1 (default) = automatic
                                            (two kernels for 12 learners and more below 2^18 and from 3M parameters on);

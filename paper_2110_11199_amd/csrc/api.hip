@@ -107,7 +107,8 @@ struct adpsgd_handle {
     int tune_rec_direct = 1;               // direct-to-LDS recurrent kernels allowed
     int tune_rec_fwd_groups = 0;           // learner groups of the forward recurrence, 0 = automatic
     int tune_rec_persist = -1;             // persistent recurrent kernels: 0 off, 1 on where the shape allows, -1 automatic
-    int64_t tune_wait_us = 2000000;        // bound of one wait between the workgroups of a persistent kernel
+    int64_t tune_wait_us = 2000000;        // bound of one wait between the workgroups of a recurrent kernel
+    int64_t tune_join_us = -1;             // how long a cluster waits for workgroups that have not started, -1: 1 ms per frame
     int cu_count = 0;                      // compute units of the device (a persistent grid must not exceed it)
     uint32_t* rec_counters = nullptr;      // [layers][2 passes][L * D] frame counters of the persistent kernels
     float* mean_buf = nullptr;             // chunk buffer of the two-kernel global mean (mix ALL)
@@ -152,6 +153,7 @@ struct adpsgd_handle {
     // recurrences over clusters of workgroups: iteration counter and [layers][2 passes] tickets behind it; exchange words
     uint32_t* epoch = nullptr;
     uint64_t* exchange = nullptr; size_t exchange_bytes = 0;
+    uint64_t* closed = nullptr; size_t closed_bytes = 0;       // a word per cluster, behind the exchange words
 };
 
 // A recorded sequence of iterations of one handle (adpsgd_capture_end), replayed by adpsgd_graph_replay.
@@ -349,6 +351,8 @@ size_t plan(adpsgd_handle* h, void* base) {
         if (words > 0) {
             h->epoch = (uint32_t*)w.take((1 + (size_t)h->layers * 2) * 4);
             h->exchange = (uint64_t*)w.take(h->exchange_bytes);
+            h->closed_bytes = (size_t)rec_cluster_count(r) * 8;
+            h->closed = (uint64_t*)w.take(h->closed_bytes);
         }
     }
     return w.used;
@@ -494,8 +498,11 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         ClusterDesc c;
         c.r = r;
         c.launches = 2 * h->layers; c.launch = 2 * l + (backward ? 1 : 0);
-        c.exchange = h->exchange; c.epoch = h->epoch; c.ticket = h->epoch + 1 + c.launch; c.status = h->status;
+        c.exchange = h->exchange; c.closed = h->closed; c.epoch = h->epoch; c.ticket = h->epoch + 1 + c.launch; c.status = h->status;
         c.wait_ticks = (unsigned long long)h->tune_wait_us * 100ull;
+        // by default several times what one workgroup takes for the cluster (0.02 to 0.3 ms a frame), and far more than the clusters before it in
+        // the same launch take (up to 0.02)
+        c.join_ticks = (unsigned long long)(h->tune_join_us < 0 ? (int64_t)1000 * T : h->tune_join_us) * 100ull;
         return c;
     };
 
@@ -770,6 +777,7 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     if (e == hipSuccess && !h->flat) e = hipMemsetAsync(h->grads, 0, slab, s);
     if (e == hipSuccess && h->epoch) e = hipMemsetAsync(h->epoch, 0, (1 + (size_t)h->layers * 2) * 4, s);
     if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes, s);   // no word carries a tag in use
+    if (e == hipSuccess && h->closed) e = hipMemsetAsync(h->closed, 0, h->closed_bytes, s);
     if (e != hipSuccess) { (void)hipHostFree(mirror); delete h; return hipfail(e, "clear models"); }
     if (cfg->init_scale > 0.f) {
         // same w_0 on every learner (Algorithm 1, input)
@@ -1237,6 +1245,9 @@ int adpsgd_set_tuning(adpsgd_t h, int key, int value) {
         case ADPSGD_TUNE_REC_WAIT_US:
             if (value < 0) return fail(ADPSGD_EINVAL, "microseconds >= 0");
             h->tune_wait_us = value; return ADPSGD_OK;
+        case ADPSGD_TUNE_REC_JOIN_US:
+            if (value < -1) return fail(ADPSGD_EINVAL, "-1 (default) or microseconds >= 0");
+            h->tune_join_us = value; return ADPSGD_OK;
         default: return fail(ADPSGD_EINVAL, "unknown tuning key");
     }
 }

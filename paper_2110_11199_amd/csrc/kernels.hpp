@@ -151,11 +151,14 @@ struct ClusterDesc {
     uint32_t* ticket;                    // zero before the launch
     const uint32_t* epoch;               // differs from iteration to iteration, 0 in none
     int launch, launches;                // this launch among those of an iteration
+    uint64_t* closed;                    // rec_cluster_count(r) words, zero before the handle's first launch
     uint32_t* status;                    // kStatusWaitExpired is or-ed in
-    unsigned long long wait_ticks;
+    unsigned long long wait_ticks;       // bound of one wait of the exchange
+    unsigned long long join_ticks;       // after which a cluster whose workgroups have not all started is left to one of them
 };
 bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count);
 int rec_cluster_batch_tiles(const RecDesc& d);
+int64_t rec_cluster_count(const RecDesc& d);
 int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward);
 hipError_t launch_rec_cluster(const ClusterDesc& p, bool backward, int cu_count, hipStream_t s);
 

@@ -20,11 +20,15 @@
 // the buffer is zeroed when the handle is made and 0 is no tag in use.  Two slots by the parity of the frame suffice: whoever
 // writes frame s has received all of frame s-1, whose senders had read frame s-2.
 //
-// Progress.  Workgroups take their place (cluster, member) from a ticket counter when they START, so a cluster consists of
-// workgroups that run: a complete cluster needs nobody else, and an incomplete one holds at most S-1 compute units until the
-// clusters before it are done, whatever else shares the device and in whatever order workgroups are dispatched.  The grid may
-// exceed the chip.  Every wait is bounded all the same (wait_ticks of the 100 MHz clock, or another workgroup's expiry):
-// the workgroup raises kStatusWaitExpired and returns.
+// Progress.  Workgroups take their place (cluster, member) from a ticket counter when they START, and exchange nothing before
+// all members of their cluster have (join_: the last one says so): from there on every member runs, whatever else shares the
+// device and in whatever order workgroups are dispatched.  The grid may exceed the chip.  A cluster that stays incomplete for
+// longer than the other workgroups of the launch can explain - other work holds the device, or other such launches with
+// incomplete clusters of their own - is closed to further members and left to one of those that wait, which does all of it
+// alone (forward_alone_, backward_alone_): the same operations in the same order, slower by the number of members and by W_h
+// from the caches (us per frame, forward / backward, cluster against alone: fp32 256 cells 4.5 / 4.3 against 42 / 55, bf16 640 cells
+// 4.3 / 7.4 against 116 / 272).  So nothing waits for workgroups that may not come.  Every wait of the exchange is bounded all the same
+// (wait_ticks of the 100 MHz clock, or another workgroup's expiry): the workgroup raises kStatusWaitExpired and returns.
 //
 // MFMA operand mapping (16x16 tiles) as in lstm_resident.hip.
 #include "gemm_core.hpp"
@@ -89,22 +93,318 @@ __device__ inline bool get_(const ClusterDesc& p, const word_t* base, Off off, u
     }
 }
 
-// Place of this workgroup, and the tag of the launch's frame 0.
+// Place of this workgroup, and the tag of the launch's frame 0, which the word that closes a cluster carries.
 struct Place { int li, d, b0, blk, m, cluster; uint32_t tag0; };
+constexpr uint32_t kTogether = 1u, kAlone = 2u;            // that word: all members have started; left to member x - kAlone
 template <class C> __device__ inline bool place_(const ClusterDesc& p, Place& w) {
     __shared__ uint32_t sh[2];
+    const int blocks = (p.r.B + 15) / 16;
     if (threadIdx.x == 0) {
-        sh[0] = __hip_atomic_fetch_add(p.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh[1] = *p.epoch;
+        // (a bound of 0: every cluster consists of one workgroup, which takes all its places)
+        const uint32_t t = __hip_atomic_fetch_add(p.ticket, p.join_ticks == 0 ? (uint32_t)C::S : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t tag0 = (*p.epoch * (uint32_t)p.launches + (uint32_t)p.launch) * (uint32_t)p.r.T + 1u;
+        sh[0] = t; sh[1] = tag0;
+        if (t % C::S == C::S - 1 && t < (uint32_t)(p.r.L * p.r.D * blocks) * (uint32_t)C::S) put_((word_t*)p.closed, t / C::S * 8u, kTogether, tag0);
     }
     __syncthreads();
     const int t = __builtin_amdgcn_readfirstlane((int)sh[0]);
-    const int blocks = (p.r.B + 15) / 16, cluster = t / C::S, pair = cluster / blocks;
+    const int cluster = t / C::S, pair = cluster / blocks;
     if (pair >= p.r.L * p.r.D) return false;
     w.m = t % C::S; w.cluster = cluster; w.blk = cluster % blocks; w.b0 = w.blk * C::RB;
     w.li = __builtin_amdgcn_readfirstlane(p.r.lmap.idx[pair / p.r.D]); w.d = pair % p.r.D;
-    w.tag0 = ((uint32_t)__builtin_amdgcn_readfirstlane((int)sh[1]) * (uint32_t)p.launches + (uint32_t)p.launch) * (uint32_t)p.r.T + 1u;
+    w.tag0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh[1]);
     return true;
+}
+
+// Waits until the cluster is closed: kTogether, or kAlone + the member it is left to.  Exactly one of the two is decided, by the
+// ticket counter: whoever takes the last place, or whoever moves the counter past the places that are left.
+template <class C> __device__ inline uint32_t join_(const ClusterDesc& p, const Place& w) {
+    if (p.join_ticks == 0) return kAlone + (uint32_t)w.m;
+    word_t* const closed = (word_t*)p.closed + w.cluster;
+    const uint32_t end = (uint32_t)(w.cluster + 1) * (uint32_t)C::S;
+    uint64_t t0 = 0;
+    bool half = false;
+#pragma unroll 1
+    for (uint32_t tries = 0;; ++tries) {
+        const uint64_t x = __hip_atomic_load(closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) == w.tag0) return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+        if ((tries & 15) != 15) continue;
+        const uint64_t now = wall_clock64();
+        if (t0 == 0) t0 = now;
+        if (now - t0 < p.join_ticks) continue;
+        uint32_t seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (seen < end) {
+            if (threadIdx.x == 0 && __hip_atomic_compare_exchange_strong(p.ticket, &seen, end, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                put_(closed, 0u, kAlone + (uint32_t)w.m, w.tag0);
+        } else if (now - t0 - p.join_ticks >= p.wait_ticks / 2) {      // (decided, the word is on its way: as any other exchange)
+            if (half) { raise_status_(p.status, kStatusWaitExpired); return 0u; }
+            half = true; t0 = now - p.join_ticks;
+        }
+    }
+}
+
+// One 16-byte fragment of a row of W_h (forward): gate q of unit u, k-chunk at k0.
+template <typename T, class C> __device__ inline uint4 fwd_frag_(buf_t wh, int H, int q, int u, int k0, int g) {
+    const int k = k0 + g * C::EL;                          // H is a multiple of 4
+    const uint32_t vw = u < H && k < H ? (uint32_t)(u * H + g * C::EL) * (uint32_t)sizeof(T) : kOutOfRange;
+    uint4 v = buf_load16_(wh, vw, (uint32_t)(q * H * H + k0) * (uint32_t)sizeof(T));
+    if (k + C::EL > H) v.z = v.w = 0u;                     // bf16, H = 4 mod 8: half a fragment
+    return v;
+}
+
+// Gates from pre-activations, in place, and the new cell state; returns h.
+__device__ inline float fwd_cell_(f32x4_t (&acc)[4], int i, float& c) {
+    acc[0][i] = sigmoidf_(acc[0][i]); acc[1][i] = sigmoidf_(acc[1][i]);
+    acc[2][i] = tanhf_(acc[2][i]); acc[3][i] = sigmoidf_(acc[3][i]);
+    c = acc[1][i] * c + acc[0][i] * acc[2][i];
+    return acc[3][i] * tanhf_(c);
+}
+
+// The da of one cell from dh, dc, the gates, c_t and c_{t'}; dc becomes that of the next frame.
+// (rows past the batch and units past H: all gates were read as 0, so all four results are 0)
+__device__ inline void bwd_cell_(float (&a)[4], float dh, float& dc, const float (&gate)[4], float c, float c_prev) {
+    const float ig = gate[0], fg = gate[1], gg = gate[2], og = gate[3];
+    const float tc = tanhf_(c);
+    const float dov = dh * tc;
+    const float dcv = dc + dh * og * (1.f - tc * tc);
+    const float di = dcv * gg, dg = dcv * ig, df = dcv * c_prev;
+    dc = dcv * fg;
+    a[0] = di * ig * (1.f - ig); a[1] = df * fg * (1.f - fg);
+    a[2] = dg * (1.f - gg * gg); a[3] = dov * og * (1.f - og);
+}
+
+// fp32: the two waves of a unit hold halves of the contraction; each finishes two of the four rows of a lane.
+template <class C> __device__ inline void swap_halves_(f32x4_t (&acc)[4], float* red, int kh, int wave, int lane) {
+    float* mine = red + (wave * 8) * 64 + lane;
+    const float* other = red + ((wave ^ C::NU) * 8) * 64 + lane;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        mine[(2 * q) * 64] = kh == 0 ? acc[q][2] : acc[q][0];
+        mine[(2 * q + 1) * 64] = kh == 0 ? acc[q][3] : acc[q][1];
+    }
+    lds_barrier_();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        acc[q][0] = (kh == 0 ? acc[q][0] : acc[q][2]) + other[(2 * q) * 64];
+        acc[q][1] = (kh == 0 ? acc[q][1] : acc[q][3]) + other[(2 * q + 1) * 64];
+    }
+}
+
+// Four bytes of h: a value, or (bf16) two units of one row, swapped with the neighbouring unit's lane: row 2 i + r % 2.
+template <typename T, int PR> __device__ inline uint32_t h_word_(const float (&h)[PR], int i, int r) {
+    if constexpr (sizeof(T) == 2) {
+        const uint32_t own = pack_bf16(h[2 * i], h[2 * i + 1]);
+        const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+        return (r & 1) ? (nb >> 16) | (own & 0xffff0000u) : (own & 0xffffu) | (nb << 16);
+    } else {
+        return __builtin_bit_cast(uint32_t, h[i]);
+    }
+}
+
+// The 16 bytes of consecutive rows k.. of column n of gate q of W_h (backward).
+template <typename T> __device__ inline uint4 bwd_frag_(buf_t wh, int H, int q, int k, int n) {
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        constexpr int EPW = 4 / (int)sizeof(T);
+        const int k0 = k + i * EPW;                        // (H: a multiple of 4)
+        const uint32_t at = k0 < H && n < H ? (uint32_t)((q * H + k0) * H + n) * (uint32_t)sizeof(T) : kOutOfRange;
+        if constexpr (EPW == 1) v[i] = __builtin_bit_cast(uint32_t, buf_load_(wh, at, 0u));
+        else v[i] = buf_load2_(wh, at, 0u) | (buf_load2_(wh, at, (uint32_t)H * 2u) << 16);
+    }
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// Column sums of da of member mm over the threads of a unit, in order.
+template <class C> __device__ inline void bias_sums_(const ClusterDesc& cd, const Place& w, float (&bred)[4][256], const float (&bs)[4], int mm) {
+    constexpr int U = C::U, RSTEP = 256 / U;
+    const RecDesc& p = cd.r;
+    const int tid = threadIdx.x, H = p.H, cu = mm * U + tid % U;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bred[q][tid] = bs[q];
+    __syncthreads();
+    if (tid < U && cu < H) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v = bred[q][tid];
+#pragma unroll
+            for (int k = 1; k < RSTEP; ++k) v += bred[q][tid + k * U];
+            p.dbp[w.li * p.sDBi + (int64_t)w.blk * ((int64_t)p.D * H * 4) + (int64_t)w.d * 4 * H + (int64_t)q * H + cu] = v;
+        }
+    }
+}
+
+// ---- a cluster left to one workgroup --------------------------------------------------------------
+// What the members do, member after member in every frame, with the operations of the two kernels above on the same operands in
+// the same order (the results have the same bits); the fragments of W_h come from memory for every use, and what the
+// members keep in registers from frame to frame lies in memory: the cell state in its tensor (dL/dc in the buffer of the
+// frame-by-frame kernels), h in LDS, dh and the sums for the bias gradients in the exchange words, tagged 0, which is no tag in use.
+template <typename T, int S>
+__device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, char* lds, float* red) {
+    typedef Cl<T, S> C;
+    constexpr int KS = C::KS, PR = 4 / KS;
+    const RecDesc& p = cd.r;
+    const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
+    const int kh = wave / C::NU, row0 = 4 * g + (KS == 2 ? 2 * kh : 0);
+    const uint32_t DH = (uint32_t)(D * H), G4 = DH * 4;
+    const buf_t gates = make_buf_(p.gates + w.li * p.sGi, (int64_t)Tn * B * G4 * 4);
+    const buf_t cbuf = make_buf_(p.c + w.li * p.sCi + (int64_t)d * Tn * B * H, (int64_t)Tn * B * H * 4);
+    const buf_t y = make_buf_((const T*)p.y + w.li * p.sYi, (int64_t)Tn * B * DH * sizeof(T));
+    const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
+#pragma unroll 1
+    for (int s = 0; s < Tn; ++s) {
+        const uint32_t m = (uint32_t)(d == 0 ? s : Tn - 1 - s) * B, m_prev = (uint32_t)(d == 0 ? s - 1 : Tn - s) * B;
+        const char* const hl = lds + (s & 1) * (C::RB * C::FWD_ROW);
+        char* const ho = lds + ((s + 1) & 1) * (C::RB * C::FWD_ROW);
+#pragma unroll 1
+        for (int mm = 0; mm < S; ++mm) {
+            const int u = mm * C::U + (wave % C::NU) * 16 + r;
+            float pre[4][PR], cs[PR], h[PR];
+            uint32_t vg[PR], vc[PR];
+#pragma unroll
+            for (int i = 0; i < PR; ++i) {
+                const uint32_t row = w.b0 + row0 + i;
+                const bool ok = u < H && (int)row < B;
+                vg[i] = ok ? (row * G4 + d * 4 * H + u) * 4u : kOutOfRange;
+                vc[i] = ok ? (row * H + u) * 4u : kOutOfRange;
+                cs[i] = s > 0 ? buf_load_(cbuf, vc[i], m_prev * H * 4u) : 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) pre[q][i] = buf_load_(gates, vg[i], (m * G4 + q * H) * 4u);
+            }
+            f32x4_t acc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (KS == 1) acc[q] = f32x4_t{pre[q][0], pre[q][1], pre[q][2], pre[q][3]};
+                else acc[q] = kh == 0 || s == 0 ? f32x4_t{pre[q][0], pre[q][1], 0.f, 0.f} : f32x4_t{0.f, 0.f, pre[q][0], pre[q][1]};
+            }
+            if (s > 0) {
+                const char* hrow = hl + r * C::FWD_ROW + kh * (C::CW * 64) + g * 16;
+#pragma unroll 1
+                for (int c = 0; c < C::CW; ++c) {
+                    const uint4 a = *(const uint4*)(hrow + c * 64);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, fwd_frag_<T, C>(wh, H, q, u, (kh * C::CW + c) * C::KC, g));
+                }
+                if constexpr (KS == 2) swap_halves_<C>(acc, red, kh, wave, lane);
+            }
+#pragma unroll
+            for (int i = 0; i < PR; ++i) h[i] = fwd_cell_(acc, i, cs[i]);
+#pragma unroll
+            for (int i = 0; i < PR / C::VW; ++i) {
+                const int row = row0 + i * C::VW + (C::VW == 2 ? r & 1 : 0);
+                const uint32_t hw = h_word_<T>(h, i, r);
+                *(uint32_t*)(ho + row * C::FWD_ROW + u / C::VW * 4) = hw;
+                const uint32_t vy = u < H && w.b0 + row < B ? ((uint32_t)(w.b0 + row) * DH + d * H + (u & ~(C::VW - 1))) * (uint32_t)sizeof(T) : kOutOfRange;
+                buf_store_(__builtin_bit_cast(float, hw), y, vy, m * DH * (uint32_t)sizeof(T));
+            }
+#pragma unroll
+            for (int i = 0; i < PR; ++i) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) buf_store_(acc[q][i], gates, vg[i], (m * G4 + q * H) * 4u);
+                buf_store_(cs[i], cbuf, vc[i], m * H * 4u);
+            }
+            __syncthreads();
+        }
+    }
+}
+
+template <typename T, int S>
+__device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, char* lds, float (&bred)[4][256]) {
+    typedef Cl<T, S> C;
+    constexpr int U = C::U, PPT = C::PPT, RSTEP = 256 / U;
+    const RecDesc& p = cd.r;
+    const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
+    const uint32_t DH = (uint32_t)(D * H), G4 = DH * 4;
+    const buf_t gates = make_buf_(p.gates + w.li * p.sGi, (int64_t)Tn * B * G4 * 4);
+    const buf_t cbuf = make_buf_(p.c + w.li * p.sCi + (int64_t)d * Tn * B * H, (int64_t)Tn * B * H * 4);
+    const buf_t dy = make_buf_(p.dy + w.li * p.sDYi, (int64_t)Tn * B * DH * 4);
+    const buf_t da = make_buf_((const T*)p.da + w.li * p.sDAi, (int64_t)Tn * B * G4 * sizeof(T));
+    const buf_t dcb = make_buf_(p.dc + w.li * p.sDCi + (int64_t)d * B * H, (int64_t)B * H * 4);
+    const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
+    // scratch: dh [16 rows][KP] in the first slot of the cluster, sums of da [member][gate][thread] in the second
+    word_t* const dh_buf = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT;
+    word_t* const bs_buf = dh_buf + C::BWD_SLOT;
+    static_assert(S * 4 * 256 <= C::BWD_SLOT, "the sums of da fit a slot");
+    auto get = [](const word_t* at) { return __builtin_bit_cast(float, (uint32_t)__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); };
+    const int uu = tid % U;
+#pragma unroll 1
+    for (int s = 0; s < Tn; ++s) {
+        const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B, m_next = (uint32_t)(d == 0 ? Tn - 2 - s : s + 1) * B;
+        f32x4_t sum[C::NT];                                // over the members, in order
+#pragma unroll
+        for (int j = 0; j < C::NT; ++j) sum[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int mm = 0; mm < S; ++mm) {
+            const int cu = mm * U + uu;
+            float bs[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bs[q] = s > 0 ? get(bs_buf + (mm * 4 + q) * 256 + tid) : 0.f;
+#pragma unroll 1
+            for (int i = 0; i < PPT; ++i) {
+                const int lr = tid / U + i * RSTEP;
+                const uint32_t row = w.b0 + lr;
+                const bool ok = cu < H && (int)row < B;
+                const uint32_t vg = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange, vc = ok ? (row * H + cu) * 4u : kOutOfRange;
+                const uint32_t vy = ok ? (row * DH + d * H + cu) * 4u : kOutOfRange;
+                float gate[4], a4[4], dc = s > 0 ? buf_load_(dcb, vc, 0u) : 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) gate[q] = buf_load_(gates, vg, (m * G4 + q * H) * 4u);
+                const float dh = s > 0 ? get(dh_buf + lr * C::KP + cu) : 0.f;
+                const float c_prev = buf_load_(cbuf, s + 1 < Tn ? vc : kOutOfRange, s + 1 < Tn ? m_next * H * 4u : 0u);
+                bwd_cell_(a4, buf_load_(dy, vy, m * DH * 4u) + dh, dc, gate, buf_load_(cbuf, vc, m * H * 4u), c_prev);
+                buf_store_(dc, dcb, vc, 0u);
+                T* arow = (T*)(lds + lr * C::BWD_ROW) + uu;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    bs[q] += a4[q];
+                    const T v = Elem<T>::from(a4[q]);
+                    arow[q * U] = v;
+                    buf_store_(v, da, ok ? vg / (4u / (uint32_t)sizeof(T)) : kOutOfRange, (m * G4 + q * H) * (uint32_t)sizeof(T));
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) put_(bs_buf + (mm * 4 + q) * 256, (uint32_t)tid * 8u, __builtin_bit_cast(uint32_t, bs[q]), 0u);
+            __syncthreads();
+            if (s + 1 < Tn) {
+                f32x4_t acc[C::NT];
+#pragma unroll
+                for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                const char* arow = lds + r * C::BWD_ROW + g * 16;
+#pragma unroll 1
+                for (int c = 0; c < C::BCH; ++c) {
+                    const uint4 a = *(const uint4*)(arow + c * 64);
+                    const int q = c * C::KC / U, k = mm * U + c * C::KC % U + g * C::EL;       // a chunk lies in one gate
+#pragma unroll
+                    for (int j = 0; j < C::NT; ++j) {
+                        const int n = (wave + 4 * j) * 16 + r;
+                        mma16_<T>(acc[j], a, bwd_frag_<T>(wh, H, q, k, n));
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < C::NT; ++j) sum[j] += acc[j];
+            }
+            __syncthreads();                               // the operand is read
+        }
+        if (s + 1 < Tn) {
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    put_(dh_buf + (wave + 4 * j) * 16, (uint32_t)((4 * g + i) * C::KP + r) * 8u, __builtin_bit_cast(uint32_t, (float)sum[j][i]), 0u);
+            __threadfence();
+            __syncthreads();
+        }
+    }
+#pragma unroll 1
+    for (int mm = 0; mm < S; ++mm) {
+        float bs[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bs[q] = get(bs_buf + (mm * 4 + q) * 256 + tid);
+        bias_sums_<C>(cd, w, bred, bs, mm);
+        __syncthreads();
+    }
 }
 
 }  // namespace
@@ -137,16 +437,14 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
     {
         const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
 #pragma unroll
-        for (int c = 0; c < C::CW; ++c) {
-            const int k0 = (kh * C::CW + c) * C::KC;       // H is a multiple of 4
-            const int k = k0 + g * C::EL;
-            const uint32_t vw = ok_u && k < H ? (uint32_t)(u * H + g * C::EL) * (uint32_t)sizeof(T) : kOutOfRange;
+        for (int c = 0; c < C::CW; ++c)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                wf[q][c] = buf_load16_(wh, vw, (uint32_t)(q * H * H + k0) * (uint32_t)sizeof(T));
-                if (k + C::EL > H) wf[q][c].z = wf[q][c].w = 0u;         // bf16, H = 4 mod 8: half a fragment
-            }
-        }
+            for (int q = 0; q < 4; ++q) wf[q][c] = fwd_frag_<T, C>(wh, H, q, u, (kh * C::CW + c) * C::KC, g);
+    }
+    const uint32_t how = join_<C>(cd, w);
+    if (how != kTogether) {
+        if (how == kAlone + (uint32_t)w.m) forward_alone_<T, S>(cd, w, lds, red);
+        return;
     }
     // rows this lane finishes: row0 + i, i < PR
     const int row0 = 4 * g + (KS == 2 ? 2 * kh : 0);
@@ -205,21 +503,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
 #pragma unroll
                 for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, wf[q][c]);
             }
-            if constexpr (KS == 2) {                       // swap the halves: each wave finishes two of the four rows
-                float* mine = red + (wave * 8) * 64 + lane;
-                const float* other = red + ((wave ^ C::NU) * 8) * 64 + lane;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    mine[(2 * q) * 64] = kh == 0 ? acc[q][2] : acc[q][0];
-                    mine[(2 * q + 1) * 64] = kh == 0 ? acc[q][3] : acc[q][1];
-                }
-                lds_barrier_();
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc[q][0] = (kh == 0 ? acc[q][0] : acc[q][2]) + other[(2 * q) * 64];
-                    acc[q][1] = (kh == 0 ? acc[q][1] : acc[q][3]) + other[(2 * q + 1) * 64];
-                }
-            }
+            if constexpr (KS == 2) swap_halves_<C>(acc, red, kh, wave, lane);
         } else {
             if constexpr (KS == 2) {
 #pragma unroll
@@ -229,25 +513,14 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
         }
         float h[PR];
 #pragma unroll
-        for (int i = 0; i < PR; ++i) {                     // the gates replace the pre-activations
-            acc[0][i] = sigmoidf_(acc[0][i]); acc[1][i] = sigmoidf_(acc[1][i]);
-            acc[2][i] = tanhf_(acc[2][i]); acc[3][i] = sigmoidf_(acc[3][i]);
-            cs[i] = acc[1][i] * cs[i] + acc[0][i] * acc[2][i];
-            h[i] = acc[3][i] * tanhf_(cs[i]);
-        }
+        for (int i = 0; i < PR; ++i) h[i] = fwd_cell_(acc, i, cs[i]);              // (the gates replace the pre-activations)
         // h first: the other workgroups wait for it (rows past the batch and units past H too: they are read, as zeros or unused)
         word_t* const out = per_frame_(xch + ((s + 1) & 1) * C::FWD_SLOT);
         const uint32_t out_lane = (uint32_t)((row0 + (C::VW == 2 ? r & 1 : 0)) * C::RW + u / C::VW) * 8u;
         uint32_t hw[PR / C::VW];
 #pragma unroll
         for (int i = 0; i < PR / C::VW; ++i) {
-            if constexpr (C::VW == 2) {                    // swap with the neighbouring unit: two units of one row to a word
-                const uint32_t own = pack_bf16(h[2 * i], h[2 * i + 1]);
-                const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
-                hw[i] = (r & 1) ? (nb >> 16) | (own & 0xffff0000u) : (own & 0xffffu) | (nb << 16);
-            } else {
-                hw[i] = __builtin_bit_cast(uint32_t, h[i]);
-            }
+            hw[i] = h_word_<T>(h, i, r);
             if (s + 1 < Tn) put_(out + i * C::VW * C::RW, out_lane, hw[i], w.tag0 + s + 1);
         }
 #pragma unroll
@@ -364,6 +637,11 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         }
         lds_barrier_();                                    // the operand of the products goes into the same LDS
     }
+    const uint32_t how = join_<C>(cd, w);
+    if (how != kTogether) {
+        if (how == kAlone + (uint32_t)w.m) backward_alone_<T, S>(cd, w, lds, bred);
+        return;
+    }
     float dcr[PPT], bs[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < PPT; ++i) dcr[i] = 0.f;
@@ -395,15 +673,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         float a4[PPT][4];
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
-            // rows past the batch and units past H: all gates were read as 0, so all four results are 0
-            const float dhv = in_dy[i] + dh[i], ig = in_g[i][0], fg = in_g[i][1], gg = in_g[i][2], og = in_g[i][3];
-            const float tc = tanhf_(in_c[i]);
-            const float dov = dhv * tc;
-            const float dcv = dcr[i] + dhv * og * (1.f - tc * tc);
-            const float di = dcv * gg, dg = dcv * ig, df = dcv * c_prev[i];
-            dcr[i] = dcv * fg;
-            a4[i][0] = di * ig * (1.f - ig); a4[i][1] = df * fg * (1.f - fg);
-            a4[i][2] = dg * (1.f - gg * gg); a4[i][3] = dov * og * (1.f - og);
+            bwd_cell_(a4[i], in_dy[i] + dh[i], dcr[i], in_g[i], in_c[i], c_prev[i]);
             T* arow = (T*)(al + (tid / U + i * RSTEP) * C::BWD_ROW) + uu;
 #pragma unroll
             for (int q = 0; q < 4; ++q) { bs[q] += a4[i][q]; arow[q * U] = Elem<T>::from(a4[i][q]); }
@@ -441,19 +711,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             for (int q = 0; q < 4; ++q) buf_store_(Elem<T>::from(a4[i][q]), da, va, (m * G4 + q * H) * (uint32_t)sizeof(T));
         }
     }
-    // column sums over the threads of a unit, in order
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bred[q][tid] = bs[q];
-    __syncthreads();
-    if (tid < U && ok_c) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float v = bred[q][tid];
-#pragma unroll
-            for (int k = 1; k < RSTEP; ++k) v += bred[q][tid + k * U];
-            p.dbp[w.li * p.sDBi + (int64_t)w.blk * G4 + (int64_t)d * 4 * H + (int64_t)q * H + cu] = v;
-        }
-    }
+    bias_sums_<C>(cd, w, bred, bs, w.m);
 }
 
 // ---- rule and launchers -----------------------------------------------------------------------------
@@ -499,14 +757,15 @@ bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count) {
 }
 
 int rec_cluster_batch_tiles(const RecDesc& d) { return cluster_blocks(d); }
+int64_t rec_cluster_count(const RecDesc& d) { return (int64_t)d.L * d.D * cluster_blocks(d); }
 
 int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward) {
     const int64_t S = cluster_members(d), KP = S * (d.precision ? 64 : 32), row = backward ? S * KP : d.precision ? KP / 2 : KP;
-    return (int64_t)d.L * d.D * cluster_blocks(d) * 2 * 16 * row;
+    return rec_cluster_count(d) * 2 * 16 * row;
 }
 
 hipError_t launch_rec_cluster(const ClusterDesc& p, bool backward, int cu_count, hipStream_t s) {
-    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || !p.ticket || !p.epoch || !p.status) return hipErrorInvalidValue;
+    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || !p.closed || !p.ticket || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
     const int S = cluster_members(p.r);
     if (p.r.precision) {
         switch (S) {

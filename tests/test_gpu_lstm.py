@@ -433,3 +433,37 @@ def test_cluster_wait_runs_out_and_is_reported():
         e.status()
     assert ei.value.code == Bd.EHIP and "wait" in str(ei.value)
     e.close()
+
+
+def _one_step(shape, L, prec, tune):
+    import torch
+    e = _engine(shape, L, S.FIXED_RING, prec)
+    for key, value in tune:
+        e.tune(key, value)
+    e.set_params(-1, torch.from_numpy(synth.initial_model(0, e.P, 0.1)).cuda())
+    e.step(_to_dev(_batches(shape, L, 0)), 0.1)
+    e.status()
+    out = [t.cpu().numpy().view(np.uint32).copy() for i in range(L) for t in (e.grads(i), e.params(i))]
+    e.close()
+    return out
+
+
+@pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 260), (0, 384), (0, 512), (1, 136), (1, 300), (1, 360), (1, 512), (1, 640)])
+def test_cluster_left_to_one_workgroup_gives_the_same_bits(prec, hidden):
+    # every cluster size; two blocks of rows, the second of one row; a bound of 0 lets one workgroup do each cluster's work
+    from paper_2110_11199_amd import binding as Bd
+    print("clusters left to one workgroup", prec, hidden, flush=True)
+    shape = Shape(12, hidden, 2, 1, 0, 24, 17, 4)
+    for a, b in zip(_one_step(shape, 2, prec, ()), _one_step(shape, 2, prec, ((Bd.TUNE_REC_JOIN_US, 0),))):
+        assert (a == b).all()
+
+
+def test_cluster_waits_for_workgroups_that_have_not_started():
+    # 64 clusters of 6 workgroups on 256 compute units: the cluster that is short of workgroups at first waits for one of the 42
+    # before it to end (100 frames, some hundreds of microseconds).  That is no expiry of the bound on the exchange, nor
+    # does it matter whether the cluster is left to one of its workgroups instead (bound of 20 microseconds)
+    from paper_2110_11199_amd import binding as Bd
+    print("cluster short of workgroups", flush=True)
+    shape = Shape(12, 360, 1, 1, 0, 24, 64, 100)
+    for a, b in zip(_one_step(shape, 8, 1, ((Bd.TUNE_REC_WAIT_US, 150),)), _one_step(shape, 8, 1, ((Bd.TUNE_REC_JOIN_US, 20),))):
+        assert (a == b).all()
