@@ -366,7 +366,8 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
 #define ADPSGD_TUNE_REC_JOIN_US     9
 #define ADPSGD_TUNE_MEAN_CHUNK      5   /* global-mean update: elements per chunk of its two-kernel form (a multiple of
                                            1024, at most 16777216), 0 = the single-kernel form, -1 (default) = automatic
-                                           (two kernels for 12 learners and more below 2^18 and from 3M parameters on);
+                                           (two kernels for 12 learners and more from 3M parameters on, and below 2^18 with
+                                           more than 2^24 over all learners);
                                            same results bit for bit */
 #define ADPSGD_TUNE_TRI_SEGMENT     6   /* ring-neighbour update (ADPSGD_MIX_TRI): ring positions one thread owns, 1, 2, 4 or 8
                                            (a workgroup then covers the ring of its element positions and the update stays
@@ -376,7 +377,8 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
                                            many element positions x 2 members (the partner's model comes through LDS), 0 =
                                            both members per thread, -1 = default (64 from 1M parameters on); same results
                                            bit for bit */
-#define ADPSGD_TUNE_SYNC_SEGMENT    8   /* update of the synchronous baseline (ADPSGD_SDPSGD): learners one thread owns, 2, 4 or
+#define ADPSGD_TUNE_SYNC_SEGMENT    8   /* update of the synchronous baseline (ADPSGD_SDPSGD) and single-kernel form of the
+                                           global mean (ADPSGD_MIX_ALL): learners one thread owns, 2, 4 or
                                            8 (the sum then runs through the segments of a workgroup in learner order), 0 =
                                            all learners of a position in one thread, -1 = default; same results bit for bit */
 int adpsgd_set_tuning(adpsgd_t h, int key, int value);

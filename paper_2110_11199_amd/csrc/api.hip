@@ -851,11 +851,11 @@ static int step_impl(adpsgd_t h, const void* const* batch_ptrs, float lr, const 
     u.tri_segment = h->tune_tri_segment;
     u.sync_segment = h->tune_sync_segment;
     u.pair_split = h->tune_pair_split;
-    {   // Two-kernel global mean: by default with 12 learners or more (streams per thread of the single kernel) where the extra
-        // launch does not matter, or where the single kernel's few threads walk all learners one after another.  us, one kernel
-        // / two: 16 x 100k 14.4 / 9.5, x 400k 20.7 / 24.3, x 1.25M 43 / 47, x 3M 99.8 / 98.0, x 7.7M 262 / 259; 12 x 100k
-        // 10.6 / 9.5, x 7.7M 196 / 197; 5 x 100k 5.2 / 8.7, x 7.7M 74 / 89.
-        const bool two = L >= 12 && (h->P >= 3000000 || h->P < (1 << 18));
+    {   // Two-kernel global mean: by default with 12 learners or more (streams per thread of the single kernels) on models
+        // large enough for the extra launch not to matter, and on the largest of the small ones that take segments (launch_update).
+        // us, one kernel / two: 16 x 400k 20.7 / 24.3, x 1.25M 43 / 47, x 3M 99.8 / 98.0, x 7.7M 262 / 255; 12 x 7.7M 196 / 197;
+        // 5 x 7.7M 74 / 89; 128 x 250k in segments of four 72 / 66.
+        const bool two = L >= 12 && (h->P >= 3000000 || (h->P < (1 << 18) && L * h->P > (1 << 24)));
         int64_t chunk = h->tune_mean_chunk >= 0 ? h->tune_mean_chunk : (two ? kMeanChunkDefault : 0);
         if (chunk > h->mean_cap) chunk = h->mean_cap;
         u.mean_buf = chunk > 0 ? h->mean_buf : nullptr;

@@ -222,23 +222,46 @@ __global__ __launch_bounds__(256) void sync_update_kernel(AllArgs p) {
     }
 }
 
-// The same update with the learners cut into segments of SEG: a workgroup of blockDim.x positions x blockDim.y segments;
-// a thread reads the SEG models and gradients of its segment (2 SEG streams instead of 2 L), and the sum of the updated
-// models runs through the segments in learner order, one segment per barrier, through LDS: the same additions in the
-// same order as the single walk, bit-identical results.  Every model of the workgroup's positions has been read before
-// the first result is written (the writes follow the last barrier), so it stays safe in place.
-template <int SEG>
-__global__ __launch_bounds__(1024) void sync_seg_update_kernel(AllArgs p) {
+__device__ inline void all_scalar_(const AllArgs& p, int64_t t) {
+    float s = p.src[t];
+    if (p.shadow && p.emit_input) p.shadow[t] = f32_to_bf16(s);
+    for (int j = 1; j < p.L; ++j) {
+        const float v = p.src[j * p.stride + t];
+        if (p.shadow && p.emit_input) p.shadow[j * p.stride + t] = f32_to_bf16(v);
+        s = __fadd_rn(s, v);
+    }
+    const float m = __fmul_rn(s, p.inv_L);
+    for (int i = 0; i < p.L; ++i) {
+        const float r = sgd_(m, p.lr, p.g[i][t]);
+        p.dst[i * p.stride + t] = r;
+        if (p.shadow && !p.emit_input) p.shadow[i * p.stride + t] = f32_to_bf16(r);
+    }
+}
+
+// The mean of all learners with the learners cut into segments of SEG: a workgroup of blockDim.x positions x blockDim.y segments;
+// a thread reads the SEG models and gradients of its segment (2 SEG streams instead of 2 L), and the sum of the models (FIRST:
+// of the updated models, the synchronous baseline) runs through the segments in learner order, one segment per barrier,
+// through LDS: the same additions in the same order as the single walk, bit-identical results.  Every model of the workgroup's
+// positions has been read before the first result is written (the writes follow the last barrier), so it stays safe in place.
+template <int SEG, bool FIRST>
+__global__ __launch_bounds__(1024) void mean_seg_update_kernel(AllArgs p) {
     __shared__ float4 chain[64];
     const int tx = threadIdx.x, sy = threadIdx.y, nx = blockDim.x, ns = blockDim.y;
     const int64_t e = (int64_t)blockIdx.x * nx + tx;
     const bool ok = e < (p.P >> 2);
     const int j0 = sy * SEG;
-    if (blockIdx.x == 0 && sy == 0 && tx < (p.P & 3)) sync_scalar_(p, ((p.P >> 2) << 2) + tx);     // the P % 4 last elements
-    float4 u[SEG];
+    if (blockIdx.x == 0 && sy == 0 && tx < (p.P & 3)) {                                             // the P % 4 last elements
+        if constexpr (FIRST) sync_scalar_(p, ((p.P >> 2) << 2) + tx);
+        else all_scalar_(p, ((p.P >> 2) << 2) + tx);
+    }
+    float4 u[SEG], g[SEG];
 #pragma unroll
-    for (int j = 0; j < SEG; ++j)
-        if (ok && j0 + j < p.L) u[j] = pair_new_(ldnt_(p.src + (j0 + j) * p.stride, e), p.lr, ldnt_(p.g[j0 + j], e));
+    for (int j = 0; j < SEG; ++j) {
+        if (!ok || j0 + j >= p.L) continue;
+        u[j] = ldnt_(p.src + (j0 + j) * p.stride, e);
+        g[j] = ldnt_(p.g[j0 + j], e);
+        if constexpr (FIRST) u[j] = pair_new_(u[j], p.lr, g[j]);
+    }
     for (int step = 0; step < ns; ++step) {
         if (sy == step && ok) {
             float4 s = u[0];
@@ -256,34 +279,25 @@ __global__ __launch_bounds__(1024) void sync_seg_update_kernel(AllArgs p) {
 #pragma unroll
     for (int j = 0; j < SEG; ++j) {
         if (j0 + j >= p.L) break;
-        stnt_(p.dst + (j0 + j) * p.stride, e, m);
-        if (p.shadow) emit4_(p.shadow + (j0 + j) * p.stride, e, m);
+        const float4 r = FIRST ? m : pair_new_(m, p.lr, g[j]);
+        stnt_(p.dst + (j0 + j) * p.stride, e, r);
+        if (p.shadow) emit4_(p.shadow + (j0 + j) * p.stride, e, !FIRST && p.emit_input ? u[j] : r);
     }
 }
 
-template <int SEG>
-static void launch_sync_seg(const AllArgs& a, hipStream_t s) {
+template <int SEG, bool FIRST>
+static void launch_mean_seg_t(const AllArgs& a, hipStream_t s) {
     const int ns = (a.L + SEG - 1) / SEG;
     int nx = 64;
     while (nx * ns > 512 && nx > 8) nx >>= 1;
     const int64_t n4 = a.P >> 2;
-    hipLaunchKernelGGL(sync_seg_update_kernel<SEG>, dim3((unsigned)((n4 + nx - 1) / nx)), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
+    hipLaunchKernelGGL((mean_seg_update_kernel<SEG, FIRST>), dim3((unsigned)((n4 + nx - 1) / nx)), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
 }
-
-__device__ inline void all_scalar_(const AllArgs& p, int64_t t) {
-    float s = p.src[t];
-    if (p.shadow && p.emit_input) p.shadow[t] = f32_to_bf16(s);
-    for (int j = 1; j < p.L; ++j) {
-        const float v = p.src[j * p.stride + t];
-        if (p.shadow && p.emit_input) p.shadow[j * p.stride + t] = f32_to_bf16(v);
-        s = __fadd_rn(s, v);
-    }
-    const float m = __fmul_rn(s, p.inv_L);
-    for (int i = 0; i < p.L; ++i) {
-        const float r = sgd_(m, p.lr, p.g[i][t]);
-        p.dst[i * p.stride + t] = r;
-        if (p.shadow && !p.emit_input) p.shadow[i * p.stride + t] = f32_to_bf16(r);
-    }
+template <bool FIRST>
+static void launch_mean_seg(const AllArgs& a, int seg, hipStream_t s) {
+    if (seg >= 8) launch_mean_seg_t<8, FIRST>(a, s);
+    else if (seg >= 4) launch_mean_seg_t<4, FIRST>(a, s);
+    else launch_mean_seg_t<2, FIRST>(a, s);
 }
 
 // One thread owns an element index of all learners: reads L models, forms the
@@ -695,11 +709,17 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
             // after another (us, one walk -> two learners: 16 x 100k 10.4 -> 6.2, x 400k 16.2 -> 14.5, x 800k 23.3 -> 28.1;
             // 8 x 400k 8.9 -> 7.2; 5 x 400k 6.3 -> 6.4).
             const bool large = d.P >= (4 << 20) && d.L >= 4, small = d.P >= (1 << 16) && d.P < (1 << 19) && d.L >= 8;
-            const int seg = d.sync_segment >= 0 ? d.sync_segment : (large || small ? 2 : 0);
-            if (d.update_first && n4 > 0 && seg >= 2 && d.L > seg) {
-                if (seg >= 8) launch_sync_seg<8>(a, s);
-                else if (seg >= 4) launch_sync_seg<4>(a, s);
-                else launch_sync_seg<2>(a, s);
+            // The delayed mean: segments on small models (us, one walk / two learners / four / two kernels: 12 x 20k 7.6 / 4.5 /
+            // 4.7 / 7.3, 16 x 100k 12.3 / 5.6 / 6.1 / 10.5, 64 x 100k 45 / 17.6 / 14.5 / 22, 64 x 250k 55 / 36.7 / 35.2 / 36.9;
+            // 128 x 250k 106 / 90 / 72 / 66) and on the largest of 8 to 11 learners (60M, one walk / two learners / two
+            // kernels: 8 1025 / 931 / 1014, 11 1435 / 1295 / 1376).
+            const bool small_mean = d.P < (1 << 18) && d.L >= 12 && d.L * d.P <= (1 << 24), large_mean = d.P >= (1 << 25) && d.L >= 8;
+            const int seg = d.sync_segment >= 0 ? d.sync_segment
+                            : d.update_first ? (large || small ? 2 : 0)
+                            : (small_mean && d.L >= 32 ? 4 : small_mean || large_mean ? 2 : 0);
+            if (n4 > 0 && seg >= 2 && d.L > seg) {
+                if (d.update_first) launch_mean_seg<true>(a, seg, s);
+                else launch_mean_seg<false>(a, seg, s);
             } else if (d.update_first) hipLaunchKernelGGL(sync_update_kernel<true>, dim3(blocks), dim3(256), 0, s, a);
             else hipLaunchKernelGGL(all_update_kernel<true>, dim3(blocks), dim3(256), 0, s, a);
         } else {

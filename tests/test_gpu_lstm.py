@@ -277,7 +277,7 @@ def test_synchronous_baseline_small_model(prec):
     assert ora.update_first and ora.consensus() == 0.0
 
 
-@pytest.mark.parametrize("case", ["pair", "tri", "tri_d1d", "sync"])
+@pytest.mark.parametrize("case", ["pair", "tri", "tri_d1d", "mean", "sync"])
 def test_segmented_update_kernels_write_the_bf16_copy_of_a_small_model(case):
     # the update kernels that large models take by default (one member of a pair per thread; the ring or the learners in
     # segments), forced on a small bf16 model: the bf16 copy of the next gradient point they write feeds the next iteration
@@ -290,6 +290,9 @@ def test_segmented_update_kernels_write_the_bf16_copy_of_a_small_model(case):
         _run_recurrence(shape, 5, S.RANDOM_RING, 1, 3, 0.1, tune=((Bd.TUNE_TRI_SEGMENT, 2),), mix=S.MIX_TRI)
     elif case == "tri_d1d":
         _run_recurrence(shape, 5, S.D1D, 1, 3, 0.1, tune=((Bd.TUNE_TRI_SEGMENT, 2),), mix=S.MIX_TRI)
+    elif case == "mean":
+        _run_recurrence(shape, 5, S.D1D, 1, 3, 0.1, tune=((Bd.TUNE_SYNC_SEGMENT, 2),))
+        _run_recurrence(shape, 5, S.FIXED_RING, 1, 3, 0.1, tune=((Bd.TUNE_SYNC_SEGMENT, 4),), mix=S.MIX_ALL)
     else:
         _run_recurrence(shape, 5, S.SDPSGD, 1, 3, 0.1, tune=((Bd.TUNE_SYNC_SEGMENT, 2),))
 

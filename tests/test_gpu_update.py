@@ -124,6 +124,24 @@ def test_synchronous_baseline_update_with_the_learners_in_segments(L, P, seg):
     _run(L, P, S.SDPSGD, 3, tune=[(Bd.TUNE_SYNC_SEGMENT, seg)])
 
 
+@pytest.mark.parametrize("seg", [2, 4, 8])
+@pytest.mark.parametrize("L,P", [(3, 70001), (5, 4099), (16, 70003), (64, 20001), (128, 1003), (13, 2)])
+def test_global_mean_with_the_learners_in_segments(L, P, seg):
+    # the delayed mean's models and gradients in segments too: whole and ragged last segments, P % 4 tails, fewer than
+    # four elements, ping-pong (tau = 1) and in place
+    from paper_2110_11199_amd import binding as Bd
+    print("global mean, segments", L, P, seg, flush=True)
+    tune = [(Bd.TUNE_MEAN_CHUNK, 0), (Bd.TUNE_SYNC_SEGMENT, seg)]
+    _run(L, P, S.D1D, 3, tune=tune)
+    _run(L, P, S.FIXED_RING, 3, mix=S.MIX_ALL, tau=0, tune=tune)
+
+
+@pytest.mark.parametrize("L,P", [(12, 20002), (32, 50725), (128, 131071), (128, 131077)])
+def test_global_mean_of_small_models_of_many_learners_by_default(L, P):
+    # segments of two and of four learners; the last two sizes lie on either side of the two-kernel form
+    _run(L, P, S.D1D, 2)
+
+
 def test_synchronous_baseline_update_at_a_size_that_takes_the_segments_by_default():
     print("update sync, 4 x (4M + 1) elements", flush=True)
     _run(4, (4 << 20) + 1, S.SDPSGD, 2)
