@@ -706,9 +706,11 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
             const unsigned blocks = (unsigned)((n4 > 0 ? n4 : 1) + 255) / 256;
             // Two learners per thread are the measured best on large models (64 x 135M: 5.16 -> 5.48 TB/s, 16 x 145M:
             // 5.49 -> 5.99; four 5.40 / 5.75, eight 5.34 / 5.67) and on small ones, where few threads walk all learners one
-            // after another (us, one walk -> two learners: 16 x 100k 10.4 -> 6.2, x 400k 16.2 -> 14.5, x 800k 23.3 -> 28.1;
-            // 8 x 400k 8.9 -> 7.2; 5 x 400k 6.3 -> 6.4).
-            const bool large = d.P >= (4 << 20) && d.L >= 4, small = d.P >= (1 << 16) && d.P < (1 << 19) && d.L >= 8;
+            // after another and the models of all learners still fit caches (us, one walk -> two learners: 16 x 100k 10.4 -> 6.3,
+            // x 400k 15.8 -> 14.8, x 520k 16.7 -> 18.0; 8 x 400k 8.7 -> 7.4; 5 x 400k 5.8 -> 6.3; 32 x 250k 24.6 -> 19.0, x 400k
+            // 29.1 -> 31.0; 64 x 250k 46.6 -> 40.9, x 400k 57 -> 64; 128 x 100k 78 -> 47, x 250k 90 -> 100).
+            const bool large = d.P >= (4 << 20) && d.L >= 4;
+            const bool small = d.P >= (1 << 16) && d.P < (7 << 16) && d.L >= 8 && d.L * d.P <= (d.P < (1 << 18) ? 1 << 24 : 1 << 23);
             // The delayed mean: segments on small models (us, one walk / two learners / four / two kernels: 12 x 20k 7.6 / 4.5 /
             // 4.7 / 7.3, 16 x 100k 12.3 / 5.6 / 6.1 / 10.5, 64 x 100k 45 / 17.6 / 14.5 / 22, 64 x 250k 55 / 36.7 / 35.2 / 36.9;
             // 128 x 250k 106 / 90 / 72 / 66) and on the largest of 8 to 11 learners (60M, one walk / two learners / two
