@@ -389,7 +389,8 @@ struct TriArgs {
     const float* src; float* dst; int64_t stride; int64_t P; float lr; float third; int L;
     bf16_t* shadow; int emit_input;
     const float* g[128];        // gradients in ring order
-    int32_t order[128];         // learners in ring order (whole words: a scalar load each, 16-bit entries take vector loads)
+    int32_t order[128];         // learners in ring order (whole words: a scalar load each)
+    int16_t order16[128];       // the same in 16 bits (vector loads)
 };
 
 __device__ inline float tri_mean_(float l, float c, float r, float third) { return __fmul_rn(__fadd_rn(__fadd_rn(l, c), r), third); }
@@ -407,11 +408,10 @@ __device__ inline void tri_scalar_(const TriArgs& p, int64_t t) {
     }
 }
 
-// Ring positions whose loads go out together: no load passes a store (the result may replace a model), so that a walk
-// position by position waits once for each.  12 x 1.25M with whole-word orders: 37 -> 34 us, 16 x 100k: 17.7 -> 8.8.
-constexpr int kTriBlock = 4;
-
-template <bool VEC>
+// BLOCK: ring positions whose loads go out together (no load passes a store, since the result may replace a model, so that a walk
+// position by position waits once for each).  The walk one by one reads the order from 16-bit entries, by vector loads, which
+// keep its waves from running apart: with scalar loads 16 x 3.5M takes 122 us instead of 112, 64 x 1.5M 213 instead of 192.
+template <bool VEC, int BLOCK>
 __global__ __launch_bounds__(256) void tri_update_kernel(TriArgs p) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if constexpr (VEC) {
@@ -419,19 +419,19 @@ __global__ __launch_bounds__(256) void tri_update_kernel(TriArgs p) {
         if (e < n4) {
             const float4 first = ldnt_(p.src + p.order[0] * p.stride, e);
             float4 prev = ldnt_(p.src + p.order[p.L - 1] * p.stride, e), cur = first;
-            for (int q0 = 0; q0 < p.L; q0 += kTriBlock) {
-                float4 next[kTriBlock], g[kTriBlock];
+            for (int q0 = 0; q0 < p.L; q0 += BLOCK) {
+                float4 next[BLOCK], g[BLOCK];
 #pragma unroll
-                for (int j = 0; j < kTriBlock; ++j) {
+                for (int j = 0; j < BLOCK; ++j) {
                     if (q0 + j >= p.L) break;
                     g[j] = ldnt_(p.g[q0 + j], e);
                     next[j] = first;
-                    if (q0 + j + 1 < p.L) next[j] = ldnt_(p.src + p.order[q0 + j + 1] * p.stride, e);
+                    if (q0 + j + 1 < p.L) next[j] = ldnt_(p.src + (BLOCK == 1 ? (int)p.order16[q0 + j + 1] : p.order[q0 + j + 1]) * p.stride, e);
                 }
 #pragma unroll
-                for (int j = 0; j < kTriBlock; ++j) {
+                for (int j = 0; j < BLOCK; ++j) {
                     if (q0 + j >= p.L) break;
-                    const int i = p.order[q0 + j];
+                    const int i = BLOCK == 1 ? (int)p.order16[q0 + j] : p.order[q0 + j];
                     const float4 m = make_float4(tri_mean_(prev.x, cur.x, next[j].x, p.third), tri_mean_(prev.y, cur.y, next[j].y, p.third),
                                                  tri_mean_(prev.z, cur.z, next[j].z, p.third), tri_mean_(prev.w, cur.w, next[j].w, p.third));
                     const float4 r = pair_new_(m, p.lr, g[j]);
@@ -742,15 +742,21 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
             if (d.order[i] < 0 || d.order[i] >= d.L || seen[d.order[i]]) return hipErrorInvalidValue;
             seen[d.order[i]] = true;
         }
-        for (int q = 0; q < 128; ++q) { a.order[q] = q < d.L ? d.order[q] : 0; a.g[q] = q < d.L ? d.g[d.order[q]] : nullptr; }
-        // Segments against the single walk, us for segments of none / 1 / 2: the walk has the fewest loads, but a thread walks
-        // 2 L streams (long rings of large models) and takes all learners' time (small models, a few workgroups per compute
-        // unit).  L = 16: 100k 8.8 / 6.6 / 6.6, 800k 30.4 / 26.6 / 28.4, 1.25M 44 / 43 / 44, 3M 104 / 105 / 100, 7.7M 276 / 258 / 244,
-        // 145M 5.5 / 5.8 / 6.1 TB/s (four positions 5.0); L = 8: 100k 5.6 / 5.6 / 5.5, 800k 14.6 / 13.7 / 16.1, 7.7M 132 / 122 / 140;
-        // L = 5: 400k 6.5 / 6.3 / 7.5, 7.7M 81 / 86 / 117.
+        for (int q = 0; q < 128; ++q) { a.order[q] = q < d.L ? d.order[q] : 0; a.order16[q] = (int16_t)a.order[q]; a.g[q] = q < d.L ? d.g[d.order[q]] : nullptr; }
+        // Segments against the single walk: the walk has the fewest loads, but a thread walks 2 L streams (long rings of large
+        // models) and takes all learners' time (small models, a few workgroups per compute unit).  us, walk / segments of one / two:
+        // L = 5 7.7M 81 / 86 / 117, 145M 1636 / 1622 / 2232; L = 6 4.3M 55 / 54 / 70, 145M 1972 / 1804 / 2408; L = 8 7.7M 132 / 125 / 141,
+        // 145M 2641 / 2344 / 2666; L = 9 4.3M 84 / 94 / 84, 30M 602 / 646 / 579; L = 11 7.7M 183 / 185 / 173; L = 16 7.7M 276 / 258 / 244,
+        // 145M 5.5 / 5.8 / 6.1 TB/s (four positions 5.0); and L = 16 100k 8.8 / 6.6 / 6.6, 400k 15.2 / 13.4 / 15.0, 900k 30 / 33 / 33; L = 8 400k
+        // 8.7 / 7.5 / 9.0, 900k 14.1 / 16.3 / 18.0.
         const int seg = d.tri_segment >= 0 ? d.tri_segment
-                        : d.P >= (4 << 20) ? (d.L >= 12 ? 2 : 0)
-                        : (d.P < (1 << 20) && d.L >= 8 ? 1 : 0);
+                        : d.P >= (4 << 20) ? (d.L >= 9 ? 2 : d.L >= 6 ? 1 : 0)
+                        : (d.P < (1 << 19) && d.L >= 8 ? 1 : 0);
+        // The walk: four positions at a time where the last round of the grid (2^21 elements fill the chip) is short, one by one where
+        // long rings fill it.  us, one by one / four: 12 x 600k 23.6 / 16.1, x 1.25M 37 / 34, 16 x 2.1M 78 / 72, 64 x 900k 138 / 131; and 16 x
+        // 1.5M 48 / 51, x 3.5M 112 / 123, 64 x 1.2M 167 / 177, x 1.5M 192 / 222, x 3.5M 481 / 533, 12 x 3.5M 84 / 91, 8 x 3.5M 56 / 59.
+        const bool one = d.P < (4 << 20) && (d.P < (1 << 21) ? d.P >= (d.L >= 64 ? 1100000 : 1500000) && d.L >= 12
+                                                             : d.L >= 12 ? d.P >= 2800000 : d.L >= 8 && d.P >= 3300000);
         if (vec && (d.P >> 2) > 0 && seg >= 1 && d.L > seg) {
             if (seg == 1) launch_tri_seg<1>(a, s);
             else if (seg >= 8) launch_tri_seg<8>(a, s);
@@ -758,9 +764,10 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
             else launch_tri_seg<2>(a, s);
         } else if (vec) {
             const int64_t n4 = d.P >> 2;
-            hipLaunchKernelGGL(tri_update_kernel<true>, dim3((unsigned)(((n4 > 0 ? n4 : 1) + 255) / 256)), dim3(256), 0, s, a);
+            if (one) hipLaunchKernelGGL((tri_update_kernel<true, 1>), dim3((unsigned)(((n4 > 0 ? n4 : 1) + 255) / 256)), dim3(256), 0, s, a);
+            else hipLaunchKernelGGL((tri_update_kernel<true, 4>), dim3((unsigned)(((n4 > 0 ? n4 : 1) + 255) / 256)), dim3(256), 0, s, a);
         } else {
-            hipLaunchKernelGGL(tri_update_kernel<false>, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((tri_update_kernel<false, 1>), dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, a);
         }
         return hipGetLastError();
     }
