@@ -808,42 +808,45 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Consensus distance: the squared deviations of the L models from their mean, summed in fp64.  Bound by one read of the models:
-// a workgroup takes 64 positions of four elements of all learners at a time, wave w the learners w, w + 4, ..., which it holds in registers between the mean (the waves' sums meet in LDS) and the
-// deviations, so that few streams are walked per thread and nothing is read twice.  The order of the sums does not depend on the
-// alignment (VEC: every vector 16-byte aligned).  (One thread that walked all learners of an element twice ran at 2.2 TB/s.)  Block sums through LDS, then one block adds
-// the partial sums in index order (a fixed order: the result is reproducible).
-template <int NL, bool VEC>    // learners per wave
+// Consensus distance: the squared deviations of the L models from their mean, summed in fp64.  Bound by one read of the models,
+// which a thread holds in registers between the mean and the deviations: those of its position of four elements, up to
+// 8 learners all (SPLIT 1); more are split over two (up to 16) or four waves, wave w the learners w, w + SPLIT, ..., whose sums
+// meet in LDS.  us, one thread walking all learners of an element twice / four waves / SPLIT: 2 x 8M 27 / 37 / 15, 5 x
+// 1M 9.2 / 11.5 / 7.3, 8 x 8M 79 / 54 / 43; shared by two waves 12 x 450k 8.7 / 9.7 / 8.3, 16 x 8M
+// 227 / 90 / 83.  The order of the sums does not depend on the alignment (VEC:
+// every vector 16-byte aligned).  Block sums through LDS, then one block adds the partial sums in index order (a fixed
+// order: the result is reproducible).
+template <int NL, bool VEC, int SPLIT>    // learners per wave; waves that share the learners of a position
 __global__ __launch_bounds__(256) void consensus_partial_kernel(const float* x, int64_t stride, int L, int64_t P, double* partial) {
-    constexpr int W = 4;
-    __shared__ double sums[2][4][W][64];
+    constexpr int W = 4, GROUPS = 4 / SPLIT;
+    __shared__ double sums[SPLIT > 1 ? 2 : 1][SPLIT > 1 ? 4 : 1][W][64];
     __shared__ double sh[256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, part = wave % SPLIT;
     const int64_t n = (P + W - 1) / W, nv = P / W;         // positions, whole positions
     double acc = 0.0;
     int buf = 0;
-    for (int64_t p0 = (int64_t)blockIdx.x * 64; p0 < n; p0 += (int64_t)gridDim.x * 64, buf ^= 1) {
+    for (int64_t p0 = ((int64_t)blockIdx.x * GROUPS + wave / SPLIT) * 64; p0 < n; p0 += (int64_t)gridDim.x * GROUPS * 64, buf ^= 1) {
         const int64_t e = p0 + lane;
         float v[NL][W];
-        const float* q = x + wave * stride;                // of learner wave + 4 j
+        const float* q = x + part * stride;                // of learner part + SPLIT j
         if (e < nv) {
 #pragma unroll
             for (int j = 0; j < NL; ++j) {
-                if (wave + 4 * j >= L) break;
+                if (part + SPLIT * j >= L) break;
                 if constexpr (VEC) {
-                    const float4 f = ldnt_(q + 4 * j * stride, e);
+                    const float4 f = ldnt_(q + SPLIT * j * stride, e);
                     v[j][0] = f.x; v[j][1] = f.y; v[j][2] = f.z; v[j][3] = f.w;
                 } else {
 #pragma unroll
-                    for (int c = 0; c < W; ++c) v[j][c] = q[4 * j * stride + e * W + c];
+                    for (int c = 0; c < W; ++c) v[j][c] = q[SPLIT * j * stride + e * W + c];
                 }
             }
         } else {                                           // the last P % W elements; 0 past the end and past it no deviation
 #pragma unroll
             for (int j = 0; j < NL; ++j) {
-                if (wave + 4 * j >= L) break;
+                if (part + SPLIT * j >= L) break;
 #pragma unroll
-                for (int c = 0; c < W; ++c) v[j][c] = e * W + c < P ? q[4 * j * stride + e * W + c] : 0.f;
+                for (int c = 0; c < W; ++c) v[j][c] = e * W + c < P ? q[SPLIT * j * stride + e * W + c] : 0.f;
             }
         }
         double s[W];
@@ -851,20 +854,30 @@ __global__ __launch_bounds__(256) void consensus_partial_kernel(const float* x, 
         for (int c = 0; c < W; ++c) s[c] = 0.0;
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            if (wave + 4 * j >= L) break;
+            if (part + SPLIT * j >= L) break;
 #pragma unroll
             for (int c = 0; c < W; ++c) s[c] += (double)v[j][c];
         }
-#pragma unroll
-        for (int c = 0; c < W; ++c) sums[buf][wave][c][lane] = s[c];
-        __syncthreads();                                   // (one barrier a round: the next round writes the other buffer)
         double mean[W];
+        if constexpr (SPLIT > 1) {
 #pragma unroll
-        for (int c = 0; c < W; ++c)
-            mean[c] = (((sums[buf][0][c][lane] + sums[buf][1][c][lane]) + sums[buf][2][c][lane]) + sums[buf][3][c][lane]) / (double)L;
+            for (int c = 0; c < W; ++c) sums[buf][wave][c][lane] = s[c];
+            __syncthreads();                               // (one barrier a round: the next round writes the other buffer)
+#pragma unroll
+            for (int c = 0; c < W; ++c)
+            {
+                const int w0 = wave - part;
+                double t = sums[buf][w0][c][lane] + sums[buf][w0 + 1][c][lane];
+                if constexpr (SPLIT == 4) t = (t + sums[buf][w0 + 2][c][lane]) + sums[buf][w0 + 3][c][lane];
+                mean[c] = t / (double)L;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < W; ++c) mean[c] = s[c] / (double)L;
+        }
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            if (wave + 4 * j >= L) break;
+            if (part + SPLIT * j >= L) break;
 #pragma unroll
             for (int c = 0; c < W; ++c) { const double d = (double)v[j][c] - mean[c]; acc += d * d; }
         }
@@ -892,15 +905,17 @@ __global__ __launch_bounds__(256) void consensus_final_kernel(const double* part
 
 template <bool VEC>
 static void consensus_partial_t(const float* x, int64_t stride, int L, int64_t P, double* partial, unsigned blocks, hipStream_t s) {
-    if (L <= 16) hipLaunchKernelGGL((consensus_partial_kernel<4, VEC>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
-    else if (L <= 32) hipLaunchKernelGGL((consensus_partial_kernel<8, VEC>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
-    else hipLaunchKernelGGL((consensus_partial_kernel<32, VEC>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
+    if (L <= 8) hipLaunchKernelGGL((consensus_partial_kernel<8, VEC, 1>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
+    else if (L <= 16) hipLaunchKernelGGL((consensus_partial_kernel<8, VEC, 2>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
+    else if (L <= 32) hipLaunchKernelGGL((consensus_partial_kernel<8, VEC, 4>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
+    else hipLaunchKernelGGL((consensus_partial_kernel<32, VEC, 4>), dim3(blocks), dim3(256), 0, s, x, stride, L, P, partial);
 }
 
 hipError_t launch_consensus(const float* x, int64_t stride, int L, int64_t P, double* partial, double* out, hipStream_t s) {
     if (L < 1 || L > 128 || P < 1) return hipErrorInvalidValue;
     const bool vec = (uintptr_t)x % 16 == 0 && stride % 4 == 0;
-    int64_t blocks = ((P + 3) / 4 + 63) / 64;
+    const int64_t per_block = L <= 8 ? 256 : L <= 16 ? 128 : 64;          // positions of four elements
+    int64_t blocks = ((P + 3) / 4 + per_block - 1) / per_block;
     if (blocks > kConsensusBlocks) blocks = kConsensusBlocks;
     if (vec) consensus_partial_t<true>(x, stride, L, P, partial, (unsigned)blocks, s);
     else consensus_partial_t<false>(x, stride, L, P, partial, (unsigned)blocks, s);
