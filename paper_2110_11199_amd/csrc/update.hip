@@ -645,24 +645,48 @@ static hipError_t launch_hybrid(const UpdateDesc& d, bool vec, hipStream_t s) {
 
 // Learner average, the sum in learner order.  A streaming read of L vectors: a float4 of every learner per thread, eight loads
 // in flight (16 x 36M: 612 us, 4.0 TB/s, with one float per thread; with the consensus distance behind it 1668 -> 820 us).
+// Learners 1 .. L-1 of a position, eight loads at a time, added to s in order (a remainder one load after the other cost 16 x 300k 3 us).
+// NT: the models are read past the caches.
+template <bool NT, class V, class Add> __device__ inline void add_learners_(const V* x, int64_t step, int L, V& s, Add add) {
+    auto load = [](const V* p) { if constexpr (NT) return (V)__builtin_nontemporal_load(p); else return *p; };
+    int j0 = 1;
+    for (; j0 + 8 <= L; j0 += 8) {
+        V v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = load(x + (j0 + j) * step);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) add(s, v[j]);
+    }
+    V v[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        if (j0 + j >= L) break;
+        v[j] = load(x + (j0 + j) * step);
+    }
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        if (j0 + j >= L) break;
+        add(s, v[j]);
+    }
+}
+
 __global__ __launch_bounds__(256) void average_kernel(const float* x, int64_t stride, int L, int64_t P,
                                                       float inv_L, float* out, int vec) {
+    typedef __attribute__((ext_vector_type(4))) float f4_t;
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x, n4 = vec ? P >> 2 : 0;
     if (e < n4) {
-        float4 s = ldnt_(x, e);
-#pragma unroll 8
-        for (int j = 1; j < L; ++j) {
-            const float4 v = ldnt_(x + j * stride, e);
-            s.x = __fadd_rn(s.x, v.x); s.y = __fadd_rn(s.y, v.y); s.z = __fadd_rn(s.z, v.z); s.w = __fadd_rn(s.w, v.w);
-        }
+        const f4_t* p = (const f4_t*)x + e;
+        f4_t s = __builtin_nontemporal_load(p);
+        add_learners_<true>(p, stride >> 2, L, s, [](f4_t& a, const f4_t& b) {
+            a.x = __fadd_rn(a.x, b.x); a.y = __fadd_rn(a.y, b.y); a.z = __fadd_rn(a.z, b.z); a.w = __fadd_rn(a.w, b.w);
+        });
         stnt_(out, e, make_float4(__fmul_rn(s.x, inv_L), __fmul_rn(s.y, inv_L), __fmul_rn(s.z, inv_L), __fmul_rn(s.w, inv_L)));
         return;
     }
-    const int64_t t = 4 * n4 + (e - n4);                   // the last P % 4 elements, or every element of unaligned vectors
+    const int64_t t = 4 * n4 + (e - n4);                   // the last P % 4 elements, or every element
     if (t >= P) return;
     float s = x[t];
-#pragma unroll 8
-    for (int j = 1; j < L; ++j) s = __fadd_rn(s, x[j * stride + t]);
+    add_learners_<false>(x + t, stride, L, s, [](float& a, const float& b) { a = __fadd_rn(a, b); });
     out[t] = __fmul_rn(s, inv_L);
 }
 
@@ -956,7 +980,10 @@ hipError_t launch_consensus_static(const float* x, int64_t stride, int L, int64_
 }
 
 hipError_t launch_average(const float* x, int64_t stride, int L, int64_t P, float* out, hipStream_t s) {
-    const int vec = (uintptr_t)x % 16 == 0 && stride % 4 == 0 && (uintptr_t)out % 16 == 0;
+    // One element to a thread while there are too few for float4 threads to fill the chip (us, float / float4: 8 x 1M 5.8 / 6.5, 12 x
+    // 450k 4.2 / 5.2, 16 x 300k 4.0 / 4.8, 24 x 300k 5.2 / 6.4; and 9 x 1M 7.7 / 6.8, 64 x 100k 13.6 / 7.8).
+    const bool few = L * P <= (L <= 32 ? 1 << 23 : 1 << 22);
+    const int vec = !few && (uintptr_t)x % 16 == 0 && stride % 4 == 0 && (uintptr_t)out % 16 == 0;
     const int64_t work = vec ? (P >> 2) + (P & 3) : P;
     hipLaunchKernelGGL(average_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, x, stride, L, P,
                        1.0f / (float)L, out, vec);
