@@ -112,7 +112,7 @@ struct RecDesc {               // one time step of one layer, all learners and d
 int rec_backward_batch_tiles(const RecDesc& d);
 // Which kernels the steps of a layer whose tensors meet rec_aligned run on (pairs: learners x directions): 0 register-staged,
 // 1 direct-to-LDS, 2 contraction split over the waves.
-int rec_step_kind(int precision, int pairs, int H, int B);
+int rec_step_kind(int precision, bool backward, int pairs, int H, int B);
 hipError_t launch_rec_forward(const RecDesc& d, hipStream_t s);
 hipError_t launch_rec_backward(const RecDesc& d, hipStream_t s);
 // The same step with the contraction split over the waves of a workgroup and the operands read straight into registers

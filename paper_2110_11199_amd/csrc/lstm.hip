@@ -368,6 +368,12 @@ bool rec_quad_aligned(const RecDesc& d) {
 //            64: 16.3 / 16.9 against 29.7 / 32.7; 16 x 256, 128 (512 workgroups): 23.4 / 25.9 against 25.9 / 29.4; bf16 10 x
 //            360, 50: 8.4 / 11.4 against 15.0 / 17.4; and on the other side bf16 16 x 512, 64 (512 workgroups) 20.0 / 21.6
 //            against 15.5 / 18.9, fp32 32 x 512, 64 (1024) 78 / 94 against 48 / 54.
+//            Batches up to 32 leave the rows of a direct tile empty.  fp32 forward: split at any number of workgroups below
+//            1024 cells (32 x 640, batch 2: 66 against 87, 32: 75 / 94; 128 x 512, 16: 161 / 229), and for batches below 8 (48
+//            x 1024, 1: 202 / 206, 8: 217 / 211).  bf16 backward, which reads W_h column by column: up to two rounds where
+//            a column stays short (48 x 256, 16: 9.4 / 11.9) or the workgroups of a pair share an XCD and the batch is small
+//            (24 x 512, 16: 14.2 / 16.0, 24: 17.0 / 16.7; 16 x 768, 8: 17.5 / 19.3; 20 x 768, 8: 27.3 / 19.5); the bf16 forward step is
+//            the shorter on the direct kernel past 256 (24 x 512, 16: 15.7 / 13.4).
 //   kDirect  the direct-to-LDS kernels.
 //   kStaged  register-staged kernels: rows that are not 16-byte aligned, or forced (tuning).  fp32 6 x 320, 64: 31.0 /
 //            91.6; 32 x 1024, 128: 317 / 700 against 277 / 299 direct.
@@ -375,15 +381,18 @@ bool rec_quad_aligned(const RecDesc& d) {
 //            more than 4 GB (H > 16384 in fp32, 23170 with bf16 operands) is kStaged too, whose addresses have 64 bits.
 enum RecKind { kStaged, kDirect, kSplit };
 
-int rec_step_kind(int precision, int pairs, int H, int B) {
+int rec_step_kind(int precision, bool backward, int pairs, int H, int B) {
     const int64_t split_wgs = (int64_t)pairs * ((H + 31) / 32) * ((B + 31) / 32);
-    if (split_wgs <= (precision ? 256 : 512)) return kSplit;
+    bool split = split_wgs <= (precision ? 256 : 512);
+    if (B <= 32 && !precision && !backward) split = split || H < 1024 || B < 8;
+    if (B <= 32 && precision && backward) split = split || (split_wgs <= 512 && (H <= 256 || (pairs % 8 == 0 && H <= 768 && B <= 16)));
+    if (split) return kSplit;
     return (int64_t)4 * H * H * (precision ? 2 : 4) <= (int64_t)1 << 32 ? kDirect : kStaged;
 }
 
-static RecKind rec_kind(const RecDesc& d) {
+static RecKind rec_kind(const RecDesc& d, bool backward) {
     if (!d.direct || !rec_aligned(d)) return kStaged;
-    return (RecKind)rec_step_kind(d.precision, d.L * d.D, d.H, d.B);
+    return (RecKind)rec_step_kind(d.precision, backward, d.L * d.D, d.H, d.B);
 }
 
 // Rows of a backward direct tile: 128 where that leaves three quarters of the chip a workgroup, else 32 (every batch tile
@@ -395,7 +404,7 @@ static bool wide_backward_tile(const RecDesc& d) {
 }
 
 int rec_backward_batch_tiles(const RecDesc& d) {
-    const RecKind kind = rec_kind(d);
+    const RecKind kind = rec_kind(d, true);
     const bool wide = kind == kStaged ? d.B > 64 : kind == kDirect && wide_backward_tile(d);
     return wide ? (d.B + 127) / 128 : (d.B + 31) / 32;
 }
@@ -424,7 +433,7 @@ template <typename T> static void bwd_direct_t(const RecDesc& d, hipStream_t s) 
 
 hipError_t launch_rec_forward(const RecDesc& d, hipStream_t s) {
     if (!rec_ok(d)) return hipErrorInvalidValue;
-    const RecKind kind = rec_kind(d);
+    const RecKind kind = rec_kind(d, false);
     if (kind == kSplit) return launch_rec_split(d, false, s);
     if (kind == kDirect) {
         if (d.precision == 0) fwd_direct_t<float>(d, s);
@@ -437,7 +446,7 @@ hipError_t launch_rec_forward(const RecDesc& d, hipStream_t s) {
 
 hipError_t launch_rec_backward(const RecDesc& d, hipStream_t s) {
     if (!rec_ok(d)) return hipErrorInvalidValue;
-    const RecKind kind = rec_kind(d);
+    const RecKind kind = rec_kind(d, true);
     if (kind == kSplit) return launch_rec_split(d, true, s);
     if (kind == kDirect) {
         if (d.precision == 0) bwd_direct_t<float>(d, s);
