@@ -399,8 +399,16 @@ static RecKind rec_kind(const RecDesc& d, bool backward) {
 // reads its W_h slice again, but a launch that fills the chip matters more).  32 against 128 rows, us per frame:
 // bf16 16 x 640 cells, batch 96 (80 workgroups of 128 rows): 23.8 against 38.9; fp32 32 x 512, 96 (128): 76 against 148; bf16
 // 32 x 512, 128 (128): 35.6 against 44.4; 32 x 1024, 128 (256): 184 against 91, fp32 341 against 299.
+// In bf16 the 32-row tiles also have to fit the chip at once, two workgroups to a compute unit (24 x 640, 128: 480 workgroups 38
+// against 46; 40 x 512, 128: 640 56 against 49; 24 x 832, 128: 672 70 against 55), all W_h the memory-side cache, which
+// serves them again (16 x 1024, 72, 134 MB: 41 against 48; 16 x 1280, 72, 210 MB: 69 against 57; 8 x 2048, 72, 268 MB: 93
+// against 78), and the workgroups of a pair few XCDs (20 x 832, 72: 58 against 42; 12 x 1280, 72: 51 against 54).
 static bool wide_backward_tile(const RecDesc& d) {
-    return d.B > 64 && (int64_t)d.L * d.D * ((d.H + 127) / 128) * ((d.B + 127) / 128) >= 192;
+    if (d.B <= 64) return false;
+    const int pairs = d.L * d.D;
+    const int64_t units = (int64_t)pairs * ((d.H + 127) / 128);
+    if (units * ((d.B + 127) / 128) >= 192) return true;
+    return d.precision && (units * ((d.B + 31) / 32) > 512 || (int64_t)pairs * 8 * d.H * d.H > 160000000 || (pairs % 8 && pairs > 16));
 }
 
 int rec_backward_batch_tiles(const RecDesc& d) {
