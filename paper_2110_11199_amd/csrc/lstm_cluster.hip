@@ -745,19 +745,28 @@ template <typename T, int S> void launch_cluster_t(const ClusterDesc& p, bool ba
 // bf16 hidden sizes that are 4 mod 8, which frame by frame run on the register-staged kernels, take the clusters throughout: 16 x 300,
 // 32 (192) 19.5 / 30.3 against 3.5 / 5.3; 16 x 508, 128 (1024) 29 / 70 against 17 / 32; 32 x 636, 128 (2560) 77 / 119 against 51 / 134.
 // More rows to a cluster (two and four tiles) shorten nothing: 32 x 512, 64: 16 -> 15 and 18; the exchange grows with the rows.
+// A launch begins with W_h (10-20 us a round of the chip), which few frames do not earn back.  us for a whole pass, frame by frame / clusters:
+// bf16 forward 16 x 400, batch 23 (256 workgroups, one round): 2 frames 16 / 23, 3 23 / 26, 4 31 / 30; 24 x 320, 17 (288, two): 6 45 / 52, 10 75 / 72;
+// backward 16 x 400: 5 47 / 50, 8 79 / 70; 24 x 320: 10 87 / 102, 14 121 / 137 (the second round nearly empty); 32 x 512, 32 (512): 6 108 / 109, 10
+// 185 / 174; fp32 forward 16 x 400 (512, two): 6 104 / 108, 8 141 / 135; backward 24 x 320 (480, two): 8 117 / 123, 14 212 / 205; 16 x 400: 14
+// 273 / 278; 32 x 512, 32 (1024, four): 5 203 / 218, 8 359 / 340; one round of other sizes is even from 2 to 4 frames on.
 bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count) {
     if (!d.direct || d.T < 2 || d.H <= 128 || !rec_quad_aligned(d) || d.L < 1 || d.L > 128 || d.D < 1 || d.D > 2 || d.B < 1) return false;
     if ((int64_t)d.T * d.B * d.D * d.H * 16 >= (int64_t)kOutOfRange) return false;     // buffer offsets
     const int S = cluster_members(d);
     if (S == 0 || cu_count < 4 * S) return false;
-    const int64_t workgroups = (int64_t)d.L * d.D * cluster_blocks(d) * S;
+    const int64_t workgroups = rec_cluster_count(d) * S;
     if (!rec_aligned(d)) return workgroups <= 4096;        // measured up to 3200
-    if (d.precision) return workgroups <= (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640);
-    return workgroups <= (backward ? 1024 : 1280);
+    if (d.precision ? workgroups > (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640) : workgroups > (backward ? 1024 : 1280)) return false;
+    // rounds of the chip: two workgroups share a compute unit where their registers allow
+    const bool two = d.precision ? !backward && S == 4 : S == 8 || (S == 10 && !backward);
+    const int64_t at_once = (int64_t)cu_count * (two ? 2 : 1), rounds = (workgroups + at_once - 1) / at_once;
+    if (backward && d.precision && rounds > 1 && 4 * workgroups < 3 * at_once * rounds) return false;
+    return d.T >= (rounds == 1 ? (backward && d.precision && S >= 8 ? 7 : 4) : backward ? 12 : 8);
 }
 
-int rec_cluster_batch_tiles(const RecDesc& d) { return cluster_blocks(d); }
 int64_t rec_cluster_count(const RecDesc& d) { return (int64_t)d.L * d.D * cluster_blocks(d); }
+int rec_cluster_batch_tiles(const RecDesc& d) { return cluster_blocks(d); }
 
 int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward) {
     const int64_t S = cluster_members(d), KP = S * (d.precision ? 64 : 32), row = backward ? S * KP : d.precision ? KP / 2 : KP;

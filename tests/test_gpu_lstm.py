@@ -116,6 +116,13 @@ def test_gradient_with_all_frames_on_clusters_of_compute_units(prec, hidden, bat
     _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
 
 
+@pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 260), (0, 384), (0, 512), (1, 136), (1, 360), (1, 508), (1, 512), (1, 640)])
+@pytest.mark.parametrize("batch,frames", [(1, 7), (17, 8)])
+def test_gradient_on_clusters_of_compute_units_from_few_frames_on(prec, hidden, batch, frames):
+    # every cluster size at the fewest frames that both passes run on clusters for, and one more
+    _check_gradient(Shape(12, hidden, 1, 1, 0, 24, batch, frames), 2, prec)
+
+
 def _check_gradient(shape, L, prec, tune=()):
     import torch
     print("lstm grad", shape, L, prec, flush=True)
@@ -456,7 +463,7 @@ def test_cluster_left_to_one_workgroup_gives_the_same_bits(prec, hidden):
     # every cluster size; two blocks of rows, the second of one row; a bound of 0 lets one workgroup do each cluster's work
     from paper_2110_11199_amd import binding as Bd
     print("clusters left to one workgroup", prec, hidden, flush=True)
-    shape = Shape(12, hidden, 2, 1, 0, 24, 17, 4)
+    shape = Shape(12, hidden, 2, 1, 0, 24, 17, 8)
     for a, b in zip(_one_step(shape, 2, prec, ()), _one_step(shape, 2, prec, ((Bd.TUNE_REC_JOIN_US, 0),))):
         assert (a == b).all()
 
