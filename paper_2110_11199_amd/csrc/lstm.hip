@@ -372,7 +372,8 @@ bool rec_quad_aligned(const RecDesc& d) {
 //            1024 cells (32 x 640, batch 2: 66 against 87, 32: 75 / 94; 128 x 512, 16: 161 / 229), and for batches below 8 (48
 //            x 1024, 1: 202 / 206, 8: 217 / 211).  bf16 backward, which reads W_h column by column: up to two rounds where
 //            a column stays short (48 x 256, 16: 9.4 / 11.9) or the workgroups of a pair share an XCD and the batch is small
-//            (24 x 512, 16: 14.2 / 16.0, 24: 17.0 / 16.7; 16 x 768, 8: 17.5 / 19.3; 20 x 768, 8: 27.3 / 19.5); the bf16 forward step is
+//            (24 x 512, 16: 14.2 / 16.0, 24: 17.0 / 16.7; 16 x 768, 8: 17.5 / 19.3; 8 x 1240, 8: 25 / 27;
+//            20 x 768, 8: 27.3 / 19.5); the bf16 forward step is
 //            the shorter on the direct kernel past 256 (24 x 512, 16: 15.7 / 13.4).
 //   kDirect  the direct-to-LDS kernels.
 //   kStaged  register-staged kernels: rows that are not 16-byte aligned, or forced (tuning).  fp32 6 x 320, 64: 31.0 /
@@ -385,7 +386,7 @@ int rec_step_kind(int precision, bool backward, int pairs, int H, int B) {
     const int64_t split_wgs = (int64_t)pairs * ((H + 31) / 32) * ((B + 31) / 32);
     bool split = split_wgs <= (precision ? 256 : 512);
     if (B <= 32 && !precision && !backward) split = split || H < 1024 || B < 8;
-    if (B <= 32 && precision && backward) split = split || (split_wgs <= 512 && (H <= 256 || (pairs % 8 == 0 && H <= 768 && B <= 16)));
+    if (B <= 32 && precision && backward) split = split || (split_wgs <= 512 && (H <= 256 || (pairs % 8 == 0 && (H <= 768 ? B <= 16 : split_wgs <= 320 && B <= 8))));
     if (split) return kSplit;
     return (int64_t)4 * H * H * (precision ? 2 : 4) <= (int64_t)1 << 32 ? kDirect : kStaged;
 }
