@@ -501,6 +501,7 @@ bool row4_blocks(const RecDesc& d) { return (int64_t)d.L * d.D * ((d.B + 3) / 4)
 bool rec_resident_supported(const RecDesc& d) {
     // (every tensor of a learner below 2 GiB: the buffer offsets of the kernels)
     if (!rec_aligned(d) && !(rec_quad_aligned(d) && row4_blocks(d))) return false;
+    if (rec_resident_batch_tiles(d) > 65535) return false;                             // the second dimension of a grid
     if (d.T < 2 || (d.T == 2 && (int64_t)d.L * d.D * rec_resident_batch_tiles(d) > 256)) return false;
     return d.direct && d.H <= 128 && (int64_t)d.T * d.B * d.D * d.H * 16 < (int64_t)kOutOfRange && d.L >= 1 && d.L <= 128 && d.D >= 1 && d.D <= 2 && d.B >= 1;
 }

@@ -477,3 +477,22 @@ def test_cluster_waits_for_workgroups_that_have_not_started():
     shape = Shape(12, 360, 1, 1, 0, 24, 64, 100)
     for a, b in zip(_one_step(shape, 8, 1, ((Bd.TUNE_REC_WAIT_US, 150),)), _one_step(shape, 8, 1, ((Bd.TUNE_REC_JOIN_US, 20),))):
         assert (a == b).all()
+
+
+def test_batch_beyond_the_second_dimension_of_a_grid():
+    # 1 100 000 segments are 68 750 blocks of 16 rows: more than a grid's second dimension holds, so every frame is a launch
+    from paper_2110_11199_amd import binding as Bd
+    print("batch of 1.1 million", flush=True)
+    import torch
+    T, B = 3, 1_100_000
+    out = []
+    for persistent in (-1, 0):
+        e = _engine(Shape(4, 4, 1, 0, 0, 4, B, T), 1, S.FIXED_RING, 0)
+        e.tune(Bd.TUNE_REC_PERSISTENT, persistent)
+        e.set_params(-1, torch.from_numpy(synth.initial_model(0, e.P, 0.1)).cuda())
+        x = torch.arange(T * B * 4, device="cuda", dtype=torch.float32).remainder_(7.0)
+        e.step([(x, torch.zeros(T * B, dtype=torch.int32, device="cuda"))], 0.1)
+        e.status()
+        out.append(e.grads(0).cpu().numpy().view(np.uint32).copy())
+        e.close()
+    assert np.isfinite(out[0].view(np.float32)).all() and (out[0] == out[1]).all()
