@@ -343,7 +343,8 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
  *   ADPSGD_TUNE_REC_DIRECT       1 (default) / 0: specialised recurrent step kernels (direct-to-LDS loads for bf16 and
  *                                batches over 32; contraction split over the waves for batches up to 32) allowed, or
  *                                the general register-staged kernels everywhere
- *   ADPSGD_TUNE_REC_FWD_GROUPS   learner groups the forward recurrence is run in, 0 = automatic
+ *   ADPSGD_TUNE_REC_FWD_GROUPS   learner groups the forward recurrence is run in, frame by frame, whatever REC_PERSISTENT -1
+ *                                would choose; 0 = automatic
  *   ADPSGD_TUNE_REC_PERSISTENT   all frames of a layer in one launch with W_h held in registers: -1 (default) where the whole
  *                                W_h of a (learner, direction) fits one compute unit (hidden up to 128) or a group of up to
  *                                16 (hidden up to 512 in fp32, 640 with bf16 operands; not for the largest batches), whose

@@ -531,18 +531,20 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         // and a group whose per-step traffic fits the 256 MB memory-side cache finds it there (measured on the
         // 16 x 1024-unit workload: 10.7 -> 8.9 ms per iteration in two groups; three or four groups leave too
         // few workgroups per launch and are slower than one).
+        // A number of groups that the caller has set means these kernels, whatever else the layer could run on.
         const int parts = rec_forward_parts(h, n);
+        const bool grouped = h->tune_rec_fwd_groups > 0;
         if (persist) {
             if (int rc = mark(h, 2, persist_launches, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
             if (int rc = run_persistent(r, l, false)) return rc;
             continue;
         }
-        if (h->tune_rec_persist != 0 && rec_resident_supported(r)) {
+        if (!grouped && h->tune_rec_persist != 0 && rec_resident_supported(r)) {
             if (int rc = mark(h, 2, 1, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
             HIPCHK(launch_rec_resident(r, false, s), "resident recurrent forward");
             continue;
         }
-        if (use_cluster(h, r, false)) {
+        if (!grouped && use_cluster(h, r, false)) {
             if (int rc = mark(h, 2, 1, rec_flops(n), rec_bytes_fwd(n, true))) return rc;
             HIPCHK(launch_rec_cluster(cluster_desc(r, l, false), false, h->cu_count, s), "recurrent forward (clusters)");
             continue;

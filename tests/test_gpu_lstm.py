@@ -315,6 +315,23 @@ def test_forward_recurrence_in_learner_groups(groups):
                         tune=[(Bd.TUNE_REC_FWD_GROUPS, groups)])
 
 
+@pytest.mark.parametrize("prec,hidden", [(0, 64), (1, 128), (0, 256), (1, 256)])
+def test_learner_groups_are_taken_where_all_frames_would_run_in_one_launch(prec, hidden):
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    shape = Shape(12, hidden, 2, 1, 0, 20, 8, 10)
+    for groups in (0, 1, 3):
+        e = _engine(shape, 5, S.FIXED_RING, prec)
+        e.tune(Bd.TUNE_REC_FWD_GROUPS, groups)
+        e.set_params(-1, torch.from_numpy(synth.initial_model(0, e.P, 0.1)).cuda())
+        Bd.adpsgd_set_profiling(e.h, 1)
+        e.step(_to_dev(_batches(shape, 5, 0)), 0.1)
+        e.status()
+        launches = Bd.adpsgd_profile(e.h)["recurrent_fwd"]["launches"]
+        e.close()
+        assert launches == shape.layers * (groups * shape.frames if groups else 1), (groups, launches)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[10]])
 def test_small_batches_on_the_staged_kernels_too(shape, prec):
