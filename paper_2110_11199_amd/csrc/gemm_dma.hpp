@@ -159,6 +159,7 @@ struct GemmDma {
         issue<LB>(b, boff, k0, lds + A_BYTES, wave);
         wait_vm<0>();
         __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");                         // (the barrier is no memory access for the optimiser)
         for (int c = 0; c * 2 * EPC < rem; ++c) {
             const int ch = 2 * c + (lane >> 5);
             uint4 af[FM], bfr[FN];

@@ -29,10 +29,12 @@ __device__ inline uint4 column_frag_(const bf16_t* col, int64_t ld) {
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Barrier that waits for this wave's LDS accesses only: the stores of a frame's results stay in flight across it.
+// Barrier that waits for this wave's LDS accesses only: the stores of a frame's results stay in flight across it.  (The barrier is
+// no memory access for the optimiser: an empty statement that is one stands on either side.)
 __device__ inline void lds_barrier_() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 }  // namespace adpsgd
