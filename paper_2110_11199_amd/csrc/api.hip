@@ -399,9 +399,9 @@ int gemm(adpsgd_handle* h, const GemmDesc& d, const char* what, int k_alg = 0) {
 }
 
 int gemm_pair(adpsgd_handle* h, GemmDesc a, GemmDesc b, const char* what) {
-    if (int rc = mark_gemm(h, a, 1, 0)) return rc;
-    if (int rc = mark_gemm(h, b, 1, 0)) return rc;
     a.tile = b.tile = h->tune_gemm_tile;
+    if (int rc = mark_gemm(h, a, 1, 0)) return rc;
+    if (int rc = mark_gemm(h, b, gemm_pair_merged(a, b) ? 0 : 1, 0)) return rc;
     HIPCHK(launch_gemm_pair(a, b, h->stream), what);
     return ADPSGD_OK;
 }

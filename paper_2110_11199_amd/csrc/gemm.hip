@@ -387,17 +387,22 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     return launch_layout<bf16_t, 2, 2, 2, 2, 16, 64>(d, s);
 }
 
-hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
+static int64_t pair_tiles(const GemmDesc& d) { return (int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD; }
+
+bool gemm_pair_merged(const GemmDesc& a, const GemmDesc& b) {
     bool dma_a = false, dma_b = false;
     const int va = pick_tile(a, dma_a), vb = pick_tile(b, dma_b);
-    auto tiles = [](const GemmDesc& d) { return (int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD; };
-    if (va != 15 || vb != 15 || !dma_a || !dma_b || a.precision != b.precision || a.a_kc || a.b_kc || b.a_kc || b.b_kc ||
-        tiles(a) + tiles(b) > 0x7fffffff) {
+    return va == 15 && vb == 15 && dma_a && dma_b && a.precision == b.precision && !a.a_kc && !a.b_kc && !b.a_kc && !b.b_kc &&
+           pair_tiles(a) + pair_tiles(b) <= 0x7fffffff;
+}
+
+hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
+    if (!gemm_pair_merged(a, b)) {
         const hipError_t e = launch_gemm(a, s);
         return e != hipSuccess ? e : launch_gemm(b, s);
     }
-    GemmPair p{{a, b}, (int)tiles(a)};
-    const dim3 grid((unsigned)(tiles(a) + tiles(b)));
+    GemmPair p{{a, b}, (int)pair_tiles(a)};
+    const dim3 grid((unsigned)(pair_tiles(a) + pair_tiles(b)));
     if (a.precision == 0) hipLaunchKernelGGL((gemm_dma_pair_kernel<float, 64, 4>), grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((gemm_dma_pair_kernel<bf16_t, 128, 3>), grid, dim3(256), 0, s, p);
     return hipGetLastError();

@@ -32,7 +32,8 @@ struct GemmDesc {
 // Returns hipSuccess, or hipErrorInvalidValue when the operands do not meet the
 // alignment rules (rows and strides multiples of 4 elements).
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s);
-// Two independent problems, in one launch where both are small ones of the same layout.
+// Two independent problems, in one launch where both are small ones of the same layout (gemm_pair_merged).
+bool gemm_pair_merged(const GemmDesc& a, const GemmDesc& b);
 hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s);
 
 // ---- fused mixing + SGD update ------------------------------------------------

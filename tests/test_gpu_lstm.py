@@ -342,6 +342,23 @@ def test_small_batches_on_the_staged_kernels_too(shape, prec):
     _run_recurrence(shape, 2, S.FIXED_RING, prec, 2, 0.1, tune=((Bd.TUNE_REC_DIRECT, 0),))
 
 
+def test_profile_counts_two_weight_gradients_in_one_launch_once():
+    # input projection, output layer, its two gradient products and one launch for both weight gradients of the layer; with a
+    # tile that cannot take two problems at once, two
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    shape = Shape(40, 64, 1, 0, 0, 100, 4, 20)
+    for tile, want in ((-1, 5), (0, 6)):
+        e = _engine(shape, 4, S.FIXED_RING, 0)
+        e.tune(Bd.TUNE_GEMM_TILE, tile)
+        e.set_params(-1, torch.from_numpy(synth.initial_model(0, e.P, 0.1)).cuda())
+        Bd.adpsgd_set_profiling(e.h, 1)
+        e.step(_to_dev(_batches(shape, 4, 0)), 0.1)
+        e.status()
+        assert Bd.adpsgd_profile(e.h)["batched_gemm"]["launches"] == want
+        e.close()
+
+
 def test_tuning_is_per_handle():
     # two handles in one process: forcing the register-staged kernels on one must not change the other
     import torch
