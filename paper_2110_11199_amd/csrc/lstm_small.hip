@@ -19,6 +19,7 @@
 // column lane%32 of the 32x32 tile.
 #include "gemm_core.hpp"
 #include "kernels.hpp"
+#include "rec_tiles.hpp"
 
 namespace adpsgd {
 namespace {
@@ -32,19 +33,8 @@ template <typename T> __device__ inline uint4 frag_kc_(const T* row, int k, bool
     return ok ? *(const uint4*)(row + k) : zero4_();
 }
 // the same fragment of an operand stored rows-contiguous: elements k, k+1, ... of column `col` lie ld apart
-__device__ inline uint4 frag_mc_(const float* col, int64_t ld, int k, bool ok) {
-    if (!ok) return zero4_();
-    const float* p = col + (int64_t)k * ld;
-    return make_uint4(__builtin_bit_cast(uint32_t, p[0]), __builtin_bit_cast(uint32_t, p[ld]),
-                      __builtin_bit_cast(uint32_t, p[2 * ld]), __builtin_bit_cast(uint32_t, p[3 * ld]));
-}
-__device__ inline uint4 frag_mc_(const bf16_t* col, int64_t ld, int k, bool ok) {
-    if (!ok) return zero4_();
-    const bf16_t* p = col + (int64_t)k * ld;
-    uint32_t w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = (uint32_t)p[(2 * j) * ld] | ((uint32_t)p[(2 * j + 1) * ld] << 16);
-    return make_uint4(w[0], w[1], w[2], w[3]);
+template <typename T> __device__ inline uint4 frag_mc_(const T* col, int64_t ld, int k, bool ok) {
+    return ok ? column_frag_(col + (int64_t)k * ld, ld) : zero4_();
 }
 
 __device__ inline int acc_row_(int i, int g) { return 8 * (i >> 2) + 4 * g + (i & 3); }

@@ -1,4 +1,4 @@
-// 16x16 MFMA tiles of the recurrent kernels that keep W_h in registers.
+// 16x16 MFMA tiles of the recurrent kernels that keep W_h in registers, and what they share with the split-contraction ones.
 #pragma once
 #include "gemm_core.hpp"
 
