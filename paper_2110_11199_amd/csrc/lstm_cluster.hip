@@ -6,12 +6,14 @@
 // bf16 5 x 2 x 360 1396 -> 934.  What is left of a frame: the exchange (about 1.5 us), fp32 products of one wave per SIMD, the cells.
 //
 // Here a CLUSTER of S workgroups takes 16 batch rows of one (learner, direction) through all frames (batch rows do not depend
-// on each other: as many clusters as row blocks).  Workgroup m of a cluster owns U hidden units and holds their part of W_h as MFMA fragments in registers (a wave per SIMD, up to 320 of its 512 registers); the cell state (dL/dc)
-// stays in registers too.  What a frame needs of the other workgroups goes through memory:
+// on each other: as many clusters as row blocks).  Workgroup m of a cluster owns U hidden units and holds their part of W_h as
+// MFMA fragments in registers (a wave per SIMD, up to 320 of its 512 registers); the cell state (dL/dc) stays in registers too.
+// What a frame needs of the other workgroups goes through memory:
 //   forward   h_{t'} of all units (H values per row, in the operand type) - every workgroup reads all of it into LDS;
 //   backward  dh = da W_h is split over its CONTRACTION: workgroup m multiplies the da of its own units (LDS) with their rows of
-//             W_h and hands every workgroup the partial sums of its units (fp32).  Splitting over the result instead would
-//             have every workgroup read all of da, four times H values per row.
+//             W_h and hands every workgroup the partial sums of its units (fp32): H words read and H written a row and member.
+//             Splitting over the result instead would have every workgroup read all of da: 4 H words read and 4 U written in
+//             fp32; with bf16 operands, two values to a word, 2 H and 2 U, about as many in all but far fewer writes (not tried).
 //
 // Exchange.  A 32-bit payload and a 32-bit tag travel in one aligned 64-bit word, stored and loaded with single relaxed atomics
 // at device scope: a word is there or it is not, so there are no fences, no write-backs and no counters, and a frame costs one
@@ -441,11 +443,6 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
 #pragma unroll
             for (int q = 0; q < 4; ++q) wf[q][c] = fwd_frag_<T, C>(wh, H, q, u, (kh * C::CW + c) * C::KC, g);
     }
-    const uint32_t how = join_<C>(cd, w);
-    if (how != kTogether) {
-        if (how == kAlone + (uint32_t)w.m) forward_alone_<T, S>(cd, w, lds, red);
-        return;
-    }
     // rows this lane finishes: row0 + i, i < PR
     const int row0 = 4 * g + (KS == 2 ? 2 * kh : 0);
     uint32_t vg[PR], vc[PR], vy[PR / C::VW];
@@ -474,6 +471,11 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
 #pragma unroll
     for (int i = 0; i < PR; ++i) cs[i] = 0.f;
     load_pre(0);
+    const uint32_t how = join_<C>(cd, w);
+    if (__builtin_expect(how != kTogether, 0)) {
+        if (how == kAlone + (uint32_t)w.m) forward_alone_<T, S>(cd, w, lds, red);
+        return;
+    }
 #pragma unroll 1
     for (int s = 0; s < Tn; ++s) {
         const uint32_t m = (uint32_t)(d == 0 ? s : Tn - 1 - s) * B;
@@ -638,7 +640,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         lds_barrier_();                                    // the operand of the products goes into the same LDS
     }
     const uint32_t how = join_<C>(cd, w);
-    if (how != kTogether) {
+    if (__builtin_expect(how != kTogether, 0)) {
         if (how == kAlone + (uint32_t)w.m) backward_alone_<T, S>(cd, w, lds, bred);
         return;
     }
