@@ -164,8 +164,8 @@ int adpsgd_step_masked(adpsgd_t h, const void* const* batch_ptrs, float lr, cons
 
 /* HIP-graph replay of iterations, for models small enough that an iteration is a few hundred launches of
  * microseconds each (HIP streams and graphs take the place a tracing compiler has elsewhere).
- * adpsgd_step enqueues kernels and one 4-byte copy to pinned host memory and nothing else, so its stream work can
- * be recorded once and replayed.
+ * adpsgd_step enqueues kernels and nothing else (one that meets an error writes the sticky error to pinned host memory
+ * itself), so its stream work can be recorded once and replayed.
  *   adpsgd_capture_begin(h)      puts the handle's stream into capture mode.  Until adpsgd_capture_end, calls of
  *                                adpsgd_step / adpsgd_step_masked on h are RECORDED, not run; every other entry
  *                                point that takes h returns ADPSGD_EINVAL.  Needs: a stream of the handle's own (not
@@ -340,9 +340,11 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
 
 /* Tuning of ONE handle (benchmarks and tests; the defaults are the measured best):
  *   ADPSGD_TUNE_GEMM_TILE        tile configuration of the time-batched GEMMs, as tile_config above
- *   ADPSGD_TUNE_REC_DIRECT       1 (default) / 0: specialised recurrent step kernels (direct-to-LDS loads for bf16 and
- *                                batches over 32; contraction split over the waves for batches up to 32) allowed, or
- *                                the general register-staged kernels everywhere
+ *   ADPSGD_TUNE_REC_DIRECT       1 (default) / 0: specialised recurrent kernels allowed (contraction split over the waves where
+ *                                a step makes few workgroups, up to 256 with bf16 operands and 512 in fp32, and for some
+ *                                batches up to 32; direct-to-LDS loads beyond; all frames in one launch, see
+ *                                REC_PERSISTENT -1), or the general register-staged step kernels everywhere, whatever
+ *                                REC_PERSISTENT -1 would choose
  *   ADPSGD_TUNE_REC_FWD_GROUPS   learner groups the forward recurrence is run in, frame by frame, whatever REC_PERSISTENT -1
  *                                would choose; 0 = automatic
  *   ADPSGD_TUNE_REC_PERSISTENT   all frames of a layer in one launch with W_h held in registers: -1 (default) where the whole

@@ -117,8 +117,8 @@ struct adpsgd_handle {
     int tune_pair_split = -1;              // pairwise update: one member of a pair per thread (positions per workgroup), 0 off, -1 default
     int tune_sync_segment = -1;            // synchronous baseline: learners per thread of the update (0: all of them), -1: default
     int tune_tri_segment = -1;             // ring-neighbour update: ring positions per thread (0: the whole ring), -1: default
-    // device status word (kStatus* bits, sticky) and its pinned host mirror, refreshed by an asynchronous
-    // copy at the end of every step
+    // device status word (kStatus* bits, sticky) and the pinned host words, one per bit, that a kernel which raises a bit
+    // writes too (raise_status_)
     uint32_t* status = nullptr;
     volatile uint32_t* status_host = nullptr;
     int L, D, H, T, B, I, C, Bn, layers, F, ldx, ldd;
@@ -765,7 +765,7 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     }
     hipStream_t s = h->stream;
     const size_t slab = (size_t)h->L * h->Ppad * 4;
-    void* mirror = nullptr;                       // pinned host word the status is copied to after every step
+    void* mirror = nullptr;                       // pinned host words that the kernels leave the status bits in
     hipError_t e = hipHostMalloc(&mirror, 64, hipHostMallocDefault);
     if (e != hipSuccess) { delete h; return hipfail(e, "pinned status word"); }
     h->status_host = (volatile uint32_t*)mirror;
@@ -938,8 +938,7 @@ int adpsgd_step_masked(adpsgd_t h, const void* const* batch_ptrs, float lr, cons
 }
 
 // ---- HIP-graph replay of iterations ----------------------------------------------------------------
-// adpsgd_step enqueues kernels and one 4-byte copy to pinned memory, nothing else (no host wait, no allocation, no
-// memset node), so its stream work can be recorded once and replayed.  What a recording fixes: the batch pointers, the
+// adpsgd_step enqueues kernels and nothing else (no copy, no host wait, no allocation, no memset node), so its stream work can be recorded once and replayed.  What a recording fixes: the batch pointers, the
 // learning rate, and the schedule of the recorded iterations; it therefore needs a schedule that repeats (not the
 // random ring, no drawn stragglers), and on the patterns whose schedule or buffers alternate (fixed ring: the matching
 // phase; delay-by-one: the two model buffers) a whole number of periods, i.e. an even number of iterations.
@@ -1169,7 +1168,7 @@ void adpsgd_destroy(adpsgd_t h) {
     for (hipEvent_t e : h->prof.ev) (void)hipEventDestroy(e);
     for (adpsgd_graph* g : h->graphs) g->owner = nullptr;   // they can still be destroyed, no longer replayed
     if (h->status_host) {
-        (void)hipStreamSynchronize(h->stream);       // the last status copy may still be in flight
+        (void)hipStreamSynchronize(h->stream);       // a kernel may still write to them
         (void)hipHostFree((void*)h->status_host);
     }
     delete h;

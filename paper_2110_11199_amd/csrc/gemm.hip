@@ -218,8 +218,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_kernel(GemmDesc p) {
     store_tile<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
 }
 
-// Same tile bookkeeping with the direct-to-LDS main loop (16-byte aligned operands, K a multiple of
-// the stage length).
+// Same tile bookkeeping with the direct-to-LDS main loop (16-byte aligned operands, whole 16-byte chunks of K where an
+// operand is K-contiguous, or rows padded to them).
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
 __device__ __forceinline__ void dma_tile(const GemmDesc& p, int bid, int total, char* lds) {
     typedef typename std::conditional<AKC, KcSrc<T>, McSrc<T>>::type ASrc;

@@ -1,12 +1,13 @@
 // Recurrent LSTM kernels that keep W_h on one compute unit: all T frames of one layer in one launch, for hidden sizes up to 128.
 //
 // A step of such a model is a few hundred thousand multiply-adds per (learner, direction): launched frame by frame it is bound by
-// the launch itself, by reading W_h again and by the latency of the reduction over the contraction.  us per frame
-// (forward / backward), frame by frame against here: fp32 4 x 64 cells, batch 4: 8.2 / 6.4 -> 2.0 / 2.2; 16 x 128, 64: 9.9 / 8.6
-// -> 6.0 / 6.6 (bound by the fp32 products of one compute unit, 3.5); 128 x 128, 128: 33 / 40 -> 26 / 32; bf16 16 x 128,
-// 16: 5.8 / 5.9 -> 2.2 / 2.4, 128 x 128, 128: 19.8 / 25.0 -> 15.8 / 16.4 (the cell arithmetic of two waves per SIMD).  Batch rows do not depend on each other, so a
-// workgroup here takes 16 batch rows of one (learner, direction) through ALL frames (or 4: the second pair of kernels) and needs
-// nothing from any other workgroup: no launch, no global round trip and no wait between frames.
+// the launch itself, by reading W_h again and by the latency of the reduction over the contraction.  Batch rows do not depend
+// on each other, so a workgroup here takes 16 batch rows of one (learner, direction) through ALL frames (or 4: the second pair
+// of kernels) and needs nothing from any other workgroup: no launch, no global round trip and no wait between frames.  us per
+// frame (forward / backward), frame by frame against here: four rows at a time fp32 4 x 64 cells, batch 4: 8.2 / 6.4 -> 0.9 / 1.1, 32 x
+// 128, 64: 10 / 9 -> 3.9 / 4.3, bf16 16 x 128, 16: 5.8 / 5.9 -> 1.1 / 1.3; sixteen fp32 128 x 128, 128: 33 / 40 -> 26 / 32 (the fp32
+// products of one compute unit, 3.5 a frame and block, four blocks to each), bf16 128 x 128, 128: 19.8 / 25.0 -> 15.8 / 16.4 (the
+// cell arithmetic of two waves per SIMD).
 //
 // One wave per 16 hidden units.  Its slice of W_h - the four gate rows of its units (forward, h W_h') or their unit columns
 // (backward, da W_h) - stays in registers as MFMA B fragments for the whole launch (at most 128 registers: 128 units in
