@@ -153,7 +153,7 @@ struct adpsgd_handle {
     // recurrences over clusters of workgroups: iteration counter and [layers][2 passes] tickets behind it; exchange words
     uint32_t* epoch = nullptr;
     uint64_t* exchange = nullptr; size_t exchange_bytes = 0;
-    uint64_t* closed = nullptr; size_t closed_bytes = 0;       // a word per cluster, behind the exchange words
+    uint64_t* closed = nullptr; size_t closed_bytes = 0;       // a word per cluster, right behind the exchange words
 };
 
 // A recorded sequence of iterations of one handle (adpsgd_capture_end), replayed by adpsgd_graph_replay.
@@ -350,9 +350,9 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->exchange_bytes = (size_t)words * 8;
         if (words > 0) {
             h->epoch = (uint32_t*)w.take((1 + (size_t)h->layers * 2) * 4);
-            h->exchange = (uint64_t*)w.take(h->exchange_bytes);
             h->closed_bytes = (size_t)rec_cluster_count(r) * 8;
-            h->closed = (uint64_t*)w.take(h->closed_bytes);
+            h->exchange = (uint64_t*)w.take(h->exchange_bytes + h->closed_bytes);
+            h->closed = h->exchange + words;
         }
     }
     return w.used;
@@ -778,8 +778,7 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     if (e == hipSuccess && h->tau == 1) e = hipMemsetAsync(h->params[1], 0, slab, s);
     if (e == hipSuccess && !h->flat) e = hipMemsetAsync(h->grads, 0, slab, s);
     if (e == hipSuccess && h->epoch) e = hipMemsetAsync(h->epoch, 0, (1 + (size_t)h->layers * 2) * 4, s);
-    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes, s);   // no word carries a tag in use
-    if (e == hipSuccess && h->closed) e = hipMemsetAsync(h->closed, 0, h->closed_bytes, s);
+    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes + h->closed_bytes, s);   // no word carries a tag in use
     if (e != hipSuccess) { (void)hipHostFree(mirror); delete h; return hipfail(e, "clear models"); }
     if (cfg->init_scale > 0.f) {
         // same w_0 on every learner (Algorithm 1, input)
