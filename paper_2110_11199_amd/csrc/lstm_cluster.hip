@@ -33,6 +33,7 @@
 // (wait_ticks of the 100 MHz clock, or another workgroup's expiry): the workgroup raises kStatusWaitExpired and returns.
 //
 // MFMA operand mapping (16x16 tiles) as in lstm_resident.hip.
+#include <algorithm>
 #include "gemm_core.hpp"
 #include "kernels.hpp"
 #include "rec_tiles.hpp"
@@ -744,27 +745,56 @@ template <typename T, int S> void launch_cluster_t(const ClusterDesc& p, bool ba
 //                 96 (960; between the other kernels of an iteration) 20.6 / 22; 16 x 256, 128 (512) 12.1 / 7.7; 32 x 256, 128 (1024) 14.3 / 15.1
 //   bf16 backward 10 x 360, 50 (240) 11.5 / 5.9; 16 x 256, 128 (512) 13.9 / 10.0; 32 x 256, 128 (1024) 17.0 / 18.6; 32 x 512, 32 (512)
 //                 18.9 / 16.4, 64 (1024) 23 / 56 (the exchange of fp32 sums); 16 x 640, 16 (160) 18.2 / 9.5, 32 (320) 20.0 / 20.8
-// bf16 hidden sizes that are 4 mod 8, which frame by frame run on the register-staged kernels, take the clusters throughout: 16 x 300,
+// bf16 hidden sizes that are 4 mod 8, which frame by frame run on the register-staged kernels, take the clusters up to 4096: 16 x 300,
 // 32 (192) 19.5 / 30.3 against 3.5 / 5.3; 16 x 508, 128 (1024) 29 / 70 against 17 / 32; 32 x 636, 128 (2560) 77 / 119 against 51 / 134.
 // More rows to a cluster (two and four tiles) shorten nothing: 32 x 512, 64: 16 -> 15 and 18; the exchange grows with the rows.
-// A launch begins with W_h (10-20 us a round of the chip), which few frames do not earn back.  us for a whole pass, frame by frame / clusters:
-// bf16 forward 16 x 400, batch 23 (256 workgroups, one round): 2 frames 16 / 23, 3 23 / 26, 4 31 / 30; 24 x 320, 17 (288, two): 6 45 / 52, 10 75 / 72;
-// backward 16 x 400: 5 47 / 50, 8 79 / 70; 24 x 320: 10 87 / 102, 14 121 / 137 (the second round nearly empty); 32 x 512, 32 (512): 6 108 / 109, 10
-// 185 / 174; fp32 forward 16 x 400 (512, two): 6 104 / 108, 8 141 / 135; backward 24 x 320 (480, two): 8 117 / 123, 14 212 / 205; 16 x 400: 14
-// 273 / 278; 32 x 512, 32 (1024, four): 5 203 / 218, 8 359 / 340; one round of other sizes is even from 2 to 4 frames on.
+// A launch begins with W_h (10-20 us a round of the chip), which a few frames do not earn back, and a nearly empty last round costs as
+// much as a full one: within the limits above, the estimates of both ways decide.  us for a whole pass, frame by frame / clusters:
+// bf16 forward 16 x 400, batch 23 (256 workgroups, one round): 2 frames 16 / 23, 4 31 / 30; 24 x 320, 17 (288, two): 6 45 / 52, 10 75 / 72;
+// 64 x 368, 5 (384, two) 5 114 / 62; backward 16 x 400: 5 47 / 50, 8 79 / 70; 24 x 320: 10 87 / 102, 14 121 / 137; 32 x 512, 32 (512, two): 6
+// 108 / 109, 10 185 / 174; fp32 forward 16 x 400 (512, two): 6 104 / 108, 8 141 / 135; 32 x 512, 32 (1024, four): 5 185 / 192, 8 323 / 276;
+// backward 24 x 320 (480, two): 8 117 / 123, 14 212 / 205.  The estimates pick the longer way by more than 3 us and 6 per cent for 5 of
+// the 180 such pairs measured, which lose 0.1 ms in all; clusters throughout lose 0.8, frames throughout 7.2.
+namespace {
+
+bool cluster_pays(const RecDesc& d, bool backward, int cu_count) {
+    const int S = cluster_members(d);
+    const double H = d.H, mb = (double)d.L * d.D * 4.0 * H * H * (d.precision ? 2e-6 : 4e-6);          // W_h of all pairs
+    // a step: latency of its contraction, W_h from the caches, more for every further 32 rows, a launch at least; the first has no
+    // product.  Where the rows of W_h are not aligned the register-staged kernels take two to three times as long.
+    double step = d.precision ? (backward ? 4.0 + 0.014 * H : 4.5 + 0.0085 * H) + 0.12 * mb : 1.5 + 0.035 * H + 0.14 * mb;
+    if (!d.precision && backward && mb > 60.0) step += 0.1 * (mb - 60.0);
+    step *= 1.0 + 0.25 * ((d.B + 31) / 32 - 1);
+    if (!rec_aligned(d)) step *= backward ? 2.7 : 1.8;
+    step = std::max(step, d.precision ? 6.0 : 7.5);
+    // (backward, one row block: no launch of its own for the column sums of da)
+    const double frames = 7.0 + (d.T - 1) * step + (backward && cluster_blocks(d) == 1 ? 4.0 : 0.0);
+    // a frame of a cluster by its size: exchange, products, cells; the load of W_h and the first frame
+    double frame, first;
+    if (d.precision) {
+        frame = !backward ? 3.2 : S == 4 ? 3.3 : S == 6 ? 5.2 : 7.0;
+        first = 2.0 + 2.1 * S;
+    } else {
+        frame = backward ? (S == 8 ? 5.5 : S == 10 ? 7.0 : S == 12 ? 8.0 : 9.5) : S == 8 ? 4.4 : S == 10 ? 4.6 : S == 12 ? 6.0 : 7.0;
+        first = (backward ? 9.5 : 10.0) + 0.4 * S;
+    }
+    // two workgroups share a compute unit where their registers allow; in fp32 they then share its matrix rate too
+    const int64_t at_once = (int64_t)cu_count * (d.precision && !backward && S == 4 ? 2 : 1);
+    const double rounds = (double)((rec_cluster_count(d) * S + at_once - 1) / at_once);
+    return rounds * (first + (d.T - 1) * frame) <= frames;
+}
+
+}  // namespace
+
 bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count) {
     if (!d.direct || d.T < 2 || d.H <= 128 || !rec_quad_aligned(d) || d.L < 1 || d.L > 128 || d.D < 1 || d.D > 2 || d.B < 1) return false;
     if ((int64_t)d.T * d.B * d.D * d.H * 16 >= (int64_t)kOutOfRange) return false;     // buffer offsets
     const int S = cluster_members(d);
     if (S == 0 || cu_count < 4 * S) return false;
     const int64_t workgroups = rec_cluster_count(d) * S;
-    if (!rec_aligned(d)) return workgroups <= 4096;        // measured up to 3200
-    if (d.precision ? workgroups > (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640) : workgroups > (backward ? 1024 : 1280)) return false;
-    // rounds of the chip: two workgroups share a compute unit where their registers allow
-    const bool two = d.precision ? !backward && S == 4 : S == 8 || (S == 10 && !backward);
-    const int64_t at_once = (int64_t)cu_count * (two ? 2 : 1), rounds = (workgroups + at_once - 1) / at_once;
-    if (backward && d.precision && rounds > 1 && 4 * workgroups < 3 * at_once * rounds) return false;
-    return d.T >= (rounds == 1 ? (backward && d.precision && S >= 8 ? 7 : 4) : backward ? 12 : 8);
+    if (!rec_aligned(d) ? workgroups > 4096                // measured up to 3200
+        : d.precision ? workgroups > (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640) : workgroups > (backward ? 1024 : 1280)) return false;
+    return cluster_pays(d, backward, cu_count);
 }
 
 int64_t rec_cluster_count(const RecDesc& d) { return (int64_t)d.L * d.D * cluster_blocks(d); }

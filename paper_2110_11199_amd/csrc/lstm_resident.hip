@@ -496,14 +496,14 @@ bool row4_blocks(const RecDesc& d) { return (int64_t)d.L * d.D * ((d.B + 3) / 4)
 
 }  // namespace
 
-// From two frames on (a single one needs no W_h, which a launch here begins with: 64 x 112 cells, batch 32, fp32, 9.8 / 9.3 us frame by
-// frame against 19.4 / 24.0), three where the workgroups fill the chip (32 x 128, 64: two frames 15 / 14 against 17 / 19, three 21 /
-// 21 against 19 / 21; 16 x 100, 16: two 21 / 25 against 9 / 10).
+// From two frames on: a single one needs no W_h, which a launch here begins with (64 x 112 cells, batch 32, fp32, 9.8 / 9.3 us frame by
+// frame against 19.4 / 24.0), but where W_h's rows are not 16-byte aligned the kernels of a single frame are the longer all
+// the same (64 x 4, 15, bf16: 10.2 against 6.5).  Two frames: 32 x 128, 64 15 / 14 against 17 / 19; 128 x 24, 123 23 / 23 against 12 / 12.
 bool rec_resident_supported(const RecDesc& d) {
     // (every tensor of a learner below 2 GiB: the buffer offsets of the kernels)
     if (!rec_aligned(d) && !(rec_quad_aligned(d) && row4_blocks(d))) return false;
     if (rec_resident_batch_tiles(d) > 65535) return false;                             // the second dimension of a grid
-    if (d.T < 2 || (d.T == 2 && (int64_t)d.L * d.D * rec_resident_batch_tiles(d) > 256)) return false;
+    if (d.T < 1 || (d.T == 1 && rec_aligned(d))) return false;
     return d.direct && d.H <= 128 && (int64_t)d.T * d.B * d.D * d.H * 16 < (int64_t)kOutOfRange && d.L >= 1 && d.L <= 128 && d.D >= 1 && d.D <= 2 && d.B >= 1;
 }
 

@@ -98,8 +98,8 @@ def test_gradient_frame_by_frame(shape, prec):
 @pytest.mark.parametrize("hidden", [16, 48, 100, 128])
 @pytest.mark.parametrize("batch,frames", [(1, 2), (16, 5), (17, 1)])
 def test_gradient_with_all_frames_on_one_compute_unit(hidden, batch, frames, prec):
-    # one wave to eight, each register size; one row, a whole tile and one row more; an even, an odd and a single frame (which runs
-    # as a launch of its own)
+    # one wave to eight, each register size; one row, a whole tile and one row more; an even, an odd and a single frame (which
+    # runs as a launch of its own where the rows of W_h are aligned)
     _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
 
 
@@ -114,14 +114,14 @@ def test_gradient_with_all_frames_on_one_compute_unit_sixteen_rows_at_a_time(hid
 @pytest.mark.parametrize("batch,frames", [(1, 2), (17, 5), (32, 3)])
 def test_gradient_with_all_frames_on_clusters_of_compute_units(prec, hidden, batch, frames):
     # every cluster size, whole and with units past the hidden size; one row, one row more than a block, whole blocks (2 and 3
-    # frames are too few for clusters but where W_h's rows are unaligned: the next test has the fewest that run on them)
+    # frames are too few for some sizes: the next test has numbers that both passes of all of them run on clusters for)
     _check_gradient(Shape(12, hidden, 2, 1, 0, 24, batch, frames), 2, prec)
 
 
 @pytest.mark.parametrize("prec,hidden", [(0, 132), (0, 260), (0, 384), (0, 512), (1, 136), (1, 360), (1, 508), (1, 512), (1, 640)])
 @pytest.mark.parametrize("batch,frames", [(1, 7), (17, 8), (32, 7)])
 def test_gradient_on_clusters_of_compute_units_from_few_frames_on(prec, hidden, batch, frames):
-    # every cluster size at the fewest frames that both passes run on clusters for, and one more
+    # every cluster size, both passes; one row, one row more than a block, whole blocks
     _check_gradient(Shape(12, hidden, 1, 1, 0, 24, batch, frames), 2, prec)
 
 
