@@ -369,8 +369,8 @@ bool rec_quad_aligned(const RecDesc& d) {
 //            360, 50: 8.4 / 11.4 against 15.0 / 17.4; and on the other side bf16 16 x 512, 64 (512 workgroups) 20.0 / 21.6
 //            against 15.5 / 18.9, fp32 32 x 512, 64 (1024) 78 / 94 against 48 / 54.
 //            Batches up to 32 leave the rows of a direct tile empty.  fp32 forward: split at any number of workgroups below
-//            1024 cells (32 x 640, batch 2: 66 against 87, 32: 75 / 94; 128 x 512, 16: 161 / 229), and for batches below 8 (48
-//            x 1024, 1: 202 / 206, 8: 217 / 211).  bf16 backward, which reads W_h column by column: up to two rounds where
+//            1024 cells (32 x 640, batch 2: 66 against 87, 32: 75 / 94; 128 x 512, 16: 161 / 229; but 48 x 1024, 1: 202 / 206, 8: 217 /
+//            211; 32 x 1520, 2: 294 / 268).  bf16 backward, which reads W_h column by column: up to two rounds where
 //            a column stays short (48 x 256, 16: 9.4 / 11.9) or the workgroups of a pair share an XCD and the batch is small
 //            (24 x 512, 16: 14.2 / 16.0, 24: 17.0 / 16.7; 16 x 768, 8: 17.5 / 19.3; 8 x 1240, 8: 25 / 27;
 //            20 x 768, 8: 27.3 / 19.5); the bf16 forward step is
@@ -385,7 +385,7 @@ enum RecKind { kStaged, kDirect, kSplit };
 int rec_step_kind(int precision, bool backward, int pairs, int H, int B) {
     const int64_t split_wgs = (int64_t)pairs * ((H + 31) / 32) * ((B + 31) / 32);
     bool split = split_wgs <= (precision ? 256 : 512);
-    if (B <= 32 && !precision && !backward) split = split || H < 1024 || B < 8;
+    if (B <= 32 && !precision && !backward) split = split || H < 1024;
     if (B <= 32 && precision && backward) split = split || (split_wgs <= 512 && (H <= 256 || (pairs % 8 == 0 && (H <= 768 ? B <= 16 : split_wgs <= 320 && B <= 8))));
     if (split) return kSplit;
     return (int64_t)4 * H * H * (precision ? 2 : 4) <= (int64_t)1 << 32 ? kDirect : kStaged;

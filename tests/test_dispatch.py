@@ -29,10 +29,10 @@ def test_direct_step_kernels_only_where_32_bit_offsets_reach_all_of_w_h(precisio
 
 
 def test_small_batches_on_the_split_contraction_where_it_is_the_shorter():
-    for pairs, hidden, batch in ((32, 640, 2), (32, 640, 32), (128, 512, 16), (48, 1024, 1)):
+    for pairs, hidden, batch in ((32, 640, 2), (32, 640, 32), (128, 512, 16)):
         assert _step_kind(Bd.FP32, False, pairs, hidden, batch) == SPLIT
         assert _step_kind(Bd.FP32, True, pairs, hidden, batch) == DIRECT
     for pairs, hidden, batch in ((48, 256, 32), (24, 512, 16), (16, 768, 8)):
         assert _step_kind(Bd.BF16_GEMM, True, pairs, hidden, batch) == SPLIT
         assert _step_kind(Bd.BF16_GEMM, False, pairs, hidden, batch) == DIRECT
-    assert _step_kind(Bd.BF16_GEMM, True, 20, 768, 8) == DIRECT and _step_kind(Bd.FP32, False, 48, 1024, 8) == DIRECT
+    assert _step_kind(Bd.BF16_GEMM, True, 20, 768, 8) == DIRECT and _step_kind(Bd.FP32, False, 48, 1024, 2) == DIRECT
