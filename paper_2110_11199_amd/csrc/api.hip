@@ -115,7 +115,7 @@ struct adpsgd_handle {
     int64_t mean_cap = 0;                  // its size in elements: min(kMeanChunkMax, P rounded up to 1024)
     int64_t tune_mean_chunk = -1;          // elements per chunk; 0: the single-kernel global mean; -1: automatic
     int tune_pair_split = -1;              // pairwise update: one member of a pair per thread (positions per workgroup), 0 off, -1 default
-    int tune_sync_segment = -1;            // synchronous baseline: learners per thread of the update (0: all of them), -1: default
+    int tune_sync_segment = -1;            // synchronous baseline, global mean in one kernel: learners per thread of the update (0: all of them), -1: default
     int tune_tri_segment = -1;             // ring-neighbour update: ring positions per thread (0: the whole ring), -1: default
     // device status word (kStatus* bits, sticky) and the pinned host words, one per bit, that a kernel which raises a bit
     // writes too (raise_status_)

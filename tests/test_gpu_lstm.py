@@ -511,7 +511,7 @@ def test_cluster_waits_for_workgroups_that_have_not_started():
     from paper_2110_11199_amd import binding as Bd
     print("cluster short of workgroups", flush=True)
     shape = Shape(12, 360, 1, 1, 0, 24, 64, 100)
-    for a, b in zip(_one_step(shape, 8, 1, ((Bd.TUNE_REC_WAIT_US, 150),)), _one_step(shape, 8, 1, ((Bd.TUNE_REC_JOIN_US, 20),))):
+    for a, b in zip(_one_step(shape, 8, 1, ((Bd.TUNE_REC_WAIT_US, 300),)), _one_step(shape, 8, 1, ((Bd.TUNE_REC_JOIN_US, 20),))):
         assert (a == b).all()
 
 
