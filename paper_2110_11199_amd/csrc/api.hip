@@ -150,10 +150,10 @@ struct adpsgd_handle {
     float* cbuf;       // [layers][L][D][M][H]
     void* z; void* dz; float* logits; void* dlogits; float* dy; void* da; float* dc;
     float* row_loss; float* loss;
-    // recurrences over clusters of workgroups: iteration counter and [layers][2 passes] tickets behind it; exchange words
+    // recurrences over clusters of workgroups: iteration counter, [layers][2 passes] words per cluster, exchange words
     uint32_t* epoch = nullptr;
+    uint64_t* join = nullptr; int64_t joins = 0;               // joins: words of one launch
     uint64_t* exchange = nullptr; size_t exchange_bytes = 0;
-    uint64_t* closed = nullptr; size_t closed_bytes = 0;       // a word per cluster, right behind the exchange words
 };
 
 // A recorded sequence of iterations of one handle (adpsgd_capture_end), replayed by adpsgd_graph_replay.
@@ -349,10 +349,10 @@ size_t plan(adpsgd_handle* h, void* base) {
             if (rec_cluster_supported(r, backward, 1 << 20)) words = std::max(words, rec_cluster_exchange_words(r, backward));
         h->exchange_bytes = (size_t)words * 8;
         if (words > 0) {
-            h->epoch = (uint32_t*)w.take((1 + (size_t)h->layers * 2) * 4);
-            h->closed_bytes = (size_t)rec_cluster_count(r) * 8;
-            h->exchange = (uint64_t*)w.take(h->exchange_bytes + h->closed_bytes);
-            h->closed = h->exchange + words;
+            h->epoch = (uint32_t*)w.take(4);
+            h->joins = rec_cluster_count(r);
+            h->join = (uint64_t*)w.take((size_t)h->joins * h->layers * 2 * 8);
+            h->exchange = (uint64_t*)w.take(h->exchange_bytes);
         }
     }
     return w.used;
@@ -470,7 +470,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     StageDesc st;
     st.L = n; st.lmap = act; st.precision = prec; st.rows = M; st.I = h->I; st.ldx = h->ldx;
     st.x0 = h->x0; st.sX0 = M * h->ldx; st.y = h->labels; st.sY = M;
-    st.epoch = h->epoch; st.tickets = h->layers * 2;
+    st.epoch = h->epoch; st.join = h->join; st.joins = h->joins * h->layers * 2;
     for (int i = 0; i < 128; ++i) {
         st.feats[i] = i < L ? (const float*)batch_ptrs[2 * i] : nullptr;
         st.labels[i] = i < L ? (const int32_t*)batch_ptrs[2 * i + 1] : nullptr;
@@ -498,7 +498,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         ClusterDesc c;
         c.r = r;
         c.launches = 2 * h->layers; c.launch = 2 * l + (backward ? 1 : 0);
-        c.exchange = h->exchange; c.closed = h->closed; c.epoch = h->epoch; c.ticket = h->epoch + 1 + c.launch; c.status = h->status;
+        c.exchange = h->exchange; c.join = h->join + h->joins * c.launch; c.epoch = h->epoch; c.status = h->status;
         c.wait_ticks = (unsigned long long)h->tune_wait_us * 100ull;
         // by default several times what one workgroup takes for the cluster (0.02 to 0.3 ms a frame), and far more than the clusters before it in
         // the same launch take (up to 0.02)
@@ -777,8 +777,8 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     if (e == hipSuccess) e = hipMemsetAsync(h->params[0], 0, slab, s);
     if (e == hipSuccess && h->tau == 1) e = hipMemsetAsync(h->params[1], 0, slab, s);
     if (e == hipSuccess && !h->flat) e = hipMemsetAsync(h->grads, 0, slab, s);
-    if (e == hipSuccess && h->epoch) e = hipMemsetAsync(h->epoch, 0, (1 + (size_t)h->layers * 2) * 4, s);
-    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes + h->closed_bytes, s);   // no word carries a tag in use
+    if (e == hipSuccess && h->epoch) e = hipMemsetAsync(h->epoch, 0, 4, s);
+    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes, s);   // no word carries a tag in use
     if (e != hipSuccess) { (void)hipHostFree(mirror); delete h; return hipfail(e, "clear models"); }
     if (cfg->init_scale > 0.f) {
         // same w_0 on every learner (Algorithm 1, input)

@@ -11,7 +11,7 @@ struct StageArgs {
     void* x0; int64_t sX0; int32_t* y; int64_t sY;
     const float* feats[128];
     const int32_t* labels[128];
-    uint32_t* epoch; int tickets;
+    uint32_t* epoch; uint64_t* join; int64_t joins;
 };
 
 template <typename T>
@@ -26,9 +26,9 @@ __global__ __launch_bounds__(256) void stage_kernel(StageArgs p) {
         ((T*)p.x0)[li * p.sX0 + idx] = Elem<T>::from(v);
     }
     if (idx < p.rows) p.y[li * p.sY + idx] = p.labels[li][idx];
-    if (p.epoch && blockIdx.x == 0 && blockIdx.y == 0) {
-        if (threadIdx.x == 0) p.epoch[0] += 1u;
-        for (int i = threadIdx.x; i < p.tickets; i += 256) p.epoch[1 + i] = 0u;
+    if (p.epoch && blockIdx.y == 0) {
+        if (idx == 0) p.epoch[0] += 1u;
+        for (int64_t i = idx; i < p.joins; i += (int64_t)gridDim.x * 256) p.join[i] = 0ull;
     }
 }
 
@@ -38,7 +38,7 @@ hipError_t launch_stage(const StageDesc& d, hipStream_t s) {
     a.lmap = d.lmap;
     a.rows = d.rows; a.I = d.I; a.ldx = d.ldx; a.x0 = d.x0; a.sX0 = d.sX0; a.y = d.y; a.sY = d.sY;
     for (int i = 0; i < 128; ++i) { a.feats[i] = d.feats[i]; a.labels[i] = d.labels[i]; }     // indexed by learner
-    a.epoch = d.epoch; a.tickets = d.tickets;
+    a.epoch = d.epoch; a.join = d.join; a.joins = d.joins;
     dim3 grid((unsigned)((d.rows * d.ldx + 255) / 256), (unsigned)d.L);
     if (d.precision == 0) hipLaunchKernelGGL(stage_kernel<float>, grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(stage_kernel<bf16_t>, grid, dim3(256), 0, s, a);

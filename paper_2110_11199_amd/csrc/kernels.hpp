@@ -81,8 +81,8 @@ struct StageDesc {             // copy / cast the minibatches into the workspace
     const int32_t* labels[128];
     void* x0; int64_t sX0;     // [L][rows][ldx] operand type
     int32_t* y; int64_t sY;    // [L][rows]
-    uint32_t* epoch;           // incremented once (may be NULL), and the `tickets` words behind it are cleared
-    int tickets;
+    uint32_t* epoch;           // incremented once (may be NULL), and
+    uint64_t* join; int64_t joins;       // these words are cleared
 };
 hipError_t launch_stage(const StageDesc& d, hipStream_t s);
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s);
@@ -149,10 +149,10 @@ __device__ inline void raise_status_(uint32_t* status, uint32_t bit) {
 struct ClusterDesc {
     RecDesc r;
     uint64_t* exchange;                  // rec_cluster_exchange_words(r, backward) words, zero before the handle's first launch
-    uint32_t* ticket;                    // zero before the launch
     const uint32_t* epoch;               // differs from iteration to iteration, 0 in none
     int launch, launches;                // this launch among those of an iteration
-    uint64_t* closed;                    // rec_cluster_count(r) words, zero before the handle's first launch
+    uint64_t* join;                      // rec_cluster_count(r) words, zero before the launch
+    int spread;                          // set by launch_rec_cluster: the ids of a cluster's workgroups lie 8 apart
     uint32_t* status;                    // kStatusWaitExpired is or-ed in
     unsigned long long wait_ticks;       // bound of one wait of the exchange
     unsigned long long join_ticks;       // after which a cluster whose workgroups have not all started is left to one of them

@@ -15,25 +15,31 @@
 //             Splitting over the result instead would have every workgroup read all of da: 4 H words read and 4 U written in
 //             fp32; with bf16 operands, two values to a word, 2 H and 2 U, about as many in all but far fewer writes (not tried).
 //
-// Exchange.  A 32-bit payload and a 32-bit tag travel in one aligned 64-bit word, stored and loaded with single relaxed atomics
-// at device scope: a word is there or it is not, so there are no fences, no write-backs and no counters, and a frame costs one
-// store-to-load latency.  The tag counts frames over launches AND iterations (a device word that the staging kernel of
-// every iteration increments, so that a replayed recording gets new tags as well), so nothing is cleared between uses;
+// Exchange.  A 32-bit payload and a 32-bit tag travel in one aligned 64-bit word, written and read whole (two words to a
+// 16-byte access, each with its own tag): a word is there or it is not, so there are no fences, no write-backs and no counters, and a
+// frame costs one store-to-load latency.  The tag counts frames over launches AND iterations (a device word that the staging
+// kernel of every iteration increments, so that a replayed recording gets new tags as well), so nothing is cleared between uses;
 // the buffer is zeroed when the handle is made and 0 is no tag in use.  Two slots by the parity of the frame suffice: whoever
 // writes frame s has received all of frame s-1, whose senders had read frame s-2.
+// The words are read past the first-level cache (device scope), which the L2 of an XCD answers.  Members that all run on one
+// XCD therefore store them at workgroup scope, to that L2 and no further; others have to write through to memory.  An
+// all-to-all of 256 threads x N words between 8 workgroups, us: N = 1 0.64 through memory, 0.36 in one L2; 8 1.36, 0.63 (0.54 with
+// 16-byte loads); 12 1.68, 0.77 (0.71); 24 2.31, 1.35 (0.97).  Workgroup ids go round the 8 XCDs, so the members of a
+// cluster take ids 8 apart; what decides is not that, but the XCD each of them reads from its hardware register.
 //
-// Progress.  Workgroups take their place (cluster, member) from a ticket counter when they START, and exchange nothing before
-// all members of their cluster have (join_: the last one says so): from there on every member runs, whatever else shares the
-// device and in whatever order workgroups are dispatched.  The grid may exceed the chip.  A cluster that stays incomplete for
-// longer than the other workgroups of the launch can explain - other work holds the device, or other such launches with
-// incomplete clusters of their own - is closed to further members and left to one of those that wait, which does all of it
-// alone (forward_alone_, backward_alone_): the same operations in the same order, slower by the number of members and by W_h
-// from the caches (us per frame, forward / backward, cluster against alone: fp32 256 cells 4.5 / 4.3 against 42 / 55, bf16 640 cells
-// 4.3 / 7.4 against 116 / 272).  So nothing waits for workgroups that may not come.  Every wait of the exchange is bounded all the same
-// (wait_ticks of the 100 MHz clock, or another workgroup's expiry): the workgroup raises kStatusWaitExpired and returns.
+// Progress.  Every workgroup counts itself into its cluster's word when it STARTS, by XCD, and exchanges nothing before
+// all members have: from there on every member runs, whatever else shares the device and in whatever order workgroups are
+// dispatched.  The grid may exceed the chip.  A cluster that stays incomplete for longer than the other workgroups of the
+// launch can explain - other work holds the device, or other such launches with incomplete clusters of their own - is closed (a bit
+// of the same word) and left to one of those that wait, which does all of it alone (forward_alone_, backward_alone_): the
+// same operations in the same order, slower by the number of members and by W_h from the caches (us per frame, forward /
+// backward, cluster against alone: fp32 256 cells 4.5 / 4.3 against 42 / 55, bf16 640 cells 4.3 / 7.4 against 116 / 272).  So
+// nothing waits for workgroups that may not come.  Every wait of the exchange is bounded all the same (wait_ticks of
+// the 100 MHz clock, or another workgroup's expiry): the workgroup raises kStatusWaitExpired and returns.
 //
 // MFMA operand mapping (16x16 tiles) as in lstm_resident.hip.
 #include <algorithm>
+#include <type_traits>
 #include "gemm_core.hpp"
 #include "kernels.hpp"
 #include "rec_tiles.hpp"
@@ -51,33 +57,46 @@ template <typename T, int S_> struct Cl {
     static constexpr int FWD_ROW = KP * (int)sizeof(T) + 16, BWD_ROW = 4 * U * (int)sizeof(T) + 16;     // bytes of an LDS row
     static constexpr int W_ROW = KP + 4;                   // words of a row of staged W_h: rows 4 apart lie 16 banks apart
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
-    static constexpr int PPT = RB * U / 256;                                    // backward: (row, unit) positions of a thread
+    static constexpr int PPT = RB * U / 256;                                    // backward: rows of its unit that a thread finishes
     static constexpr int64_t FWD_SLOT = (int64_t)RB * RW, BWD_SLOT = (int64_t)S * RB * KP;              // exchange words
-    static_assert(NCH % KS == 0 && KP % 64 == 0, "tiling");
+    static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 32 == 0 && PPT % 2 == 0, "tiling");
 };
 
-// An exchange word is addressed by a wave-uniform base and one byte offset of the lane; the base passes through an empty asm in
-// every frame, so that the compiler forms the addresses from it there instead of keeping one per word across the frames.
+// Scratch words of a workgroup that does a cluster's work alone.
 typedef __attribute__((address_space(1))) uint64_t word_t;
-typedef __attribute__((address_space(1))) char byte_t;
-__device__ inline word_t* per_frame_(word_t* p) { asm volatile("" : "+s"(p)); return p; }
-__device__ inline void put_(word_t* base, uint32_t lane_bytes, uint32_t v, uint32_t tag) {
-    __hip_atomic_store((word_t*)((byte_t*)base + lane_bytes), (uint64_t)v | ((uint64_t)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline void scratch_put_(word_t* at, float v) {
+    __hip_atomic_store(at, (uint64_t)__builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Words base + off(0) .. base + off(N-1) of this lane, once all of them carry the tag; false when the wait ran out.  (Every branch
+__device__ inline float scratch_get_(const word_t* at) {
+    return __builtin_bit_cast(float, (uint32_t)__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// Scopes of the accesses to exchange words (cache policy bits of the buffer instructions): stores to the L2 of this XCD, or through
+// it to memory; loads past the first-level cache.
+constexpr int kToL2 = 1, kToMemory = 16, kFromL2 = 16;
+template <int SCOPE> __device__ inline void put_(buf_t x, uint32_t lane_bytes, uint32_t bytes, uint32_t v, uint32_t tag) {
+    const u32x2_t w = {v, tag};
+    __builtin_amdgcn_raw_buffer_store_b64(w, x, (int)lane_bytes, (int)bytes, SCOPE);
+}
+template <int SCOPE> __device__ inline void put2_(buf_t x, uint32_t lane_bytes, uint32_t bytes, float v0, float v1, uint32_t tag) {
+    const u32x4_t w = {__builtin_bit_cast(uint32_t, v0), tag, __builtin_bit_cast(uint32_t, v1), tag};
+    __builtin_amdgcn_raw_buffer_store_b128(w, x, (int)lane_bytes, (int)bytes, SCOPE);
+}
+// Pairs of words at lane_bytes + off(0) .. off(N-1), once all of them carry the tag; false when the wait ran out.  (Every branch
 // is wave-uniform for the compiler too: a divergent one has it copy the resident fragments around the loop.)
 template <int N, class Off>
-__device__ inline bool get_(const ClusterDesc& p, const word_t* base, Off off, uint32_t lane_bytes, uint32_t tag, uint32_t (&v)[N]) {
+__device__ inline bool get_(const ClusterDesc& p, buf_t x, uint32_t lane_bytes, Off off, uint32_t tag, uint32_t (&v)[2 * N]) {
     uint64_t t0 = 0;
     bool half = false;
 #pragma unroll 1
     for (uint32_t tries = 0;; ++tries) {
-        uint64_t x[N];
+        u32x4_t w[N];
+        asm volatile("" ::: "memory");                     // (loaded anew in every round)
 #pragma unroll
-        for (int i = 0; i < N; ++i) x[i] = __hip_atomic_load((const word_t*)((const byte_t*)(base + off(i)) + lane_bytes), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < N; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(x, (int)lane_bytes, (int)off(i), kFromL2);
         uint32_t differ = 0;
 #pragma unroll
-        for (int i = 0; i < N; ++i) { differ |= (uint32_t)(x[i] >> 32) ^ tag; v[i] = (uint32_t)x[i]; }
+        for (int i = 0; i < N; ++i) { differ |= (w[i].y ^ tag) | (w[i].w ^ tag); v[2 * i] = w[i].x; v[2 * i + 1] = w[i].z; }
         // (a bound of 0 gives up at the first exchange, whether the words are there or not)
         if (__ballot(differ != 0) == 0 && p.wait_ticks != 0) return true;
         if ((tries & 15) == 15 || p.wait_ticks == 0) {
@@ -96,53 +115,58 @@ __device__ inline bool get_(const ClusterDesc& p, const word_t* base, Off off, u
     }
 }
 
-// Place of this workgroup, and the tag of the launch's frame 0, which the word that closes a cluster carries.
+// A cluster's word: how many of its members have started, 6 bits for each XCD; kClosed and the member it is left to.
+constexpr int kXcds = 8;
+constexpr uint64_t kClosed = 1ull << 63;
+constexpr int kClosedMember = 6 * kXcds;
+
+// Place of this workgroup, and the tag of the launch's frame 0.
 struct Place { int li, d, b0, blk, m, cluster; uint32_t tag0; };
-constexpr uint32_t kTogether = 1u, kAlone = 2u;            // that word: all members have started; left to member x - kAlone
 template <class C> __device__ inline bool place_(const ClusterDesc& p, Place& w) {
-    __shared__ uint32_t sh[2];
-    const int blocks = (p.r.B + 15) / 16;
-    if (threadIdx.x == 0) {
-        // (a bound of 0: every cluster consists of one workgroup, which takes all its places)
-        const uint32_t t = __hip_atomic_fetch_add(p.ticket, p.join_ticks == 0 ? (uint32_t)C::S : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t tag0 = (*p.epoch * (uint32_t)p.launches + (uint32_t)p.launch) * (uint32_t)p.r.T + 1u;
-        sh[0] = t; sh[1] = tag0;
-        if (t % C::S == C::S - 1 && t < (uint32_t)(p.r.L * p.r.D * blocks) * (uint32_t)C::S) put_((word_t*)p.closed, t / C::S * 8u, kTogether, tag0);
-    }
-    __syncthreads();
-    const int t = __builtin_amdgcn_readfirstlane((int)sh[0]);
-    const int cluster = t / C::S, pair = cluster / blocks;
+    static_assert(C::S < 64, "members of a cluster");
+    const int blocks = (p.r.B + 15) / 16, id = (int)blockIdx.x;
+    const int cluster = p.spread ? (id / kXcds / C::S) * kXcds + id % kXcds : id / C::S, pair = cluster / blocks;
     if (pair >= p.r.L * p.r.D) return false;
-    w.m = t % C::S; w.cluster = cluster; w.blk = cluster % blocks; w.b0 = w.blk * C::RB;
+    w.m = (p.spread ? id / kXcds : id) % C::S;
+    w.cluster = cluster; w.blk = cluster % blocks; w.b0 = w.blk * C::RB;
     w.li = __builtin_amdgcn_readfirstlane(p.r.lmap.idx[pair / p.r.D]); w.d = pair % p.r.D;
-    w.tag0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh[1]);
+    w.tag0 = (*p.epoch * (uint32_t)p.launches + (uint32_t)p.launch) * (uint32_t)p.r.T + 1u;
+    if (threadIdx.x == 0) {
+        uint32_t xcd;
+        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcd));
+        __hip_atomic_fetch_add(p.join + cluster, 1ull << (6 * (xcd % kXcds)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     return true;
 }
 
-// Waits until the cluster is closed: kTogether, or kAlone + the member it is left to.  Exactly one of the two is decided, by the
-// ticket counter: whoever takes the last place, or whoever moves the counter past the places that are left.
+// Waits until every member has started - kTogether: on several XCDs, kOneXcd: on one - or the cluster is left to one of those
+// that have: kAlone + that member.  Exactly one of these is decided, by the cluster's word: it is closed only while
+// members are missing, and those that start later find it closed.
+constexpr uint32_t kTogether = 0u, kOneXcd = 1u, kAlone = 2u;
 template <class C> __device__ inline uint32_t join_(const ClusterDesc& p, const Place& w) {
-    if (p.join_ticks == 0) return kAlone + (uint32_t)w.m;
-    word_t* const closed = (word_t*)p.closed + w.cluster;
-    const uint32_t end = (uint32_t)(w.cluster + 1) * (uint32_t)C::S;
+    if (p.join_ticks == 0) return kAlone;                  // (a bound of 0: the first member takes every cluster)
+    uint64_t* const word = p.join + w.cluster;
     uint64_t t0 = 0;
-    bool half = false;
 #pragma unroll 1
     for (uint32_t tries = 0;; ++tries) {
-        const uint64_t x = __hip_atomic_load(closed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) == w.tag0) return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+        const uint64_t x = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32));
+        const uint64_t seen = (uint64_t)lo | ((uint64_t)hi << 32);
+        if (seen & kClosed) return kAlone + (uint32_t)(seen >> kClosedMember) % 64u;
+        uint32_t all = 0, most = 0;
+#pragma unroll
+        for (int i = 0; i < kXcds; ++i) {
+            const uint32_t n = (uint32_t)(seen >> (6 * i)) % 64u;
+            all += n; most = n > most ? n : most;
+        }
+        if (all == (uint32_t)C::S) return most == all ? kOneXcd : kTogether;
         if ((tries & 15) != 15) continue;
         const uint64_t now = wall_clock64();
         if (t0 == 0) t0 = now;
         if (now - t0 < p.join_ticks) continue;
-        uint32_t seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        if (seen < end) {
-            if (threadIdx.x == 0 && __hip_atomic_compare_exchange_strong(p.ticket, &seen, end, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                put_(closed, 0u, kAlone + (uint32_t)w.m, w.tag0);
-        } else if (now - t0 - p.join_ticks >= p.wait_ticks / 2) {      // (decided, the word is on its way: as any other exchange)
-            if (half) { raise_status_(p.status, kStatusWaitExpired); return 0u; }
-            half = true; t0 = now - p.join_ticks;
-        }
+        uint64_t expected = seen;
+        if (threadIdx.x == 0)
+            __hip_atomic_compare_exchange_strong(word, &expected, kClosed | ((uint64_t)w.m << kClosedMember), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -315,7 +339,7 @@ __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, cha
 template <typename T, int S>
 __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, char* lds, float (&bred)[4][256]) {
     typedef Cl<T, S> C;
-    constexpr int U = C::U, PPT = C::PPT, RSTEP = 256 / U;
+    constexpr int U = C::U, PPT = C::PPT;
     const RecDesc& p = cd.r;
     const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
@@ -330,7 +354,6 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
     word_t* const dh_buf = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT;
     word_t* const bs_buf = dh_buf + C::BWD_SLOT;
     static_assert(S * 4 * 256 <= C::BWD_SLOT, "the sums of da fit a slot");
-    auto get = [](const word_t* at) { return __builtin_bit_cast(float, (uint32_t)__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); };
     const int uu = tid % U;
 #pragma unroll 1
     for (int s = 0; s < Tn; ++s) {
@@ -343,10 +366,10 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
             const int cu = mm * U + uu;
             float bs[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) bs[q] = s > 0 ? get(bs_buf + (mm * 4 + q) * 256 + tid) : 0.f;
+            for (int q = 0; q < 4; ++q) bs[q] = s > 0 ? scratch_get_(bs_buf + (mm * 4 + q) * 256 + tid) : 0.f;
 #pragma unroll 1
             for (int i = 0; i < PPT; ++i) {
-                const int lr = tid / U + i * RSTEP;
+                const int lr = tid / U * PPT + i;
                 const uint32_t row = w.b0 + lr;
                 const bool ok = cu < H && (int)row < B;
                 const uint32_t vg = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange, vc = ok ? (row * H + cu) * 4u : kOutOfRange;
@@ -354,7 +377,7 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
                 float gate[4], a4[4], dc = s > 0 ? buf_load_(dcb, vc, 0u) : 0.f;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) gate[q] = buf_load_(gates, vg, (m * G4 + q * H) * 4u);
-                const float dh = s > 0 ? get(dh_buf + lr * C::KP + cu) : 0.f;
+                const float dh = s > 0 ? scratch_get_(dh_buf + lr * C::KP + cu) : 0.f;
                 const float c_prev = buf_load_(cbuf, s + 1 < Tn ? vc : kOutOfRange, s + 1 < Tn ? m_next * H * 4u : 0u);
                 bwd_cell_(a4, buf_load_(dy, vy, m * DH * 4u) + dh, dc, gate, buf_load_(cbuf, vc, m * H * 4u), c_prev);
                 buf_store_(dc, dcb, vc, 0u);
@@ -368,7 +391,7 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
                 }
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) put_(bs_buf + (mm * 4 + q) * 256, (uint32_t)tid * 8u, __builtin_bit_cast(uint32_t, bs[q]), 0u);
+            for (int q = 0; q < 4; ++q) scratch_put_(bs_buf + (mm * 4 + q) * 256 + tid, bs[q]);
             __syncthreads();
             if (s + 1 < Tn) {
                 f32x4_t acc[C::NT];
@@ -395,7 +418,7 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
             for (int j = 0; j < C::NT; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    put_(dh_buf + (wave + 4 * j) * 16, (uint32_t)((4 * g + i) * C::KP + r) * 8u, __builtin_bit_cast(uint32_t, (float)sum[j][i]), 0u);
+                    scratch_put_(dh_buf + (4 * g + i) * C::KP + (wave + 4 * j) * 16 + r, sum[j][i]);
             __threadfence();
             __syncthreads();
         }
@@ -404,7 +427,7 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
     for (int mm = 0; mm < S; ++mm) {
         float bs[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) bs[q] = get(bs_buf + (mm * 4 + q) * 256 + tid);
+        for (int q = 0; q < 4; ++q) bs[q] = scratch_get_(bs_buf + (mm * 4 + q) * 256 + tid);
         bias_sums_<C>(cd, w, bred, bs, mm);
         __syncthreads();
     }
@@ -423,8 +446,9 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
     __shared__ int expired;
     const RecDesc& p = cd.r;
     Place w;
-    if (threadIdx.x == 0) expired = 0;
     if (!place_<C>(cd, w)) return;
+    if (threadIdx.x == 0) expired = 0;
+    __syncthreads();
     const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
     const int kh = wave / C::NU;                           // which part of the contraction
@@ -434,7 +458,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
     const buf_t gates = make_buf_(p.gates + w.li * p.sGi, (int64_t)Tn * B * G4 * 4);
     const buf_t cbuf = make_buf_(p.c + w.li * p.sCi + (int64_t)d * Tn * B * H, (int64_t)Tn * B * H * 4);
     const buf_t y = make_buf_((const T*)p.y + w.li * p.sYi, (int64_t)Tn * B * DH * sizeof(T));
-    word_t* const xch = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::FWD_SLOT;
+    const buf_t xch = make_buf_(cd.exchange + (int64_t)w.cluster * 2 * C::FWD_SLOT, 2 * C::FWD_SLOT * 8);
 
     uint4 wf[4][C::CW];
     {
@@ -473,7 +497,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
     for (int i = 0; i < PR; ++i) cs[i] = 0.f;
     load_pre(0);
     const uint32_t how = join_<C>(cd, w);
-    if (__builtin_expect(how != kTogether, 0)) {
+    if (__builtin_expect(how >= kAlone, 0)) {
         if (how == kAlone + (uint32_t)w.m) forward_alone_<T, S>(cd, w, lds, red);
         return;
     }
@@ -487,14 +511,14 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
             else acc[q] = kh == 0 ? f32x4_t{pre[q][0], pre[q][1], 0.f, 0.f} : f32x4_t{0.f, 0.f, pre[q][0], pre[q][1]};
         }
         if (s > 0) {
-            // h of the frame before, all units, into LDS: 16 threads to a row, words tid % 16 + 16 i
-            constexpr int N = C::RW / 16;
+            // h of the frame before, all units, into LDS: 16 threads to a row, words 2 (tid % 16) + 32 i and the next
+            constexpr int N = C::RW / 32;
             char* const hl = lds + (s & 1) * (C::RB * C::FWD_ROW);
-            const word_t* const slot = per_frame_(xch + (s & 1) * C::FWD_SLOT);
-            uint32_t v[N];
-            const bool ok = get_<N>(cd, slot, [](int i) { return 16 * i; }, (uint32_t)((tid >> 4) * C::RW + (tid & 15)) * 8u, w.tag0 + s, v);
+            const uint32_t slot = (uint32_t)(s & 1) * (uint32_t)(C::FWD_SLOT * 8);
+            uint32_t v[2 * N];
+            const bool ok = get_<N>(cd, xch, (uint32_t)((tid >> 4) * C::RW + 2 * (tid & 15)) * 8u, [&](int i) { return slot + 256u * i; }, w.tag0 + s, v);
 #pragma unroll
-            for (int i = 0; i < N; ++i) *(uint32_t*)(hl + (tid >> 4) * C::FWD_ROW + (tid & 15) * 4 + i * 64) = v[i];
+            for (int i = 0; i < N; ++i) *(uint2*)(hl + (tid >> 4) * C::FWD_ROW + (tid & 15) * 8 + i * 128) = make_uint2(v[2 * i], v[2 * i + 1]);
             if (!ok) expired = 1;
             load_pre(s + 1 < Tn ? s + 1 : s);              // (after the exchange: its loads return in order behind these)
             lds_barrier_();
@@ -518,13 +542,19 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
 #pragma unroll
         for (int i = 0; i < PR; ++i) h[i] = fwd_cell_(acc, i, cs[i]);              // (the gates replace the pre-activations)
         // h first: the other workgroups wait for it (rows past the batch and units past H too: they are read, as zeros or unused)
-        word_t* const out = per_frame_(xch + ((s + 1) & 1) * C::FWD_SLOT);
+        const uint32_t out = (uint32_t)((s + 1) & 1) * (uint32_t)(C::FWD_SLOT * 8);
         const uint32_t out_lane = (uint32_t)((row0 + (C::VW == 2 ? r & 1 : 0)) * C::RW + u / C::VW) * 8u;
         uint32_t hw[PR / C::VW];
 #pragma unroll
-        for (int i = 0; i < PR / C::VW; ++i) {
-            hw[i] = h_word_<T>(h, i, r);
-            if (s + 1 < Tn) put_(out + i * C::VW * C::RW, out_lane, hw[i], w.tag0 + s + 1);
+        for (int i = 0; i < PR / C::VW; ++i) hw[i] = h_word_<T>(h, i, r);
+        if (s + 1 < Tn) {
+            if (how == kOneXcd) {
+#pragma unroll
+                for (int i = 0; i < PR / C::VW; ++i) put_<kToL2>(xch, out_lane, out + (uint32_t)(i * C::VW * C::RW) * 8u, hw[i], w.tag0 + s + 1);
+            } else {
+#pragma unroll
+                for (int i = 0; i < PR / C::VW; ++i) put_<kToMemory>(xch, out_lane, out + (uint32_t)(i * C::VW * C::RW) * 8u, hw[i], w.tag0 + s + 1);
+            }
         }
 #pragma unroll
         for (int i = 0; i < PR / C::VW; ++i) buf_store_(__builtin_bit_cast(float, hw[i]), y, vy[i], m * DH * (uint32_t)sizeof(T));
@@ -542,20 +572,21 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
 //   do = dh tanh(c_t)            dc = dc_rec + dh o (1 - tanh^2 c_t)
 //   di = dc g, dg = dc i, df = dc c_{t'}, dc_rec <- dc f
 //   da = (di i(1-i), df f(1-f), dg (1-g^2), do o(1-o))
-// A thread finishes one unit of the workgroup, rows tid / U + i * 256 / U; it adds the partial sums of its positions in the order
+// A thread finishes PPT consecutive rows of one unit of the workgroup; it adds the partial sums of its positions in the order
 // of the members.  The column sums of da (bias gradients) run over all frames in registers: one row per row block.
 template <typename T, int S>
 __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDesc cd) {
     typedef Cl<T, S> C;
-    constexpr int U = C::U, PPT = C::PPT, RSTEP = 256 / U;
+    constexpr int U = C::U, PPT = C::PPT;
     constexpr int OP_BYTES = 2 * C::RB * C::BWD_ROW, W_BYTES = 2 * 16 * C::W_ROW * 4;
     __shared__ __attribute__((aligned(16))) char lds[OP_BYTES > W_BYTES ? OP_BYTES : W_BYTES];
     __shared__ float bred[4][256];
     __shared__ int expired;
     const RecDesc& p = cd.r;
     Place w;
-    if (threadIdx.x == 0) expired = 0;
     if (!place_<C>(cd, w)) return;
+    if (threadIdx.x == 0) expired = 0;
+    __syncthreads();
     const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
     const uint32_t DH = (uint32_t)(D * H), G4 = DH * 4;
@@ -563,7 +594,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     const buf_t cbuf = make_buf_(p.c + w.li * p.sCi + (int64_t)d * Tn * B * H, (int64_t)Tn * B * H * 4);
     const buf_t dy = make_buf_(p.dy + w.li * p.sDYi, (int64_t)Tn * B * DH * 4);
     const buf_t da = make_buf_((const T*)p.da + w.li * p.sDAi, (int64_t)Tn * B * G4 * sizeof(T));
-    word_t* const xch = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT;
+    const buf_t xch = make_buf_(cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT, 2 * C::BWD_SLOT * 8);
 
     // cell part: this thread's unit and rows
     const int uu = tid % U, cu = w.m * U + uu;
@@ -571,7 +602,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     uint32_t vg[PPT], vc[PPT], vy[PPT];
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-        const uint32_t row = w.b0 + tid / U + i * RSTEP;
+        const uint32_t row = w.b0 + tid / U * PPT + i;
         const bool ok = ok_c && (int)row < B;
         vg[i] = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange;
         vc[i] = ok ? (row * H + cu) * 4u : kOutOfRange;
@@ -641,7 +672,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         lds_barrier_();                                    // the operand of the products goes into the same LDS
     }
     const uint32_t how = join_<C>(cd, w);
-    if (__builtin_expect(how != kTogether, 0)) {
+    if (__builtin_expect(how >= kAlone, 0)) {
         if (how == kAlone + (uint32_t)w.m) backward_alone_<T, S>(cd, w, lds, bred);
         return;
     }
@@ -656,19 +687,19 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
         for (int i = 0; i < PPT; ++i) dh[i] = 0.f;
         if (s > 0) {
-            // partial sums for this workgroup's units: words [member][row][unit]
-            const word_t* const slot = per_frame_(xch + (s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U);
-            constexpr int PB = PPT * S <= 32 ? PPT : 2;          // positions gathered together
+            // partial sums for this workgroup's units: words [member][pair of rows of a thread][thread][row]
+            const uint32_t slot = (uint32_t)((s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U) * 8u;
+            constexpr int PB = PPT * S <= 32 ? PPT : 2;          // rows gathered together
             static_assert(PPT % PB == 0, "gather blocks");
             bool ok = true;
 #pragma unroll
             for (int i0 = 0; i0 < PPT; i0 += PB) {
                 uint32_t v[PB * S];
-                ok &= get_<PB * S>(cd, slot, [&](int j) { return (j % S) * C::RB * U + 256 * (i0 + j / S); }, (uint32_t)tid * 8u, w.tag0 + s, v);
+                ok &= get_<PB * S / 2>(cd, xch, (uint32_t)tid * 16u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U + (i0 / 2 + j / S) * 512) * 8u; }, w.tag0 + s, v);
 #pragma unroll
                 for (int i = 0; i < PB; ++i)
 #pragma unroll
-                    for (int j = 0; j < S; ++j) dh[i0 + i] += __builtin_bit_cast(float, v[i * S + j]);
+                    for (int j = 0; j < S; ++j) dh[i0 + i] += __builtin_bit_cast(float, v[2 * (i / 2 * S + j) + i % 2]);
             }
             if (!ok) expired = 1;
         }
@@ -677,7 +708,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
             bwd_cell_(a4[i], in_dy[i] + dh[i], dcr[i], in_g[i], in_c[i], c_prev[i]);
-            T* arow = (T*)(al + (tid / U + i * RSTEP) * C::BWD_ROW) + uu;
+            T* arow = (T*)(al + (tid / U * PPT + i) * C::BWD_ROW) + uu;
 #pragma unroll
             for (int q = 0; q < 4; ++q) { bs[q] += a4[i][q]; arow[q * U] = Elem<T>::from(a4[i][q]); }
             in_c[i] = c_prev[i];
@@ -697,15 +728,21 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a, wf[j][c]);
             }
-            word_t* const out = per_frame_(xch + ((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U);
+            // (a tile lies in one workgroup's units: U is a multiple of 16; rows 4 g .. 4 g + 3 of a lane are those of one or two threads)
+            const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;
+            const uint32_t out_lane = (uint32_t)(g * (4 / PPT) * U + r) * 16u;
+            constexpr uint32_t next = PPT == 4 ? 512u * 8u : (uint32_t)U * 16u;        // from rows 0, 1 to rows 2, 3
+            auto send = [&](auto scope) {
 #pragma unroll
-            for (int j = 0; j < C::NT; ++j) {
-                const int n0 = (wave + 4 * j) * 16;        // (a tile lies in one workgroup's units: U is a multiple of 16)
-                word_t* const to = out + ((n0 / U) * S * C::RB * U + n0 % U);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    put_(to + i * U, (uint32_t)(4 * g * U + r) * 8u, __builtin_bit_cast(uint32_t, (float)acc[j][i]), w.tag0 + s + 1);
-            }
+                for (int j = 0; j < C::NT; ++j) {
+                    const int n0 = (wave + 4 * j) * 16;
+                    const uint32_t to = out + (uint32_t)((n0 / U) * S * C::RB * U) * 8u + (uint32_t)(n0 % U) * 16u;
+                    put2_<decltype(scope)::value>(xch, out_lane, to, acc[j][0], acc[j][1], w.tag0 + s + 1);
+                    put2_<decltype(scope)::value>(xch, out_lane, to + next, acc[j][2], acc[j][3], w.tag0 + s + 1);
+                }
+            };
+            if (how == kOneXcd) send(std::integral_constant<int, kToL2>{});
+            else send(std::integral_constant<int, kToMemory>{});
         }
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
@@ -728,8 +765,11 @@ int cluster_members(const RecDesc& d) {
 }
 int cluster_blocks(const RecDesc& d) { return (d.B + 15) / 16; }
 
-template <typename T, int S> void launch_cluster_t(const ClusterDesc& p, bool backward, hipStream_t s) {
-    const unsigned grid = (unsigned)(p.r.L * p.r.D * cluster_blocks(p.r) * S);
+template <typename T, int S> void launch_cluster_t(ClusterDesc& p, bool backward, int cu_count, hipStream_t s) {
+    // The members of a cluster on one XCD, unless the compute units that are left of each then cost a round of the chip.
+    const int64_t clusters = rec_cluster_count(p.r), per_xcd = cu_count / kXcds / S, anywhere = cu_count / S;
+    p.spread = per_xcd > 0 && (clusters + kXcds * per_xcd - 1) / (kXcds * per_xcd) <= (clusters + anywhere - 1) / anywhere;
+    const unsigned grid = (unsigned)((p.spread ? round_up(clusters, kXcds) : clusters) * S);
     if (backward) hipLaunchKernelGGL((rec_backward_cluster_kernel<T, S>), dim3(grid), dim3(256), 0, s, p);
     else hipLaunchKernelGGL((rec_forward_cluster_kernel<T, S>), dim3(grid), dim3(256), 0, s, p);
 }
@@ -805,22 +845,23 @@ int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward) {
     return rec_cluster_count(d) * 2 * 16 * row;
 }
 
-hipError_t launch_rec_cluster(const ClusterDesc& p, bool backward, int cu_count, hipStream_t s) {
-    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || !p.closed || !p.ticket || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
+hipError_t launch_rec_cluster(const ClusterDesc& desc, bool backward, int cu_count, hipStream_t s) {
+    ClusterDesc p = desc;
+    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || !p.join || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
     const int S = cluster_members(p.r);
     if (p.r.precision) {
         switch (S) {
-            case 4: launch_cluster_t<bf16_t, 4>(p, backward, s); break;
-            case 6: launch_cluster_t<bf16_t, 6>(p, backward, s); break;
-            case 8: launch_cluster_t<bf16_t, 8>(p, backward, s); break;
-            default: launch_cluster_t<bf16_t, 10>(p, backward, s); break;
+            case 4: launch_cluster_t<bf16_t, 4>(p, backward, cu_count, s); break;
+            case 6: launch_cluster_t<bf16_t, 6>(p, backward, cu_count, s); break;
+            case 8: launch_cluster_t<bf16_t, 8>(p, backward, cu_count, s); break;
+            default: launch_cluster_t<bf16_t, 10>(p, backward, cu_count, s); break;
         }
     } else {
         switch (S) {
-            case 8: launch_cluster_t<float, 8>(p, backward, s); break;
-            case 10: launch_cluster_t<float, 10>(p, backward, s); break;
-            case 12: launch_cluster_t<float, 12>(p, backward, s); break;
-            default: launch_cluster_t<float, 16>(p, backward, s); break;
+            case 8: launch_cluster_t<float, 8>(p, backward, cu_count, s); break;
+            case 10: launch_cluster_t<float, 10>(p, backward, cu_count, s); break;
+            case 12: launch_cluster_t<float, 12>(p, backward, cu_count, s); break;
+            default: launch_cluster_t<float, 16>(p, backward, cu_count, s); break;
         }
     }
     return hipGetLastError();
