@@ -13,13 +13,13 @@
 //   13  128x256 tile on 4 waves (64x128 each), three 64-byte stages, two workgroups per CU: K-contiguous
 //       operands with K < 512 or a narrow output (output layer, layer-0 input projection), whose tiles spend
 //       as long storing as computing; the second workgroup's loop runs during the first one's epilogue.
-//   14  128x128 tile on 4 waves (64x64 each), two 128-byte stages (bf16) or three 64-byte ones (fp32).
-//   15  64x64 tile on 4 waves (32x32 each), three 128-byte stages (bf16) or four 64-byte ones (fp32).
-//       14 and 15 are for problems with too few 256x256 tiles for the 256 CUs, and for fp32 operands.  A small problem
-//       is bound by the latency of its K loop (a 64x64 tile alone on its CU takes 5 ns per k in bf16, a 128x128 one 13)
+//   14  128x128 tile on 4 waves (64x64 each), two 128-byte stages.
+//   15  64x64 tile on 4 waves (32x32 each), three 128-byte stages (smallest fp32 problems: four 64-byte ones).
+//       14 and 15 are for problems with too few 256x256 tiles for the 256 CUs.  A small problem
+//       is bound by the latency of its K loop (a 64x64 tile alone on its CU takes 5 ns per k, a 128x128 one 13)
 //       and by how evenly its tiles cover the CUs, not by operand bytes per flop.  Against the register-staged
-//       kernel 0, us: fp32 (matrix-pipe bound) 672x512x2048x8 217 -> 97, 2000x320x1280x6 234 -> 86, 2688x4096x1024x8
-//       1422 -> 1232 (146 TFLOP/s); bf16 336x256x1024x8 30.8 -> 8.4, 1050x720x2880x5 91 -> 38, 1050x120x3000x5 81 -> 18.
+//       kernel 0, us: 336x256x1024x8 30.8 -> 8.4, 1050x720x2880x5 91 -> 38, 1050x120x3000x5 81 -> 18.
+//       Other fp32 problems that meet the same conditions run in tiles of these two sizes on the bf16 matrix units (gemm_split.hip).
 //   5   256x256 tile on 8 waves (128x64 each) staged through registers, the transposition done between
 //       the registers and LDS.  Large bf16 problems that miss the conditions of 11-15.
 //   0   128x128 tile, 4 waves (64x64 each), 64-byte stages, staged through registers.  Small
@@ -31,163 +31,10 @@
 #include <type_traits>
 #include "gemm_core.hpp"
 #include "gemm_dma.hpp"
+#include "gemm_tile.hpp"
 #include "kernels.hpp"
 
 namespace adpsgd {
-
-// Workgroup ids are handed to the 8 XCDs round-robin; this maps them back so that each
-// XCD (its own L2) works on a contiguous range of tiles.
-__device__ inline int xcd_contiguous_id(int bid, int nb) {
-    const int q = nb >> 3, r = nb & 7;
-    const int xcd = bid & 7, local = bid >> 3;
-    const int start = xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q;
-    return start + local;
-}
-
-// Workgroup -> (group, tile row, tile column).  The grid is one-dimensional over all tiles of all
-// groups.  Each XCD (own L2, 32 CUs) owns a contiguous range of the ordered tile list, so it works on
-// whole groups when there are enough of them instead of on a slice of every group; inside a group
-// the tiles are ordered in bands of gm <= 8 tile rows walked column by column, so that the 32 tiles an
-// XCD runs at one time form a gm x 32/gm patch that shares gm + 32/gm operand panels (an m-fastest
-// walk of the whole group needs tiles_m + 32/tiles_m and re-reads every A panel in every round).
-__device__ inline void map_tile(int bid, int total, int tiles_m, int tiles_n, int& grp, int& tm, int& tn) {
-    const int id = xcd_contiguous_id(bid, total);
-    const int per = tiles_m * tiles_n;
-    grp = id / per;
-    const int t = id - grp * per;
-    const int nband = (tiles_m + 7) >> 3;
-    const int gm = (tiles_m + nband - 1) / nband;
-    const int band = t / (gm * tiles_n);
-    const int first = band * gm;
-    const int rows = tiles_m - first < gm ? tiles_m - first : gm;
-    const int r = t - band * gm * tiles_n;
-    tn = r / rows;
-    tm = first + r - tn * rows;
-}
-
-// Epilogue shared by the GEMM kernels: C tile = acc (+ bias), fp32 or operand type.
-// Every store reads its data from a register of its own (the bias is added in place, the
-// bf16 values are converted into a separate array first): with one temporary register
-// reused for all stores the compiler has to wait for each store before the next one.
-// Bias of this lane's FN accumulator columns (0 without a bias or past the last column).  Loaded before the
-// main loop: in the epilogue the load's latency would stand in front of the stores of every tile.
-template <class Core, int FN>
-__device__ inline void load_bias(float (&bv)[FN], const GemmDesc& p, int n0, int gi, int gd) {
-    const float* bias = p.bias ? p.bias + gi * p.sBiasI + gd * p.sBiasD : nullptr;
-#pragma unroll
-    for (int fn = 0; fn < FN; ++fn) {
-        const int col = n0 + Core::acc_col(fn);
-        bv[fn] = (bias && col < p.N) ? bias[col] : 0.f;
-    }
-}
-
-template <typename T, class Core, int FM, int FN>
-__device__ inline void store_tile(f32x16_t (&acc)[FM][FN], const float (&bias)[FN], const GemmDesc& p, int m0, int n0, int gi, int gd) {
-    const int64_t coff = gi * p.sCi + gd * p.sCd;
-#pragma unroll
-    for (int fn = 0; fn < FN; ++fn) {
-        const int col = n0 + Core::acc_col(fn);
-        if (col >= p.N) continue;
-        const float bv = bias[fn];
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-            const int row0 = m0 + Core::acc_row(fm, 0);          // rows of this lane: row0 + 8*(i/4) + i%4
-            const int64_t o = coff + (int64_t)row0 * p.ldc + col;
-            if (p.c_elem) {
-                T* c = (T*)p.C + o;
-                if constexpr (sizeof(T) == 2) {
-                    uint32_t hb[16];
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) hb[i] = f32_to_bf16(acc[fm][fn][i] + bv);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int r = 8 * (i >> 2) + (i & 3);
-                        if (row0 + r < p.M) c[(int64_t)r * p.ldc] = (bf16_t)hb[i];
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[fm][fn][i] += bv;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int r = 8 * (i >> 2) + (i & 3);
-                        if (row0 + r < p.M) c[(int64_t)r * p.ldc] = acc[fm][fn][i];
-                    }
-                }
-            } else {
-                float* c = (float*)p.C + o;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[fm][fn][i] += bv;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int r = 8 * (i >> 2) + (i & 3);
-                    // written once, read by a later kernel: keep it from displacing the operand panels in L2
-                    if (row0 + r < p.M) __builtin_nontemporal_store(acc[fm][fn][i], c + (int64_t)r * p.ldc);
-                }
-            }
-        }
-    }
-}
-
-// Stores whose address is a wave-uniform 64-bit pointer (SGPR pair) plus a per-lane 32-bit byte offset.
-// Written as inline asm because the compiler otherwise folds the uniform part into a 64-bit vector
-// address and recomputes it with vector multiply-adds for every store.
-__device__ inline void store_u_f32_(uint32_t off, float v, const void* base_uniform) {
-    asm volatile("global_store_dword %0, %1, %2" :: "v"(off), "v"(v), "s"(base_uniform) : "memory");
-}
-__device__ inline void store_u_f32_nt_(uint32_t off, float v, const void* base_uniform) {
-    asm volatile("global_store_dword %0, %1, %2 nt" :: "v"(off), "v"(v), "s"(base_uniform) : "memory");
-}
-__device__ inline void store_u_b16_(uint32_t off, uint32_t v, const void* base_uniform) {
-    asm volatile("global_store_short %0, %1, %2" :: "v"(off), "v"(v), "s"(base_uniform) : "memory");
-}
-
-// The same for a tile that lies wholly inside C (no row or column guard): every store is one
-// instruction whose address is a wave-uniform row pointer plus a per-lane byte offset that is the
-// same for all stores of the lane, so the epilogue costs no vector address arithmetic and no branches.
-// Needs (4 * ldc + 32) * 4 bytes to fit the 32-bit offset (checked by the caller).
-template <typename T, class Core, int FM, int FN>
-__device__ inline void store_tile_interior(f32x16_t (&acc)[FM][FN], const float (&bias)[FN], const GemmDesc& p, int m0, int n0, int gi, int gd) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave_m = wave / Core::kWN, wave_n = wave % Core::kWN;
-    const uint32_t lane_elem = (uint32_t)(4 * (lane >> 5)) * (uint32_t)p.ldc + (uint32_t)(lane & 31);
-    const int64_t tile_off = gi * p.sCi + gd * p.sCd + (int64_t)(m0 + wave_m * FM * 32) * p.ldc + n0 + wave_n * FN * 32;
-    const bool narrow = p.c_elem && sizeof(T) == 2;
-    const int esz = narrow ? 2 : 4;
-    const char* cbase = (const char*)p.C + tile_off * esz;
-    const uint32_t lane_off = lane_elem * (uint32_t)esz;
-    const int64_t row_bytes = (int64_t)p.ldc * esz;
-#pragma unroll
-    for (int fn = 0; fn < FN; ++fn) {
-        const float bv = bias[fn];
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) {
-            const char* fbase = cbase + (int64_t)(fm * 32) * row_bytes + fn * 32 * esz;
-            if (narrow) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    store_u_b16_(lane_off, f32_to_bf16(acc[fm][fn][i] + bv), fbase + (8 * (i >> 2) + (i & 3)) * row_bytes);
-            } else if (p.c_elem) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    store_u_f32_(lane_off, acc[fm][fn][i] + bv, fbase + (8 * (i >> 2) + (i & 3)) * row_bytes);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)   // written once, read by a later kernel: keep it out of L2
-                    store_u_f32_nt_(lane_off, acc[fm][fn][i] + bv, fbase + (8 * (i >> 2) + (i & 3)) * row_bytes);
-            }
-        }
-    }
-}
-
-template <int FM, int FN> __device__ inline void zero_tile(f32x16_t (&acc)[FM][FN]) {
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-}
 
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int VB, int SB>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_kernel(GemmDesc p) {
@@ -259,9 +106,8 @@ __global__ __launch_bounds__(64 * WM * WN, FM * FN <= 4 ? 3 : FM * FN == 8 ? 2 :
 }
 
 // Two independent problems of one layout in one launch (the two weight gradients of a layer): small problems pay for a launch
-// each (4.5 us) and for a last round that leaves part of the chip idle (6 x 1280 x 320 x 1280 and x 1216, fp32: 600 tiles of 64 x
+// each (4.5 us) and for a last round that leaves part of the chip idle (6 x 1280 x 320 x 1280 and x 1216: 600 tiles of 64 x
 // 64 each, three rounds of the chip and three, together five).
-struct GemmPair { GemmDesc d[2]; int tiles0; };
 template <typename T, int SB, int NS>
 __global__ __launch_bounds__(256, 3) void gemm_dma_pair_kernel(GemmPair p) {
     typedef GemmDma<T, KcSrc<T>, KcSrc<T>, 2, 2, 1, 1, SB, NS> Core;
@@ -344,9 +190,10 @@ static int pick_tile(const GemmDesc& d, bool& dma) {
           (d.b_kc ? d.K % epc == 0 || d.k_padded : d.ldb >= (d.N + epc - 1) / epc * epc);
     int v = d.tile;
     if (d.precision == 0) {
-        // fp32 tiles are bound by the matrix pipe (256 flop per clock and CU) in either size: what decides is how evenly
-        // the tiles cover the CUs
-        if (v < 0) v = !dma ? 0 : tile_time(d, 64, 64, 14.0, 20.0) < tile_time(d, 128, 128, 53.0, 60.0) ? 15 : 14;
+        // ns per k of a tile, with others on its compute unit and alone on it (gemm_split.hip): what decides is how evenly the tiles cover
+        // the compute units.  us, 128x128 / 64x64: 672x2048x512x8 70 / 83, 1280x2000x320x6 58 / 71, 1000x512x672x8 42 / 44; and
+        // 672x512x2048x8 98 / 85, 1280x320x1280x6 58 / 52, 2000x320x1280x6 91 / 75.
+        if (v < 0) v = !dma ? 0 : tile_time(d, 64, 64, 12.8, 15.5) < tile_time(d, 128, 128, 36.0, 43.0) ? 15 : 14;
         return v;
     }
     if (v < 0) {
@@ -367,13 +214,22 @@ static int pick_tile(const GemmDesc& d, bool& dma) {
     return v;
 }
 
+static int64_t tiles_of(const GemmDesc& d, int edge) {
+    return (int64_t)((d.M + edge - 1) / edge) * ((d.N + edge - 1) / edge) * d.groupsI * d.groupsD;
+}
+
+// fp32 problems of one round of 64x64 tiles and a short contraction stay on fp32 MFMAs: there a launch costs the fetch of its
+// instructions, of which the split kernels have several times as many (an iteration of the 4 x 64-unit model, five such launches: 74.6 us
+// against 79.2), and a tile alone on its compute unit takes 20 ns per k here and 15.5 there.
+static bool plain_fp32(const GemmDesc& d) { return tiles_of(d, 64) <= 256 && d.K <= 192; }
+
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     bool dma = false;
     const int v = pick_tile(d, dma);
     if (v < 0) return hipErrorInvalidValue;
     if (d.precision == 0) {
-        if (v == 15 && dma) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
-        if (v >= 11 && dma) return launch_dma<float, 2, 2, 2, 2, 64, 3>(d, s);
+        if (v == 15 && dma && plain_fp32(d)) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
+        if (v >= 11 && dma) return launch_gemm_split(d, v != 15, s);
         return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
     }
     const bool wide_a = aligned_to(d.A, d.lda, d.sAi, d.sAd, 2, 16), wide_b = aligned_to(d.B, d.ldb, d.sBi, d.sBd, 2, 16);
@@ -387,24 +243,31 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     return launch_layout<bf16_t, 2, 2, 2, 2, 16, 64>(d, s);
 }
 
-static int64_t pair_tiles(const GemmDesc& d) { return (int64_t)((d.M + 63) / 64) * ((d.N + 63) / 64) * d.groupsI * d.groupsD; }
-
-bool gemm_pair_merged(const GemmDesc& a, const GemmDesc& b) {
+// The edge of the tiles that both problems run on in one launch, 0 if they do not.
+static int pair_edge(const GemmDesc& a, const GemmDesc& b) {
     bool dma_a = false, dma_b = false;
     const int va = pick_tile(a, dma_a), vb = pick_tile(b, dma_b);
-    return va == 15 && vb == 15 && dma_a && dma_b && a.precision == b.precision && !a.a_kc && !a.b_kc && !b.a_kc && !b.b_kc &&
-           pair_tiles(a) + pair_tiles(b) <= 0x7fffffff;
+    if (va != vb || !dma_a || !dma_b || a.precision != b.precision || a.a_kc || a.b_kc || b.a_kc || b.b_kc) return 0;
+    const int edge = va == 15 ? 64 : va == 14 && a.precision == 0 ? 128 : 0;
+    return edge && tiles_of(a, edge) + tiles_of(b, edge) <= 0x7fffffff ? edge : 0;
 }
 
+bool gemm_pair_merged(const GemmDesc& a, const GemmDesc& b) { return pair_edge(a, b) != 0; }
+
 hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
-    if (!gemm_pair_merged(a, b)) {
+    const int edge = pair_edge(a, b);
+    if (!edge) {
         const hipError_t e = launch_gemm(a, s);
         return e != hipSuccess ? e : launch_gemm(b, s);
     }
-    GemmPair p{{a, b}, (int)pair_tiles(a)};
-    const dim3 grid((unsigned)(pair_tiles(a) + pair_tiles(b)));
-    if (a.precision == 0) hipLaunchKernelGGL((gemm_dma_pair_kernel<float, 64, 4>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((gemm_dma_pair_kernel<bf16_t, 128, 3>), grid, dim3(256), 0, s, p);
+    const int64_t tiles = tiles_of(a, edge) + tiles_of(b, edge);
+    GemmPair p{{a, b}, (int)tiles_of(a, edge)};
+    if (a.precision == 0) {
+        if (edge == 128 || !plain_fp32(a) || !plain_fp32(b)) return launch_gemm_split_pair(p, tiles, edge == 128, s);
+        hipLaunchKernelGGL((gemm_dma_pair_kernel<float, 64, 4>), dim3((unsigned)tiles), dim3(256), 0, s, p);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((gemm_dma_pair_kernel<bf16_t, 128, 3>), dim3((unsigned)tiles), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 

@@ -127,3 +127,43 @@ def test_gemm_k_past_the_last_whole_stage(prec, tile, a_k, b_k, M, N, K):
     lda_pad = 8 if K % 8 == 0 else 4
     assert _run(prec, a_k, b_k, 0, M, N, K, 3, True, pad=lda_pad, tile=tile) < 2e-6
     assert _run(prec, a_k, b_k, 1, M, N, K, 2, False, tile=tile) < (6e-3 if prec else 2e-6)
+
+
+@pytest.mark.parametrize("tile,edge", [(14, 128), (15, 64)])
+@pytest.mark.parametrize("a_k,b_k", LAYOUTS)
+@pytest.mark.parametrize("K", [196, 224, 240, 256, 257])
+def test_gemm_fp32_on_the_bf16_matrix_units(tile, edge, a_k, b_k, K):
+    # past the sizes that stay on fp32 MFMAs: one tile more than a whole number in rows and less in columns; an odd and an even
+    # number of 16- and 32-element stages, whole ones and a last one of 1 and 4 elements.  Sums of K products rounded
+    # once each: sqrt(K) 2^-24 of the result's scale, 1e-6
+    K = K if not (a_k or b_k) else (K + 3) // 4 * 4
+    print("gemm fp32 split", tile, a_k, b_k, K, flush=True)
+    assert _run(0, a_k, b_k, 0, 2 * edge + 1, edge - 3, K, 3, True, pad=4, tile=tile) < 1e-6
+    assert _run(0, a_k, b_k, 1, edge - 4, 3 * edge, K, 2, False, tile=tile) < 1e-6
+
+
+@pytest.mark.parametrize("tile", [14, 15])
+@pytest.mark.parametrize("a_k,b_k", LAYOUTS)
+def test_gemm_fp32_of_values_that_have_no_finite_bf16_part(tile, a_k, b_k):
+    # an infinity, a NaN and the largest fp32 value among ordinary ones: what the fp32 sums give, in their rows and nowhere else
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("gemm fp32 non-finite", tile, a_k, b_k, flush=True)
+    M, N, K = 260, 136, 256
+    r = np.random.default_rng(3)
+    A, B = r.standard_normal((M, K)).astype(np.float32), r.standard_normal((N, K)).astype(np.float32)
+    B[:, :16] = 0.5                                        # (its second and third parts are 0)
+    B[:, 5] = 0.0
+    A[3, 4], A[140, 7], A[259, 9], A[200, 5] = np.inf, -np.inf, np.nan, np.float32(3.4028235e38)
+    A[201, 6] = np.float32(3.4e38)
+    dA = torch.from_numpy(np.ascontiguousarray(A if a_k else A.T)).cuda()
+    dB = torch.from_numpy(np.ascontiguousarray(B if b_k else B.T)).cuda()
+    dC = torch.empty(M, N, device="cuda")
+    Bd.adpsgd_gemm(0, a_k, b_k, 0, M, N, K, dA.data_ptr(), K if a_k else M, 0, dB.data_ptr(), K if b_k else N, 0, dC.data_ptr(), N, 0,
+                   None, 0, 1, torch.cuda.current_stream().cuda_stream, tile_config=tile)
+    got = dC.cpu().numpy()
+    assert (got[3] == np.inf).all() and (got[140] == -np.inf).all() and np.isnan(got[259]).all()
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+    rest = np.isfinite(ref).all(axis=1)
+    assert rest.sum() == M - 3 and np.isfinite(got[rest]).all()
+    assert (np.abs(got[rest] - ref[rest]) <= 2e-6 * np.abs(ref[rest]).max(axis=1, keepdims=True)).all()
