@@ -55,11 +55,17 @@ template <typename T, int S_> struct Cl {
     static constexpr int RB = 16;                          // batch rows of a cluster
     static constexpr int VW = 4 / (int)sizeof(T), RW = KP / VW;                 // values per exchange word, words per row of h
     static constexpr int FWD_ROW = KP * (int)sizeof(T) + 16, BWD_ROW = 4 * U * (int)sizeof(T) + 16;     // bytes of an LDS row
+    // PARTS: fp32 as three bf16 parts, up to 320 cells (more than 240 registers of W_h a lane, 360 at 384 cells, and the compiler moves them about:
+    // us per frame, fp32 MFMAs / parts: 256 cells 3.8 / 3.2, 320 4.3 / 3.7, 384 4.8 / 4.5 and 3 us more a launch, 512 6.2 / 6.6).  Bytes of an LDS row of a part, of the 16 rows; chunks of 32 k of a wave
+    static constexpr int FWD_PART_ROW = KP * 2 + 16, BWD_PART_ROW = 4 * U * 2 + 16, FWD_PART = RB * FWD_PART_ROW, BWD_PART = RB * BWD_PART_ROW;
+    static constexpr bool PARTS = sizeof(T) == 4 && S <= 10;
+    static constexpr int PCW = KP / (32 * KS), PBCH = 4 * U / 32;
+    static constexpr int FWD_BUF = PARTS ? 3 * FWD_PART : RB * FWD_ROW, BWD_BUF = PARTS ? 3 * BWD_PART : RB * BWD_ROW;   // one frame's operand
     static constexpr int W_ROW = KP + 4;                   // words of a row of staged W_h: rows 4 apart lie 16 banks apart
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
     static constexpr int PPT = RB * U / 256;                                    // backward: rows of its unit that a thread finishes
     static constexpr int64_t FWD_SLOT = (int64_t)RB * RW, BWD_SLOT = (int64_t)S * RB * KP;              // exchange words
-    static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 32 == 0 && PPT % 2 == 0, "tiling");
+    static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 64 == 0 && PPT % 2 == 0, "tiling");
 };
 
 // Scratch words of a workgroup that does a cluster's work alone.
@@ -179,6 +185,44 @@ template <typename T, class C> __device__ inline uint4 fwd_frag_(buf_t wh, int H
     return v;
 }
 
+// ---- fp32 products on the bf16 matrix units --------------------------------------------------------------
+// An fp32 value as the sum of three bf16 values, and six of the nine products of two such sums (gemm_split.hip): the products of
+// a frame at one wave per SIMD, 1.9 us of fp32 MFMAs at 256 cells, take 0.7.  A value without a finite first part makes
+// check infinite or NaN; where one turns up, the workgroup multiplies in fp32, W_h from memory.
+__device__ inline void parts2_(float x, float y, uint32_t (&p)[3], float& check) {
+    p[0] = pack_bf16(x, y);
+    x -= __builtin_bit_cast(float, p[0] << 16); y -= __builtin_bit_cast(float, p[0] & 0xffff0000u);
+    p[1] = pack_bf16(x, y);
+    x -= __builtin_bit_cast(float, p[1] << 16); y -= __builtin_bit_cast(float, p[1] & 0xffff0000u);
+    p[2] = pack_bf16(x, y);
+    check = fmaf(x, y, check);
+}
+__device__ inline void parts8_(const uint4& lo, const uint4& hi, uint4 (&p)[3], float& check) {
+    uint32_t w[4][3];
+    parts2_(__builtin_bit_cast(float, lo.x), __builtin_bit_cast(float, lo.y), w[0], check);
+    parts2_(__builtin_bit_cast(float, lo.z), __builtin_bit_cast(float, lo.w), w[1], check);
+    parts2_(__builtin_bit_cast(float, hi.x), __builtin_bit_cast(float, hi.y), w[2], check);
+    parts2_(__builtin_bit_cast(float, hi.z), __builtin_bit_cast(float, hi.w), w[3], check);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p[i] = make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]);
+}
+__device__ inline bool not_finite_(float check) { return !(check - check == 0.f); }
+// acc[0..N) += a b[0..N), smallest products first
+template <int N, class B> __device__ inline void mma_parts_(f32x4_t (&acc)[N], const uint4 (&a)[3], B b) {
+    constexpr int QA[6] = {0, 2, 1, 0, 1, 0}, QB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int j = 0; j < N; ++j) mma16_<bf16_t>(acc[j], a[QA[t]], b(j)[QB[t]]);
+}
+// Eight fp32 values k .. k + 7 of a row of W_h (forward): gate q of unit u.
+__device__ inline void fwd_row8_(buf_t wh, int H, int q, int u, int k0, int g, uint4& lo, uint4& hi) {
+    const int k = k0 + 8 * g;                              // H is a multiple of 4
+    const uint32_t at = (uint32_t)(u * H + 8 * g) * 4u, base = (uint32_t)(q * H * H + k0) * 4u;
+    lo = buf_load16_(wh, u < H && k < H ? at : kOutOfRange, base);
+    hi = buf_load16_(wh, u < H && k + 4 < H ? at : kOutOfRange, base + 16u);
+}
+
 // Gates from pre-activations, in place, and the new cell state; returns h.
 __device__ inline float fwd_cell_(f32x4_t (&acc)[4], int i, float& c) {
     acc[0][i] = sigmoidf_(acc[0][i]); acc[1][i] = sigmoidf_(acc[1][i]);
@@ -261,6 +305,30 @@ template <class C> __device__ inline void bias_sums_(const ClusterDesc& cd, cons
     }
 }
 
+// The products of a frame with W_h from memory, operand rows in the operand type in LDS.
+template <typename T, class C> __device__ inline void fwd_plain_(f32x4_t (&acc)[4], const char* hl, buf_t wh, int H, int u, int kh, int r, int g) {
+    const char* hrow = hl + r * C::FWD_ROW + kh * (C::CW * 64) + g * 16;
+#pragma unroll 1
+    for (int c = 0; c < C::CW; ++c) {
+        const uint4 a = *(const uint4*)(hrow + c * 64);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, fwd_frag_<T, C>(wh, H, q, u, (kh * C::CW + c) * C::KC, g));
+    }
+}
+template <typename T, class C> __device__ inline void bwd_plain_(f32x4_t (&acc)[C::NT], const char* al, buf_t wh, int H, int m, int wave, int r, int g) {
+    const char* arow = al + r * C::BWD_ROW + g * 16;
+#pragma unroll 1
+    for (int c = 0; c < C::BCH; ++c) {
+        const uint4 a = *(const uint4*)(arow + c * 64);
+        const int q = c * C::KC / C::U, k = m * C::U + c * C::KC % C::U + g * C::EL;           // a chunk lies in one gate
+#pragma unroll
+        for (int j = 0; j < C::NT; ++j) {
+            const int n = (wave + 4 * j) * 16 + r;
+            mma16_<T>(acc[j], a, bwd_frag_<T>(wh, H, q, k, n));
+        }
+    }
+}
+
 // ---- a cluster left to one workgroup --------------------------------------------------------------
 // What the members do, member after member in every frame, with the operations of the two kernels above on the same operands in
 // the same order (the results have the same bits); the fragments of W_h come from memory for every use, and what the
@@ -270,6 +338,7 @@ template <typename T, int S>
 __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, char* lds, float* red) {
     typedef Cl<T, S> C;
     constexpr int KS = C::KS, PR = 4 / KS;
+    constexpr bool PARTS = C::PARTS;
     const RecDesc& p = cd.r;
     const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
@@ -306,13 +375,30 @@ __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, cha
                 else acc[q] = kh == 0 || s == 0 ? f32x4_t{pre[q][0], pre[q][1], 0.f, 0.f} : f32x4_t{0.f, 0.f, pre[q][0], pre[q][1]};
             }
             if (s > 0) {
-                const char* hrow = hl + r * C::FWD_ROW + kh * (C::CW * 64) + g * 16;
+                bool plain = true;
+                if constexpr (PARTS) {
+                    const char* hrow = hl + r * C::FWD_ROW + kh * (C::PCW * 128) + g * 32;
+                    f32x4_t sum[4] = {acc[0], acc[1], acc[2], acc[3]};
+                    float check = 0.f;
 #pragma unroll 1
-                for (int c = 0; c < C::CW; ++c) {
-                    const uint4 a = *(const uint4*)(hrow + c * 64);
+                    for (int c = 0; c < C::PCW; ++c) {
+                        uint4 a[3], b[4][3];
+                        parts8_(*(const uint4*)(hrow + c * 128), *(const uint4*)(hrow + c * 128 + 16), a, check);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, fwd_frag_<T, C>(wh, H, q, u, (kh * C::CW + c) * C::KC, g));
+                        for (int q = 0; q < 4; ++q) {
+                            uint4 lo, hi;
+                            fwd_row8_(wh, H, q, u, (kh * C::PCW + c) * 32, g, lo, hi);
+                            parts8_(lo, hi, b[q], check);
+                        }
+                        mma_parts_<4>(sum, a, [&](int q) -> const uint4 (&)[3] { return b[q]; });
+                    }
+                    plain = __ballot(not_finite_(check)) != 0;
+                    if (!plain) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[q] = sum[q];
+                    }
                 }
+                if (plain) fwd_plain_<T, C>(acc, hl, wh, H, u, kh, r, g);
                 if constexpr (KS == 2) swap_halves_<C>(acc, red, kh, wave, lane);
             }
 #pragma unroll
@@ -397,17 +483,29 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
                 f32x4_t acc[C::NT];
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                const char* arow = lds + r * C::BWD_ROW + g * 16;
+                bool plain = true;
+                if constexpr (C::PARTS) {
+                    const char* arow = lds + r * C::BWD_ROW + g * 16;
+                    float check = 0.f;
 #pragma unroll 1
-                for (int c = 0; c < C::BCH; ++c) {
-                    const uint4 a = *(const uint4*)(arow + c * 64);
-                    const int q = c * C::KC / U, k = mm * U + c * C::KC % U + g * C::EL;       // a chunk lies in one gate
+                    for (int c = 0; c < C::PBCH; ++c) {
+                        uint4 a[3], b[C::NT][3];
+                        parts8_(*(const uint4*)(arow + c * 128), *(const uint4*)(arow + c * 128 + 64), a, check);
+                        const int k = mm * U + 4 * g;      // rows 4 g .. and 16 + 4 g .. of gate c
 #pragma unroll
-                    for (int j = 0; j < C::NT; ++j) {
-                        const int n = (wave + 4 * j) * 16 + r;
-                        mma16_<T>(acc[j], a, bwd_frag_<T>(wh, H, q, k, n));
+                        for (int j = 0; j < C::NT; ++j) {
+                            const int n = (wave + 4 * j) * 16 + r;
+                            parts8_(bwd_frag_<T>(wh, H, c, k, n), bwd_frag_<T>(wh, H, c, k + 16, n), b[j], check);
+                        }
+                        mma_parts_<C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return b[j]; });
+                    }
+                    plain = __ballot(not_finite_(check)) != 0;
+                    if (plain) {
+#pragma unroll
+                        for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
                     }
                 }
+                if (plain) bwd_plain_<T, C>(acc, lds, wh, H, mm, wave, r, g);
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) sum[j] += acc[j];
             }
@@ -441,7 +539,8 @@ template <typename T, int S>
 __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc cd) {
     typedef Cl<T, S> C;
     constexpr int KS = C::KS, PR = 4 / KS;                 // rows of a 16-row tile that a lane finishes
-    __shared__ __attribute__((aligned(16))) char lds[2 * C::RB * C::FWD_ROW];
+    constexpr bool PARTS = C::PARTS;
+    __shared__ __attribute__((aligned(16))) char lds[2 * C::FWD_BUF];
     __shared__ float red[KS == 2 ? 4 * 8 * 64 : 1];
     __shared__ int expired;
     const RecDesc& p = cd.r;
@@ -460,13 +559,25 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
     const buf_t y = make_buf_((const T*)p.y + w.li * p.sYi, (int64_t)Tn * B * DH * sizeof(T));
     const buf_t xch = make_buf_(cd.exchange + (int64_t)w.cluster * 2 * C::FWD_SLOT, 2 * C::FWD_SLOT * 8);
 
-    uint4 wf[4][C::CW];
+    constexpr int NW = PARTS ? C::PCW : C::CW;               // k-chunks of a wave
+    uint4 wf[4][NW][PARTS ? 3 : 1];
+    bool plain = false;                                    // W_h has values that the parts cannot hold
     {
         const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
+        float check = 0.f;
 #pragma unroll
-        for (int c = 0; c < C::CW; ++c)
+        for (int c = 0; c < NW; ++c)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) wf[q][c] = fwd_frag_<T, C>(wh, H, q, u, (kh * C::CW + c) * C::KC, g);
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (PARTS) {
+                    uint4 lo, hi;
+                    fwd_row8_(wh, H, q, u, (kh * NW + c) * 32, g, lo, hi);
+                    parts8_(lo, hi, wf[q][c], check);
+                } else {
+                    wf[q][c][0] = fwd_frag_<T, C>(wh, H, q, u, (kh * NW + c) * C::KC, g);
+                }
+            }
+        if constexpr (PARTS) plain = __syncthreads_or(not_finite_(check));
     }
     // rows this lane finishes: row0 + i, i < PR
     const int row0 = 4 * g + (KS == 2 ? 2 * kh : 0);
@@ -511,24 +622,49 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
             else acc[q] = kh == 0 ? f32x4_t{pre[q][0], pre[q][1], 0.f, 0.f} : f32x4_t{0.f, 0.f, pre[q][0], pre[q][1]};
         }
         if (s > 0) {
-            // h of the frame before, all units, into LDS: 16 threads to a row, words 2 (tid % 16) + 32 i and the next
-            constexpr int N = C::RW / 32;
-            char* const hl = lds + (s & 1) * (C::RB * C::FWD_ROW);
+            // h of the frame before, all units, into LDS: 32 threads to a row, words 2 (tid % 32) + 64 i and the next
+            constexpr int N = C::RW / 64;
+            char* const hl = lds + (s & 1) * C::FWD_BUF;
             const uint32_t slot = (uint32_t)(s & 1) * (uint32_t)(C::FWD_SLOT * 8);
-            uint32_t v[2 * N];
-            const bool ok = get_<N>(cd, xch, (uint32_t)((tid >> 4) * C::RW + 2 * (tid & 15)) * 8u, [&](int i) { return slot + 256u * i; }, w.tag0 + s, v);
+            uint32_t v[4 * N];
+            const bool ok = get_<2 * N>(cd, xch, (uint32_t)((tid >> 5) * C::RW + 2 * (tid & 31)) * 8u,
+                                        [&](int i) { return slot + (uint32_t)(i / N * 8 * C::RW + i % N * 64) * 8u; }, w.tag0 + s, v);
 #pragma unroll
-            for (int i = 0; i < N; ++i) *(uint2*)(hl + (tid >> 4) * C::FWD_ROW + (tid & 15) * 8 + i * 128) = make_uint2(v[2 * i], v[2 * i + 1]);
+            for (int i = 0; i < 2 * N; ++i) {
+                const int row = (tid >> 5) + i / N * 8;
+                if (!PARTS || plain) {
+                    *(uint2*)(hl + row * C::FWD_ROW + (tid & 31) * 8 + i % N * 256) = make_uint2(v[2 * i], v[2 * i + 1]);
+                } else {
+                    uint32_t h3[3];
+                    float check = 0.f;                     // (h is finite, or NaN and so are its parts)
+                    parts2_(__builtin_bit_cast(float, v[2 * i]), __builtin_bit_cast(float, v[2 * i + 1]), h3, check);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) *(uint32_t*)(hl + k * C::FWD_PART + row * C::FWD_PART_ROW + (tid & 31) * 4 + i % N * 128) = h3[k];
+                }
+            }
             if (!ok) expired = 1;
             load_pre(s + 1 < Tn ? s + 1 : s);              // (after the exchange: its loads return in order behind these)
             lds_barrier_();
             if (__builtin_amdgcn_readfirstlane(expired)) return;
-            const char* hrow = hl + r * C::FWD_ROW + kh * (C::CW * 64) + g * 16;
+            if constexpr (PARTS) {
+                if (__builtin_expect(plain, 0)) {
+                    fwd_plain_<T, C>(acc, hl, make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T)), H, u, kh, r, g);
+                } else {
+                    const char* hrow = hl + r * C::FWD_PART_ROW + kh * (NW * 64) + g * 16;
 #pragma unroll
-            for (int c = 0; c < C::CW; ++c) {
-                const uint4 a = *(const uint4*)(hrow + c * 64);
+                    for (int c = 0; c < NW; ++c) {
+                        const uint4 a[3] = {*(const uint4*)(hrow + c * 64), *(const uint4*)(hrow + c * 64 + C::FWD_PART), *(const uint4*)(hrow + c * 64 + 2 * C::FWD_PART)};
+                        mma_parts_<4>(acc, a, [&](int q) -> const uint4 (&)[3] { return wf[q][c]; });
+                    }
+                }
+            } else {
+                const char* hrow = hl + r * C::FWD_ROW + kh * (NW * 64) + g * 16;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, wf[q][c]);
+                for (int c = 0; c < NW; ++c) {
+                    const uint4 a = *(const uint4*)(hrow + c * 64);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, wf[q][c][0]);
+                }
             }
             if constexpr (KS == 2) swap_halves_<C>(acc, red, kh, wave, lane);
         } else {
@@ -578,14 +714,15 @@ template <typename T, int S>
 __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDesc cd) {
     typedef Cl<T, S> C;
     constexpr int U = C::U, PPT = C::PPT;
-    constexpr int OP_BYTES = 2 * C::RB * C::BWD_ROW, W_BYTES = 2 * 16 * C::W_ROW * 4;
+    constexpr bool PARTS = C::PARTS;
+    constexpr int OP_BYTES = 2 * C::BWD_BUF, W_BYTES = 2 * 16 * C::W_ROW * 4;
     __shared__ __attribute__((aligned(16))) char lds[OP_BYTES > W_BYTES ? OP_BYTES : W_BYTES];
     __shared__ float bred[4][256];
-    __shared__ int expired;
+    __shared__ int expired, not_finite[2];                 // not_finite: by the parity of the frame
     const RecDesc& p = cd.r;
     Place w;
     if (!place_<C>(cd, w)) return;
-    if (threadIdx.x == 0) expired = 0;
+    if (threadIdx.x == 0) { expired = 0; not_finite[0] = not_finite[1] = 0; }
     __syncthreads();
     const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
@@ -632,8 +769,12 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     // product part: columns n of W_h (tiles wave, wave + 4, ...), rows: the four gates of this workgroup's units
     // Rows of W_h come in as they lie, a k-chunk (16 words of a column's fragments deep) at a time, two chunks ahead, and the
     // fragments are read from LDS: column by column from memory they took 384 two-byte loads a lane (bf16 x 360: 60 us).
-    uint4 wf[C::NT][C::BCH];
+    constexpr int NW = PARTS ? C::PBCH : C::BCH;
+    uint4 wf[C::NT][NW][PARTS ? 3 : 1];
+    bool plain = false;                                    // W_h has values that the parts cannot hold
     {
+        uint4 half[PARTS ? C::NT : 1];                       // fp32: rows 4 g .. of a chunk of 32 k, rows 16 + 4 g .. come with the next 16
+        float check = 0.f;
         constexpr int EPW = 4 / (int)sizeof(T);            // rows of W_h to a word
         const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
         uint4 st[3][C::NT];                                // words tid + 256 j of the chunk's 16 x KP / 4 quadruples
@@ -666,9 +807,14 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             lds_barrier_();
             const uint32_t* col = buf + 4 * g * C::W_ROW + wave * 16 + r;
 #pragma unroll
-            for (int j = 0; j < C::NT; ++j)
-                wf[j][c] = make_uint4(col[64 * j], col[64 * j + C::W_ROW], col[64 * j + 2 * C::W_ROW], col[64 * j + 3 * C::W_ROW]);
+            for (int j = 0; j < C::NT; ++j) {
+                const uint4 x = make_uint4(col[64 * j], col[64 * j + C::W_ROW], col[64 * j + 2 * C::W_ROW], col[64 * j + 3 * C::W_ROW]);
+                if constexpr (!PARTS) wf[j][c][0] = x;
+                else if (c % 2 == 0) half[j] = x;
+                else parts8_(half[j], x, wf[j][c / 2], check);
+            }
         }
+        if constexpr (PARTS) plain = __syncthreads_or(not_finite_(check));
         lds_barrier_();                                    // the operand of the products goes into the same LDS
     }
     const uint32_t how = join_<C>(cd, w);
@@ -703,16 +849,33 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             }
             if (!ok) expired = 1;
         }
-        char* const al = lds + (s & 1) * (C::RB * C::BWD_ROW);
-        float a4[PPT][4];
+        char* const al = lds + (s & 1) * C::BWD_BUF;
+        float a4[PPT][4], check = 0.f;
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
             bwd_cell_(a4[i], in_dy[i] + dh[i], dcr[i], in_g[i], in_c[i], c_prev[i]);
-            T* arow = (T*)(al + (tid / U * PPT + i) * C::BWD_ROW) + uu;
+            const int row = tid / U * PPT + i;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) { bs[q] += a4[i][q]; arow[q * U] = Elem<T>::from(a4[i][q]); }
+            for (int q = 0; q < 4; ++q) {
+                bs[q] += a4[i][q];
+                if constexpr (!PARTS) *((T*)(al + row * C::BWD_ROW) + uu + q * U) = Elem<T>::from(a4[i][q]);
+            }
+            if constexpr (PARTS) {                           // 32 k of a gate: in the order in which the fragments of W_h hold them
+                bf16_t* const at = (bf16_t*)(al + row * C::BWD_PART_ROW) + 8 * (uu % 16 / 4) + 4 * (uu / 16) + uu % 4;
+#pragma unroll
+                for (int q = 0; q < 4; q += 2) {
+                    uint32_t a3[3];
+                    parts2_(a4[i][q], a4[i][q + 1], a3, check);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        at[k * (C::BWD_PART / 2) + q * U] = (bf16_t)a3[k];
+                        at[k * (C::BWD_PART / 2) + (q + 1) * U] = (bf16_t)(a3[k] >> 16);
+                    }
+                }
+            }
             in_c[i] = c_prev[i];
         }
+        if (PARTS && (plain || not_finite_(check))) not_finite[s & 1] = 1;
         if (s + 1 < Tn) {
             load_in(s + 1);
             load_c(s + 2, c_prev);
@@ -721,12 +884,30 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             f32x4_t acc[C::NT];
 #pragma unroll
             for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            const char* arow = al + r * C::BWD_ROW + g * 16;
+            if constexpr (PARTS) {
+                if (__builtin_expect(__builtin_amdgcn_readfirstlane(not_finite[s & 1]), 0)) {
 #pragma unroll
-            for (int c = 0; c < C::BCH; ++c) {
-                const uint4 a = *(const uint4*)(arow + c * 64);
+                    for (int i = 0; i < PPT; ++i)
 #pragma unroll
-                for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a, wf[j][c]);
+                        for (int q = 0; q < 4; ++q) *((float*)(al + (tid / U * PPT + i) * C::BWD_ROW) + uu + q * U) = a4[i][q];
+                    lds_barrier_();
+                    bwd_plain_<T, C>(acc, al, make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T)), H, w.m, wave, r, g);
+                } else {
+                    const char* arow = al + r * C::BWD_PART_ROW + g * 16;
+#pragma unroll
+                    for (int c = 0; c < NW; ++c) {
+                        const uint4 a[3] = {*(const uint4*)(arow + c * 64), *(const uint4*)(arow + c * 64 + C::BWD_PART), *(const uint4*)(arow + c * 64 + 2 * C::BWD_PART)};
+                        mma_parts_<C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return wf[j][c]; });
+                    }
+                }
+            } else {
+                const char* arow = al + r * C::BWD_ROW + g * 16;
+#pragma unroll
+                for (int c = 0; c < NW; ++c) {
+                    const uint4 a = *(const uint4*)(arow + c * 64);
+#pragma unroll
+                    for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a, wf[j][c][0]);
+                }
             }
             // (a tile lies in one workgroup's units: U is a multiple of 16; rows 4 g .. 4 g + 3 of a lane are those of one or two threads)
             const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;

@@ -532,3 +532,33 @@ def test_batch_beyond_the_second_dimension_of_a_grid():
         out.append(e.grads(0).cpu().numpy().view(np.uint32).copy())
         e.close()
     assert np.isfinite(out[0].view(np.float32)).all() and (out[0] == out[1]).all()
+
+
+@pytest.mark.parametrize("hidden", [132, 256, 320])
+def test_clusters_in_fp32_with_weights_that_no_bf16_parts_hold(hidden):
+    # infinite and the largest recurrent weights: gates saturate, everything else is as frame by frame.  The values that are added to
+    # an infinity have no place in the comparison of sums (1e-5, as elsewhere), so the gradients of the cells they belong to are left out
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("clusters, weights without finite parts", hidden, flush=True)
+    shape = Shape(12, hidden, 1, 1, 0, 24, 5, 8)
+    out = []
+    for persistent in (-1, 0):
+        e = _engine(shape, 2, S.FIXED_RING, 0)
+        e.tune(Bd.TUNE_REC_PERSISTENT, persistent)
+        w = synth.initial_model(0, e.P, 0.1)
+        names = {n: (o, r, c) for n, o, r, c in lstm.layout(shape)[0]}
+        o, rows, cols = [v for k, v in names.items() if v[1] == 8 * hidden and v[2] == hidden][0]
+        wh = w[o:o + rows * cols].reshape(rows, cols)
+        wh[3, :] = 0.0
+        wh[3, 7] = np.inf                                  # the input gate of cell 3, first direction
+        wh[hidden + 9, 11] = np.float32(3.4028235e38)      # the forget gate of cell 9
+        e.set_params(-1, torch.from_numpy(w).cuda())
+        e.step(_to_dev(_batches(shape, 2, 0)), 0.0)
+        e.status()
+        out.append(e.grads(0).cpu().numpy().copy())
+        e.close()
+    a, b = out
+    assert (np.isnan(a) == np.isnan(b)).mean() > 0.999
+    both = np.isfinite(a) & np.isfinite(b)
+    assert both.sum() > 0 and np.abs(a[both] - b[both]).max() <= 1e-4 * np.abs(b[both]).max()
