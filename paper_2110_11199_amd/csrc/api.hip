@@ -344,9 +344,12 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->loss = (float*)w.take(L * 4);
         RecDesc r{};
         r.precision = h->prec; r.L = h->L; r.D = h->D; r.B = h->B; r.H = h->H; r.T = h->T; r.direct = 1;
+        // for every number of learners that may take part (use_cluster asks again, with the compute units of the stream)
         int64_t words = 0;                                 // (the alignment of the tensors follows from the layout)
-        for (bool backward : {false, true})
-            if (rec_cluster_supported(r, backward, 1 << 20)) words = std::max(words, rec_cluster_exchange_words(r, backward));
+        for (r.L = 1; r.L <= h->L; ++r.L)
+            for (bool backward : {false, true})
+                if (rec_cluster_supported(r, backward, 256)) words = std::max(words, rec_cluster_exchange_words(r, backward));
+        r.L = h->L;
         h->exchange_bytes = (size_t)words * 8;
         if (words > 0) {
             h->epoch = (uint32_t*)w.take(4);

@@ -47,8 +47,8 @@ constexpr uint32_t kOutOfRange = 0x80000000u;
 __device__ inline buf_t make_buf_(const void* base_uniform, int64_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)base_uniform, 0, (int)bytes, 0x00027000);
 }
-__device__ inline float buf_load_(buf_t b, uint32_t voff, uint32_t soff) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)voff, (int)soff, 0));
+template <int POLICY = 0> __device__ inline float buf_load_(buf_t b, uint32_t voff, uint32_t soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)voff, (int)soff, POLICY));
 }
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 __device__ inline uint4 buf_load16_(buf_t b, uint32_t voff, uint32_t soff) {
@@ -63,11 +63,11 @@ __device__ inline uint2 buf_load8_(buf_t b, uint32_t voff, uint32_t soff) {
 __device__ inline uint32_t buf_load2_(buf_t b, uint32_t voff, uint32_t soff) {
     return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(b, (int)voff, (int)soff, 0);
 }
-__device__ inline void buf_store_(float v, buf_t b, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, (int)voff, (int)soff, 0);
+template <int POLICY = 0> __device__ inline void buf_store_(float v, buf_t b, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, (int)voff, (int)soff, POLICY);
 }
-__device__ inline void buf_store_(bf16_t v, buf_t b, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_buffer_store_b16(v, b, (int)voff, (int)soff, 0);
+template <int POLICY = 0> __device__ inline void buf_store_(bf16_t v, buf_t b, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_buffer_store_b16(v, b, (int)voff, (int)soff, POLICY);
 }
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }

@@ -88,6 +88,10 @@ template <int SCOPE> __device__ inline void put2_(buf_t x, uint32_t lane_bytes, 
     const u32x4_t w = {__builtin_bit_cast(uint32_t, v0), tag, __builtin_bit_cast(uint32_t, v1), tag};
     __builtin_amdgcn_raw_buffer_store_b128(w, x, (int)lane_bytes, (int)bytes, SCOPE);
 }
+// Cache policy of what a backward frame reads and writes once: the exchange words, 4 MB an XCD at 512 cells, have to stay in its L2
+// beside it (us per frame, without / with: bf16 8 x 2 x 256 cells, batch 64 4.2 / 3.4, 512, 32 6.9 / 5.8, 5 x 2 x 360, 50 4.8 / 4.3; of which the
+// loads 0.3 to 0.5).  The forward pass, which reads the lines that it writes, is the slower for it (2.7 / 3.1).
+constexpr int kPassing = 2;
 // Pairs of words at lane_bytes + off(0) .. off(N-1), once all of them carry the tag; false when the wait ran out.  (Every branch
 // is wave-uniform for the compiler too: a divergent one has it copy the resident fragments around the loop.)
 template <int N, class Off>
@@ -750,16 +754,16 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;                    // reverse of the forward order
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
-            in_dy[i] = buf_load_(dy, vy[i], m * DH * 4u);
+            in_dy[i] = buf_load_<kPassing>(dy, vy[i], m * DH * 4u);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) in_g[i][q] = buf_load_(gates, vg[i], (m * G4 + q * H) * 4u);
+            for (int q = 0; q < 4; ++q) in_g[i][q] = buf_load_<kPassing>(gates, vg[i], (m * G4 + q * H) * 4u);
         }
     };
     auto load_c = [&](int s, float (&c)[PPT]) {            // s = T: the cell state before the first frame is 0
         const bool end = s >= Tn;
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - (end ? Tn - 1 : s) : (end ? Tn - 1 : s)) * B;
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) c[i] = buf_load_(cbuf, end ? kOutOfRange : vc[i], m * H * 4u);
+        for (int i = 0; i < PPT; ++i) c[i] = buf_load_<kPassing>(cbuf, end ? kOutOfRange : vc[i], m * H * 4u);
     };
     float c_prev[PPT];
     load_c(0, in_c);
@@ -929,7 +933,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         for (int i = 0; i < PPT; ++i) {
             const uint32_t va = vg[i] == kOutOfRange ? kOutOfRange : vg[i] / (4u / (uint32_t)sizeof(T));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) buf_store_(Elem<T>::from(a4[i][q]), da, va, (m * G4 + q * H) * (uint32_t)sizeof(T));
+            for (int q = 0; q < 4; ++q) buf_store_<kPassing>(Elem<T>::from(a4[i][q]), da, va, (m * G4 + q * H) * (uint32_t)sizeof(T));
         }
     }
     bias_sums_<C>(cd, w, bred, bs, w.m);
@@ -946,10 +950,18 @@ int cluster_members(const RecDesc& d) {
 }
 int cluster_blocks(const RecDesc& d) { return (d.B + 15) / 16; }
 
+// Clusters that run at once with their members on one XCD each, and anywhere (a workgroup takes a compute unit: a SIMD's register
+// file per wave).  One XCD unless the compute units that are left of each then cost a round of the chip.
+struct Rounds { bool spread; int64_t at_once; };
+Rounds cluster_rounds(int64_t clusters, int S, int cu_count) {
+    const int64_t spread = (int64_t)(cu_count / kXcds / S) * kXcds, anywhere = cu_count / S;
+    const bool one_xcd = spread > 0 && (clusters + spread - 1) / spread <= (clusters + anywhere - 1) / anywhere;
+    return {one_xcd, one_xcd ? spread : anywhere};
+}
+
 template <typename T, int S> void launch_cluster_t(ClusterDesc& p, bool backward, int cu_count, hipStream_t s) {
-    // The members of a cluster on one XCD, unless the compute units that are left of each then cost a round of the chip.
-    const int64_t clusters = rec_cluster_count(p.r), per_xcd = cu_count / kXcds / S, anywhere = cu_count / S;
-    p.spread = per_xcd > 0 && (clusters + kXcds * per_xcd - 1) / (kXcds * per_xcd) <= (clusters + anywhere - 1) / anywhere;
+    const int64_t clusters = rec_cluster_count(p.r);
+    p.spread = cluster_rounds(clusters, S, cu_count).spread;
     const unsigned grid = (unsigned)((p.spread ? round_up(clusters, kXcds) : clusters) * S);
     if (backward) hipLaunchKernelGGL((rec_backward_cluster_kernel<T, S>), dim3(grid), dim3(256), 0, s, p);
     else hipLaunchKernelGGL((rec_forward_cluster_kernel<T, S>), dim3(grid), dim3(256), 0, s, p);
@@ -957,52 +969,52 @@ template <typename T, int S> void launch_cluster_t(ClusterDesc& p, bool backward
 
 }  // namespace
 
-// Where the clusters run, by their workgroups: a workgroup takes a compute unit (a SIMD's whole register file per wave; in fp32 up to
-// 320 cells two share one), the rest of a larger grid waits, and the frame-by-frame kernels win once they stream W_h for enough
-// rows at a time.  us per frame, frame by frame against clusters (workgroups):
-//   fp32 forward  16 x 256 cells, batch 32 (256) 11.9 / 4.5; 16 x 320, 128 (1280) 29.1 / 25.3; 32 x 256, 128 (2048) 28.1 / 29.6
-//   fp32 backward 16 x 256, 32 (256) 12.8 / 5.6; 16 x 512, 64 (1024) 47 / 41; 32 x 320, 64 (1280) 34 / 33; 32 x 256, 128 (2048) 33 / 41
-//   bf16 forward  10 x 360, 50 (240) 8.2 / 3.4; 32 x 512, 64 (1024) 21.3 / 16.1, 128 (2048) 28.5 / 31.0; 16 x 640, 64 (640) 17.3 / 13.4,
-//                 96 (960; between the other kernels of an iteration) 20.6 / 22; 16 x 256, 128 (512) 12.1 / 7.7; 32 x 256, 128 (1024) 14.3 / 15.1
-//   bf16 backward 10 x 360, 50 (240) 11.5 / 5.9; 16 x 256, 128 (512) 13.9 / 10.0; 32 x 256, 128 (1024) 17.0 / 18.6; 32 x 512, 32 (512)
-//                 18.9 / 16.4, 64 (1024) 23 / 56 (the exchange of fp32 sums); 16 x 640, 16 (160) 18.2 / 9.5, 32 (320) 20.0 / 20.8
-// bf16 hidden sizes that are 4 mod 8, which frame by frame run on the register-staged kernels, take the clusters up to 4096: 16 x 300,
-// 32 (192) 19.5 / 30.3 against 3.5 / 5.3; 16 x 508, 128 (1024) 29 / 70 against 17 / 32; 32 x 636, 128 (2560) 77 / 119 against 51 / 134.
-// More rows to a cluster (two and four tiles) shorten nothing: 32 x 512, 64: 16 -> 15 and 18; the exchange grows with the rows.
-// A launch begins with W_h (10-20 us a round of the chip), which a few frames do not earn back, and a nearly empty last round costs as
-// much as a full one: within the limits above, the estimates of both ways decide.  us for a whole pass, frame by frame / clusters:
-// bf16 forward 16 x 400, batch 23 (256 workgroups, one round): 2 frames 16 / 23, 4 31 / 30; 24 x 320, 17 (288, two): 6 45 / 52, 10 75 / 72;
-// 64 x 368, 5 (384, two) 5 114 / 62; backward 16 x 400: 5 47 / 50, 8 79 / 70; 24 x 320: 10 87 / 102, 14 121 / 137; 32 x 512, 32 (512, two): 6
-// 108 / 109, 10 185 / 174; fp32 forward 16 x 400 (512, two): 6 104 / 108, 8 141 / 135; 32 x 512, 32 (1024, four): 5 185 / 192, 8 323 / 276;
-// backward 24 x 320 (480, two): 8 117 / 123, 14 212 / 205.  The estimates pick the longer way by more than 3 us and 6 per cent for 5 of
-// the 180 such pairs measured, which lose 0.1 ms in all; clusters throughout lose 0.8, frames throughout 7.2.
+// Where the clusters run: estimates of a pass both ways decide.  A round of the chip begins with W_h and takes a frame's latencies (first,
+// frame), more the fuller the chip (full: gate and exchange traffic).  us for a pass of 20 frames, frame by frame / clusters (workgroups):
+//   fp32 forward  16 x 256 cells, batch 32 (256) 235 / 74; 32 x 256, 64 (1024) 505 / 271, 128 (2048) 548 / 533; 32 x 320, 128 (2560) 970 / 870;
+//                 16 x 384, 64 (768) 644 / 406; 24 x 512, 64 (1536) 858 / 797, 32 x 512, 64 (2048) 905 / 1065
+//   fp32 backward 16 x 256, 32 254 / 73; 32 x 256, 128 641 / 501; 32 x 384, 64 (1536) 793 / 1037; 24 x 512, 64 977 / 923
+//   bf16 forward  10 x 360, 50 (240) 166 / 61; 32 x 256, 128 (1024) 276 / 172; 32 x 512, 64 (1024) 417 / 260, 128 (2048) 562 / 513; 16 x 640, 64 (640)
+//                 340 / 226, 96 (960) 399 / 301; 32 x 640, 128 (2560) 820 / 841
+//   bf16 backward 10 x 360, 50 230 / 87; 32 x 256, 128 334 / 265; 16 x 512, 64 (512) 364 / 235; 32 x 512, 64 452 / 432, 128 713 / 837; 16 x 640, 32 (320)
+//                 400 / 256, 64 415 / 437
+// and of 5 frames: bf16 forward 32 x 512, 64 95 / 109, backward 16 x 640, 48 (480) 97 / 101; fp32 forward 32 x 512, 64 200 / 331.
+// Of 388 such pairs the estimates pick the longer way by more than 3 us and 5 per cent for 10, and lose 0.3 ms in all; clusters throughout
+// lose 4.4, frames throughout 31.  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
 namespace {
 
-bool cluster_pays(const RecDesc& d, bool backward, int cu_count) {
-    const int S = cluster_members(d);
-    const double H = d.H, mb = (double)d.L * d.D * 4.0 * H * H * (d.precision ? 2e-6 : 4e-6);          // W_h of all pairs
+double frames_time(const RecDesc& d, bool backward) {
+    const int64_t pairs = (int64_t)d.L * d.D, split_wgs = pairs * ((d.H + 31) / 32) * ((d.B + 31) / 32);
+    const double H = d.H, mb = pairs * 4.0 * H * H * (d.precision ? 2e-6 : 4e-6);          // W_h of all pairs
     // a step: latency of its contraction, W_h from the caches, more for every further 32 rows, a launch at least; the first has no
     // product.  Where the rows of W_h are not aligned the register-staged kernels take two to three times as long.
-    double step = d.precision ? (backward ? 4.0 + 0.014 * H : 4.5 + 0.0085 * H) + 0.12 * mb : 1.5 + 0.035 * H + 0.14 * mb;
-    if (!d.precision && backward && mb > 60.0) step += 0.1 * (mb - 60.0);
-    step *= 1.0 + 0.25 * ((d.B + 31) / 32 - 1);
-    if (!rec_aligned(d)) step *= backward ? 2.7 : 1.8;
-    step = std::max(step, d.precision ? 6.0 : 7.5);
-    // (backward, one row block: no launch of its own for the column sums of da)
-    const double frames = 7.0 + (d.T - 1) * step + (backward && cluster_blocks(d) == 1 ? 4.0 : 0.0);
-    // a frame of a cluster by its size: exchange, products, cells; the load of W_h and the first frame
-    double frame, first;
+    double step;
     if (d.precision) {
-        frame = !backward ? 3.2 : S == 4 ? 3.3 : S == 6 ? 5.2 : 7.0;
-        first = 2.0 + 2.1 * S;
+        step = std::max(((backward ? 4.0 + 0.014 * H : 4.5 + 0.0085 * H) + 0.12 * mb) * (1.0 + 0.25 * ((d.B + 31) / 32 - 1)), 6.0);
+    } else if (split_wgs <= 512) {                         // one round or two of the split-contraction kernels
+        step = std::max(1.5 + 0.035 * H + 0.14 * mb + (backward && mb > 60.0 ? 0.1 * (mb - 60.0) : 0.0), 7.5);
+        if (split_wgs > 256) step *= d.B > 32 ? 1.8 : 1.25;
     } else {
-        frame = backward ? (S == 8 ? 5.5 : S == 10 ? 7.0 : S == 12 ? 8.0 : 9.5) : S == 8 ? 4.4 : S == 10 ? 4.6 : S == 12 ? 6.0 : 7.0;
-        first = (backward ? 9.5 : 10.0) + 0.4 * S;
+        step = 1.5 + 0.075 * H + 0.05 * mb;
+        if (d.B > 64) step *= std::max(1.0, (double)(pairs * ((d.H + 31) / 32) * ((d.B + 127) / 128)) / 200.0);
     }
-    // two workgroups share a compute unit where their registers allow; in fp32 they then share its matrix rate too
-    const int64_t at_once = (int64_t)cu_count * (d.precision && !backward && S == 4 ? 2 : 1);
-    const double rounds = (double)((rec_cluster_count(d) * S + at_once - 1) / at_once);
-    return rounds * (first + (d.T - 1) * frame) <= frames;
+    if (!rec_aligned(d)) step *= backward ? 2.7 : 1.8;
+    // (backward, one row block: no launch of its own for the column sums of da)
+    return 7.0 + (d.T - 1) * step + (backward && cluster_blocks(d) == 1 ? 4.0 : 0.0);
+}
+
+double cluster_time(const RecDesc& d, bool backward, int cu_count) {
+    struct Fit { double first, frame, full; };
+    // 4, 6, 8, 10 members (bf16), 8, 10, 12, 16 (fp32)
+    static const Fit fit[2][2][4] = {{{{13.2, 3.05, 0.0}, {14.9, 3.6, 0.0}, {14.2, 4.54, 0.64}, {17.8, 6.34, 0.0}},
+                                      {{13.8, 2.43, 0.36}, {15.2, 2.91, 0.46}, {12.0, 3.81, 2.71}, {17.4, 5.58, 1.74}}},
+                                     {{{10.7, 1.92, 0.0}, {13.8, 2.11, 0.0}, {16.8, 2.43, 0.17}, {19.5, 2.75, 0.27}},
+                                      {{12.2, 1.86, 0.93}, {14.3, 2.31, 1.13}, {18.6, 2.33, 2.56}, {20.1, 3.3, 3.96}}}};
+    const int S = cluster_members(d), size = d.precision ? (S - 4) / 2 : S == 16 ? 3 : (S - 8) / 2;
+    const Fit& f = fit[d.precision ? 1 : 0][backward ? 1 : 0][size];
+    const int64_t clusters = rec_cluster_count(d), at_once = cluster_rounds(clusters, S, cu_count).at_once;
+    auto round = [&](int64_t n) { return f.first + (d.T - 1) * (f.frame + f.full * std::min(1.0, (double)(n * S) / 256.0)); };
+    return (double)(clusters / at_once) * round(at_once) + (clusters % at_once ? round(clusters % at_once) : 0.0);
 }
 
 }  // namespace
@@ -1012,10 +1024,8 @@ bool rec_cluster_supported(const RecDesc& d, bool backward, int cu_count) {
     if ((int64_t)d.T * d.B * d.D * d.H * 16 >= (int64_t)kOutOfRange) return false;     // buffer offsets
     const int S = cluster_members(d);
     if (S == 0 || cu_count < 4 * S) return false;
-    const int64_t workgroups = rec_cluster_count(d) * S;
-    if (!rec_aligned(d) ? workgroups > 4096                // measured up to 3200
-        : d.precision ? workgroups > (backward ? (S <= 8 ? 512 : 256) : S == 4 ? 512 : S <= 8 ? 1024 : 640) : workgroups > (backward ? 1024 : 1280)) return false;
-    return cluster_pays(d, backward, cu_count);
+    if (rec_cluster_count(d) * S > 4096) return false;     // measured up to 3200
+    return cluster_time(d, backward, cu_count) <= frames_time(d, backward);
 }
 
 int64_t rec_cluster_count(const RecDesc& d) { return (int64_t)d.L * d.D * cluster_blocks(d); }
