@@ -283,10 +283,12 @@ int adpsgd_consensus_static(const float* dev_x, int64_t stride, int32_t L, int64
  * stream at every change of phase (no host synchronisation inside the step).
  * Phases: 0 minibatch staging + bf16 weight copy, 1 time-batched GEMMs,
  * 2 recurrent forward steps, 3 recurrent backward steps, 4 softmax
- * cross-entropy, 5 bias-gradient column sums, 6 mixing + update.
+ * cross-entropy, 5 bias-gradient column sums (those that share a launch with
+ * products are in 1), 6 mixing + update.
  * adpsgd_profile waits for the stream, reports the totals over all steps since
  * profiling was switched on or last read, and starts a new total:
- * host_ms[7] GPU milliseconds, host_launches[7] kernel launches, host_work[7]
+ * host_ms[7] GPU milliseconds, host_launches[7] kernel launches (one that holds
+ * a layer's input gradient and its weight gradients counts for either), host_work[7]
  * algorithmic work (flops 2*M*N*K summed for phases 1-3; bytes, 12 per active
  * learner and element (14 when the bf16 copy of the model is written along), for
  * phase 6; 0 elsewhere), host_bytes[7] algorithmic HBM bytes of phases 1-3 and 6

@@ -401,11 +401,21 @@ int gemm(adpsgd_handle* h, const GemmDesc& d, const char* what, int k_alg = 0) {
     return ADPSGD_OK;
 }
 
-int gemm_pair(adpsgd_handle* h, GemmDesc a, GemmDesc b, const char* what) {
-    a.tile = b.tile = h->tune_gemm_tile;
-    if (int rc = mark_gemm(h, a, 1, 0)) return rc;
-    if (int rc = mark_gemm(h, b, gemm_pair_merged(a, b) ? 0 : 1, 0)) return rc;
-    HIPCHK(launch_gemm_pair(a, b, h->stream), what);
+int grad_products(adpsgd_handle* h, GradProducts& g, const char* what) {
+    g.dx.tile = g.dw[0].tile = g.dw[1].tile = h->tune_gemm_tile;
+    bool colsum_apart = false;
+    int launches = grad_product_launches(g, colsum_apart);
+    if (g.has_dx) if (int rc = mark_gemm(h, g.dx, 1, 0)) return rc;
+    for (int i = 0; i < g.ndw; ++i) { if (int rc = mark_gemm(h, g.dw[i], launches, 0)) return rc; launches = 0; }
+    if (g.has_cs && colsum_apart) {                        // (marked where it begins)
+        GradProducts products = g;
+        products.has_cs = false;
+        HIPCHK(launch_grad_products(products, h->stream), what);
+        if (int rc = mark(h, 5, 1)) return rc;
+        HIPCHK(launch_colsum(g.cs, h->stream), what);
+        return ADPSGD_OK;
+    }
+    HIPCHK(launch_grad_products(g, h->stream), what);
     return ADPSGD_OK;
 }
 
@@ -596,30 +606,31 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     HIPCHK(launch_softmax_ce(sm, s), "softmax cross-entropy");
 
     // ---- backward: output layer(s) ----
-    // dW_o = dlogits' z
+    // dW_o = dlogits' z, db_o and the losses, d(z) = dlogits W_o
+    GradProducts gp{};
+    gp.has_dx = gp.has_cs = true; gp.ndw = 1;
     g = G();
     g.a_kc = 0; g.b_kc = 0; g.c_elem = 0;
     g.M = C; g.N = F; g.K = (int)M;
     g.A = h->dlogits; g.lda = h->ldd; g.sAi = M * h->ldd;
     g.B = zin; g.ldb = ldz; g.sBi = M * ldz;
     g.C = Gr(h->ix_wo); g.ldc = F; g.sCi = Pp;
-    if (int rc = gemm(h, g, "dW_o GEMM")) return rc;
-    if (int rc = mark(h, 5, 1)) return rc;
+    gp.dw[0] = g;
     ColsumDesc cs{};
     cs.precision = prec; cs.L = n; cs.lmap = act; cs.rows = M; cs.sOi = Pp;
     cs.in = h->dlogits; cs.ld = h->ldd; cs.sIi = M * h->ldd; cs.N = C; cs.out = Gr(h->ix_bo);
     cs.loss = h->loss; cs.row_loss = h->row_loss; cs.L_all = L;
     for (int i = 0; i < 4; ++i) cs.active_bits[i] = bits[i];
-    HIPCHK(launch_colsum(cs, s), "db_o and losses");
+    gp.cs = cs;
     cs.loss = nullptr;
-    // d(z) = dlogits W_o
     g = G();
     g.a_kc = 1; g.b_kc = 0; g.c_elem = h->Bn ? 1 : 0;
     g.M = (int)M; g.N = F; g.K = C; g.k_padded = 1;
     g.A = h->dlogits; g.lda = h->ldd; g.sAi = M * h->ldd;
     g.B = W(h->ix_wo); g.ldb = F; g.sBi = Pp;
     g.C = h->Bn ? h->dz : (void*)h->dy; g.ldc = F; g.sCi = M * F;
-    if (int rc = gemm(h, g, "dz GEMM")) return rc;
+    gp.dx = g;
+    if (int rc = grad_products(h, gp, "gradients of the output layer")) return rc;
     if (h->Bn) {
         g = G();
         g.a_kc = 0; g.b_kc = 0; g.c_elem = 0;
@@ -627,17 +638,17 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         g.A = h->dz; g.lda = h->Bn; g.sAi = M * h->Bn;
         g.B = top; g.ldb = DH; g.sBi = M * DH;
         g.C = Gr(h->ix_wp); g.ldc = DH; g.sCi = Pp;
-        if (int rc = gemm(h, g, "dW_p GEMM")) return rc;
-        if (int rc = mark(h, 5, 1)) return rc;
+        gp.dw[0] = g;
         cs.in = h->dz; cs.ld = h->Bn; cs.sIi = M * h->Bn; cs.N = h->Bn; cs.out = Gr(h->ix_bp);
-        HIPCHK(launch_colsum(cs, s), "db_p");
+        gp.cs = cs;
         g = G();
         g.a_kc = 1; g.b_kc = 0; g.c_elem = 0;
         g.M = (int)M; g.N = (int)DH; g.K = h->Bn;
         g.A = h->dz; g.lda = h->Bn; g.sAi = M * h->Bn;
         g.B = W(h->ix_wp); g.ldb = DH; g.sBi = Pp;
         g.C = h->dy; g.ldc = DH; g.sCi = M * DH;
-        if (int rc = gemm(h, g, "dY GEMM")) return rc;
+        gp.dx = g;
+        if (int rc = grad_products(h, gp, "gradients of the bottleneck")) return rc;
     }
     // ---- backward through the LSTM layers ----
     for (int l = h->layers - 1; l >= 0; --l) {
@@ -684,7 +695,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         g.A = h->da; g.lda = G4; g.sAi = M * G4;
         g.B = in; g.ldb = ldin; g.sBi = M * ldin;
         g.C = Gr(h->ix_wx[l]); g.ldc = Il; g.sCi = Pp;
-        const GemmDesc gx = g;
+        gp.dw[0] = g; gp.ndw = 1;
         // dW_h[d] = da_d' h_{t'}: frames with a predecessor only (T-1 of them)
         if (T > 1) {
             g = G();
@@ -697,20 +708,17 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
             g.B = Y(l); g.ldb = DH; g.sBi = M * DH; g.sBd = (int64_t)B * DH + H;
             g.C = Gr(h->ix_wh[l]); g.ldc = H; g.sCi = Pp; g.sCd = (int64_t)4 * H * H;
             g.groupsD = D;
-            if (int rc = gemm_pair(h, gx, g, "dW_x and dW_h GEMMs")) return rc;
+            gp.dw[1] = g; gp.ndw = 2;
         } else {
-            if (int rc = gemm(h, gx, "dW_x GEMM")) return rc;
             // a single frame has no predecessor: dW_h = 0 (a fill kernel, so that the step holds no memset node)
             if (int rc = mark(h, 5, 1)) return rc;
             HIPCHK(launch_zero(Gr(h->ix_wh[l]), Pp, G4 * H, n, act, s), "zero dW_h");
         }
         // db = sum over the frames (and batch tiles) of the column sums the backward steps left behind
-        if (!db_direct) {
-            if (int rc = mark(h, 5, 1)) return rc;
-            ColsumDesc cd = cs;
-            cd.precision = 0; cd.in = h->dbp; cd.ld = G4; cd.sIi = dbrows * G4; cd.rows = dbrows; cd.N = (int)G4; cd.out = Gr(h->ix_b[l]);
-            HIPCHK(launch_colsum(cd, s), "db");
-        }
+        gp.has_cs = !db_direct;
+        gp.cs = cs;
+        gp.cs.precision = 0; gp.cs.in = h->dbp; gp.cs.ld = G4; gp.cs.sIi = dbrows * G4; gp.cs.rows = dbrows; gp.cs.N = (int)G4; gp.cs.out = Gr(h->ix_b[l]);
+        gp.has_dx = l > 0;
         if (l > 0) {
             // dY_{l-1} = da W_x  (sum over both directions: K = D*4H)
             g = G();
@@ -719,8 +727,9 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
             g.A = h->da; g.lda = G4; g.sAi = M * G4;
             g.B = W(h->ix_wx[l]); g.ldb = DH; g.sBi = Pp;
             g.C = h->dy; g.ldc = DH; g.sCi = M * DH;
-            if (int rc = gemm(h, g, "dX GEMM")) return rc;
+            gp.dx = g;
         }
+        if (int rc = grad_products(h, gp, "gradients of a layer")) return rc;
     }
     return ADPSGD_OK;
 }

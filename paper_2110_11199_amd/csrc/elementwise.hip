@@ -1,6 +1,7 @@
 // Bandwidth-bound helper kernels of the LSTM gradient: staging/casting of the
 // minibatch and of the bf16 weight copy, softmax cross-entropy with its
 // gradient, and the column sums that give the bias gradients.
+#include "colsum.hpp"
 #include "kernels.hpp"
 
 namespace adpsgd {
@@ -138,8 +139,6 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(SoftmaxDesc p) {
 
 // Single-pass version: the whole row of logits lives in registers (NV float4 per thread, C <= 4*NT*NV),
 // so the logits are read from HBM once.
-typedef float vf4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t vu2_t __attribute__((ext_vector_type(2)));
 
 template <typename T, int NV, int NT = 256>
 __global__ __launch_bounds__(NT) void softmax_ce_row_kernel(SoftmaxDesc p) {
@@ -230,86 +229,11 @@ hipError_t launch_softmax_ce(const SoftmaxDesc& d, hipStream_t s) {
     return hipGetLastError();
 }
 
-// ---- column sums -----------------------------------------------------------------
-// Workgroup = 128 columns, four to a thread, x SL row slices; a slice's sums of four rows at a time and the slices are added in a
-// fixed order (deterministic).  Bound by the read of the input once enough of it is in flight: with 64 columns x 4 slices, one
-// column to a thread, 1050 rows took 33 us at any width (bf16 5 x 1050 x 120: 33 -> 5 us, x 3000: 35 -> 9).
-// The workgroups behind the columns add the row losses of a learner, if asked for; a learner that took no part reports 0.
-template <typename T> struct Quad;
-template <> struct Quad<float> {
-    __device__ static float4 load(const float* p) {
-        const vf4_t v = __builtin_nontemporal_load((const vf4_t*)p);
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
-};
-template <> struct Quad<bf16_t> {
-    __device__ static float4 load(const bf16_t* p) {
-        const vu2_t v = __builtin_nontemporal_load((const vu2_t*)p);
-        return make_float4(__builtin_bit_cast(float, v.x << 16), __builtin_bit_cast(float, v.x & 0xffff0000u),
-                           __builtin_bit_cast(float, v.y << 16), __builtin_bit_cast(float, v.y & 0xffff0000u));
-    }
-};
-__device__ inline float4 add4_(const float4& a, const float4& b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
-
+// ---- column sums (colsum.hpp) -----------------------------------------------------
 template <typename T, int SL>
 __global__ __launch_bounds__(32 * SL) void colsum_kernel(ColsumDesc p) {
-    __shared__ float4 sh[SL][32];
-    const int tid = threadIdx.x;
-    if ((int)blockIdx.x * 128 >= p.N) {                    // row losses: blockIdx.x runs to L_all past the columns, y = 0
-        const int li = blockIdx.x - (p.N + 127) / 128;
-        if (blockIdx.y != 0) return;
-        if (!((p.active_bits[li >> 5] >> (li & 31)) & 1u)) {
-            if (tid == 0) p.loss[li] = 0.f;
-            return;
-        }
-        float s = 0.f;
-        for (int64_t r = tid; r < p.rows; r += 32 * SL) s += p.row_loss[li * p.rows + r];
-        float* f = (float*)sh;
-        f[tid] = s;
-        __syncthreads();
-        for (int off = 16 * SL; off > 0; off >>= 1) {
-            if (tid < off) f[tid] += f[tid + off];
-            __syncthreads();
-        }
-        if (tid == 0) p.loss[li] = f[0] / (float)p.rows;
-        return;
-    }
-    const int li = p.lmap.idx[blockIdx.y], tx = tid & 31, slice = tid >> 5;
-    const int col = blockIdx.x * 128 + 4 * tx;
-    const T* src = (const T*)p.in + li * p.sIi + col;
-    float4 s[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (col < p.N) {
-        int64_t r = slice;
-        for (; r + 7 * SL < p.rows; r += 8 * SL) {
-            float4 v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = Quad<T>::load(src + (r + j * SL) * p.ld);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s[j & 3] = add4_(s[j & 3], v[j]);
-        }
-        for (; r + 3 * SL < p.rows; r += 4 * SL) {
-            float4 v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = Quad<T>::load(src + (r + j * SL) * p.ld);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] = add4_(s[j], v[j]);
-        }
-        for (; r < p.rows; r += SL) s[0] = add4_(s[0], Quad<T>::load(src + r * p.ld));
-    }
-    sh[slice][tx] = add4_(add4_(s[0], s[1]), add4_(s[2], s[3]));
-    __syncthreads();
-    if (slice < 4) {                                       // a quarter of the slices each, then the quarters
-        float4 t = sh[slice * (SL / 4)][tx];
-#pragma unroll
-        for (int j = 1; j < SL / 4; ++j) t = add4_(t, sh[slice * (SL / 4) + j][tx]);
-        s[0] = t;
-    }
-    __syncthreads();
-    if (slice < 4) sh[slice][tx] = s[0];
-    __syncthreads();
-    if (slice == 0 && col < p.N) *(float4*)(p.out + li * p.sOi + col) = add4_(add4_(sh[0][tx], sh[1][tx]), add4_(sh[2][tx], sh[3][tx]));
+    __shared__ __attribute__((aligned(16))) char lds[SL * 32 * 16];
+    colsum_block<T, SL, 32>(p, blockIdx.x, blockIdx.y, lds);
 }
 
 template <typename T> static void launch_colsum_t(const ColsumDesc& d, hipStream_t s) {
@@ -318,11 +242,15 @@ template <typename T> static void launch_colsum_t(const ColsumDesc& d, hipStream
     else hipLaunchKernelGGL((colsum_kernel<T, 8>), grid, dim3(256), 0, s, d);
 }
 
-hipError_t launch_colsum(const ColsumDesc& d, hipStream_t s) {
+bool colsum_ok(const ColsumDesc& d) {
     // four columns at a time (every width and offset of the layout is a multiple of 4)
     const int quad = d.precision ? 8 : 16;
-    if (d.L < 1 || d.L > 128 || d.L_all > 128 || d.N % 4 || d.ld % 4 || d.sIi % 4 || d.sOi % 4 || (uintptr_t)d.in % quad || (uintptr_t)d.out % 16)
-        return hipErrorInvalidValue;
+    return d.L >= 1 && d.L <= 128 && d.L_all <= 128 && d.N % 4 == 0 && d.ld % 4 == 0 && d.sIi % 4 == 0 && d.sOi % 4 == 0 && (uintptr_t)d.in % quad == 0 &&
+           (uintptr_t)d.out % 16 == 0;
+}
+
+hipError_t launch_colsum(const ColsumDesc& d, hipStream_t s) {
+    if (!colsum_ok(d)) return hipErrorInvalidValue;
     if (d.precision == 0) launch_colsum_t<float>(d, s);
     else launch_colsum_t<bf16_t>(d, s);
     return hipGetLastError();

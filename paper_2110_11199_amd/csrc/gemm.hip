@@ -19,7 +19,7 @@
 //       is bound by the latency of its K loop (a 64x64 tile alone on its CU takes 5 ns per k, a 128x128 one 13)
 //       and by how evenly its tiles cover the CUs, not by operand bytes per flop.  Against the register-staged
 //       kernel 0, us: 336x256x1024x8 30.8 -> 8.4, 1050x720x2880x5 91 -> 38, 1050x120x3000x5 81 -> 18.
-//       Other fp32 problems that meet the same conditions run in tiles of these two sizes on the bf16 matrix units (gemm_split.hip).
+//       Other fp32 problems that meet the same conditions run in tiles of these two sizes on the bf16 matrix units (gemm_split.hpp).
 //   5   256x256 tile on 8 waves (128x64 each) staged through registers, the transposition done between
 //       the registers and LDS.  Large bf16 problems that miss the conditions of 11-15.
 //   0   128x128 tile, 4 waves (64x64 each), 64-byte stages, staged through registers.  Small
@@ -65,56 +65,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_kernel(GemmDesc p) {
     store_tile<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
 }
 
-// Same tile bookkeeping with the direct-to-LDS main loop (16-byte aligned operands, whole 16-byte chunks of K where an
-// operand is K-contiguous, or rows padded to them).
-template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
-__device__ __forceinline__ void dma_tile(const GemmDesc& p, int bid, int total, char* lds) {
-    typedef typename std::conditional<AKC, KcSrc<T>, McSrc<T>>::type ASrc;
-    typedef typename std::conditional<BKC, KcSrc<T>, McSrc<T>>::type BSrc;
-    typedef GemmDma<T, ASrc, BSrc, WM, WN, FM, FN, SB, NS> Core;
-
-    const int tiles_m = (p.M + Core::BM - 1) / Core::BM, tiles_n = (p.N + Core::BN - 1) / Core::BN;
-    int grp, tm, tn;
-    map_tile(bid, total, tiles_m, tiles_n, grp, tm, tn);
-    const int gi = p.lmap.idx[grp / p.groupsD], gd = grp % p.groupsD;
-    const int m0 = tm * Core::BM, n0 = tn * Core::BN;
-    const T* A = (const T*)p.A + gi * p.sAi + gd * p.sAd;
-    const T* B = (const T*)p.B + gi * p.sBi + gd * p.sBd;
-    ASrc a; BSrc b;
-    // A rows-contiguous operand is loaded in 16-byte chunks of rows: its row count is rounded up (its k-rows
-    // are ld >= that many elements long, so the extra rows are readable; their products are never stored).
-    constexpr int EPC = 16 / (int)sizeof(T);
-    if constexpr (AKC) { a.base = A + (int64_t)m0 * p.lda; a.R = p.M - m0; } else { a.base = A + m0; a.R = (p.M - m0 + EPC - 1) & ~(EPC - 1); }
-    a.ld = p.lda;
-    if constexpr (BKC) { b.base = B + (int64_t)n0 * p.ldb; b.R = p.N - n0; } else { b.base = B + n0; b.R = (p.N - n0 + EPC - 1) & ~(EPC - 1); }
-    b.ld = p.ldb;
-
-    float bias[FN];
-    load_bias<Core, FN>(bias, p, n0, gi, gd);
-    f32x16_t acc[FM][FN];
-    zero_tile<FM, FN>(acc);
-    Core::run_deep(acc, a, b, p.K, lds);
-    if (m0 + Core::BM <= p.M && n0 + Core::BN <= p.N && p.ldc < (1 << 26)) store_tile_interior<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
-    else store_tile<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
-}
-
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
 __global__ __launch_bounds__(64 * WM * WN, FM * FN <= 4 ? 3 : FM * FN == 8 ? 2 : 1) void gemm_dma_kernel(GemmDesc p) {
     typedef GemmDma<T, KcSrc<T>, KcSrc<T>, WM, WN, FM, FN, SB, NS> Core;
     __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
     dma_tile<T, AKC, BKC, WM, WN, FM, FN, SB, NS>(p, blockIdx.x, gridDim.x, lds);
-}
-
-// Two independent problems of one layout in one launch (the two weight gradients of a layer): small problems pay for a launch
-// each (4.5 us) and for a last round that leaves part of the chip idle (6 x 1280 x 320 x 1280 and x 1216: 600 tiles of 64 x
-// 64 each, three rounds of the chip and three, together five).
-template <typename T, int SB, int NS>
-__global__ __launch_bounds__(256, 3) void gemm_dma_pair_kernel(GemmPair p) {
-    typedef GemmDma<T, KcSrc<T>, KcSrc<T>, 2, 2, 1, 1, SB, NS> Core;
-    __shared__ __attribute__((aligned(1024))) char lds[Core::LDS_BYTES];
-    const int which = (int)blockIdx.x >= p.tiles0;
-    dma_tile<T, false, false, 2, 2, 1, 1, SB, NS>(p.d[which], which ? blockIdx.x - p.tiles0 : blockIdx.x,
-                                                  which ? gridDim.x - p.tiles0 : p.tiles0, lds);
 }
 
 template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int VB, int SB>
@@ -172,7 +127,7 @@ static double tile_time(const GemmDesc& d, int bm, int bn, double rate, double l
 }
 
 // The tile configuration of a problem (-1: not a valid problem), and whether its operands meet the rules of the direct loads.
-static int pick_tile(const GemmDesc& d, bool& dma) {
+int gemm_pick_tile(const GemmDesc& d, bool& dma) {
     if (d.M < 1 || d.N < 1 || d.K < 1 || d.groupsI < 1 || d.groupsI > 128 || d.groupsD < 1) return -1;
     if (d.tile != -1 && d.tile != 0 && d.tile != 5 && (d.tile < 11 || d.tile > 15)) return -1;
     // one-dimensional grid over all tiles of all groups (smallest tile 64 x 64)
@@ -190,7 +145,7 @@ static int pick_tile(const GemmDesc& d, bool& dma) {
           (d.b_kc ? d.K % epc == 0 || d.k_padded : d.ldb >= (d.N + epc - 1) / epc * epc);
     int v = d.tile;
     if (d.precision == 0) {
-        // ns per k of a tile, with others on its compute unit and alone on it (gemm_split.hip): what decides is how evenly the tiles cover
+        // ns per k of a tile, with others on its compute unit and alone on it (gemm_split.hpp): what decides is how evenly the tiles cover
         // the compute units.  us, 128x128 / 64x64: 672x2048x512x8 70 / 83, 1280x2000x320x6 58 / 71, 1000x512x672x8 42 / 44; and
         // 672x512x2048x8 98 / 85, 1280x320x1280x6 58 / 52, 2000x320x1280x6 91 / 75.
         if (v < 0) v = !dma ? 0 : tile_time(d, 64, 64, 12.8, 15.5) < tile_time(d, 128, 128, 36.0, 43.0) ? 15 : 14;
@@ -214,21 +169,17 @@ static int pick_tile(const GemmDesc& d, bool& dma) {
     return v;
 }
 
-static int64_t tiles_of(const GemmDesc& d, int edge) {
-    return (int64_t)((d.M + edge - 1) / edge) * ((d.N + edge - 1) / edge) * d.groupsI * d.groupsD;
-}
-
 // fp32 problems of one round of 64x64 tiles and a short contraction stay on fp32 MFMAs: there a launch costs the fetch of its
 // instructions, of which the split kernels have several times as many (an iteration of the 4 x 64-unit model, five such launches: 74.6 us
 // against 79.2), and a tile alone on its compute unit takes 20 ns per k here and 15.5 there.
-static bool plain_fp32(const GemmDesc& d) { return tiles_of(d, 64) <= 256 && d.K <= 192; }
+bool gemm_plain_fp32(const GemmDesc& d) { return gemm_tiles(d, 64, 64) <= 256 && d.K <= 192; }
 
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     bool dma = false;
-    const int v = pick_tile(d, dma);
+    const int v = gemm_pick_tile(d, dma);
     if (v < 0) return hipErrorInvalidValue;
     if (d.precision == 0) {
-        if (v == 15 && dma && plain_fp32(d)) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
+        if (v == 15 && dma && gemm_plain_fp32(d)) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
         if (v >= 11 && dma) return launch_gemm_split(d, v != 15, s);
         return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
     }
@@ -241,34 +192,6 @@ hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     if (v == 11 && dma) return launch_dma<bf16_t, 2, 2, 4, 4, 128, 2>(d, s);
     if (v >= 5 && v < 14) return launch_layout<bf16_t, 2, 4, 4, 2, 16, 128>(d, s);
     return launch_layout<bf16_t, 2, 2, 2, 2, 16, 64>(d, s);
-}
-
-// The edge of the tiles that both problems run on in one launch, 0 if they do not.
-static int pair_edge(const GemmDesc& a, const GemmDesc& b) {
-    bool dma_a = false, dma_b = false;
-    const int va = pick_tile(a, dma_a), vb = pick_tile(b, dma_b);
-    if (va != vb || !dma_a || !dma_b || a.precision != b.precision || a.a_kc || a.b_kc || b.a_kc || b.b_kc) return 0;
-    const int edge = va == 15 ? 64 : va == 14 && a.precision == 0 ? 128 : 0;
-    return edge && tiles_of(a, edge) + tiles_of(b, edge) <= 0x7fffffff ? edge : 0;
-}
-
-bool gemm_pair_merged(const GemmDesc& a, const GemmDesc& b) { return pair_edge(a, b) != 0; }
-
-hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s) {
-    const int edge = pair_edge(a, b);
-    if (!edge) {
-        const hipError_t e = launch_gemm(a, s);
-        return e != hipSuccess ? e : launch_gemm(b, s);
-    }
-    const int64_t tiles = tiles_of(a, edge) + tiles_of(b, edge);
-    GemmPair p{{a, b}, (int)tiles_of(a, edge)};
-    if (a.precision == 0) {
-        if (edge == 128 || !plain_fp32(a) || !plain_fp32(b)) return launch_gemm_split_pair(p, tiles, edge == 128, s);
-        hipLaunchKernelGGL((gemm_dma_pair_kernel<float, 64, 4>), dim3((unsigned)tiles), dim3(256), 0, s, p);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((gemm_dma_pair_kernel<bf16_t, 128, 3>), dim3((unsigned)tiles), dim3(256), 0, s, p);
-    return hipGetLastError();
 }
 
 }  // namespace adpsgd

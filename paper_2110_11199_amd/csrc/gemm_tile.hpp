@@ -2,6 +2,7 @@
 #pragma once
 #include <type_traits>
 #include "gemm_core.hpp"
+#include "gemm_dma.hpp"
 #include "kernels.hpp"
 
 namespace adpsgd {
@@ -160,12 +161,48 @@ template <int FM, int FN> __device__ inline void zero_tile(f32x16_t (&acc)[FM][F
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 }
 
-// Two problems in one launch: the first tiles0 workgroups work on d[0].
-struct GemmPair { GemmDesc d[2]; int tiles0; };
+// Same tile bookkeeping with the direct-to-LDS main loop (16-byte aligned operands, whole 16-byte chunks of K where an
+// operand is K-contiguous, or rows padded to them).
+template <typename T, bool AKC, bool BKC, int WM, int WN, int FM, int FN, int SB, int NS>
+__device__ __forceinline__ void dma_tile(const GemmDesc& p, int bid, int total, char* lds) {
+    typedef typename std::conditional<AKC, KcSrc<T>, McSrc<T>>::type ASrc;
+    typedef typename std::conditional<BKC, KcSrc<T>, McSrc<T>>::type BSrc;
+    typedef GemmDma<T, ASrc, BSrc, WM, WN, FM, FN, SB, NS> Core;
 
-// fp32 operands on the bf16 matrix units (gemm_split.hip), in 128x128 (large) or 64x64 tiles; operands as for the direct-to-LDS
-// kernels.  The pair: both operands of both problems rows-contiguous.
+    const int tiles_m = (p.M + Core::BM - 1) / Core::BM, tiles_n = (p.N + Core::BN - 1) / Core::BN;
+    int grp, tm, tn;
+    map_tile(bid, total, tiles_m, tiles_n, grp, tm, tn);
+    const int gi = p.lmap.idx[grp / p.groupsD], gd = grp % p.groupsD;
+    const int m0 = tm * Core::BM, n0 = tn * Core::BN;
+    const T* A = (const T*)p.A + gi * p.sAi + gd * p.sAd;
+    const T* B = (const T*)p.B + gi * p.sBi + gd * p.sBd;
+    ASrc a; BSrc b;
+    // A rows-contiguous operand is loaded in 16-byte chunks of rows: its row count is rounded up (its k-rows
+    // are ld >= that many elements long, so the extra rows are readable; their products are never stored).
+    constexpr int EPC = 16 / (int)sizeof(T);
+    if constexpr (AKC) { a.base = A + (int64_t)m0 * p.lda; a.R = p.M - m0; } else { a.base = A + m0; a.R = (p.M - m0 + EPC - 1) & ~(EPC - 1); }
+    a.ld = p.lda;
+    if constexpr (BKC) { b.base = B + (int64_t)n0 * p.ldb; b.R = p.N - n0; } else { b.base = B + n0; b.R = (p.N - n0 + EPC - 1) & ~(EPC - 1); }
+    b.ld = p.ldb;
+
+    float bias[FN];
+    load_bias<Core, FN>(bias, p, n0, gi, gd);
+    f32x16_t acc[FM][FN];
+    zero_tile<FM, FN>(acc);
+    Core::run_deep(acc, a, b, p.K, lds);
+    if (m0 + Core::BM <= p.M && n0 + Core::BN <= p.N && p.ldc < (1 << 26)) store_tile_interior<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
+    else store_tile<T, Core, FM, FN>(acc, bias, p, m0, n0, gi, gd);
+}
+
+// The tile configuration of a problem (see gemm.hip; -1: not a valid problem), whether its operands meet the rules of the direct
+// loads, and whether an fp32 problem in 64x64 tiles runs on fp32 MFMAs.
+int gemm_pick_tile(const GemmDesc& d, bool& dma);
+bool gemm_plain_fp32(const GemmDesc& d);
+inline int64_t gemm_tiles(const GemmDesc& d, int bm, int bn) {
+    return (int64_t)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.groupsI * d.groupsD;
+}
+
+// fp32 operands on the bf16 matrix units (gemm_split.hpp), in 128x128 (large) or 64x64 tiles; operands as for the direct-to-LDS kernels.
 hipError_t launch_gemm_split(const GemmDesc& d, bool large, hipStream_t s);
-hipError_t launch_gemm_split_pair(const GemmPair& p, int64_t tiles, bool large, hipStream_t s);
 
 }  // namespace adpsgd

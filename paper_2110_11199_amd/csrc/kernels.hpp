@@ -32,10 +32,6 @@ struct GemmDesc {
 // Returns hipSuccess, or hipErrorInvalidValue when the operands do not meet the
 // alignment rules (rows and strides multiples of 4 elements).
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s);
-// Two independent problems, in one launch where both are small ones of the same layout (gemm_pair_merged).
-bool gemm_pair_merged(const GemmDesc& a, const GemmDesc& b);
-hipError_t launch_gemm_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t s);
-
 // ---- fused mixing + SGD update ------------------------------------------------
 struct UpdateDesc {
     int L;
@@ -209,6 +205,19 @@ struct ColsumDesc {
     float* loss; const float* row_loss; int L_all; uint32_t active_bits[4];
 };
 hipError_t launch_colsum(const ColsumDesc& d, hipStream_t s);
+bool colsum_ok(const ColsumDesc& d);
+
+// What follows from one gradient matrix dA: dX = dA W, weight gradients dW = dA' X, column sums.  They are independent, and share a
+// launch as far as their tiles allow (gemm_multi.hip).
+struct GradProducts {
+    bool has_dx, has_cs;
+    GemmDesc dx;                         // a_kc = 1, b_kc = 0
+    int ndw; GemmDesc dw[2];             // a_kc = b_kc = 0
+    ColsumDesc cs;
+};
+// Launches that the weight gradients take part in (dX has one of its own or shares theirs), and whether the column sums are apart.
+int grad_product_launches(const GradProducts& g, bool& colsum_apart);
+hipError_t launch_grad_products(const GradProducts& g, hipStream_t s);
 // dst[z][0..n) = 0 for z = lmap.idx[0..L)  (a fill kernel, not a memset node: safe under stream capture)
 hipError_t launch_zero(float* dst, int64_t sDi, int64_t n, int L, const LearnerMap& lmap, hipStream_t s);
 

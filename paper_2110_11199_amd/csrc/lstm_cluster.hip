@@ -190,7 +190,7 @@ template <typename T, class C> __device__ inline uint4 fwd_frag_(buf_t wh, int H
 }
 
 // ---- fp32 products on the bf16 matrix units --------------------------------------------------------------
-// An fp32 value as the sum of three bf16 values, and six of the nine products of two such sums (gemm_split.hip): the products of
+// An fp32 value as the sum of three bf16 values, and six of the nine products of two such sums (gemm_split.hpp): the products of
 // a frame at one wave per SIMD, 1.9 us of fp32 MFMAs at 256 cells, take 0.7.  A value without a finite first part makes
 // check infinite or NaN; where one turns up, the workgroup multiplies in fp32, W_h from memory.
 __device__ inline void parts2_(float x, float y, uint32_t (&p)[3], float& check) {
