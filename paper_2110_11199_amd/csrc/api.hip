@@ -153,7 +153,8 @@ struct adpsgd_handle {
     // recurrences over clusters of workgroups: iteration counter, [layers][2 passes] words per cluster, exchange words
     uint32_t* epoch = nullptr;
     uint64_t* join = nullptr; int64_t joins = 0;               // joins: words of one launch
-    uint64_t* exchange = nullptr; size_t exchange_bytes = 0;
+    uint64_t* exchange = nullptr; size_t exchange_bytes = 0;   // with the raw words behind them
+    uint32_t* raw = nullptr; size_t raw_bytes = 0;
 };
 
 // A recorded sequence of iterations of one handle (adpsgd_capture_end), replayed by adpsgd_graph_replay.
@@ -204,7 +205,8 @@ bool use_persistent(const adpsgd_handle* h) {
 // Whether the recurrences of `n` learners run on clusters of workgroups, W_h on their registers.
 bool use_cluster(const adpsgd_handle* h, const RecDesc& r, bool backward) {
     return h->tune_rec_persist != 0 && h->exchange_bytes > 0 && rec_cluster_supported(r, backward, h->cu_count) &&
-           (size_t)rec_cluster_exchange_words(r, backward) * 8 <= h->exchange_bytes;
+           (size_t)rec_cluster_exchange_words(r, backward) * 8 <= h->exchange_bytes &&
+           (!backward || (size_t)rec_cluster_raw_words(r) * 4 <= h->raw_bytes);
 }
 
 // Turns the status bits that kernels have raised into an error.
@@ -345,17 +347,23 @@ size_t plan(adpsgd_handle* h, void* base) {
         RecDesc r{};
         r.precision = h->prec; r.L = h->L; r.D = h->D; r.B = h->B; r.H = h->H; r.T = h->T; r.direct = 1;
         // for every number of learners that may take part (use_cluster asks again, with the compute units of the stream)
-        int64_t words = 0;                                 // (the alignment of the tensors follows from the layout)
+        int64_t words = 0, raw = 0;                        // (the alignment of the tensors follows from the layout)
         for (r.L = 1; r.L <= h->L; ++r.L)
-            for (bool backward : {false, true})
-                if (rec_cluster_supported(r, backward, 256)) words = std::max(words, rec_cluster_exchange_words(r, backward));
+            for (bool backward : {false, true}) {
+                if (!rec_cluster_supported(r, backward, 256)) continue;
+                words = std::max(words, rec_cluster_exchange_words(r, backward));
+                if (backward) raw = std::max(raw, rec_cluster_raw_words(r));
+            }
         r.L = h->L;
         h->exchange_bytes = (size_t)words * 8;
         if (words > 0) {
             h->epoch = (uint32_t*)w.take(4);
             h->joins = rec_cluster_count(r);
             h->join = (uint64_t*)w.take((size_t)h->joins * h->layers * 2 * 8);
-            h->exchange = (uint64_t*)w.take(h->exchange_bytes);
+            h->raw_bytes = (size_t)raw * 4;
+            h->exchange_bytes = (size_t)round_up((int64_t)h->exchange_bytes, 256);
+            h->exchange = (uint64_t*)w.take(h->exchange_bytes + h->raw_bytes);
+            h->raw = (uint32_t*)((char*)h->exchange + h->exchange_bytes);
         }
     }
     return w.used;
@@ -511,7 +519,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         ClusterDesc c;
         c.r = r;
         c.launches = 2 * h->layers; c.launch = 2 * l + (backward ? 1 : 0);
-        c.exchange = h->exchange; c.join = h->join + h->joins * c.launch; c.epoch = h->epoch; c.status = h->status;
+        c.exchange = h->exchange; c.raw = h->raw; c.join = h->join + h->joins * c.launch; c.epoch = h->epoch; c.status = h->status;
         c.wait_ticks = (unsigned long long)h->tune_wait_us * 100ull;
         // by default several times what one workgroup takes for the cluster (0.02 to 0.3 ms a frame), and far more than the clusters before it in
         // the same launch take (up to 0.02)
@@ -790,7 +798,7 @@ static int create_impl(const adpsgd_config* cfg, void* dev_workspace, size_t byt
     if (e == hipSuccess && h->tau == 1) e = hipMemsetAsync(h->params[1], 0, slab, s);
     if (e == hipSuccess && !h->flat) e = hipMemsetAsync(h->grads, 0, slab, s);
     if (e == hipSuccess && h->epoch) e = hipMemsetAsync(h->epoch, 0, 4, s);
-    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes, s);   // no word carries a tag in use
+    if (e == hipSuccess && h->exchange) e = hipMemsetAsync(h->exchange, 0, h->exchange_bytes + h->raw_bytes, s);   // no word carries a tag in use
     if (e != hipSuccess) { (void)hipHostFree(mirror); delete h; return hipfail(e, "clear models"); }
     if (cfg->init_scale > 0.f) {
         // same w_0 on every learner (Algorithm 1, input)

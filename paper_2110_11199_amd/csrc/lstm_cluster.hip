@@ -26,6 +26,12 @@
 // all-to-all of 256 threads x N words between 8 workgroups, us: N = 1 0.64 through memory, 0.36 in one L2; 8 1.36, 0.63 (0.54 with
 // 16-byte loads); 12 1.68, 0.77 (0.71); 24 2.31, 1.35 (0.97).  Workgroup ids go round the 8 XCDs, so the members of a
 // cluster take ids 8 apart; what decides is not that, but the XCD each of them reads from its hardware register.
+// The backward pass of bf16 models exchanges the most for its size, H words of 64 bits a row written and read by every member: 5 MB an XCD
+// in two slots at 640 cells, more than its L2 holds.  On one XCD it writes bare values instead, waits until they are there (the
+// L2 acknowledges a store) and then writes a flag to each member, tagged as above; whoever finds the flags loads the values: half the
+// bytes for one more latency.  us per frame, tagged words / flags: 4 x 512 cells, batch 16 3.6 / 3.1, 16 x 512, 32 6.1 / 4.0, 32 x 512, 64 22.0 / 15.3,
+// 10 x 360, 50 4.8 / 3.2, 10 x 640, 32 7.7 / 4.8, 16 x 256, 64 3.8 / 3.1.  (Values and tagged words have memory of their own: a value could
+// pass for a tag.)
 //
 // Progress.  Every workgroup counts itself into its cluster's word when it STARTS, by XCD, and exchanges nothing before
 // all members have: from there on every member runs, whatever else shares the device and in whatever order workgroups are
@@ -65,6 +71,9 @@ template <typename T, int S_> struct Cl {
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
     static constexpr int PPT = RB * U / 256;                                    // backward: rows of its unit that a thread finishes
     static constexpr int64_t FWD_SLOT = (int64_t)RB * RW, BWD_SLOT = (int64_t)S * RB * KP;              // exchange words
+    // FLAGGED: backward on one XCD, values without tags behind flags: 32-bit words of a slot, values and then a flag per (target, sender, wave)
+    static constexpr bool FLAGGED = sizeof(T) == 2;
+    static constexpr int64_t RAW_VALUES = BWD_SLOT, RAW_SLOT = RAW_VALUES + (int64_t)S * 4 * S;
     static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 64 == 0 && PPT % 2 == 0, "tiling");
 };
 
@@ -88,10 +97,26 @@ template <int SCOPE> __device__ inline void put2_(buf_t x, uint32_t lane_bytes, 
     const u32x4_t w = {__builtin_bit_cast(uint32_t, v0), tag, __builtin_bit_cast(uint32_t, v1), tag};
     __builtin_amdgcn_raw_buffer_store_b128(w, x, (int)lane_bytes, (int)bytes, SCOPE);
 }
-// Cache policy of what a backward frame reads and writes once: the exchange words, 4 MB an XCD at 512 cells, have to stay in its L2
-// beside it (us per frame, without / with: bf16 8 x 2 x 256 cells, batch 64 4.2 / 3.4, 512, 32 6.9 / 5.8, 5 x 2 x 360, 50 4.8 / 4.3; of which the
+// Cache policy of what a backward frame reads and writes once: the exchange has to stay in the L2
+// beside it (us per frame, without / with, all words tagged: bf16 8 x 2 x 256 cells, batch 64 4.2 / 3.4, 512, 32 6.9 / 5.8, 5 x 2 x 360, 50 4.8 / 4.3; of which the
 // loads 0.3 to 0.5).  The forward pass, which reads the lines that it writes, is the slower for it (2.7 / 3.1).
 constexpr int kPassing = 2;
+// Whether a wait that has looked tries + 1 times may look again.
+__device__ inline bool go_on_(const ClusterDesc& p, uint32_t tries, uint64_t& t0, bool& half) {
+    if ((tries & 15) != 15 && p.wait_ticks != 0) return true;
+    const uint64_t now = wall_clock64();
+    if (t0 == 0) t0 = now;
+    const uint32_t st = __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const bool late = now - t0 >= p.wait_ticks / 2;
+    if ((late && half) || p.wait_ticks == 0 || (st & kStatusWaitExpired)) {
+        raise_status_(p.status, kStatusWaitExpired);
+        return false;
+    }
+    // the bound runs out in two halves: time in which this wave and those it waits for were off the device counts
+    // as one of them at most
+    if (late) { half = true; t0 = now; }
+    return true;
+}
 // Pairs of words at lane_bytes + off(0) .. off(N-1), once all of them carry the tag; false when the wait ran out.  (Every branch
 // is wave-uniform for the compiler too: a divergent one has it copy the resident fragments around the loop.)
 template <int N, class Off>
@@ -109,19 +134,20 @@ __device__ inline bool get_(const ClusterDesc& p, buf_t x, uint32_t lane_bytes, 
         for (int i = 0; i < N; ++i) { differ |= (w[i].y ^ tag) | (w[i].w ^ tag); v[2 * i] = w[i].x; v[2 * i + 1] = w[i].z; }
         // (a bound of 0 gives up at the first exchange, whether the words are there or not)
         if (__ballot(differ != 0) == 0 && p.wait_ticks != 0) return true;
-        if ((tries & 15) == 15 || p.wait_ticks == 0) {
-            const uint64_t now = wall_clock64();
-            if (t0 == 0) t0 = now;
-            const uint32_t st = __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            const bool late = now - t0 >= p.wait_ticks / 2;
-            if ((late && half) || p.wait_ticks == 0 || (st & kStatusWaitExpired)) {
-                raise_status_(p.status, kStatusWaitExpired);
-                return false;
-            }
-            // the bound runs out in two halves: time in which this wave and those it waits for were off the device counts
-            // as one of them at most
-            if (late) { half = true; t0 = now; }
-        }
+        if (!go_on_(p, tries, t0, half)) return false;
+    }
+}
+
+// Waits until the n words at lane_bytes = 4 lane carry the tag; false when the wait ran out.
+__device__ inline bool wait_flags_(const ClusterDesc& p, buf_t x, uint32_t bytes, int n, int lane, uint32_t tag) {
+    uint64_t t0 = 0;
+    bool half = false;
+#pragma unroll 1
+    for (uint32_t tries = 0;; ++tries) {
+        asm volatile("" ::: "memory");
+        const uint32_t v = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(x, lane * 4, (int)bytes, kFromL2);
+        if (__ballot(lane < n && v != tag) == 0 && p.wait_ticks != 0) return true;
+        if (!go_on_(p, tries, t0, half)) return false;
     }
 }
 
@@ -736,6 +762,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     const buf_t dy = make_buf_(p.dy + w.li * p.sDYi, (int64_t)Tn * B * DH * 4);
     const buf_t da = make_buf_((const T*)p.da + w.li * p.sDAi, (int64_t)Tn * B * G4 * sizeof(T));
     const buf_t xch = make_buf_(cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT, 2 * C::BWD_SLOT * 8);
+    const buf_t raw = make_buf_(C::FLAGGED ? cd.raw + (int64_t)w.cluster * 2 * C::RAW_SLOT : nullptr, C::FLAGGED ? 2 * C::RAW_SLOT * 4 : 0);
 
     // cell part: this thread's unit and rows
     const int uu = tid % U, cu = w.m * U + uu;
@@ -837,19 +864,32 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
         for (int i = 0; i < PPT; ++i) dh[i] = 0.f;
         if (s > 0) {
-            // partial sums for this workgroup's units: words [member][pair of rows of a thread][thread][row]
-            const uint32_t slot = (uint32_t)((s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U) * 8u;
-            constexpr int PB = PPT * S <= 32 ? PPT : 2;          // rows gathered together
-            static_assert(PPT % PB == 0, "gather blocks");
             bool ok = true;
+            if (C::FLAGGED && how == kOneXcd) {            // values [member][thread][row]
+                const uint32_t slot = (uint32_t)(s & 1) * (uint32_t)(C::RAW_SLOT * 4);
+                ok = wait_flags_(cd, raw, slot + (uint32_t)(C::RAW_VALUES + w.m * 4 * S) * 4u, 4 * S, lane, w.tag0 + s);
+                asm volatile("" ::: "memory");             // (the values are loaded after the flags)
+                u32x4_t v[S];
 #pragma unroll
-            for (int i0 = 0; i0 < PPT; i0 += PB) {
-                uint32_t v[PB * S];
-                ok &= get_<PB * S / 2>(cd, xch, (uint32_t)tid * 16u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U + (i0 / 2 + j / S) * 512) * 8u; }, w.tag0 + s, v);
+                for (int j = 0; j < S; ++j) v[j] = __builtin_amdgcn_raw_buffer_load_b128(raw, tid * 16, (int)(slot + (uint32_t)((w.m * S + j) * C::RB * U) * 4u), kFromL2);
 #pragma unroll
-                for (int i = 0; i < PB; ++i)
+                for (int j = 0; j < S; ++j)
 #pragma unroll
-                    for (int j = 0; j < S; ++j) dh[i0 + i] += __builtin_bit_cast(float, v[2 * (i / 2 * S + j) + i % 2]);
+                    for (int i = 0; i < PPT; ++i) dh[i] += __builtin_bit_cast(float, (uint32_t)v[j][i]);
+            } else {
+                // partial sums for this workgroup's units: words [member][pair of rows of a thread][thread][row]
+                const uint32_t slot = (uint32_t)((s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U) * 8u;
+                constexpr int PB = PPT * S <= 32 ? PPT : 2;          // rows gathered together
+                static_assert(PPT % PB == 0, "gather blocks");
+#pragma unroll
+                for (int i0 = 0; i0 < PPT; i0 += PB) {
+                    uint32_t v[PB * S];
+                    ok &= get_<PB * S / 2>(cd, xch, (uint32_t)tid * 16u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U + (i0 / 2 + j / S) * 512) * 8u; }, w.tag0 + s, v);
+#pragma unroll
+                    for (int i = 0; i < PB; ++i)
+#pragma unroll
+                        for (int j = 0; j < S; ++j) dh[i0 + i] += __builtin_bit_cast(float, v[2 * (i / 2 * S + j) + i % 2]);
+                }
             }
             if (!ok) expired = 1;
         }
@@ -926,8 +966,26 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
                     put2_<decltype(scope)::value>(xch, out_lane, to + next, acc[j][2], acc[j][3], w.tag0 + s + 1);
                 }
             };
-            if (how == kOneXcd) send(std::integral_constant<int, kToL2>{});
-            else send(std::integral_constant<int, kToMemory>{});
+            if constexpr (C::FLAGGED) {
+                if (how == kOneXcd) {
+                    // the four rows of a lane are those of one thread: 16 bytes; they are in the L2 when the wait ends
+                    const uint32_t to_slot = (uint32_t)((s + 1) & 1) * (uint32_t)(C::RAW_SLOT * 4);
+#pragma unroll
+                    for (int j = 0; j < C::NT; ++j) {
+                        const int n0 = (wave + 4 * j) * 16;
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[j]), raw, (g * U + r) * 16,
+                                                               (int)(to_slot + (uint32_t)(((n0 / U) * S + w.m) * C::RB * U + n0 % U * 4) * 4u), kToL2);
+                    }
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_raw_buffer_store_b32(w.tag0 + s + 1, raw, lane < S ? (lane * 4 * S + w.m * 4 + wave) * 4 : (int)kOutOfRange,
+                                                          (int)(to_slot + (uint32_t)C::RAW_VALUES * 4u), kToL2);
+                } else {
+                    send(std::integral_constant<int, kToMemory>{});
+                }
+            } else {
+                if (how == kOneXcd) send(std::integral_constant<int, kToL2>{});
+                else send(std::integral_constant<int, kToMemory>{});
+            }
         }
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
@@ -976,11 +1034,11 @@ template <typename T, int S> void launch_cluster_t(ClusterDesc& p, bool backward
 //   fp32 backward 16 x 256, 32 254 / 73; 32 x 256, 128 641 / 501; 32 x 384, 64 (1536) 793 / 1037; 24 x 512, 64 977 / 923
 //   bf16 forward  10 x 360, 50 (240) 166 / 61; 32 x 256, 128 (1024) 276 / 172; 32 x 512, 64 (1024) 417 / 260, 128 (2048) 562 / 513; 16 x 640, 64 (640)
 //                 340 / 226, 96 (960) 399 / 301; 32 x 640, 128 (2560) 820 / 841
-//   bf16 backward 10 x 360, 50 230 / 87; 32 x 256, 128 334 / 265; 16 x 512, 64 (512) 364 / 235; 32 x 512, 64 452 / 432, 128 713 / 837; 16 x 640, 32 (320)
-//                 400 / 256, 64 415 / 437
-// and of 5 frames: bf16 forward 32 x 512, 64 95 / 109, backward 16 x 640, 48 (480) 97 / 101; fp32 forward 32 x 512, 64 200 / 331.
-// Of 388 such pairs the estimates pick the longer way by more than 3 us and 5 per cent for 10, and lose 0.3 ms in all; clusters throughout
-// lose 4.4, frames throughout 31.  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
+//   bf16 backward 10 x 360, 50 230 / 64; 16 x 512, 64 (512) 364 / 157; 32 x 512, 64 453 / 297, 128 726 / 575; 16 x 640, 32 (320)
+//                 402 / 169, 96 (960) 453 / 381; 32 x 640, 128 1017 / 1027
+// and of 5 frames: bf16 forward 32 x 512, 64 94 / 107, backward 121 / 103; fp32 forward 32 x 512, 64 200 / 331.
+// Of 388 such pairs the estimates pick the longer way by more than 3 us and 5 per cent for 5, and lose 0.2 ms in all; clusters throughout
+// lose 2.8, frames throughout 34.  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
 namespace {
 
 double frames_time(const RecDesc& d, bool backward) {
@@ -1008,8 +1066,8 @@ double cluster_time(const RecDesc& d, bool backward, int cu_count) {
     // 4, 6, 8, 10 members (bf16), 8, 10, 12, 16 (fp32)
     static const Fit fit[2][2][4] = {{{{13.2, 3.05, 0.0}, {14.9, 3.6, 0.0}, {14.2, 4.54, 0.64}, {17.8, 6.34, 0.0}},
                                       {{13.8, 2.43, 0.36}, {15.2, 2.91, 0.46}, {12.0, 3.81, 2.71}, {17.4, 5.58, 1.74}}},
-                                     {{{10.7, 1.92, 0.0}, {13.8, 2.11, 0.0}, {16.8, 2.43, 0.17}, {19.5, 2.75, 0.27}},
-                                      {{12.2, 1.86, 0.93}, {14.3, 2.31, 1.13}, {18.6, 2.33, 2.56}, {20.1, 3.3, 3.96}}}};
+                                     {{{10.4, 1.93, 0.0}, {13.7, 2.08, 0.02}, {16.8, 2.44, 0.2}, {19.2, 2.8, 0.24}},
+                                      {{11.7, 1.95, 0.39}, {13.9, 2.17, 0.26}, {18.0, 2.2, 0.86}, {20.4, 2.6, 1.44}}}};
     const int S = cluster_members(d), size = d.precision ? (S - 4) / 2 : S == 16 ? 3 : (S - 8) / 2;
     const Fit& f = fit[d.precision ? 1 : 0][backward ? 1 : 0][size];
     const int64_t clusters = rec_cluster_count(d), at_once = cluster_rounds(clusters, S, cu_count).at_once;
@@ -1036,9 +1094,14 @@ int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward) {
     return rec_cluster_count(d) * 2 * 16 * row;
 }
 
+int64_t rec_cluster_raw_words(const RecDesc& d) {
+    const int64_t S = cluster_members(d);
+    return d.precision ? rec_cluster_count(d) * 2 * (16 * S * S * 64 + 4 * S * S) : 0;
+}
+
 hipError_t launch_rec_cluster(const ClusterDesc& desc, bool backward, int cu_count, hipStream_t s) {
     ClusterDesc p = desc;
-    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || !p.join || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
+    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || (backward && p.r.precision && !p.raw) || !p.join || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
     const int S = cluster_members(p.r);
     if (p.r.precision) {
         switch (S) {
