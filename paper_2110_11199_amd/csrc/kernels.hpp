@@ -145,7 +145,7 @@ __device__ inline void raise_status_(uint32_t* status, uint32_t bit) {
 struct ClusterDesc {
     RecDesc r;
     uint64_t* exchange;                  // rec_cluster_exchange_words(r, backward) words, zero before the handle's first launch
-    uint32_t* raw;                       // backward, bf16: rec_cluster_raw_words(r) words, zero before the handle's first launch
+    uint32_t* raw;                       // backward: rec_cluster_raw_words(r) words, zero before the handle's first launch
     const uint32_t* epoch;               // differs from iteration to iteration, 0 in none
     int launch, launches;                // this launch among those of an iteration
     uint64_t* join;                      // rec_cluster_count(r) words, zero before the launch

@@ -71,8 +71,7 @@ template <typename T, int S_> struct Cl {
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
     static constexpr int PPT = RB * U / 256;                                    // backward: rows of its unit that a thread finishes
     static constexpr int64_t FWD_SLOT = (int64_t)RB * RW, BWD_SLOT = (int64_t)S * RB * KP;              // exchange words
-    // FLAGGED: backward on one XCD, values without tags behind flags: 32-bit words of a slot, values and then a flag per (target, sender, wave)
-    static constexpr bool FLAGGED = sizeof(T) == 2;
+    // backward on one XCD: values without tags, and flags: 32-bit words of a slot, values and then a flag per (target, sender, wave)
     static constexpr int64_t RAW_VALUES = BWD_SLOT, RAW_SLOT = RAW_VALUES + (int64_t)S * 4 * S;
     static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 64 == 0 && PPT % 2 == 0, "tiling");
 };
@@ -150,6 +149,26 @@ __device__ inline bool wait_flags_(const ClusterDesc& p, buf_t x, uint32_t bytes
         if (!go_on_(p, tries, t0, half)) return false;
     }
 }
+
+// Values of the rows of one unit that a thread finishes, and the four rows 4 g .. of column r of an accumulator: those of one thread
+// or of two.
+template <int PPT> struct Rows;
+template <> struct Rows<4> {
+    typedef u32x4_t type;
+    __device__ static type load(buf_t x, int tid, uint32_t bytes) { return __builtin_amdgcn_raw_buffer_load_b128(x, tid * 16, (int)bytes, kFromL2); }
+    template <int U> __device__ static void store(const f32x4_t& a, buf_t x, int g, int r, uint32_t bytes) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, a), x, (g * U + r) * 16, (int)bytes, kToL2);
+    }
+};
+template <> struct Rows<2> {
+    typedef u32x2_t type;
+    __device__ static type load(buf_t x, int tid, uint32_t bytes) { return __builtin_amdgcn_raw_buffer_load_b64(x, tid * 8, (int)bytes, kFromL2); }
+    template <int U> __device__ static void store(const f32x4_t& a, buf_t x, int g, int r, uint32_t bytes) {
+        const u32x4_t v = __builtin_bit_cast(u32x4_t, a);
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v.x, v.y}, x, (2 * g * U + r) * 8, (int)bytes, kToL2);
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v.z, v.w}, x, (2 * g * U + r) * 8, (int)(bytes + (uint32_t)U * 8u), kToL2);
+    }
+};
 
 // A cluster's word: how many of its members have started, 6 bits for each XCD; kClosed and the member it is left to.
 constexpr int kXcds = 8;
@@ -762,7 +781,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     const buf_t dy = make_buf_(p.dy + w.li * p.sDYi, (int64_t)Tn * B * DH * 4);
     const buf_t da = make_buf_((const T*)p.da + w.li * p.sDAi, (int64_t)Tn * B * G4 * sizeof(T));
     const buf_t xch = make_buf_(cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT, 2 * C::BWD_SLOT * 8);
-    const buf_t raw = make_buf_(C::FLAGGED ? cd.raw + (int64_t)w.cluster * 2 * C::RAW_SLOT : nullptr, C::FLAGGED ? 2 * C::RAW_SLOT * 4 : 0);
+    const buf_t raw = make_buf_(cd.raw + (int64_t)w.cluster * 2 * C::RAW_SLOT, 2 * C::RAW_SLOT * 4);
 
     // cell part: this thread's unit and rows
     const int uu = tid % U, cu = w.m * U + uu;
@@ -865,13 +884,13 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         for (int i = 0; i < PPT; ++i) dh[i] = 0.f;
         if (s > 0) {
             bool ok = true;
-            if (C::FLAGGED && how == kOneXcd) {            // values [member][thread][row]
+            if (how == kOneXcd) {                          // values [member][thread][row]
                 const uint32_t slot = (uint32_t)(s & 1) * (uint32_t)(C::RAW_SLOT * 4);
                 ok = wait_flags_(cd, raw, slot + (uint32_t)(C::RAW_VALUES + w.m * 4 * S) * 4u, 4 * S, lane, w.tag0 + s);
                 asm volatile("" ::: "memory");             // (the values are loaded after the flags)
-                u32x4_t v[S];
+                typename Rows<PPT>::type v[S];
 #pragma unroll
-                for (int j = 0; j < S; ++j) v[j] = __builtin_amdgcn_raw_buffer_load_b128(raw, tid * 16, (int)(slot + (uint32_t)((w.m * S + j) * C::RB * U) * 4u), kFromL2);
+                for (int j = 0; j < S; ++j) v[j] = Rows<PPT>::load(raw, tid, slot + (uint32_t)((w.m * S + j) * C::RB * U) * 4u);
 #pragma unroll
                 for (int j = 0; j < S; ++j)
 #pragma unroll
@@ -957,34 +976,25 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;
             const uint32_t out_lane = (uint32_t)(g * (4 / PPT) * U + r) * 16u;
             constexpr uint32_t next = PPT == 4 ? 512u * 8u : (uint32_t)U * 16u;        // from rows 0, 1 to rows 2, 3
-            auto send = [&](auto scope) {
+            if (how == kOneXcd) {
+                // the rows of a lane are those of one thread or two; they are in the L2 when the wait ends
+                const uint32_t to_slot = (uint32_t)((s + 1) & 1) * (uint32_t)(C::RAW_SLOT * 4);
+#pragma unroll
+                for (int j = 0; j < C::NT; ++j) {
+                    const int n0 = (wave + 4 * j) * 16;
+                    Rows<PPT>::template store<U>(acc[j], raw, g, r, to_slot + (uint32_t)(((n0 / U) * S + w.m) * C::RB * U + n0 % U * PPT) * 4u);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __builtin_amdgcn_raw_buffer_store_b32(w.tag0 + s + 1, raw, lane < S ? (lane * 4 * S + w.m * 4 + wave) * 4 : (int)kOutOfRange,
+                                                      (int)(to_slot + (uint32_t)C::RAW_VALUES * 4u), kToL2);
+            } else {
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) {
                     const int n0 = (wave + 4 * j) * 16;
                     const uint32_t to = out + (uint32_t)((n0 / U) * S * C::RB * U) * 8u + (uint32_t)(n0 % U) * 16u;
-                    put2_<decltype(scope)::value>(xch, out_lane, to, acc[j][0], acc[j][1], w.tag0 + s + 1);
-                    put2_<decltype(scope)::value>(xch, out_lane, to + next, acc[j][2], acc[j][3], w.tag0 + s + 1);
+                    put2_<kToMemory>(xch, out_lane, to, acc[j][0], acc[j][1], w.tag0 + s + 1);
+                    put2_<kToMemory>(xch, out_lane, to + next, acc[j][2], acc[j][3], w.tag0 + s + 1);
                 }
-            };
-            if constexpr (C::FLAGGED) {
-                if (how == kOneXcd) {
-                    // the four rows of a lane are those of one thread: 16 bytes; they are in the L2 when the wait ends
-                    const uint32_t to_slot = (uint32_t)((s + 1) & 1) * (uint32_t)(C::RAW_SLOT * 4);
-#pragma unroll
-                    for (int j = 0; j < C::NT; ++j) {
-                        const int n0 = (wave + 4 * j) * 16;
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[j]), raw, (g * U + r) * 16,
-                                                               (int)(to_slot + (uint32_t)(((n0 / U) * S + w.m) * C::RB * U + n0 % U * 4) * 4u), kToL2);
-                    }
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    __builtin_amdgcn_raw_buffer_store_b32(w.tag0 + s + 1, raw, lane < S ? (lane * 4 * S + w.m * 4 + wave) * 4 : (int)kOutOfRange,
-                                                          (int)(to_slot + (uint32_t)C::RAW_VALUES * 4u), kToL2);
-                } else {
-                    send(std::integral_constant<int, kToMemory>{});
-                }
-            } else {
-                if (how == kOneXcd) send(std::integral_constant<int, kToL2>{});
-                else send(std::integral_constant<int, kToMemory>{});
             }
         }
 #pragma unroll
@@ -1096,12 +1106,12 @@ int64_t rec_cluster_exchange_words(const RecDesc& d, bool backward) {
 
 int64_t rec_cluster_raw_words(const RecDesc& d) {
     const int64_t S = cluster_members(d);
-    return d.precision ? rec_cluster_count(d) * 2 * (16 * S * S * 64 + 4 * S * S) : 0;
+    return rec_cluster_count(d) * 2 * (16 * S * S * (d.precision ? 64 : 32) + 4 * S * S);
 }
 
 hipError_t launch_rec_cluster(const ClusterDesc& desc, bool backward, int cu_count, hipStream_t s) {
     ClusterDesc p = desc;
-    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || (backward && p.r.precision && !p.raw) || !p.join || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
+    if (!rec_cluster_supported(p.r, backward, cu_count) || !p.exchange || (backward && !p.raw) || !p.join || !p.epoch || !p.status || (backward && !p.r.dc)) return hipErrorInvalidValue;
     const int S = cluster_members(p.r);
     if (p.r.precision) {
         switch (S) {
