@@ -449,7 +449,7 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     // weights as GEMM operands: the fp32 models themselves, or their bf16 copy
     const char* wbase = (const char*)at;
     const bool persist = use_persistent(h);
-    if (int rc = mark(h, 0, (prec ? (h->wx0p ? 3 : 2) : 1) + (persist ? 1 : 0))) return rc;
+    if (int rc = mark(h, 0, 1 + (prec && !h->shadow_valid ? 1 : 0) + (persist ? 1 : 0))) return rc;
     if (persist)     // frame counters of the persistent kernels start from zero (a fill kernel, not a memset node)
         HIPCHK(launch_zero((float*)h->rec_counters, 0, (int64_t)h->layers * 2 * L * 2, 1, ident, s), "zero frame counters");
     // the (learner, direction) pairs of the active learners, in the order the persistent launches take them
@@ -480,21 +480,22 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         // the update of the previous iteration has normally written this copy already
         if (!h->shadow_valid) HIPCHK(launch_cast_bf16(at, h->shadow, (int64_t)L * Pp, s), "cast weights to bf16");
         wbase = (const char*)h->shadow;
-        if (h->wx0p)
-            HIPCHK(launch_pad_rows_bf16(at + h->tensors[h->ix_wx[0]].off, Pp, h->wx0p, (int64_t)G4 * h->ldx, G4, h->I, h->ldx,
-                                        L, s), "pad W_x of layer 0");
     }
     auto W = [&](int ix) { return (const void*)(wbase + h->tensors[ix].off * esz); };
     auto Bias = [&](int ix) { return at + h->tensors[ix].off; };
     auto Gr = [&](int ix) { return h->grads + h->tensors[ix].off; };
 
-    StageDesc st;
+    StageDesc st{};
     st.L = n; st.lmap = act; st.precision = prec; st.rows = M; st.I = h->I; st.ldx = h->ldx;
     st.x0 = h->x0; st.sX0 = M * h->ldx; st.y = h->labels; st.sY = M;
     st.epoch = h->epoch; st.join = h->join; st.joins = h->joins * h->layers * 2;
     for (int i = 0; i < 128; ++i) {
         st.feats[i] = i < L ? (const float*)batch_ptrs[2 * i] : nullptr;
         st.labels[i] = i < L ? (const int32_t*)batch_ptrs[2 * i + 1] : nullptr;
+    }
+    if (h->wx0p) {
+        st.pad_src = at + h->tensors[h->ix_wx[0]].off; st.pad_sS = Pp;
+        st.pad_dst = h->wx0p; st.pad_sD = G4 * h->ldx; st.pad_rows = G4;
     }
     HIPCHK(launch_stage(st, s), "stage minibatches");
 

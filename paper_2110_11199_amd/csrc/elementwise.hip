@@ -6,6 +6,26 @@
 
 namespace adpsgd {
 
+// Rows of cols floats into rows of ld elements of the operand type, zero-padded; cols and ld multiples of 4, four elements to a thread
+// (quad: of rows * ld / 4).  One element to a thread, with a 64-bit division each, took 58 us for the 16 x 4096 rows of 260 weights of the 512-cell
+// model (126 MB) and a launch of its own beside the staging.
+template <typename T> __device__ inline void copy_quad_(const float* src, T* dst, int64_t rows, int cols, int ld, int64_t first, int tid, bool wide) {
+    const int per = ld / 4;
+    const int64_t row0 = first / per;                      // (the same for the workgroup)
+    const int x = (int)(first - row0 * per) + tid, dr = x / per, c = (x - dr * per) * 4;
+    const int64_t row = row0 + dr;
+    if (row >= rows) return;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c < cols) {
+        const float* p = src + row * cols + c;
+        if (wide) v = *(const float4*)p;
+        else { v.x = p[0]; v.y = p[1]; v.z = p[2]; v.w = p[3]; }
+    }
+    T* q = dst + row * ld + c;
+    if constexpr (sizeof(T) == 2) *(uint2*)q = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
+    else *(float4*)q = v;
+}
+
 struct StageArgs {
     LearnerMap lmap;
     int64_t rows; int I, ldx;
@@ -13,34 +33,38 @@ struct StageArgs {
     const float* feats[128];
     const int32_t* labels[128];
     uint32_t* epoch; uint64_t* join; int64_t joins;
+    int blocks;                                            // workgroups of the minibatch; those behind them pad weights
+    const float* pad_src; int64_t pad_sS; bf16_t* pad_dst; int64_t pad_sD, pad_rows;
 };
 
 template <typename T>
 __global__ __launch_bounds__(256) void stage_kernel(StageArgs p) {
     const int li = p.lmap.idx[blockIdx.y];
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t n = p.rows * p.ldx;
-    if (idx < n) {
-        const int64_t r = idx / p.ldx;
-        const int c = (int)(idx % p.ldx);
-        const float v = c < p.I ? p.feats[li][r * p.I + c] : 0.f;
-        ((T*)p.x0)[li * p.sX0 + idx] = Elem<T>::from(v);
+    if ((int)blockIdx.x >= p.blocks) {
+        copy_quad_<bf16_t>(p.pad_src + li * p.pad_sS, p.pad_dst + li * p.pad_sD, p.pad_rows, p.I, p.ldx, (int64_t)((int)blockIdx.x - p.blocks) * 256, threadIdx.x, true);
+        return;
     }
-    if (idx < p.rows) p.y[li * p.sY + idx] = p.labels[li][idx];
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const float* x = p.feats[li];
+    copy_quad_<T>(x, (T*)p.x0 + li * p.sX0, p.rows, p.I, p.ldx, (int64_t)blockIdx.x * 256, threadIdx.x, ((uintptr_t)x & 15) == 0);
+    if (idx < p.rows) p.y[li * p.sY + idx] = p.labels[li][idx];        // (a row is two quads at least)
     if (p.epoch && blockIdx.y == 0) {
         if (idx == 0) p.epoch[0] += 1u;
-        for (int64_t i = idx; i < p.joins; i += (int64_t)gridDim.x * 256) p.join[i] = 0ull;
+        for (int64_t i = idx; i < p.joins; i += (int64_t)p.blocks * 256) p.join[i] = 0ull;
     }
 }
 
 hipError_t launch_stage(const StageDesc& d, hipStream_t s) {
-    if (d.L < 1 || d.L > 128) return hipErrorInvalidValue;
+    if (d.L < 1 || d.L > 128 || d.I % 4 || d.ldx % 8 || (uintptr_t)d.pad_src % 16 || d.pad_sS % 4) return hipErrorInvalidValue;
     StageArgs a;
     a.lmap = d.lmap;
     a.rows = d.rows; a.I = d.I; a.ldx = d.ldx; a.x0 = d.x0; a.sX0 = d.sX0; a.y = d.y; a.sY = d.sY;
     for (int i = 0; i < 128; ++i) { a.feats[i] = d.feats[i]; a.labels[i] = d.labels[i]; }     // indexed by learner
     a.epoch = d.epoch; a.join = d.join; a.joins = d.joins;
-    dim3 grid((unsigned)((d.rows * d.ldx + 255) / 256), (unsigned)d.L);
+    a.blocks = (int)((d.rows * (d.ldx / 4) + 255) / 256);
+    a.pad_src = d.pad_src; a.pad_sS = d.pad_sS; a.pad_dst = d.pad_dst; a.pad_sD = d.pad_sD; a.pad_rows = d.pad_rows;
+    const int64_t pad = d.pad_src ? (d.pad_rows * (d.ldx / 4) + 255) / 256 : 0;
+    dim3 grid((unsigned)(a.blocks + pad), (unsigned)d.L);
     if (d.precision == 0) hipLaunchKernelGGL(stage_kernel<float>, grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(stage_kernel<bf16_t>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
@@ -65,24 +89,6 @@ hipError_t launch_cast_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_
     int64_t blocks = (n4 + 255) / 256;
     if (blocks > 256 * 32) blocks = 256 * 32;
     hipLaunchKernelGGL(cast_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const float4*)src, (uint2*)dst, n4);
-    return hipGetLastError();
-}
-
-// dst[z][r][0..ld) = bf16(src[z][r][0..cols)) followed by zeros: rows of a weight matrix padded to
-// a row length the direct-to-LDS GEMM can load (16-byte aligned rows, whole K stages).
-__global__ __launch_bounds__(256) void pad_rows_bf16_kernel(const float* src, int64_t sS, bf16_t* dst, int64_t sD,
-                                                            int64_t rows, int cols, int ld) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= rows * ld) return;
-    const int64_t r = idx / ld;
-    const int c = (int)(idx % ld);
-    dst[blockIdx.y * sD + idx] = c < cols ? f32_to_bf16(src[blockIdx.y * sS + r * cols + c]) : (bf16_t)0;
-}
-
-hipError_t launch_pad_rows_bf16(const float* src, int64_t sS, bf16_t* dst, int64_t sD, int64_t rows, int cols, int ld,
-                                int L, hipStream_t s) {
-    dim3 grid((unsigned)((rows * ld + 255) / 256), (unsigned)L);
-    hipLaunchKernelGGL(pad_rows_bf16_kernel, grid, dim3(256), 0, s, src, sS, dst, sD, rows, cols, ld);
     return hipGetLastError();
 }
 

@@ -79,13 +79,11 @@ struct StageDesc {             // copy / cast the minibatches into the workspace
     int32_t* y; int64_t sY;    // [L][rows]
     uint32_t* epoch;           // incremented once (may be NULL), and
     uint64_t* join; int64_t joins;       // these words are cleared
+    // optional (bf16): W_x of layer 0, pad_rows rows of I floats, learner stride pad_sS, into bf16 rows of ldx, zero-padded, as the inputs
+    const float* pad_src; int64_t pad_sS; bf16_t* pad_dst; int64_t pad_sD, pad_rows;
 };
 hipError_t launch_stage(const StageDesc& d, hipStream_t s);
 hipError_t launch_cast_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t s);
-// dst[z][r][0..ld) = bf16(src[z][r][0..cols)), zero padded; z < L, strides sS / sD in elements
-hipError_t launch_pad_rows_bf16(const float* src, int64_t sS, bf16_t* dst, int64_t sD, int64_t rows, int cols, int ld,
-                                int L, hipStream_t s);
-
 struct RecDesc {               // one time step of one layer, all learners and directions
     int precision;
     int L, D, B, H, T;         // L: learners of this launch (entries of lmap)
