@@ -661,8 +661,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
         if (how == kAlone + (uint32_t)w.m) forward_alone_<T, S>(cd, w, lds, red);
         return;
     }
-#pragma unroll 1
-    for (int s = 0; s < Tn; ++s) {
+    auto frame = [&](int s, auto later) -> bool {
         const uint32_t m = (uint32_t)(d == 0 ? s : Tn - 1 - s) * B;
         f32x4_t acc[4];
 #pragma unroll
@@ -670,7 +669,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
             if constexpr (KS == 1) acc[q] = f32x4_t{pre[q][0], pre[q][1], pre[q][2], pre[q][3]};
             else acc[q] = kh == 0 ? f32x4_t{pre[q][0], pre[q][1], 0.f, 0.f} : f32x4_t{0.f, 0.f, pre[q][0], pre[q][1]};
         }
-        if (s > 0) {
+        if constexpr (decltype(later)::value) {
             // h of the frame before, all units, into LDS: 32 threads to a row, words 2 (tid % 32) + 64 i and the next
             constexpr int N = C::RW / 64;
             char* const hl = lds + (s & 1) * C::FWD_BUF;
@@ -694,7 +693,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
             if (!ok) expired = 1;
             load_pre(s + 1 < Tn ? s + 1 : s);              // (after the exchange: its loads return in order behind these)
             lds_barrier_();
-            if (__builtin_amdgcn_readfirstlane(expired)) return;
+            if (__builtin_amdgcn_readfirstlane(expired)) return false;
             if constexpr (PARTS) {
                 if (__builtin_expect(plain, 0)) {
                     fwd_plain_<T, C>(acc, hl, make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T)), H, u, kh, r, g);
@@ -749,7 +748,12 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
             for (int q = 0; q < 4; ++q) buf_store_(acc[q][i], gates, vg[i], (m * G4 + q * H) * 4u);
             buf_store_(cs[i], cbuf, vc[i], m * H * 4u);
         }
-    }
+        return true;
+    };
+    frame(0, std::false_type{});                           // (outside the loop, so that the loop is entered with its stores in flight)
+#pragma unroll 1
+    for (int s = 1; s < Tn; ++s)
+        if (!frame(s, std::true_type{})) return;
 }
 
 // ---- backward -----------------------------------------------------------------------------------
