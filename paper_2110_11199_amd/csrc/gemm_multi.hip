@@ -89,6 +89,13 @@ Plan make_plan(const GradProducts& g) {
     Family f[3] = {kNone, kNone, kNone};
     if (g.has_dx) f[0] = family(g.dx, true, p.v[0]);
     for (int i = 0; i < g.ndw; ++i) f[1 + i] = family(g.dw[i], false, p.v[1 + i]);
+    // 256x256 tiles of one weight gradient that leave a third of their rounds of the chip empty, beside a dX of smaller ones (an output
+    // layer behind a bottleneck): 128x256 tiles, in dX's launch (8 learners, 2016 x 256 x 9000 and 9000 x 256 x 2016, 288 tiles: dX 153 us, dW 124,
+    // column sums 71, one after the other; 299 together).
+    if (g.ndw == 1 && f[0] == kBf16Mid && f[1] == kBf16Large) {
+        const int64_t tiles = gemm_tiles(g.dw[0], 256, 256), rounds = (tiles + 255) / 256;
+        if (3 * tiles <= 2 * 256 * rounds) { p.v[1] = 13; f[1] = kBf16Mid; }
+    }
     if (g.ndw < 1 || f[1] == kNone || (g.ndw > 1 && f[2] != f[1])) return p;
     p.fam = f[1];
     p.dx = g.has_dx && f[0] == f[1];

@@ -125,6 +125,14 @@ def test_gradient_on_clusters_of_compute_units_from_few_frames_on(prec, hidden, 
     _check_gradient(Shape(12, hidden, 1, 1, 0, 24, batch, frames), 2, prec)
 
 
+@pytest.mark.parametrize("shape,L", [
+    (Shape(12, 20, 1, 0, 132, 4104, 193, 8), 16),  # 272 tiles of 256x256 of dW_o, two rounds with a third empty: in the launch of dz, in 128x256 tiles
+    (Shape(12, 20, 1, 1, 0, 1000, 5, 3), 2),       # more workgroups of column sums than of products
+])
+def test_gradient_of_output_layers_that_share_a_launch(shape, L):
+    _check_gradient(shape, L, 1)
+
+
 def _check_gradient(shape, L, prec, tune=()):
     import torch
     print("lstm grad", shape, L, prec, flush=True)
