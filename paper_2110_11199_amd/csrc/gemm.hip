@@ -174,12 +174,16 @@ int gemm_pick_tile(const GemmDesc& d, bool& dma) {
 // against 79.2), and a tile alone on its compute unit takes 20 ns per k here and 15.5 there.
 bool gemm_plain_fp32(const GemmDesc& d) { return gemm_tiles(d, 64, 64) <= 256 && d.K <= 192; }
 
+// The rounding of fp32 contractions this long is 1e-6 of the result in any order of the sums: they keep theirs, on fp32 MFMAs.
+bool gemm_long_fp32(const GemmDesc& d) { return d.precision == 0 && d.K > 2560; }
+
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {
     bool dma = false;
     const int v = gemm_pick_tile(d, dma);
     if (v < 0) return hipErrorInvalidValue;
     if (d.precision == 0) {
         if (v == 15 && dma && gemm_plain_fp32(d)) return launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s);
+        if (v >= 11 && dma && gemm_long_fp32(d)) return v == 15 ? launch_dma<float, 2, 2, 1, 1, 64, 4>(d, s) : launch_dma<float, 2, 2, 2, 2, 64, 3>(d, s);
         if (v >= 11 && dma) return launch_gemm_split(d, v != 15, s);
         return launch_layout<float, 2, 2, 2, 2, 16, 64>(d, s);
     }

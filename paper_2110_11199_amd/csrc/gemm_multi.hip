@@ -78,7 +78,7 @@ Family family(const GemmDesc& d, bool dx, int& v) {
     bool dma = false;
     v = gemm_pick_tile(d, dma);
     if (v < 0 || !dma || d.b_kc || (d.a_kc != 0) != dx) return kNone;
-    if (d.precision == 0) return v >= 14 ? kFp32 : kNone;
+    if (d.precision == 0) return v >= 14 && !gemm_long_fp32(d) ? kFp32 : kNone;
     return v == 12 ? kBf16Large : v >= 13 ? kBf16Mid : kNone;
 }
 

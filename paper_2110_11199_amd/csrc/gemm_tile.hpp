@@ -198,6 +198,7 @@ __device__ __forceinline__ void dma_tile(const GemmDesc& p, int bid, int total, 
 // loads, and whether an fp32 problem in 64x64 tiles runs on fp32 MFMAs.
 int gemm_pick_tile(const GemmDesc& d, bool& dma);
 bool gemm_plain_fp32(const GemmDesc& d);
+bool gemm_long_fp32(const GemmDesc& d);
 inline int64_t gemm_tiles(const GemmDesc& d, int bm, int bn) {
     return (int64_t)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.groupsI * d.groupsD;
 }
