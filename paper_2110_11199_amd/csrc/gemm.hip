@@ -145,10 +145,14 @@ int gemm_pick_tile(const GemmDesc& d, bool& dma) {
           (d.b_kc ? d.K % epc == 0 || d.k_padded : d.ldb >= (d.N + epc - 1) / epc * epc);
     int v = d.tile;
     if (d.precision == 0) {
-        // ns per k of a tile, with others on its compute unit and alone on it (gemm_split.hpp): what decides is how evenly the tiles cover
-        // the compute units.  us, 128x128 / 64x64: 672x2048x512x8 70 / 83, 1280x2000x320x6 58 / 71, 1000x512x672x8 42 / 44; and
-        // 672x512x2048x8 98 / 85, 1280x320x1280x6 58 / 52, 2000x320x1280x6 91 / 75.
-        if (v < 0) v = !dma ? 0 : tile_time(d, 64, 64, 12.8, 15.5) < tile_time(d, 128, 128, 36.0, 43.0) ? 15 : 14;
+        // ns per k of a tile, with others on its compute unit and alone on it, of the kernels that run it: what decides is how evenly the
+        // tiles cover the compute units.  On the bf16 matrix units (gemm_split.hpp), us, 128x128 / 64x64: 672x2048x512x8 70 / 83, 1280x2000x320x6
+        // 58 / 71, 1000x512x672x8 42 / 44; and 672x512x2048x8 98 / 85, 1280x320x1280x6 58 / 52, 2000x320x1280x6 91 / 75.  On fp32 MFMAs
+        // (gemm_long_fp32): 672x1024x9000x8 1035 / 889, 672x1024x4096x8 474 / 406, 1344x1024x3000x8 521 / 509; 2688x1024x9000x4 1559 / 1654.
+        if (v < 0) {
+            const bool mfma = gemm_long_fp32(d);
+            v = !dma ? 0 : tile_time(d, 64, 64, mfma ? 14.0 : 12.8, mfma ? 20.0 : 15.5) < tile_time(d, 128, 128, mfma ? 53.0 : 36.0, mfma ? 60.0 : 43.0) ? 15 : 14;
+        }
         return v;
     }
     if (v < 0) {
@@ -174,7 +178,10 @@ int gemm_pick_tile(const GemmDesc& d, bool& dma) {
 // against 79.2), and a tile alone on its compute unit takes 20 ns per k here and 15.5 there.
 bool gemm_plain_fp32(const GemmDesc& d) { return gemm_tiles(d, 64, 64) <= 256 && d.K <= 192; }
 
-// The rounding of fp32 contractions this long is 1e-6 of the result in any order of the sums: they keep theirs, on fp32 MFMAs.
+// fp32 contractions this long stay on fp32 MFMAs, for the sake of the results' continuity and not of their accuracy: results of the two
+// kinds of kernels differ by 7.5e-7 of the 2-norm at K = 1024, 1.07e-6 at 2048 and 1.2e-6 at 2560, growing as the square root (each has rounding
+// errors of its own: fp32 MFMAs 9.0e-7 against 64 bits at 2560, 1.14e-6 at 4096, the bf16 matrix units 7.9e-7 at 2560, 5.5e-7 in 64x64 tiles), and
+// gradients with longer sums were seen to move by 1.4e-6 in all.
 bool gemm_long_fp32(const GemmDesc& d) { return d.precision == 0 && d.K > 2560; }
 
 hipError_t launch_gemm(const GemmDesc& d, hipStream_t s) {

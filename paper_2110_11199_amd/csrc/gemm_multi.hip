@@ -37,7 +37,7 @@ struct Bf16Large {                       // 12
     static constexpr int kLds = 3 * 512 * 64, kWaves = 1;
     template <bool AKC> __device__ __forceinline__ static void tile(const GemmDesc& d, int, int bid, int n, char* lds) { dma_tile<bf16_t, AKC, false, 2, 2, 4, 4, 64, 3>(d, bid, n, lds); }
 };
-struct Fp32Plain {                       // the smallest fp32 problems
+struct Fp32Plain {                       // the smallest fp32 problems, and long contractions
     static constexpr int kLds = 4 * 128 * 64, kWaves = 3;
     template <bool AKC> __device__ __forceinline__ static void tile(const GemmDesc& d, int, int bid, int n, char* lds) { dma_tile<float, AKC, false, 2, 2, 1, 1, 64, 4>(d, bid, n, lds); }
 };
@@ -72,13 +72,15 @@ template <class Kind> void launch_multi_t(const MultiArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((gemm_multi_kernel<Kind>), dim3((unsigned)(a.cs_blocks + a.end[2])), dim3(256), 0, s, a);
 }
 
-// Problems of one family can share a launch.
-enum Family { kNone, kBf16Mid, kBf16Large, kFp32 };
+// Problems of one family can share a launch.  Of the long fp32 contractions, on fp32 MFMAs, two weight gradients in 64x64 tiles do (us, an
+// iteration with a launch each / with one: 4 x 128 cells in both directions, 4200 frames 1152 / 1081, 3 x 2 x 64, 3360 frames 495 / 377).
+enum Family { kNone, kBf16Mid, kBf16Large, kFp32, kFp32Long };
 Family family(const GemmDesc& d, bool dx, int& v) {
     bool dma = false;
     v = gemm_pick_tile(d, dma);
     if (v < 0 || !dma || d.b_kc || (d.a_kc != 0) != dx) return kNone;
-    if (d.precision == 0) return v >= 14 && !gemm_long_fp32(d) ? kFp32 : kNone;
+    if (d.precision == 0 && gemm_long_fp32(d)) return v == 15 && !dx ? kFp32Long : kNone;
+    if (d.precision == 0) return v >= 14 ? kFp32 : kNone;
     return v == 12 ? kBf16Large : v >= 13 ? kBf16Mid : kNone;
 }
 
@@ -100,7 +102,7 @@ Plan make_plan(const GradProducts& g) {
     p.fam = f[1];
     p.dx = g.has_dx && f[0] == f[1];
     // (a large problem's one workgroup to a compute unit would leave the column sums too few loads in flight)
-    p.cs = g.has_cs && p.fam != kBf16Large && colsum_ok(g.cs);
+    p.cs = g.has_cs && p.fam != kBf16Large && p.fam != kFp32Long && colsum_ok(g.cs);
     p.dw = p.dx || p.cs || g.ndw > 1;
     int64_t blocks = p.cs ? (int64_t)((g.cs.N + 31) / 32 + g.cs.L_all) * g.cs.L : 0;
     if (p.dx) blocks += gemm_tiles(g.dx, 64, 64);
@@ -145,7 +147,9 @@ hipError_t launch_grad_products(const GradProducts& g, hipStream_t s) {
             a.cs_x = (g.cs.N + cols - 1) / cols + (g.cs.loss ? g.cs.L_all : 0);
             a.cs_blocks = a.cs_x * g.cs.L;
         }
-        if (p.fam == kFp32) {
+        if (p.fam == kFp32Long) {
+            launch_multi_t<Fp32Plain>(a, s);
+        } else if (p.fam == kFp32) {
             bool plain = (!p.dx || (p.v[0] == 15 && gemm_plain_fp32(g.dx)));
             for (int i = 0; i < g.ndw; ++i) plain = plain && p.v[1 + i] == 15 && gemm_plain_fp32(g.dw[i]);
             if (plain) launch_multi_t<Fp32Plain>(a, s);

@@ -195,7 +195,7 @@ __device__ __forceinline__ void dma_tile(const GemmDesc& p, int bid, int total, 
 }
 
 // The tile configuration of a problem (see gemm.hip; -1: not a valid problem), whether its operands meet the rules of the direct
-// loads, and whether an fp32 problem in 64x64 tiles runs on fp32 MFMAs.
+// loads, and whether an fp32 problem runs on fp32 MFMAs: the smallest ones in 64x64 tiles, long contractions in tiles of either size.
 int gemm_pick_tile(const GemmDesc& d, bool& dma);
 bool gemm_plain_fp32(const GemmDesc& d);
 bool gemm_long_fp32(const GemmDesc& d);

@@ -36,3 +36,47 @@ def test_small_batches_on_the_split_contraction_where_it_is_the_shorter():
         assert _step_kind(Bd.BF16_GEMM, True, pairs, hidden, batch) == SPLIT
         assert _step_kind(Bd.BF16_GEMM, False, pairs, hidden, batch) == DIRECT
     assert _step_kind(Bd.BF16_GEMM, True, 20, 768, 8) == DIRECT and _step_kind(Bd.FP32, False, 48, 1024, 2) == DIRECT
+
+
+class _Gemm(ctypes.Structure):         # adpsgd::GemmDesc
+    _fields_ = [(n, ctypes.c_int) for n in ("precision", "a_kc", "b_kc", "c_elem", "M", "N", "K")] + \
+               [(n, ctypes.c_int64) for n in ("A", "lda", "sAi", "sAd", "B", "ldb", "sBi", "sBd", "C", "ldc", "sCi", "sCd", "bias", "sBiasI", "sBiasD")] + \
+               [(n, ctypes.c_int) for n in ("groupsI", "groupsD", "k_padded", "tile")] + [("lmap", ctypes.c_uint8 * 128)]
+
+
+class _Colsum(ctypes.Structure):       # adpsgd::ColsumDesc
+    _fields_ = [("precision", ctypes.c_int), ("L", ctypes.c_int), ("lmap", ctypes.c_uint8 * 128), ("in_", ctypes.c_int64), ("ld", ctypes.c_int64), ("sIi", ctypes.c_int64),
+                ("rows", ctypes.c_int64), ("N", ctypes.c_int), ("out", ctypes.c_int64), ("sOi", ctypes.c_int64), ("loss", ctypes.c_int64), ("row_loss", ctypes.c_int64),
+                ("L_all", ctypes.c_int), ("active_bits", ctypes.c_uint32 * 4)]
+
+
+class _Products(ctypes.Structure):     # adpsgd::GradProducts
+    _fields_ = [("has_dx", ctypes.c_bool), ("has_cs", ctypes.c_bool), ("dx", _Gemm), ("ndw", ctypes.c_int), ("dw", _Gemm * 2), ("cs", _Colsum)]
+
+
+def _gemm_desc(M, N, K, groups, a_kc=0, b_kc=0, precision=Bd.FP32):
+    lda, ldb = (K if a_kc else M), (K if b_kc else N)
+    return _Gemm(precision=precision, a_kc=a_kc, b_kc=b_kc, M=M, N=N, K=K, lda=lda, sAi=M * K, ldb=ldb, sBi=N * K, ldc=N, sCi=M * N, groupsI=groups, groupsD=1, tile=-1)
+
+
+@pytest.mark.parametrize("M,N,K,groups,want", [
+    (672, 1024, 2560, 8, 14), (672, 1024, 2564, 8, 15),      # six rounds of 64x64 tiles against two of 128x128
+    (672, 1024, 4096, 8, 15), (672, 1024, 9000, 8, 15), (1344, 1024, 3000, 8, 15), (640, 640, 9000, 8, 15),
+    (2688, 2048, 4096, 8, 14),                               # 42 rounds of 14 against 11 of 53
+    (2048, 2048, 4096, 1, 15), (2048, 2048, 2048, 1, 14),    # 4 rounds of 14 against one of 60; 4 of 12.8 against one of 43
+])
+def test_fp32_tile_follows_the_rates_of_the_kernels_that_run_it(M, N, K, groups, want):
+    # ns per k: on the bf16 matrix units 12.8 a round (15.5 alone) in 64x64 tiles, 36 (43) in 128x128; on fp32 MFMAs, K > 2560, 14 (20) and 53 (60)
+    dma = ctypes.c_bool()
+    pick = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd14gemm_pick_tileERKNS_8GemmDescERb"]
+    assert pick(ctypes.byref(_gemm_desc(M, N, K, groups, a_kc=1)), ctypes.byref(dma)) == want and dma.value
+
+
+@pytest.mark.parametrize("frames,before,want", [(2016, 1920, 1), (2688, 2560, 2), (2688, 2624, 1), (4200, 4000, 1)])
+def test_fp32_weight_gradients_of_a_layer_share_a_launch_whatever_their_length(frames, before, want):
+    # (one that is long and one that is not run on kernels of either kind)
+    g = _Products(ndw=2)
+    g.dw[0], g.dw[1] = _gemm_desc(1280, 320, frames, 6), _gemm_desc(1280, 320, before, 6)
+    apart = ctypes.c_bool()
+    launches = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd21grad_product_launchesERKNS_12GradProductsERb"]
+    assert launches(ctypes.byref(g), ctypes.byref(apart)) == want

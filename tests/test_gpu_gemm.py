@@ -142,6 +142,20 @@ def test_gemm_fp32_on_the_bf16_matrix_units(tile, edge, a_k, b_k, K):
     assert _run(0, a_k, b_k, 1, edge - 4, 3 * edge, K, 2, False, tile=tile) < 1e-6
 
 
+@pytest.mark.parametrize("tile,edge", [(14, 128), (15, 64)])
+@pytest.mark.parametrize("a_k,b_k", LAYOUTS)
+@pytest.mark.parametrize("K", [2560, 2564, 2577, 4096])
+def test_gemm_fp32_of_long_contractions(tile, edge, a_k, b_k, K):
+    # the last that runs on the bf16 matrix units and the first on fp32 MFMAs, an odd one, a whole number of stages.  K additions, each rounded by up to
+    # 2^-24 of a partial sum, none of them (statistically) above the largest result: four standard deviations of K such errors, evenly spread,
+    # relative to that result (2.4e-6 of 7.0e-6 measured at K = 2564)
+    K = K if not (a_k or b_k) else (K + 3) // 4 * 4
+    bound = 4 * (K / 3) ** 0.5 * 2.0 ** -24
+    print("gemm fp32 long", tile, a_k, b_k, K, flush=True)
+    assert _run(0, a_k, b_k, 0, 2 * edge + 1, edge - 3, K, 2, True, pad=4, tile=tile) < bound
+    assert _run(0, a_k, b_k, 1, edge, 2 * edge, K, 2, False, tile=tile) < bound
+
+
 @pytest.mark.parametrize("tile", [14, 15])
 @pytest.mark.parametrize("a_k,b_k", LAYOUTS)
 def test_gemm_fp32_of_values_that_have_no_finite_bf16_part(tile, a_k, b_k):

@@ -133,6 +133,15 @@ def test_gradient_of_output_layers_that_share_a_launch(shape, L):
     _check_gradient(shape, L, 1)
 
 
+@pytest.mark.parametrize("shape", [
+    Shape(12, 20, 2, 1, 0, 24, 330, 9),            # 2970 frames, 2640 with a predecessor: both weight gradients long, in one launch
+    Shape(12, 20, 2, 1, 0, 24, 440, 6),            # 2640 and 2200: one long
+    Shape(12, 20, 1, 1, 8, 2564, 5, 3),            # the gradient of a bottleneck over 2564 states
+])
+def test_gradient_with_long_fp32_contractions(shape):
+    _check_gradient(shape, 2, 0)
+
+
 def _check_gradient(shape, L, prec, tune=()):
     import torch
     print("lstm grad", shape, L, prec, flush=True)
