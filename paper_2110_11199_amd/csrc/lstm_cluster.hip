@@ -237,7 +237,9 @@ template <typename T, class C> __device__ inline uint4 fwd_frag_(buf_t wh, int H
 // ---- fp32 products on the bf16 matrix units --------------------------------------------------------------
 // An fp32 value as the sum of three bf16 values, and six of the nine products of two such sums (gemm_split.hpp): the products of
 // a frame at one wave per SIMD, 1.9 us of fp32 MFMAs at 256 cells, take 0.7.  A value without a finite first part makes
-// check infinite or NaN; where one turns up, the workgroup multiplies in fp32, W_h from memory.
+// check infinite or NaN (so do ordinary ones from about 2^81 on, whose third parts' products overflow); where one turns up in a member's W_h or,
+// backward, in its da of the frame, the member multiplies in fp32, W_h from memory.  The decision is the member's, over its whole workgroup, and a
+// workgroup that does a cluster's work alone takes the same one for each member.
 __device__ inline void parts2_(float x, float y, uint32_t (&p)[3], float& check) {
     p[0] = pack_bf16(x, y);
     x -= __builtin_bit_cast(float, p[0] << 16); y -= __builtin_bit_cast(float, p[0] & 0xffff0000u);
@@ -428,11 +430,11 @@ __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, cha
                 if constexpr (PARTS) {
                     const char* hrow = hl + r * C::FWD_ROW + kh * (C::PCW * 128) + g * 32;
                     f32x4_t sum[4] = {acc[0], acc[1], acc[2], acc[3]};
-                    float check = 0.f;
+                    float check = 0.f, unused = 0.f;
 #pragma unroll 1
                     for (int c = 0; c < C::PCW; ++c) {
                         uint4 a[3], b[4][3];
-                        parts8_(*(const uint4*)(hrow + c * 128), *(const uint4*)(hrow + c * 128 + 16), a, check);
+                        parts8_(*(const uint4*)(hrow + c * 128), *(const uint4*)(hrow + c * 128 + 16), a, unused);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             uint4 lo, hi;
@@ -441,7 +443,7 @@ __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, cha
                         }
                         mma_parts_<4>(sum, a, [&](int q) -> const uint4 (&)[3] { return b[q]; });
                     }
-                    plain = __ballot(not_finite_(check)) != 0;
+                    plain = __syncthreads_or(not_finite_(check));
                     if (!plain) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) acc[q] = sum[q];
@@ -488,8 +490,9 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
     // scratch: dh [16 rows][KP] in the first slot of the cluster, sums of da [member][gate][thread] in the second
     word_t* const dh_buf = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT;
     word_t* const bs_buf = dh_buf + C::BWD_SLOT;
-    static_assert(S * 4 * 256 <= C::BWD_SLOT, "the sums of da fit a slot");
+    static_assert(S * 4 * 256 <= C::BWD_SLOT && S <= 16, "the sums of da fit a slot, the members a half of in_fp32");
     const int uu = tid % U;
+    uint32_t in_fp32 = 0;                                  // members that multiply in fp32, by the parity of the frame (not_finite of the kernel below)
 #pragma unroll 1
     for (int s = 0; s < Tn; ++s) {
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B, m_next = (uint32_t)(d == 0 ? Tn - 2 - s : s + 1) * B;
@@ -499,7 +502,7 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
 #pragma unroll 1
         for (int mm = 0; mm < S; ++mm) {
             const int cu = mm * U + uu;
-            float bs[4];
+            float bs[4], check = 0.f;
 #pragma unroll
             for (int q = 0; q < 4; ++q) bs[q] = s > 0 ? scratch_get_(bs_buf + (mm * 4 + q) * 256 + tid) : 0.f;
 #pragma unroll 1
@@ -524,6 +527,10 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
                     arow[q * U] = v;
                     buf_store_(v, da, ok ? vg / (4u / (uint32_t)sizeof(T)) : kOutOfRange, (m * G4 + q * H) * (uint32_t)sizeof(T));
                 }
+                if constexpr (C::PARTS) {
+                    uint32_t a3[3];
+                    parts2_(a4[0], a4[1], a3, check); parts2_(a4[2], a4[3], a3, check);
+                }
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) scratch_put_(bs_buf + (mm * 4 + q) * 256 + tid, bs[q]);
@@ -535,20 +542,22 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
                 bool plain = true;
                 if constexpr (C::PARTS) {
                     const char* arow = lds + r * C::BWD_ROW + g * 16;
-                    float check = 0.f;
+                    float check_w = 0.f, unused = 0.f;
 #pragma unroll 1
                     for (int c = 0; c < C::PBCH; ++c) {
                         uint4 a[3], b[C::NT][3];
-                        parts8_(*(const uint4*)(arow + c * 128), *(const uint4*)(arow + c * 128 + 64), a, check);
+                        parts8_(*(const uint4*)(arow + c * 128), *(const uint4*)(arow + c * 128 + 64), a, unused);
                         const int k = mm * U + 4 * g;      // rows 4 g .. and 16 + 4 g .. of gate c
 #pragma unroll
                         for (int j = 0; j < C::NT; ++j) {
                             const int n = (wave + 4 * j) * 16 + r;
-                            parts8_(bwd_frag_<T>(wh, H, c, k, n), bwd_frag_<T>(wh, H, c, k + 16, n), b[j], check);
+                            parts8_(bwd_frag_<T>(wh, H, c, k, n), bwd_frag_<T>(wh, H, c, k + 16, n), b[j], check_w);
                         }
                         mma_parts_<C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return b[j]; });
                     }
-                    plain = __ballot(not_finite_(check)) != 0;
+                    const uint32_t bit = 1u << (mm + 16 * (s & 1));
+                    if (__syncthreads_or(not_finite_(check) || not_finite_(check_w))) in_fp32 |= bit;
+                    plain = (in_fp32 & bit) != 0;
                     if (plain) {
 #pragma unroll
                         for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -771,7 +780,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     constexpr int OP_BYTES = 2 * C::BWD_BUF, W_BYTES = 2 * 16 * C::W_ROW * 4;
     __shared__ __attribute__((aligned(16))) char lds[OP_BYTES > W_BYTES ? OP_BYTES : W_BYTES];
     __shared__ float bred[4][256];
-    __shared__ int expired, not_finite[2];                 // not_finite: by the parity of the frame
+    __shared__ int expired, not_finite[2];                 // not_finite: by the parity of the frame, and never cleared
     const RecDesc& p = cd.r;
     Place w;
     if (!place_<C>(cd, w)) return;
@@ -942,6 +951,8 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             }
             in_c[i] = c_prev[i];
         }
+        // (Once set it holds for all later frames of the parity.  One word for each wave, written in every frame, or three words in turn cost about 1 us
+        // of a pass of 20 frames at 256 cells.)
         if (PARTS && (plain || not_finite_(check))) not_finite[s & 1] = 1;
         if (s + 1 < Tn) {
             load_in(s + 1);

@@ -579,3 +579,71 @@ def test_clusters_in_fp32_with_weights_that_no_bf16_parts_hold(hidden):
     assert (np.isnan(a) == np.isnan(b)).mean() > 0.999
     both = np.isfinite(a) & np.isfinite(b)
     assert both.sum() > 0 and np.abs(a[both] - b[both]).max() <= 1e-4 * np.abs(b[both]).max()
+
+
+def _one_gradient(shape, L, w, batches, tune):
+    import torch
+    e = _engine(shape, L, S.FIXED_RING, 0)
+    for key, value in tune:
+        e.tune(key, value)
+    e.set_params(-1, torch.from_numpy(w).cuda())
+    e.step(_to_dev(batches), 0.0)
+    e.status()
+    out = [e.grads(i).cpu().numpy().copy() for i in range(L)]
+    e.close()
+    return out
+
+
+def _tensor(shape, w, name):
+    off, r, c = {n: (o, r, c) for n, o, r, c in lstm.layout(shape)[0]}[name]
+    return w[off:off + r * c].reshape(r, c)
+
+
+def _check_cluster_against_alone_and_frames(shape, L, w, batches):
+    # a cluster, one workgroup for a cluster: the same bits; frame by frame: the same sums in another order (1e-5 of a tensor's largest value, as for
+    # other sums of this length)
+    from paper_2110_11199_amd import binding as Bd
+    together = _one_gradient(shape, L, w, batches, ())
+    alone = _one_gradient(shape, L, w, batches, ((Bd.TUNE_REC_JOIN_US, 0),))
+    frames = _one_gradient(shape, L, w, batches, ((Bd.TUNE_REC_PERSISTENT, 0),))
+    for a, b, f in zip(together, alone, frames):
+        assert np.isfinite(f).all() and np.isfinite(a).all()
+        assert _per_tensor_err(shape, a, f) < 1e-5, _per_tensor_err(shape, a, f)
+        assert (a.view(np.uint32) == b.view(np.uint32)).all(), (a.view(np.uint32) != b.view(np.uint32)).sum()
+    return frames
+
+
+@pytest.mark.parametrize("hidden", [132, 256, 320])
+def test_clusters_in_fp32_with_finite_weights_that_no_bf16_parts_hold(hidden):
+    # the largest fp32 value, whose first bf16 part is infinite, in a gate of one unit in either direction: times any h it saturates the gate, so
+    # that the da of the gate is 0 in every frame that hands one on, and all gradients are finite.  The unit's member multiplies in fp32, the others in parts
+    print("clusters, finite weights without finite parts", hidden, flush=True)
+    shape = Shape(12, hidden, 1, 1, 0, 24, 17, 8)
+    w = synth.initial_model(0, lstm.param_count(shape), 0.1)
+    wh = _tensor(shape, w, "Wh0")
+    big = np.float32(3.4028235e38)
+    wh[3, 7] = big                                         # input gate of cell 3, first direction: the first member
+    wh[hidden + hidden - 2, hidden - 3] = -big             # forget gate of the last but one: the last member that has units
+    wh[4 * hidden + 3 * hidden + 70, 1] = big              # output gate of cell 70, second direction
+    grads = _check_cluster_against_alone_and_frames(shape, 2, w, _batches(shape, 2, 0))
+    g = _tensor(shape, grads[0], "Wh0")
+    assert (g[3] == 0).all() and (g[4 * hidden + 3 * hidden + 70] == 0).all()      # (the saturated gates)
+    assert (np.abs(g).max(axis=1) > 0).sum() >= 8 * hidden - 3                     # (and no others)
+
+
+@pytest.mark.parametrize("hidden", [132, 256, 320])
+def test_clusters_in_fp32_with_gradients_that_become_ordinary_again(hidden):
+    # a loss in the last frame only, whose gradient is so large (2^93) that the check of the parts overflows there, and halves from frame to
+    # frame: the first frames multiply in fp32, later ones in parts
+    print("clusters, large gradients", hidden, flush=True)
+    frames, batch = 40, 17
+    shape = Shape(12, hidden, 1, 0, 0, 8, batch, frames)
+    w = synth.initial_model(0, lstm.param_count(shape), 0.02)
+    wo, bo = _tensor(shape, w, "Wo"), _tensor(shape, w, "bo")
+    wo *= np.float32(2.0 ** 108)                           # 0.02 x 2^108: about 2^102, divided by the 680 rows of the minibatch
+    bo[:] = 0.0
+    bo[0, 0] = 2.0 ** 120                                  # state 0 has all the probability, whatever h
+    y = np.zeros((frames, batch), np.int32)
+    y[-1] = 1
+    b = [(f, y.reshape(l.shape)) for f, l in _batches(shape, 2, 0)]
+    _check_cluster_against_alone_and_frames(shape, 2, w, b)
