@@ -4,6 +4,7 @@ import ctypes
 import pytest
 
 from paper_2110_11199_amd import binding as Bd
+from tests.test_gpu_lstm import ACROSS_XCDS
 
 STAGED, DIRECT, SPLIT = 0, 1, 2
 
@@ -80,3 +81,20 @@ def test_fp32_weight_gradients_of_a_layer_share_a_launch_whatever_their_length(f
     apart = ctypes.c_bool()
     launches = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd21grad_product_launchesERKNS_12GradProductsERb"]
     assert launches(ctypes.byref(g), ctypes.byref(apart)) == want
+
+
+class _Rec(ctypes.Structure):          # adpsgd::RecDesc
+    _fields_ = [(n, ctypes.c_int) for n in ("precision", "L", "D", "B", "H", "T")] + [("lmap", ctypes.c_uint8 * 128), ("direct", ctypes.c_int), ("step", ctypes.c_int)] + \
+               [(n, ctypes.c_int64) for n in "gates sGi c sCi y sYi wh sWi sWd dy sDYi da sDAi dc sDCi dbp sDBi".split()]
+
+
+@pytest.mark.parametrize("prec,shape,L,members", ACROSS_XCDS)
+def test_numbers_of_clusters_that_are_meant_to_exchange_through_memory_do(prec, shape, L, members):
+    r = _Rec(precision=prec, L=L, D=2 if shape.bidirectional else 1, B=shape.batch, H=shape.hidden, T=shape.frames, direct=1)
+    supported = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd21rec_cluster_supportedERKNS_7RecDescEbi"]
+    supported.restype = ctypes.c_bool
+    assert supported(ctypes.byref(r), ctypes.c_bool(False), 256) and supported(ctypes.byref(r), ctypes.c_bool(True), 256)
+    clusters, units = L * r.D * -(-shape.batch // 16), 64 if prec else 32
+    assert members * units >= shape.hidden and (members - 2) * units < shape.hidden
+    one_xcd, anywhere = 256 // 8 // members * 8, 256 // members
+    assert -(-clusters // one_xcd) > -(-clusters // anywhere)

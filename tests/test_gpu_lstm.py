@@ -125,6 +125,24 @@ def test_gradient_on_clusters_of_compute_units_from_few_frames_on(prec, hidden, 
     _check_gradient(Shape(12, hidden, 1, 1, 0, 24, batch, frames), 2, prec)
 
 
+# Numbers of clusters that would take a round of the chip more on one XCD each, so that their members lie on several and exchange through memory:
+# 18 and 36 of 12 members (21 fit the 256 compute units anywhere, 16 on one XCD each), 42 and 84 of 6 (42, 40), 25 and 50 of 10 (25, 24).
+ACROSS_XCDS = [
+    (0, Shape(12, 348, 1, 1, 0, 24, 48, 7), 3, 12), (0, Shape(12, 384, 1, 1, 0, 24, 40, 7), 6, 12),
+    (0, Shape(12, 320, 1, 0, 0, 24, 65, 7), 5, 10), (0, Shape(12, 260, 1, 1, 0, 24, 80, 7), 5, 10),
+    (1, Shape(12, 360, 1, 1, 0, 24, 48, 7), 7, 6), (1, Shape(12, 264, 1, 1, 0, 24, 48, 7), 14, 6),
+    (1, Shape(12, 640, 1, 0, 0, 24, 80, 7), 5, 10), (1, Shape(12, 516, 1, 1, 0, 24, 80, 7), 5, 10),
+]
+
+
+@pytest.mark.parametrize("prec,shape,L,members", ACROSS_XCDS)
+def test_gradient_on_clusters_that_exchange_through_memory(prec, shape, L, members):
+    from paper_2110_11199_amd import binding as Bd
+    _check_gradient(shape, L, prec)
+    for a, b in zip(_one_step(shape, L, prec, ()), _one_step(shape, L, prec, ((Bd.TUNE_REC_JOIN_US, 0),))):
+        assert (a == b).all()
+
+
 @pytest.mark.parametrize("shape,L", [
     (Shape(12, 20, 1, 0, 132, 4104, 193, 8), 16),  # 272 tiles of 256x256 of dW_o, two rounds with a third empty: in the launch of dz, in 128x256 tiles
     (Shape(12, 20, 1, 1, 0, 1000, 5, 3), 2),       # more workgroups of column sums than of products
