@@ -571,8 +571,9 @@ def test_batch_beyond_the_second_dimension_of_a_grid():
 
 @pytest.mark.parametrize("hidden", [132, 256, 320])
 def test_clusters_in_fp32_with_weights_that_no_bf16_parts_hold(hidden):
-    # infinite and the largest recurrent weights: gates saturate, everything else is as frame by frame.  The values that are added to
-    # an infinity have no place in the comparison of sums (1e-5, as elsewhere), so the gradients of the cells they belong to are left out
+    # an infinite recurrent weight: the forward pass saturates a gate, and backward 0 x inf makes all gradients of the first direction NaN, frame by frame
+    # as on clusters.  What is finite and compared - the output layer and the second direction - shows that forward pass and nothing of the backward
+    # products of the first direction: those are compared with finite weights, below
     import torch
     from paper_2110_11199_amd import binding as Bd
     print("clusters, weights without finite parts", hidden, flush=True)
