@@ -181,3 +181,26 @@ def test_gemm_fp32_of_values_that_have_no_finite_bf16_part(tile, a_k, b_k):
     rest = np.isfinite(ref).all(axis=1)
     assert rest.sum() == M - 3 and np.isfinite(got[rest]).all()
     assert (np.abs(got[rest] - ref[rest]) <= 2e-6 * np.abs(ref[rest]).max(axis=1, keepdims=True)).all()
+
+
+@pytest.mark.parametrize("tile", [14, 15])
+@pytest.mark.parametrize("a_k,b_k", LAYOUTS)
+@pytest.mark.parametrize("scale_a,scale_b", [(-108, 0), (0, -108), (-108, 60), (-55, -55), (85, -85), (85, 30)])
+def test_gemm_fp32_of_small_and_large_values(tile, a_k, b_k, scale_a, scale_b):
+    # operands times powers of two, down to the values whose three bf16 parts still hold all 24 bits (2^-110; the largest of the distribution lie a little
+    # above the scale, and those below it are a small share of a sum) and up to those whose check overflows: the same error as without
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("gemm fp32 scaled", tile, a_k, b_k, scale_a, scale_b, flush=True)
+    M, N, K = 136, 132, 256
+    r = np.random.default_rng(5)
+    A = (r.standard_normal((M, K)) * 2.0 ** scale_a).astype(np.float32)
+    B = (r.standard_normal((N, K)) * 2.0 ** scale_b).astype(np.float32)
+    dA = torch.from_numpy(np.ascontiguousarray(A if a_k else A.T)).cuda()
+    dB = torch.from_numpy(np.ascontiguousarray(B if b_k else B.T)).cuda()
+    dC = torch.empty(M, N, device="cuda")
+    Bd.adpsgd_gemm(0, a_k, b_k, 0, M, N, K, dA.data_ptr(), K if a_k else M, 0, dB.data_ptr(), K if b_k else N, 0, dC.data_ptr(), N, 0,
+                   None, 0, 1, torch.cuda.current_stream().cuda_stream, tile_config=tile)
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+    # (as test_gemm_fp32_of_long_contractions: four standard deviations of K roundings of 2^-24)
+    assert np.abs(dC.cpu().numpy() - ref).max() < 4 * (K / 3) ** 0.5 * 2.0 ** -24 * np.abs(ref).max()
