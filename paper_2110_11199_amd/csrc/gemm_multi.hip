@@ -5,7 +5,7 @@
 // round of the chip that is partly empty: a small model's are all latency, a middle one's leave half of the 512 places of 128x256 tiles free (5
 // learners of 2 x 360 cells: 135 tiles of dX 30 us, 240 of dW_x 28, 120 of dW_h 10, column sums 5).  In one launch the tiles of
 // all follow each other; those of dX come first, and before them the column sums, which are bound by memory while the tiles are
-// bound by the matrix units.  Every problem keeps the tile configuration it has alone (gemm.hip).
+// bound by the matrix units.  Every problem keeps the tile configuration it has alone (gemm.hip), but for one kind of dW (make_plan).
 #include "colsum.hpp"
 #include "gemm_split.hpp"
 #include "gemm_tile.hpp"
@@ -93,10 +93,14 @@ Plan make_plan(const GradProducts& g) {
     for (int i = 0; i < g.ndw; ++i) f[1 + i] = family(g.dw[i], false, p.v[1 + i]);
     // 256x256 tiles of one weight gradient that leave a third of their rounds of the chip empty, beside a dX of smaller ones (an output
     // layer behind a bottleneck): 128x256 tiles, in dX's launch (8 learners, 2016 x 256 x 9000 and 9000 x 256 x 2016, 288 tiles: dX 153 us, dW 124,
-    // column sums 71, one after the other; 299 together).
+    // column sums 71, one after the other; 299 together).  Not where dX has more than 128 blocks of 128 rows in 128x256 tiles: on half of the compute units its
+    // tiles still have a compute unit each, on more they take each other's time.  Iterations of one layer of 64 cells in us, together / apart (blocks):
+    // 8 x 9000 states, bottleneck 256 905 / 965 (128), 1045 / 1026 (136), 1504 / 1460 (216); 4 x 9000, 256 820 / 852 (112), 1057 / 987 (132);
+    // 7 x 12000, 256 853 / 892 (126), 1026 / 952 (133); 6 x 12000, 200 850 / 916 (126), 991 / 962 (132); 4 x 9000, 512 900 / 923 (100), 1041 / 1039 (132).
+    // Of 150 sizes up to 128 blocks four are slower, by 1.5 to 4 % (3 x 11600, 256, 4096 rows 809 / 775), most of the others faster, by up to 13 %.
     if (g.ndw == 1 && f[0] == kBf16Mid && f[1] == kBf16Large) {
-        const int64_t tiles = gemm_tiles(g.dw[0], 256, 256), rounds = (tiles + 255) / 256;
-        if (3 * tiles <= 2 * 256 * rounds) { p.v[1] = 13; f[1] = kBf16Mid; }
+        const int64_t tiles = gemm_tiles(g.dw[0], 256, 256), rounds = (tiles + 255) / 256, rows = (int64_t)((g.dx.M + 127) / 128) * g.dx.groupsI * g.dx.groupsD;
+        if (3 * tiles <= 2 * 256 * rounds && (p.v[0] != 13 || rows <= 128)) { p.v[1] = 13; f[1] = kBf16Mid; }
     }
     if (g.ndw < 1 || f[1] == kNone || (g.ndw > 1 && f[2] != f[1])) return p;
     p.fam = f[1];

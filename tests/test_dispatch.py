@@ -83,6 +83,24 @@ def test_fp32_weight_gradients_of_a_layer_share_a_launch_whatever_their_length(f
     assert launches(ctypes.byref(g), ctypes.byref(apart)) == want
 
 
+@pytest.mark.parametrize("learners,states,width,rows,apart", [
+    (8, 9000, 256, 2048, False), (8, 9000, 256, 2049, True),       # 288 tiles of dW; 128 blocks of 128 rows of dX, 136
+    (4, 9000, 512, 3840, False), (4, 9000, 512, 4096, True),       # 240 tiles of dX; 128 of 256x256, which dX takes then
+    (10, 10600, 256, 1600, True),                                  # 420 tiles of dW: no third of two rounds empty
+    (8, 9000, 64, 2688, False),                                    # dX in 64x64 tiles
+])
+def test_bf16_output_layer_behind_a_bottleneck_shares_a_launch_where_dx_leaves_half_of_the_chip(learners, states, width, rows, apart):
+    # (the column sums are apart unless dW runs in tiles of which two fit a compute unit)
+    g = _Products(has_dx=True, has_cs=True, ndw=1)
+    g.dx = _gemm_desc(rows, width, states, learners, a_kc=1, precision=Bd.BF16_GEMM)
+    g.dw[0] = _gemm_desc(states, width, rows, learners, precision=Bd.BF16_GEMM)
+    g.dw[0].lda = (states + 63) // 64 * 64                         # (k-rows padded to whole chunks, as the handle lays them out)
+    g.cs = _Colsum(precision=1, L=learners, ld=states, rows=rows, N=states)
+    got = ctypes.c_bool()
+    assert ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd21grad_product_launchesERKNS_12GradProductsERb"](ctypes.byref(g), ctypes.byref(got)) == 1
+    assert got.value == apart
+
+
 class _Rec(ctypes.Structure):          # adpsgd::RecDesc
     _fields_ = [(n, ctypes.c_int) for n in ("precision", "L", "D", "B", "H", "T")] + [("lmap", ctypes.c_uint8 * 128), ("direct", ctypes.c_int), ("step", ctypes.c_int)] + \
                [(n, ctypes.c_int64) for n in "gates sGi c sCi y sYi wh sWi sWd dy sDYi da sDAi dc sDCi dbp sDBi".split()]

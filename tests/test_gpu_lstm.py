@@ -144,7 +144,8 @@ def test_gradient_on_clusters_that_exchange_through_memory(prec, shape, L, membe
 
 
 @pytest.mark.parametrize("shape,L", [
-    (Shape(12, 20, 1, 0, 132, 4104, 193, 8), 16),  # 272 tiles of 256x256 of dW_o, two rounds with a third empty: in the launch of dz, in 128x256 tiles
+    (Shape(12, 20, 1, 0, 132, 4104, 193, 8), 16),  # 272 tiles of 256x256 of dW_o, two rounds with a third empty, beside 208 blocks of rows of dz: launches of their own
+    (Shape(12, 20, 1, 0, 132, 8200, 193, 8), 8),   # 264 tiles and 104 blocks: dW_o in 128x256 tiles in the launch of dz
     (Shape(12, 20, 1, 1, 0, 1000, 5, 3), 2),       # more workgroups of column sums than of products
 ])
 def test_gradient_of_output_layers_that_share_a_launch(shape, L):
