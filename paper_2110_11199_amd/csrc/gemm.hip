@@ -152,6 +152,13 @@ int gemm_pick_tile(const GemmDesc& d, bool& dma) {
         if (v < 0) {
             const bool mfma = gemm_long_fp32(d);
             v = !dma ? 0 : tile_time(d, 64, 64, mfma ? 14.0 : 12.8, mfma ? 20.0 : 15.5) < tile_time(d, 128, 128, mfma ? 53.0 : 36.0, mfma ? 60.0 : 43.0) ? 15 : 14;
+            // Short contractions are bound by how a tile starts and by its stores.  Where rows of C are not whole 64 bytes the stores of 128x128 tiles take
+            // half as long again; elsewhere those tiles pay once there are a few rounds of them.  us, 128x128 on the bf16 matrix units / 64x64 on fp32
+            // MFMAs: 168x5000x40x12 25 / 19, 1344x3000x64x12 108 / 78, 2000x320x64x6 12.3 / 9.8, 512x1024x40x8 9.1 / 8.6; 1280x1280x80x6 16.3 / 20.4, 3360x1280x80x8
+            // 42 / 59, 672x2048x40x16 26 / 31; and up to 112 terms 128x128 / 64x64, both on the bf16 matrix units: 1344x3000x96x12 112 / 92, 168x5000x96x12 30 / 26.
+            const bool whole = d.ldc % 16 == 0;
+            if (dma && d.K <= 80) v = whole && 2.6 * (gemm_tiles(d, 128, 128) + 256) < gemm_tiles(d, 64, 64) + 256 ? 14 : 15;
+            else if (dma && d.K <= 112 && !whole) v = 15;
         }
         return v;
     }
@@ -173,10 +180,11 @@ int gemm_pick_tile(const GemmDesc& d, bool& dma) {
     return v;
 }
 
-// fp32 problems of one round of 64x64 tiles and a short contraction stay on fp32 MFMAs: there a launch costs the fetch of its
-// instructions, of which the split kernels have several times as many (an iteration of the 4 x 64-unit model, five such launches: 74.6 us
-// against 79.2), and a tile alone on its compute unit takes 20 ns per k here and 15.5 there.
-bool gemm_plain_fp32(const GemmDesc& d) { return gemm_tiles(d, 64, 64) <= 256 && d.K <= 192; }
+// fp32 problems in 64x64 tiles with a short contraction stay on fp32 MFMAs, up to 192 terms in one round of the chip: there a launch costs the fetch
+// of its instructions, of which the split kernels have several times as many (an iteration of the 4 x 64-unit model, five such launches: 74.6 us
+// against 79.2), and a tile alone on its compute unit takes 20 ns per k here and 15.5 there; up to 80 terms in any number of rounds (split / here,
+// us: 168x5000x40x12 21.7 / 19.2, 1008x256x40x16 10.7 / 8.5, 2000x320x64x6 10.7 / 9.8, 1344x3000x80x12 96 / 87).
+bool gemm_plain_fp32(const GemmDesc& d) { return d.K <= 80 || (gemm_tiles(d, 64, 64) <= 256 && d.K <= 192); }
 
 // fp32 contractions this long stay on fp32 MFMAs, for the sake of the results' continuity and not of their accuracy: results of the two
 // kinds of kernels differ by 7.5e-7 of the 2-norm at K = 1024, 1.07e-6 at 2048 and 1.2e-6 at 2560, growing as the square root (each has rounding

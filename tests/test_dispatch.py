@@ -73,6 +73,17 @@ def test_fp32_tile_follows_the_rates_of_the_kernels_that_run_it(M, N, K, groups,
     assert pick(ctypes.byref(_gemm_desc(M, N, K, groups, a_kc=1)), ctypes.byref(dma)) == want and dma.value
 
 
+@pytest.mark.parametrize("M,N,K,groups,want", [
+    (168, 5000, 40, 12, 15), (1344, 3000, 64, 12, 15), (1344, 3000, 96, 12, 15), (1344, 3000, 116, 12, 14),      # rows of C that are no whole 64 bytes
+    (1280, 1280, 80, 6, 14), (3360, 1280, 64, 8, 14), (512, 1024, 64, 8, 15), (2000, 320, 80, 6, 15),            # rows that are: few rounds of 128x128, or many
+])
+def test_fp32_tile_of_short_contractions(M, N, K, groups, want):
+    dma = ctypes.c_bool()
+    pick = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd14gemm_pick_tileERKNS_8GemmDescERb"]
+    for kc in (0, 1):
+        assert pick(ctypes.byref(_gemm_desc(M, N, K, groups, a_kc=kc, b_kc=kc)), ctypes.byref(dma)) == want and dma.value
+
+
 @pytest.mark.parametrize("frames,before,want", [(2016, 1920, 1), (2688, 2560, 2), (2688, 2624, 1), (4200, 4000, 1)])
 def test_fp32_weight_gradients_of_a_layer_share_a_launch_whatever_their_length(frames, before, want):
     # (one that is long and one that is not run on kernels of either kind)

@@ -142,6 +142,18 @@ def test_gemm_fp32_on_the_bf16_matrix_units(tile, edge, a_k, b_k, K):
     assert _run(0, a_k, b_k, 1, edge - 4, 3 * edge, K, 2, False, tile=tile) < 1e-6
 
 
+@pytest.mark.parametrize("a_k,b_k", LAYOUTS)
+@pytest.mark.parametrize("K", [20, 77, 80, 81, 112, 113])
+def test_gemm_fp32_of_short_contractions(a_k, b_k, K):
+    # several rounds of 64x64 tiles, the last of a row and a column ragged; rows of C that are whole 64 bytes and rows that are not.  A sum of K products
+    # with K roundings of at most 2^-24 of a partial sum: as in test_gemm_fp32_of_long_contractions
+    K = K if not (a_k or b_k) else (K + 3) // 4 * 4
+    bound = 4 * max(K / 3, 4) ** 0.5 * 2.0 ** -24
+    print("gemm fp32 short", a_k, b_k, K, flush=True)
+    assert _run(0, a_k, b_k, 0, 1092, 1040, K, 2, True) < bound
+    assert _run(0, a_k, b_k, 1, 1028, 1092, K, 2, False, pad=4) < bound
+
+
 @pytest.mark.parametrize("tile,edge", [(14, 128), (15, 64)])
 @pytest.mark.parametrize("a_k,b_k", LAYOUTS)
 @pytest.mark.parametrize("K", [2560, 2564, 2577, 4096])
