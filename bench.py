@@ -29,6 +29,8 @@ if ROOT not in sys.path:
 METRIC = "frames/sec & learner-steps/sec (1 MI355X); mix/update HBM GB/s"
 PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 PEAK_HBM_GBS = 8000.0
+# (adpsgd_profile counts a launch that holds an input gradient and weight gradients for either)
+GEMM_KERNELS = "gemm_dma_kernel, gemm_multi_kernel (time-batched GEMMs; launches that hold dX and dW count twice)"
 
 
 def _config(Bd, wl, seed, variant=None):
@@ -345,7 +347,7 @@ def main():
                          "traffic": traffic.get("%s/batched_gemm" % wl.name),
                          "traffic_source": "profiles/hbm_traffic_cfg4_cfg5.txt (rocprofv3 counter runs of this command; not "
                                            "measured in this run)",
-                         "kernel": "gemm_dma_kernel (time-batched GEMMs)",
+                         "kernel": GEMM_KERNELS,
                          "launches_per_step": g["launches"] / args.steps,
                          "avg_launch_ms": g["ms"] / max(g["launches"], 1),
                          "flops_per_launch": g["work"] / max(g["launches"], 1),
@@ -386,7 +388,7 @@ def main():
             ms3 = dt3 / args.cfg3_steps * 1e3
             out["roofline_cfg3"] = {
                 "bound": "mfma", "achieved": tf3, "peak": PEAK_TFLOPS["bf16"], "unit": "TFLOP/s", "frac": tf3 / PEAK_TFLOPS["bf16"],
-                "traffic": None, "kernel": "gemm_dma_kernel (time-batched GEMMs)", "workload": "cfg3", "steps": args.cfg3_steps,
+                "traffic": None, "kernel": GEMM_KERNELS, "workload": "cfg3", "steps": args.cfg3_steps,
                 "ms_per_step": ms3, "frames_per_s": w3.L * w3.batch * w3.frames / (ms3 * 1e-3),
                 "launches_per_step": g3["launches"] / args.cfg3_steps, "avg_launch_ms": g3["ms"] / max(g3["launches"], 1),
                 "flops_per_launch": g3["work"] / max(g3["launches"], 1),

@@ -541,8 +541,8 @@ def test_cluster_left_to_one_workgroup_gives_the_same_bits(prec, hidden):
 
 
 def test_cluster_waits_for_workgroups_that_have_not_started():
-    # 64 clusters of 6 workgroups on 256 compute units: the cluster that is short of workgroups at first waits for one of the 42
-    # before it to end (100 frames, some hundreds of microseconds).  That is no expiry of the bound on the exchange, nor
+    # 64 clusters of 6 workgroups on 256 compute units: the cluster that is short of workgroups at first waits for one of the 40
+    # before it (five to an XCD) to end (100 frames, some hundreds of microseconds).  That is no expiry of the bound on the exchange, nor
     # does it matter whether the cluster is left to one of its workgroups instead (bound of 20 microseconds)
     from paper_2110_11199_amd import binding as Bd
     print("cluster short of workgroups", flush=True)
