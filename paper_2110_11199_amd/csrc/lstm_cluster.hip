@@ -2,8 +2,8 @@
 // hidden sizes above what one compute unit holds (lstm_resident.hip).
 //
 // Frame by frame such a layer costs a launch, W_h from the caches and a latency-bound product per frame: 8-20 us, of which the
-// products are 1-4; here 3.4-8 (both sides at the rule below).  Iterations: fp32 8 x 2 x 256 cells 1722 -> 1090 us, 6 x 320 2984 -> 1644,
-// bf16 5 x 2 x 360 1396 -> 934.  What is left of a frame: the exchange (about 1.5 us), fp32 products of one wave per SIMD, the cells.
+// products are 1-4; here 2.9-4 where all clusters run at once (both sides at the rule below).  Iterations: fp32 8 x 2 x 256 cells 1556 -> 789 us,
+// 6 x 320 2709 -> 1196, bf16 5 x 2 x 360 1316 -> 699.  What is left of a frame: the exchange (0.5-1 us), products of one wave per SIMD, the cells.
 //
 // Here a CLUSTER of S workgroups takes 16 batch rows of one (learner, direction) through all frames (batch rows do not depend
 // on each other: as many clusters as row blocks).  Workgroup m of a cluster owns U hidden units and holds their part of W_h as
@@ -26,11 +26,11 @@
 // all-to-all of 256 threads x N words between 8 workgroups, us: N = 1 0.64 through memory, 0.36 in one L2; 8 1.36, 0.63 (0.54 with
 // 16-byte loads); 12 1.68, 0.77 (0.71); 24 2.31, 1.35 (0.97).  Workgroup ids go round the 8 XCDs, so the members of a
 // cluster take ids 8 apart; what decides is not that, but the XCD each of them reads from its hardware register.
-// The backward pass of bf16 models exchanges the most for its size, H words of 64 bits a row written and read by every member: 5 MB an XCD
-// in two slots at 640 cells, more than its L2 holds.  On one XCD it writes bare values instead, waits until they are there (the
+// The backward pass exchanges the most for its size, H words of 64 bits a row written and read by every member: 5 MB an XCD
+// in two slots at 640 cells in bf16, more than its L2 holds.  On one XCD it writes bare values instead, waits until they are there (the
 // L2 acknowledges a store) and then writes a flag to each member, tagged as above; whoever finds the flags loads the values: half the
 // bytes for one more latency.  us per frame, tagged words / flags: 4 x 512 cells, batch 16 3.6 / 3.1, 16 x 512, 32 6.1 / 4.0, 32 x 512, 64 22.0 / 15.3,
-// 10 x 360, 50 4.8 / 3.2, 10 x 640, 32 7.7 / 4.8, 16 x 256, 64 3.8 / 3.1.  (Values and tagged words have memory of their own: a value could
+// 10 x 360, 50 4.8 / 3.2, 10 x 640, 32 7.7 / 4.8, 16 x 256, 64 3.8 / 3.1; fp32 16 x 512, 32 15.9 / 13.6, 6 x 320, 64 4.4 / 3.9.  (Values and tagged words have memory of their own: a value could
 // pass for a tag.)
 //
 // Progress.  Every workgroup counts itself into its cluster's word when it STARTS, by XCD, and exchanges nothing before
@@ -39,7 +39,8 @@
 // launch can explain - other work holds the device, or other such launches with incomplete clusters of their own - is closed (a bit
 // of the same word) and left to one of those that wait, which does all of it alone (forward_alone_, backward_alone_): the
 // same operations in the same order, slower by the number of members and by W_h from the caches (us per frame, forward /
-// backward, cluster against alone: fp32 256 cells 4.5 / 4.3 against 42 / 55, bf16 640 cells 4.3 / 7.4 against 116 / 272).  So
+// backward, one cluster, together against alone: fp32 256 cells 3.2 / 3.1 against 44 / 61, bf16 640 cells 3.7 / 3.8 against 96 / 247; all 32 of
+// 16 x 640, batch 32 7.3 / 8.5 against 123 / 516).  So
 // nothing waits for workgroups that may not come.  Every wait of the exchange is bounded all the same (wait_ticks of
 // the 100 MHz clock, or another workgroup's expiry): the workgroup raises kStatusWaitExpired and returns.
 //
@@ -1062,8 +1063,9 @@ template <typename T, int S> void launch_cluster_t(ClusterDesc& p, bool backward
 //   bf16 backward 10 x 360, 50 230 / 64; 16 x 512, 64 (512) 364 / 157; 32 x 512, 64 453 / 297, 128 726 / 575; 16 x 640, 32 (320)
 //                 402 / 169, 96 (960) 453 / 381; 32 x 640, 128 1017 / 1027
 // and of 5 frames: bf16 forward 32 x 512, 64 94 / 107, backward 121 / 103; fp32 forward 32 x 512, 64 200 / 331.
-// Of 388 such pairs the estimates pick the longer way by more than 3 us and 5 per cent for 5, and lose 0.2 ms in all; clusters throughout
-// lose 2.8, frames throughout 34.  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
+// Of 388 such pairs the estimates picked the longer way by more than 3 us and 5 per cent for 5, and lost 0.2 ms in all; clusters throughout
+// lose 2.8, frames throughout 34.  The bf16 rows were fitted again when backward partial sums went bare, the fp32 rows and the fp32 figures above
+// were not (16 x 512, batch 32 backward 313 us by the estimate, 275 measured): some fp32 passes whose two ways are close still run frame by frame.  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
 namespace {
 
 double frames_time(const RecDesc& d, bool backward) {
