@@ -346,7 +346,7 @@ def main():
             "roofline": {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak,
                          "traffic": traffic.get("%s/batched_gemm" % wl.name),
                          "traffic_source": "profiles/hbm_traffic_cfg4_cfg5.txt (rocprofv3 counter runs of this command; not "
-                                           "measured in this run)",
+                                           "measured in this run, and with one product to a launch)",
                          "kernel": GEMM_KERNELS,
                          "launches_per_step": g["launches"] / args.steps,
                          "avg_launch_ms": g["ms"] / max(g["launches"], 1),
