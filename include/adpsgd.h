@@ -360,8 +360,8 @@ int adpsgd_probe_stream(int reads, int writes_f32, int writes_bf16, void* dev_bu
  *                                handle's sticky error becomes ADPSGD_EHIP
  *   ADPSGD_TUNE_REC_JOIN_US      how long, in microseconds, a group of up to 16 workgroups waits for those that have not started
  *                                (other work may hold the device) before one of those that wait does the group's work
- *                                alone: same results bit for bit, several times slower.  -1 (default): 1000 per
- *                                frame of the segment; 0: always alone
+ *                                alone: same results bit for bit, several times slower.  -1 (default): 200 and
+ *                                25 per frame of the segment; 0: always alone
  * Takes effect from the next adpsgd_step of that handle; other handles are not touched. */
 #define ADPSGD_TUNE_GEMM_TILE       0
 #define ADPSGD_TUNE_REC_DIRECT      1

@@ -108,7 +108,7 @@ struct adpsgd_handle {
     int tune_rec_fwd_groups = 0;           // learner groups of the forward recurrence, 0 = automatic
     int tune_rec_persist = -1;             // persistent recurrent kernels: 0 off, 1 on where the shape allows, -1 automatic
     int64_t tune_wait_us = 2000000;        // bound of one wait between the workgroups of a recurrent kernel
-    int64_t tune_join_us = -1;             // how long a cluster waits for workgroups that have not started, -1: 1 ms per frame
+    int64_t tune_join_us = -1;             // how long a cluster waits for workgroups that have not started, -1: 200 and 25 per frame
     int cu_count = 0;                      // compute units of the device (a persistent grid must not exceed it)
     uint32_t* rec_counters = nullptr;      // [layers][2 passes][L * D] frame counters of the persistent kernels
     float* mean_buf = nullptr;             // chunk buffer of the two-kernel global mean (mix ALL)
@@ -522,9 +522,11 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
         c.launches = 2 * h->layers; c.launch = 2 * l + (backward ? 1 : 0);
         c.exchange = h->exchange; c.raw = h->raw; c.join = h->join + h->joins * c.launch; c.epoch = h->epoch; c.status = h->status;
         c.wait_ticks = (unsigned long long)h->tune_wait_us * 100ull;
-        // by default several times what one workgroup takes for the cluster (0.02 to 0.3 ms a frame), and far more than the clusters before it in
-        // the same launch take (up to 0.02)
-        c.join_ticks = (unsigned long long)(h->tune_join_us < 0 ? (int64_t)1000 * T : h->tune_join_us) * 100ull;
+        // by default three times what the cluster before it in the same launch takes (3 to 8.5 us a frame and W_h) and less than one workgroup takes for
+        // the cluster (40 to 250 us a frame).  Launches of several streams can stand in each other's way on an XCD of 32 compute units (three and more of
+        // 16 members, four of 10), and one of them has to give way: ms a pass of two iterations of four handles on streams of their own,
+        // 1000 / 100 / 50 / 25 us per frame: fp32 10 x 396 cells, batch 137 58 / 13.4 / 11.2 / 9.4 (5.4 before clusters stayed on one XCD), bf16 10 x 640, 64 5.5 / 1.5 / 1.9 / 1.5
+        c.join_ticks = (unsigned long long)(h->tune_join_us < 0 ? 200 + (int64_t)25 * T : h->tune_join_us) * 100ull;
         return c;
     };
 

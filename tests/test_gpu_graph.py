@@ -215,3 +215,44 @@ def test_what_cannot_be_recorded_is_refused():
         with pytest.raises(Bd.AdpsgdError):
             eng.capture_begin()
     eng.close()
+
+
+def test_recordings_of_four_handles_replayed_on_four_streams():
+    # forward recurrences of 90 clusters of 16 workgroups each: of four launches, every one can hold part of an XCD's 32 compute units with a cluster that
+    # is short of members, and one has to give way after 200 microseconds and 25 per frame.  With a bound of 1000 per frame a replay took 58 ms, with
+    # this one 9; 25 lies between
+    import time
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("four recordings on four streams", flush=True)
+    shape, L = Shape(28, 396, 1, 1, 0, 80, 137, 32), 5
+    batch = [(torch.from_numpy(f).cuda(), torch.from_numpy(y).cuda()) for f, y in _batch(shape, L, 0)]
+    w0 = torch.from_numpy(synth.initial_model(0, lstm.param_count(shape), 0.05)).cuda()
+    torch.cuda.synchronize()
+    engines, graphs = [], []
+    for _ in range(4):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            e = Bd.Adpsgd(Bd.make_config(L, S.FIXED_RING, seed=0, precision=0, input_dim=28, hidden=396, layers=1, bidirectional=1, bottleneck=0,
+                                         classes=80, batch=137, frames=32))
+            e.set_params(-1, w0)
+            e.step(batch, 0.0)
+            e.status()
+            e.capture_begin()
+            e.step(batch, 0.0); e.step(batch, 0.0)
+            graphs.append(e.capture_end())
+        engines.append(e)
+    want = engines[0].grads(0).clone()
+    torch.cuda.synchronize()
+    begun = time.perf_counter()
+    for _ in range(6):
+        for g in graphs:
+            Bd.adpsgd_graph_replay(g)
+    torch.cuda.synchronize()
+    ms = (time.perf_counter() - begun) * 1e3 / 24
+    for e, g in zip(engines, graphs):
+        e.status()
+        assert torch.equal(e.grads(0), want)
+        Bd.adpsgd_graph_destroy(g)
+        e.close()
+    assert ms < 25, ms
