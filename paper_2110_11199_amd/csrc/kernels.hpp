@@ -187,7 +187,7 @@ struct SoftmaxDesc {
     LearnerMap lmap;
     uint32_t* status;          // device status word: kStatusBadLabel is or-ed in
     int64_t rows; int C;
-    const float* logits; int64_t sLi;    // [L][rows][C]
+    const float* logits; int64_t ldl, sLi;    // [L][rows][C], rows ldl apart
     const int32_t* y; int64_t sYi;
     void* dlogits; int64_t ldd, sDi;     // [L][rows][C] operand type, rows ldd apart: (softmax - onehot)/rows
     float* row_loss;                     // [L][rows]

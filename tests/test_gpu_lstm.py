@@ -95,6 +95,13 @@ def test_gradient_frame_by_frame(shape, prec):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("classes", [4, 28, 32, 36, 60, 64, 68, 132])
+def test_gradient_with_padded_rows_of_logits(classes, prec):
+    # rows of logits are 32 elements apart and multiples of it, those of their gradient 64 (bf16): one column less, none, one more
+    _check_gradient(Shape(8, 16, 1, 0, 0, classes, 9, 3), 2, prec)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("hidden", [16, 48, 100, 128])
 @pytest.mark.parametrize("batch,frames", [(1, 2), (16, 5), (17, 1)])
 def test_gradient_with_all_frames_on_one_compute_unit(hidden, batch, frames, prec):
