@@ -67,6 +67,7 @@ template <typename T, int S_> struct Cl {
     static constexpr int FWD_PART_ROW = KP * 2 + 16, BWD_PART_ROW = 4 * U * 2 + 16, FWD_PART = RB * FWD_PART_ROW, BWD_PART = RB * BWD_PART_ROW;
     static constexpr bool PARTS = sizeof(T) == 4 && S <= 10;
     static constexpr int PCW = KP / (32 * KS), PBCH = 4 * U / 32;
+    static constexpr bool SETTLE_F = sizeof(T) == 2 || PARTS, SETTLE_B = PARTS || (sizeof(T) == 2 && S <= 8);   // (settle_)
     static constexpr int FWD_BUF = PARTS ? 3 * FWD_PART : RB * FWD_ROW, BWD_BUF = PARTS ? 3 * BWD_PART : RB * BWD_ROW;   // one frame's operand
     static constexpr int W_ROW = KP + 4;                   // words of a row of staged W_h: rows 4 apart lie 16 banks apart
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
@@ -259,6 +260,18 @@ __device__ inline void parts8_(const uint4& lo, const uint4& hi, uint4 (&p)[3], 
     for (int i = 0; i < 3; ++i) p[i] = make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]);
 }
 __device__ inline bool not_finite_(float check) { return !(check - check == 0.f); }
+// Fragment i of a member's W_h, when ordinary code has done with it: the first 60 of a lane go to its accumulation registers, which matrix instructions
+// read as they are (16 registers are left for sums).  Left to itself the compiler spreads W_h over both halves of the register file and copies
+// fragments between them in every frame, 112 copies at 512 cells in bf16, and has no registers to read a frame's operand from the LDS ahead of its products:
+// 16 reads and waits one after the other.  us of a pass of 21 frames, before / with both: forward bf16 16 x 2 x 512 cells, batch 64 297 / 270, 8 x 2 x 640, 96
+// 333 / 296, fp32 6 x 320, 64 84 / 80; backward 317 / 312, -, 82 / 79.  SETTLE_F, SETTLE_B: where both passes are the faster for it; not
+// backward at 640 cells in bf16 (415 / 426), nor with W_h in fp32 (16 x 2 x 512, 16 313 / 328 and 303 / 313).
+__device__ inline void settle_(uint4& w, int i) {
+    if (i >= 60) return;
+    u32x4_t x = __builtin_bit_cast(u32x4_t, w);
+    asm volatile("" : "+a"(x));
+    w = __builtin_bit_cast(uint4, x);
+}
 // acc[0..N) += a b[0..N), smallest products first
 template <int N, class B> __device__ inline void mma_parts_(f32x4_t (&acc)[N], const uint4 (&a)[3], B b) {
     constexpr int QA[6] = {0, 2, 1, 0, 1, 0}, QB[6] = {2, 0, 1, 1, 0, 0};
@@ -637,6 +650,14 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
                 }
             }
         if constexpr (PARTS) plain = __syncthreads_or(not_finite_(check));
+        if constexpr (C::SETTLE_F) {
+#pragma unroll
+            for (int c = 0; c < NW; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int k = 0; k < (PARTS ? 3 : 1); ++k) settle_(wf[q][c][k], (c * 4 + q) * (PARTS ? 3 : 1) + k);
+        }
     }
     // rows this lane finishes: row0 + i, i < PR
     const int row0 = 4 * g + (KS == 2 ? 2 * kh : 0);
@@ -709,20 +730,25 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
                     fwd_plain_<T, C>(acc, hl, make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T)), H, u, kh, r, g);
                 } else {
                     const char* hrow = hl + r * C::FWD_PART_ROW + kh * (NW * 64) + g * 16;
+                    uint4 a[NW][3];
 #pragma unroll
-                    for (int c = 0; c < NW; ++c) {
-                        const uint4 a[3] = {*(const uint4*)(hrow + c * 64), *(const uint4*)(hrow + c * 64 + C::FWD_PART), *(const uint4*)(hrow + c * 64 + 2 * C::FWD_PART)};
-                        mma_parts_<4>(acc, a, [&](int q) -> const uint4 (&)[3] { return wf[q][c]; });
-                    }
+                    for (int c = 0; c < NW; ++c)
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) a[c][k] = *(const uint4*)(hrow + c * 64 + k * C::FWD_PART);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = 0; c < NW; ++c) mma_parts_<4>(acc, a[c], [&](int q) -> const uint4 (&)[3] { return wf[q][c]; });
                 }
             } else {
                 const char* hrow = hl + r * C::FWD_ROW + kh * (NW * 64) + g * 16;
+                uint4 a[NW];
 #pragma unroll
-                for (int c = 0; c < NW; ++c) {
-                    const uint4 a = *(const uint4*)(hrow + c * 64);
+                for (int c = 0; c < NW; ++c) a[c] = *(const uint4*)(hrow + c * 64);
+                if constexpr (C::SETTLE_F) __builtin_amdgcn_sched_barrier(0);      // (all reads ahead of the products)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a, wf[q][c][0]);
-                }
+                for (int c = 0; c < NW; ++c)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) mma16_<T>(acc[q], a[c], wf[q][c][0]);
             }
             if constexpr (KS == 2) swap_halves_<C>(acc, red, kh, wave, lane);
         } else {
@@ -880,6 +906,14 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         }
         if constexpr (PARTS) plain = __syncthreads_or(not_finite_(check));
         lds_barrier_();                                    // the operand of the products goes into the same LDS
+        if constexpr (C::SETTLE_B) {
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j)
+#pragma unroll
+                for (int c = 0; c < NW; ++c)
+#pragma unroll
+                    for (int k = 0; k < (PARTS ? 3 : 1); ++k) settle_(wf[j][c][k], (j * NW + c) * (PARTS ? 3 : 1) + k);
+        }
     }
     const uint32_t how = join_<C>(cd, w);
     if (__builtin_expect(how >= kAlone, 0)) {
@@ -981,12 +1015,14 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
                 }
             } else {
                 const char* arow = al + r * C::BWD_ROW + g * 16;
+                uint4 a[NW];
 #pragma unroll
-                for (int c = 0; c < NW; ++c) {
-                    const uint4 a = *(const uint4*)(arow + c * 64);
+                for (int c = 0; c < NW; ++c) a[c] = *(const uint4*)(arow + c * 64);
+                if constexpr (C::SETTLE_B) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a, wf[j][c][0]);
-                }
+                for (int c = 0; c < NW; ++c)
+#pragma unroll
+                    for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a[c], wf[j][c][0]);
             }
             // (a tile lies in one workgroup's units: U is a multiple of 16; rows 4 g .. 4 g + 3 of a lane are those of one or two threads)
             const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;
