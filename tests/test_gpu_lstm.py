@@ -101,6 +101,13 @@ def test_gradient_with_padded_rows_of_logits(classes, prec):
     _check_gradient(Shape(8, 16, 1, 0, 0, classes, 9, 3), 2, prec)
 
 
+@pytest.mark.parametrize("hidden", [64, 100])
+@pytest.mark.parametrize("frames", [2, 3, 4, 6, 7, 8, 9])
+def test_gradient_with_inputs_requested_some_frames_ahead(hidden, frames):
+    # backward in fp32 on one compute unit: fewer frames than are requested ahead, whole rounds of the four sets of inputs, one to three more
+    _check_gradient(Shape(8, hidden, 1, 1, 0, 8, 6, frames), 2, 0)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("hidden", [16, 48, 100, 128])
 @pytest.mark.parametrize("batch,frames", [(1, 2), (16, 5), (17, 1)])
