@@ -71,11 +71,11 @@ template <typename T, int S_> struct Cl {
     static constexpr int FWD_BUF = PARTS ? 3 * FWD_PART : RB * FWD_ROW, BWD_BUF = PARTS ? 3 * BWD_PART : RB * BWD_ROW;   // one frame's operand
     static constexpr int W_ROW = KP + 4;                   // words of a row of staged W_h: rows 4 apart lie 16 banks apart
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
-    static constexpr int PPT = RB * U / 256;                                    // backward: rows of its unit that a thread finishes
+    static constexpr int PR = RB * U / 256;                                     // backward: consecutive units of a row that a thread finishes
     static constexpr int64_t FWD_SLOT = (int64_t)RB * RW, BWD_SLOT = (int64_t)S * RB * KP;              // exchange words
     // backward on one XCD: values without tags, and flags: 32-bit words of a slot, values and then a flag per (target, sender, wave)
     static constexpr int64_t RAW_VALUES = BWD_SLOT, RAW_SLOT = RAW_VALUES + (int64_t)S * 4 * S;
-    static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 64 == 0 && PPT % 2 == 0, "tiling");
+    static_assert(NCH % KS == 0 && KP % 64 == 0 && RW % 64 == 0 && PR * (int)sizeof(T) == 8, "tiling");
 };
 
 // Scratch words of a workgroup that does a cluster's work alone.
@@ -152,25 +152,34 @@ __device__ inline bool wait_flags_(const ClusterDesc& p, buf_t x, uint32_t bytes
     }
 }
 
-// Values of the rows of one unit that a thread finishes, and the four rows 4 g .. of column r of an accumulator: those of one thread
-// or of two.
-template <int PPT> struct Rows;
-template <> struct Rows<4> {
-    typedef u32x4_t type;
-    __device__ static type load(buf_t x, int tid, uint32_t bytes) { return __builtin_amdgcn_raw_buffer_load_b128(x, tid * 16, (int)bytes, kFromL2); }
-    template <int U> __device__ static void store(const f32x4_t& a, buf_t x, int g, int r, uint32_t bytes) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, a), x, (g * U + r) * 16, (int)bytes, kToL2);
+// The N values of one row that a thread finishes backward, one access.
+template <int N> struct Vec;
+template <> struct Vec<4> {
+    typedef __attribute__((ext_vector_type(4))) float type;
+    template <int POLICY = 0> __device__ static type load(buf_t x, uint32_t lane_bytes, uint32_t bytes) {
+        return __builtin_bit_cast(type, __builtin_amdgcn_raw_buffer_load_b128(x, (int)lane_bytes, (int)bytes, POLICY));
+    }
+    template <int POLICY = 0> __device__ static void store(type v, buf_t x, uint32_t lane_bytes, uint32_t bytes) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), x, (int)lane_bytes, (int)bytes, POLICY);
     }
 };
-template <> struct Rows<2> {
-    typedef u32x2_t type;
-    __device__ static type load(buf_t x, int tid, uint32_t bytes) { return __builtin_amdgcn_raw_buffer_load_b64(x, tid * 8, (int)bytes, kFromL2); }
-    template <int U> __device__ static void store(const f32x4_t& a, buf_t x, int g, int r, uint32_t bytes) {
-        const u32x4_t v = __builtin_bit_cast(u32x4_t, a);
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v.x, v.y}, x, (2 * g * U + r) * 8, (int)bytes, kToL2);
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v.z, v.w}, x, (2 * g * U + r) * 8, (int)(bytes + (uint32_t)U * 8u), kToL2);
+template <> struct Vec<2> {
+    typedef f32x2_t type;
+    template <int POLICY = 0> __device__ static type load(buf_t x, uint32_t lane_bytes, uint32_t bytes) {
+        return __builtin_bit_cast(type, __builtin_amdgcn_raw_buffer_load_b64(x, (int)lane_bytes, (int)bytes, POLICY));
+    }
+    template <int POLICY = 0> __device__ static void store(type v, buf_t x, uint32_t lane_bytes, uint32_t bytes) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), x, (int)lane_bytes, (int)bytes, POLICY);
     }
 };
+// The same N values in the operand type: 8 bytes, four or two of them.
+template <class V> __device__ inline u32x2_t operand8_(const V& v) {
+    if constexpr (sizeof(V) == 16) return u32x2_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    else return __builtin_bit_cast(u32x2_t, v);            // (whole: an element of a vector, cast by itself, is its first element)
+}
+template <int POLICY = 0> __device__ inline void buf_store8_(u32x2_t v, buf_t x, uint32_t lane_bytes, uint32_t bytes) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, x, (int)lane_bytes, (int)bytes, POLICY);
+}
 
 // A cluster's word: how many of its members have started, 6 bits for each XCD; kClosed and the member it is left to.
 constexpr int kXcds = 8;
@@ -260,12 +269,18 @@ __device__ inline void parts8_(const uint4& lo, const uint4& hi, uint4 (&p)[3], 
     for (int i = 0; i < 3; ++i) p[i] = make_uint4(w[0][i], w[1][i], w[2][i], w[3][i]);
 }
 __device__ inline bool not_finite_(float check) { return !(check - check == 0.f); }
+// Ends the wave if the flag (in LDS, the same for all waves behind a barrier) is set.  Not a branch for the compiler, which has every exit from a loop
+// join the way back into it, and waits at the top of the loop for all that may be outstanding on either.
+__device__ inline void end_if_(const int& flag) {
+    const int f = __builtin_amdgcn_readfirstlane(flag);
+    asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 .Lgo_on%=\n\ts_endpgm\n.Lgo_on%=:" ::"s"(f) : "scc");
+}
 // Fragment i of a member's W_h, when ordinary code has done with it: the first 60 of a lane go to its accumulation registers, which matrix instructions
 // read as they are (16 registers are left for sums).  Left to itself the compiler spreads W_h over both halves of the register file and copies
 // fragments between them in every frame, 112 copies at 512 cells in bf16, and has no registers to read a frame's operand from the LDS ahead of its products:
-// 16 reads and waits one after the other.  us of a pass of 21 frames, before / with both: forward bf16 16 x 2 x 512 cells, batch 64 297 / 270, 8 x 2 x 640, 96
+// 8 to 16 reads and waits one after the other.  us of a pass of 21 frames, before / with both: forward bf16 16 x 2 x 512 cells, batch 64 297 / 270, 8 x 2 x 640, 96
 // 333 / 296, fp32 6 x 320, 64 84 / 80; backward 317 / 312, -, 82 / 79.  SETTLE_F, SETTLE_B: where both passes are the faster for it; not
-// backward at 640 cells in bf16 (415 / 426), nor with W_h in fp32 (16 x 2 x 512, 16 313 / 328 and 303 / 313).
+// backward at 640 cells in bf16 (415 / 426; there the operand is read three chunks ahead, 404), nor with W_h in fp32 (16 x 2 x 512, 16 313 / 328 and 303 / 313).
 __device__ inline void settle_(uint4& w, int i) {
     if (i >= 60) return;
     u32x4_t x = __builtin_bit_cast(u32x4_t, w);
@@ -273,12 +288,15 @@ __device__ inline void settle_(uint4& w, int i) {
     w = __builtin_bit_cast(uint4, x);
 }
 // acc[0..N) += a b[0..N), smallest products first
-template <int N, class B> __device__ inline void mma_parts_(f32x4_t (&acc)[N], const uint4 (&a)[3], B b) {
+template <bool W_FIRST, int N, class B> __device__ inline void mma_parts_(f32x4_t (&acc)[N], const uint4 (&a)[3], B b) {
     constexpr int QA[6] = {0, 2, 1, 0, 1, 0}, QB[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
     for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int j = 0; j < N; ++j) mma16_<bf16_t>(acc[j], a[QA[t]], b(j)[QB[t]]);
+        for (int j = 0; j < N; ++j) {
+            if constexpr (W_FIRST) mma16_<bf16_t>(acc[j], b(j)[QB[t]], a[QA[t]]);
+            else mma16_<bf16_t>(acc[j], a[QA[t]], b(j)[QB[t]]);
+        }
 }
 // Eight fp32 values k .. k + 7 of a row of W_h (forward): gate q of unit u.
 __device__ inline void fwd_row8_(buf_t wh, int H, int q, int u, int k0, int g, uint4& lo, uint4& hi) {
@@ -296,17 +314,17 @@ __device__ inline float fwd_cell_(f32x4_t (&acc)[4], int i, float& c) {
     return acc[3][i] * tanhf_(c);
 }
 
-// The da of one cell from dh, dc, the gates, c_t and c_{t'}; dc becomes that of the next frame.
+// The da of cell i of a thread from dh, dc, the gates, c_t and c_{t'}; dc becomes that of the next frame.
 // (rows past the batch and units past H: all gates were read as 0, so all four results are 0)
-__device__ inline void bwd_cell_(float (&a)[4], float dh, float& dc, const float (&gate)[4], float c, float c_prev) {
-    const float ig = gate[0], fg = gate[1], gg = gate[2], og = gate[3];
+template <class V> __device__ inline void bwd_cell_(V (&a)[4], int i, float dh, float& dc, const V (&gate)[4], float c, float c_prev) {
+    const float ig = gate[0][i], fg = gate[1][i], gg = gate[2][i], og = gate[3][i];
     const float tc = tanhf_(c);
     const float dov = dh * tc;
     const float dcv = dc + dh * og * (1.f - tc * tc);
     const float di = dcv * gg, dg = dcv * ig, df = dcv * c_prev;
     dc = dcv * fg;
-    a[0] = di * ig * (1.f - ig); a[1] = df * fg * (1.f - fg);
-    a[2] = dg * (1.f - gg * gg); a[3] = dov * og * (1.f - og);
+    a[0][i] = di * ig * (1.f - ig); a[1][i] = df * fg * (1.f - fg);
+    a[2][i] = dg * (1.f - gg * gg); a[3][i] = dov * og * (1.f - og);
 }
 
 // fp32: the two waves of a unit hold halves of the contraction; each finishes two of the four rows of a lane.
@@ -351,22 +369,20 @@ template <typename T> __device__ inline uint4 bwd_frag_(buf_t wh, int H, int q, 
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// Column sums of da of member mm over the threads of a unit, in order.
-template <class C> __device__ inline void bias_sums_(const ClusterDesc& cd, const Place& w, float (&bred)[4][256], const float (&bs)[4], int mm) {
-    constexpr int U = C::U, RSTEP = 256 / U;
+// Column sums of da of member mm over the rows of its cluster, in order; bs: a thread's sums over the frames.
+template <class C> __device__ inline void bias_sums_(const ClusterDesc& cd, const Place& w, float (&bred)[4][C::RB * C::U], const typename Vec<C::PR>::type (&bs)[4], int mm) {
+    constexpr int U = C::U;
     const RecDesc& p = cd.r;
     const int tid = threadIdx.x, H = p.H, cu = mm * U + tid % U;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) bred[q][tid] = bs[q];
+    for (int q = 0; q < 4; ++q) *(typename Vec<C::PR>::type*)&bred[q][tid * C::PR] = bs[q];
     __syncthreads();
-    if (tid < U && cu < H) {
+    if (tid < 4 * U && cu < H) {
+        const int q = tid / U;
+        float v = bred[q][tid % U];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float v = bred[q][tid];
-#pragma unroll
-            for (int k = 1; k < RSTEP; ++k) v += bred[q][tid + k * U];
-            p.dbp[w.li * p.sDBi + (int64_t)w.blk * ((int64_t)p.D * H * 4) + (int64_t)w.d * 4 * H + (int64_t)q * H + cu] = v;
-        }
+        for (int k = 1; k < C::RB; ++k) v += bred[q][k * U + tid % U];
+        p.dbp[w.li * p.sDBi + (int64_t)w.blk * ((int64_t)p.D * H * 4) + (int64_t)w.d * 4 * H + (int64_t)q * H + cu] = v;
     }
 }
 
@@ -389,7 +405,7 @@ template <typename T, class C> __device__ inline void bwd_plain_(f32x4_t (&acc)[
 #pragma unroll
         for (int j = 0; j < C::NT; ++j) {
             const int n = (wave + 4 * j) * 16 + r;
-            mma16_<T>(acc[j], a, bwd_frag_<T>(wh, H, q, k, n));
+            mma16_<T>(acc[j], bwd_frag_<T>(wh, H, q, k, n), a);
         }
     }
 }
@@ -455,7 +471,7 @@ __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, cha
                             fwd_row8_(wh, H, q, u, (kh * C::PCW + c) * 32, g, lo, hi);
                             parts8_(lo, hi, b[q], check);
                         }
-                        mma_parts_<4>(sum, a, [&](int q) -> const uint4 (&)[3] { return b[q]; });
+                        mma_parts_<false, 4>(sum, a, [&](int q) -> const uint4 (&)[3] { return b[q]; });
                     }
                     plain = __syncthreads_or(not_finite_(check));
                     if (!plain) {
@@ -488,9 +504,10 @@ __device__ inline void forward_alone_(const ClusterDesc& cd, const Place& w, cha
 }
 
 template <typename T, int S>
-__device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, char* lds, float (&bred)[4][256]) {
+__device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, char* lds, float (&bred)[4][Cl<T, S>::RB * Cl<T, S>::U]) {
     typedef Cl<T, S> C;
-    constexpr int U = C::U, PPT = C::PPT;
+    constexpr int U = C::U, PR = C::PR;
+    typedef typename Vec<PR>::type V;
     const RecDesc& p = cd.r;
     const int D = p.D, H = p.H, B = p.B, Tn = p.T, d = w.d;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
@@ -501,11 +518,11 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
     const buf_t da = make_buf_((const T*)p.da + w.li * p.sDAi, (int64_t)Tn * B * G4 * sizeof(T));
     const buf_t dcb = make_buf_(p.dc + w.li * p.sDCi + (int64_t)d * B * H, (int64_t)B * H * 4);
     const buf_t wh = make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T));
-    // scratch: dh [16 rows][KP] in the first slot of the cluster, sums of da [member][gate][thread] in the second
+    // scratch: dh [16 rows][KP] in the first slot of the cluster, sums of da [member][gate][unit of a thread][thread] in the second
     word_t* const dh_buf = (word_t*)cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT;
     word_t* const bs_buf = dh_buf + C::BWD_SLOT;
-    static_assert(S * 4 * 256 <= C::BWD_SLOT && S <= 16, "the sums of da fit a slot, the members a half of in_fp32");
-    const int uu = tid % U;
+    static_assert(S * 4 * PR * 256 <= C::BWD_SLOT && S <= 16, "the sums of da fit a slot, the members a half of in_fp32");
+    const int crow = tid / 16, uu = tid % 16 * PR;           // this thread's row, and the first of its units
     uint32_t in_fp32 = 0;                                  // members that multiply in fp32, by the parity of the frame (not_finite of the kernel below)
 #pragma unroll 1
     for (int s = 0; s < Tn; ++s) {
@@ -516,38 +533,39 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
 #pragma unroll 1
         for (int mm = 0; mm < S; ++mm) {
             const int cu = mm * U + uu;
-            float bs[4], check = 0.f;
+            const uint32_t row = w.b0 + crow;
+            const bool ok = cu < H && (int)row < B;
+            const uint32_t vg = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange, vc = ok ? (row * H + cu) * 4u : kOutOfRange;
+            const uint32_t vy = ok ? (row * DH + d * H + cu) * 4u : kOutOfRange;
+            float check = 0.f;
+            V gate[4], a4[4], dcv = s > 0 ? Vec<PR>::load(dcb, vc, 0u) : V{};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) bs[q] = s > 0 ? scratch_get_(bs_buf + (mm * 4 + q) * 256 + tid) : 0.f;
-#pragma unroll 1
-            for (int i = 0; i < PPT; ++i) {
-                const int lr = tid / U * PPT + i;
-                const uint32_t row = w.b0 + lr;
-                const bool ok = cu < H && (int)row < B;
-                const uint32_t vg = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange, vc = ok ? (row * H + cu) * 4u : kOutOfRange;
-                const uint32_t vy = ok ? (row * DH + d * H + cu) * 4u : kOutOfRange;
-                float gate[4], a4[4], dc = s > 0 ? buf_load_(dcb, vc, 0u) : 0.f;
+            for (int q = 0; q < 4; ++q) gate[q] = Vec<PR>::load(gates, vg, (m * G4 + q * H) * 4u);
+            const V in_dy = Vec<PR>::load(dy, vy, m * DH * 4u), in_c = Vec<PR>::load(cbuf, vc, m * H * 4u);
+            const V c_prev = Vec<PR>::load(cbuf, s + 1 < Tn ? vc : kOutOfRange, s + 1 < Tn ? m_next * H * 4u : 0u);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) gate[q] = buf_load_(gates, vg, (m * G4 + q * H) * 4u);
-                const float dh = s > 0 ? scratch_get_(dh_buf + lr * C::KP + cu) : 0.f;
-                const float c_prev = buf_load_(cbuf, s + 1 < Tn ? vc : kOutOfRange, s + 1 < Tn ? m_next * H * 4u : 0u);
-                bwd_cell_(a4, buf_load_(dy, vy, m * DH * 4u) + dh, dc, gate, buf_load_(cbuf, vc, m * H * 4u), c_prev);
-                buf_store_(dc, dcb, vc, 0u);
-                T* arow = (T*)(lds + lr * C::BWD_ROW) + uu;
+            for (int i = 0; i < PR; ++i) {
+                const float dh = s > 0 ? scratch_get_(dh_buf + crow * C::KP + cu + i) : 0.f;
+                float dc = dcv[i];
+                bwd_cell_(a4, i, in_dy[i] + dh, dc, gate, in_c[i], c_prev[i]);
+                dcv[i] = dc;
+            }
+            Vec<PR>::store(dcv, dcb, vc, 0u);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    bs[q] += a4[q];
-                    const T v = Elem<T>::from(a4[q]);
-                    arow[q * U] = v;
-                    buf_store_(v, da, ok ? vg / (4u / (uint32_t)sizeof(T)) : kOutOfRange, (m * G4 + q * H) * (uint32_t)sizeof(T));
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int i = 0; i < PR; ++i) {
+                    word_t* const at = bs_buf + ((mm * 4 + q) * PR + i) * 256 + tid;
+                    scratch_put_(at, (s > 0 ? scratch_get_(at) : 0.f) + a4[q][i]);
                 }
+                const u32x2_t v = operand8_(a4[q]);
+                *(u32x2_t*)(lds + crow * C::BWD_ROW + (uu + q * U) * (int)sizeof(T)) = v;
+                buf_store8_(v, da, ok ? vg / (4u / (uint32_t)sizeof(T)) : kOutOfRange, (m * G4 + q * H) * (uint32_t)sizeof(T));
                 if constexpr (C::PARTS) {
                     uint32_t a3[3];
-                    parts2_(a4[0], a4[1], a3, check); parts2_(a4[2], a4[3], a3, check);
+                    parts2_(a4[q][0], a4[q][1], a3, check);
                 }
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) scratch_put_(bs_buf + (mm * 4 + q) * 256 + tid, bs[q]);
             __syncthreads();
             if (s + 1 < Tn) {
                 f32x4_t acc[C::NT];
@@ -567,7 +585,7 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
                             const int n = (wave + 4 * j) * 16 + r;
                             parts8_(bwd_frag_<T>(wh, H, c, k, n), bwd_frag_<T>(wh, H, c, k + 16, n), b[j], check_w);
                         }
-                        mma_parts_<C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return b[j]; });
+                        mma_parts_<true, C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return b[j]; });
                     }
                     const uint32_t bit = 1u << (mm + 16 * (s & 1));
                     if (__syncthreads_or(not_finite_(check) || not_finite_(check_w))) in_fp32 |= bit;
@@ -588,16 +606,18 @@ __device__ inline void backward_alone_(const ClusterDesc& cd, const Place& w, ch
             for (int j = 0; j < C::NT; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    scratch_put_(dh_buf + (4 * g + i) * C::KP + (wave + 4 * j) * 16 + r, sum[j][i]);
+                    scratch_put_(dh_buf + r * C::KP + (wave + 4 * j) * 16 + 4 * g + i, sum[j][i]);
             __threadfence();
             __syncthreads();
         }
     }
 #pragma unroll 1
     for (int mm = 0; mm < S; ++mm) {
-        float bs[4];
+        V bs[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) bs[q] = scratch_get_(bs_buf + (mm * 4 + q) * 256 + tid);
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < PR; ++i) bs[q][i] = scratch_get_(bs_buf + ((mm * 4 + q) * PR + i) * 256 + tid);
         bias_sums_<C>(cd, w, bred, bs, mm);
         __syncthreads();
     }
@@ -737,7 +757,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
                         for (int k = 0; k < 3; ++k) a[c][k] = *(const uint4*)(hrow + c * 64 + k * C::FWD_PART);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int c = 0; c < NW; ++c) mma_parts_<4>(acc, a[c], [&](int q) -> const uint4 (&)[3] { return wf[q][c]; });
+                    for (int c = 0; c < NW; ++c) mma_parts_<false, 4>(acc, a[c], [&](int q) -> const uint4 (&)[3] { return wf[q][c]; });
                 }
             } else {
                 const char* hrow = hl + r * C::FWD_ROW + kh * (NW * 64) + g * 16;
@@ -797,16 +817,22 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
 //   do = dh tanh(c_t)            dc = dc_rec + dh o (1 - tanh^2 c_t)
 //   di = dc g, dg = dc i, df = dc c_{t'}, dc_rec <- dc f
 //   da = (di i(1-i), df f(1-f), dg (1-g^2), do o(1-o))
-// A thread finishes PPT consecutive rows of one unit of the workgroup; it adds the partial sums of its positions in the order
-// of the members.  The column sums of da (bias gradients) run over all frames in registers: one row per row block.
+// A thread finishes PR consecutive units of one row, in accesses of 16 bytes (8 of the operand type): W_h is the first operand of the products, so that a
+// lane's four results are consecutive units of a row too, and partial sums lie [16 units][16 rows][unit], whole lines to a wave's store (rows of 64 units,
+// half lines of 16 rows to a store: 48 cycles a store instead of 15).  With four rows of one unit to a thread a frame's inputs and da are 40 accesses of 2 and
+// 4 bytes instead of 10 (us of a pass, before / after: bf16 16 x 2 x 512, batch 64 308 / 299, 32 x 2 x 256, 64 246 / 235, 8 x 2 x 640, 96 399 / 405; fp32 16 x 2 x 256, 32
+// 76 / 72).  It adds
+// the partial sums of its positions in the order of the members.  The sums of da over the frames (bias gradients) stay in registers: one row per row
+// block.
 template <typename T, int S>
 __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDesc cd) {
     typedef Cl<T, S> C;
-    constexpr int U = C::U, PPT = C::PPT;
+    constexpr int U = C::U, PR = C::PR;
+    typedef typename Vec<PR>::type V;
     constexpr bool PARTS = C::PARTS;
     constexpr int OP_BYTES = 2 * C::BWD_BUF, W_BYTES = 2 * 16 * C::W_ROW * 4;
     __shared__ __attribute__((aligned(16))) char lds[OP_BYTES > W_BYTES ? OP_BYTES : W_BYTES];
-    __shared__ float bred[4][256];
+    __shared__ __attribute__((aligned(16))) float bred[4][C::RB * U];
     __shared__ int expired, not_finite[2];                 // not_finite: by the parity of the frame, and never cleared
     const RecDesc& p = cd.r;
     Place w;
@@ -823,38 +849,26 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     const buf_t xch = make_buf_(cd.exchange + (int64_t)w.cluster * 2 * C::BWD_SLOT, 2 * C::BWD_SLOT * 8);
     const buf_t raw = make_buf_(cd.raw + (int64_t)w.cluster * 2 * C::RAW_SLOT, 2 * C::RAW_SLOT * 4);
 
-    // cell part: this thread's unit and rows
-    const int uu = tid % U, cu = w.m * U + uu;
-    const bool ok_c = cu < H;
-    uint32_t vg[PPT], vc[PPT], vy[PPT];
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) {
-        const uint32_t row = w.b0 + tid / U * PPT + i;
-        const bool ok = ok_c && (int)row < B;
-        vg[i] = ok ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange;
-        vc[i] = ok ? (row * H + cu) * 4u : kOutOfRange;
-        vy[i] = ok ? (row * DH + d * H + cu) * 4u : kOutOfRange;
-    }
-    float in_dy[PPT], in_c[PPT], in_g[PPT][4];             // inputs of the next frame to be finished
-    auto load_in = [&](int s) {
+    // cell part: this thread's row and units
+    const int crow = tid / 16, uu = tid % 16 * PR, cu = w.m * U + uu;
+    const uint32_t row = w.b0 + crow;
+    const bool ok_c = cu < H && (int)row < B;              // (H: a multiple of 4)
+    const uint32_t vg = ok_c ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange, vc = ok_c ? (row * H + cu) * 4u : kOutOfRange;
+    const uint32_t vy = ok_c ? (row * DH + d * H + cu) * 4u : kOutOfRange;
+    const uint32_t at_values = (uint32_t)(uu / 16 * 256 + crow * 16 + uu % 16);      // of 16 rows of U partial sums
+    struct In { V dy, g[4], c; };                          // what a frame reads: dY, the gates, the cell state of the frame handled after it
+    auto load_in = [&](int s, In& in) {
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;                    // reverse of the forward order
+        in.dy = Vec<PR>::template load<kPassing>(dy, vy, m * DH * 4u);
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            in_dy[i] = buf_load_<kPassing>(dy, vy[i], m * DH * 4u);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) in_g[i][q] = buf_load_<kPassing>(gates, vg[i], (m * G4 + q * H) * 4u);
-        }
+        for (int q = 0; q < 4; ++q) in.g[q] = Vec<PR>::template load<kPassing>(gates, vg, (m * G4 + q * H) * 4u);
+        const bool end = s + 1 >= Tn;                      // the cell state before the first frame is 0
+        const uint32_t mc = (uint32_t)(d == 0 ? Tn - 1 - (end ? Tn - 1 : s + 1) : (end ? Tn - 1 : s + 1)) * B;
+        in.c = Vec<PR>::template load<kPassing>(cbuf, end ? kOutOfRange : vc, mc * H * 4u);
     };
-    auto load_c = [&](int s, float (&c)[PPT]) {            // s = T: the cell state before the first frame is 0
-        const bool end = s >= Tn;
-        const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - (end ? Tn - 1 : s) : (end ? Tn - 1 : s)) * B;
-#pragma unroll
-        for (int i = 0; i < PPT; ++i) c[i] = buf_load_<kPassing>(cbuf, end ? kOutOfRange : vc[i], m * H * 4u);
-    };
-    float c_prev[PPT];
-    load_c(0, in_c);
-    load_in(0);
-    load_c(1, c_prev);
+    V c = Vec<PR>::template load<kPassing>(cbuf, vc, (uint32_t)(d == 0 ? Tn - 1 : 0) * B * H * 4u);
+    In in;
+    load_in(0, in);
 
     // product part: columns n of W_h (tiles wave, wave + 4, ...), rows: the four gates of this workgroup's units
     // Rows of W_h come in as they lie, a k-chunk (16 words of a column's fragments deep) at a time, two chunks ahead, and the
@@ -920,38 +934,48 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
         if (how == kAlone + (uint32_t)w.m) backward_alone_<T, S>(cd, w, lds, bred);
         return;
     }
-    float dcr[PPT], bs[4] = {0.f, 0.f, 0.f, 0.f};
+    float dcr[PR];
+    V bs[4];
 #pragma unroll
-    for (int i = 0; i < PPT; ++i) dcr[i] = 0.f;
+    for (int i = 0; i < PR; ++i) {
+        dcr[i] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bs[q][i] = 0.f;
+    }
 
-#pragma unroll 1
-    for (int s = 0; s < Tn; ++s) {
+    // The two ways of the exchange, the first frame and the last each have their own code: where branches meet the compiler waits for all that may be
+    // outstanding on either, here inputs of the next frame on their way from memory and the flags just stored (us of a pass of 21 frames, one code for
+    // all / this: bf16 16 x 2 x 512, batch 64 306 / 284, 10 x 2 x 360, 50 130 / 119, 32 x 2 x 256, 64 240 / 220, 8 x 2 x 640, 96 417 / 396; fp32 16 x 2 x 256, 32 73 / 69, 16 x 2 x
+    // 512, 16 305 / 278).  Inputs requested earlier, with the partial sums, delay those: 366, 156, 268.
+    auto frame = [&](int s, auto one_xcd_, auto first_, auto last_) {
+        constexpr bool one_xcd = decltype(one_xcd_)::value, first = decltype(first_)::value, last = decltype(last_)::value;
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;
-        float dh[PPT];
+        float dh[PR];
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) dh[i] = 0.f;
-        if (s > 0) {
+        for (int i = 0; i < PR; ++i) dh[i] = 0.f;
+        In next;
+        if constexpr (!first) {
             bool ok = true;
-            if (how == kOneXcd) {                          // values [member][thread][row]
+            if constexpr (one_xcd) {                          // values [member][16 units][row][unit]
                 const uint32_t slot = (uint32_t)(s & 1) * (uint32_t)(C::RAW_SLOT * 4);
                 ok = wait_flags_(cd, raw, slot + (uint32_t)(C::RAW_VALUES + w.m * 4 * S) * 4u, 4 * S, lane, w.tag0 + s);
                 asm volatile("" ::: "memory");             // (the values are loaded after the flags)
-                typename Rows<PPT>::type v[S];
+                V v[S];
 #pragma unroll
-                for (int j = 0; j < S; ++j) v[j] = Rows<PPT>::load(raw, tid, slot + (uint32_t)((w.m * S + j) * C::RB * U) * 4u);
+                for (int j = 0; j < S; ++j) v[j] = Vec<PR>::template load<kFromL2>(raw, at_values * 4u, slot + (uint32_t)((w.m * S + j) * C::RB * U) * 4u);
 #pragma unroll
                 for (int j = 0; j < S; ++j)
 #pragma unroll
-                    for (int i = 0; i < PPT; ++i) dh[i] += __builtin_bit_cast(float, (uint32_t)v[j][i]);
+                    for (int i = 0; i < PR; ++i) dh[i] += v[j][i];
             } else {
-                // partial sums for this workgroup's units: words [member][pair of rows of a thread][thread][row]
+                // partial sums for this workgroup's units: words [member][16 units][row][unit]
                 const uint32_t slot = (uint32_t)((s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U) * 8u;
-                constexpr int PB = PPT * S <= 32 ? PPT : 2;          // rows gathered together
-                static_assert(PPT % PB == 0, "gather blocks");
+                constexpr int PB = PR * S <= 32 ? PR : 2;            // units gathered together
+                static_assert(PR % PB == 0, "gather blocks");
 #pragma unroll
-                for (int i0 = 0; i0 < PPT; i0 += PB) {
+                for (int i0 = 0; i0 < PR; i0 += PB) {
                     uint32_t v[PB * S];
-                    ok &= get_<PB * S / 2>(cd, xch, (uint32_t)tid * 16u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U + (i0 / 2 + j / S) * 512) * 8u; }, w.tag0 + s, v);
+                    ok &= get_<PB * S / 2>(cd, xch, at_values * 8u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U) * 8u + (uint32_t)(i0 / 2 + j / S) * 16u; }, w.tag0 + s, v);
 #pragma unroll
                     for (int i = 0; i < PB; ++i)
 #pragma unroll
@@ -961,48 +985,40 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
             if (!ok) expired = 1;
         }
         char* const al = lds + (s & 1) * C::BWD_BUF;
-        float a4[PPT][4], check = 0.f;
+        V a4[4];
+        u32x2_t op[4];
+        float check = 0.f;
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            bwd_cell_(a4[i], in_dy[i] + dh[i], dcr[i], in_g[i], in_c[i], c_prev[i]);
-            const int row = tid / U * PPT + i;
+        for (int i = 0; i < PR; ++i) bwd_cell_(a4, i, in.dy[i] + dh[i], dcr[i], in.g, c[i], in.c[i]);
+        c = in.c;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                bs[q] += a4[i][q];
-                if constexpr (!PARTS) *((T*)(al + row * C::BWD_ROW) + uu + q * U) = Elem<T>::from(a4[i][q]);
-            }
+        for (int q = 0; q < 4; ++q) {
+            op[q] = operand8_(a4[q]);
+#pragma unroll
+            for (int i = 0; i < PR; ++i) bs[q][i] += a4[q][i];
             if constexpr (PARTS) {                           // 32 k of a gate: in the order in which the fragments of W_h hold them
-                bf16_t* const at = (bf16_t*)(al + row * C::BWD_PART_ROW) + 8 * (uu % 16 / 4) + 4 * (uu / 16) + uu % 4;
+                uint32_t a3[3];
+                parts2_(a4[q][0], a4[q][1], a3, check);
 #pragma unroll
-                for (int q = 0; q < 4; q += 2) {
-                    uint32_t a3[3];
-                    parts2_(a4[i][q], a4[i][q + 1], a3, check);
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        at[k * (C::BWD_PART / 2) + q * U] = (bf16_t)a3[k];
-                        at[k * (C::BWD_PART / 2) + (q + 1) * U] = (bf16_t)(a3[k] >> 16);
-                    }
-                }
+                for (int k = 0; k < 3; ++k) *(uint32_t*)(al + k * C::BWD_PART + crow * C::BWD_PART_ROW + (8 * (uu % 16 / 4) + 4 * (uu / 16) + uu % 4 + q * U) * 2) = a3[k];
+            } else {
+                *(u32x2_t*)(al + crow * C::BWD_ROW + (uu + q * U) * (int)sizeof(T)) = op[q];
             }
-            in_c[i] = c_prev[i];
         }
         // (Once set it holds for all later frames of the parity.  One word for each wave, written in every frame, or three words in turn cost about 1 us
         // of a pass of 20 frames at 256 cells.)
         if (PARTS && (plain || not_finite_(check))) not_finite[s & 1] = 1;
-        if (s + 1 < Tn) {
-            load_in(s + 1);
-            load_c(s + 2, c_prev);
+        if constexpr (!last) {
+            load_in(s + 1, next);
             lds_barrier_();
-            if (__builtin_amdgcn_readfirstlane(expired)) return;
+            end_if_(expired);
             f32x4_t acc[C::NT];
 #pragma unroll
             for (int j = 0; j < C::NT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             if constexpr (PARTS) {
                 if (__builtin_expect(__builtin_amdgcn_readfirstlane(not_finite[s & 1]), 0)) {
 #pragma unroll
-                    for (int i = 0; i < PPT; ++i)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) *((float*)(al + (tid / U * PPT + i) * C::BWD_ROW) + uu + q * U) = a4[i][q];
+                    for (int q = 0; q < 4; ++q) *(V*)(al + crow * C::BWD_ROW + (uu + q * U) * 4) = a4[q];
                     lds_barrier_();
                     bwd_plain_<T, C>(acc, al, make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T)), H, w.m, wave, r, g);
                 } else {
@@ -1010,52 +1026,59 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
                     for (int c = 0; c < NW; ++c) {
                         const uint4 a[3] = {*(const uint4*)(arow + c * 64), *(const uint4*)(arow + c * 64 + C::BWD_PART), *(const uint4*)(arow + c * 64 + 2 * C::BWD_PART)};
-                        mma_parts_<C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return wf[j][c]; });
+                        mma_parts_<true, C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return wf[j][c]; });
                     }
                 }
             } else {
                 const char* arow = al + r * C::BWD_ROW + g * 16;
+                constexpr int A = C::SETTLE_B ? NW : 3;    // chunks that the operand is read ahead
                 uint4 a[NW];
 #pragma unroll
-                for (int c = 0; c < NW; ++c) a[c] = *(const uint4*)(arow + c * 64);
-                if constexpr (C::SETTLE_B) __builtin_amdgcn_sched_barrier(0);
+                for (int c = 0; c < NW && c < A; ++c) a[c] = *(const uint4*)(arow + c * 64);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int c = 0; c < NW; ++c)
+                for (int c = 0; c < NW; ++c) {
+                    if (c + A < NW) a[c + A] = *(const uint4*)(arow + (c + A) * 64);
 #pragma unroll
-                    for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], a[c], wf[j][c][0]);
+                    for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], wf[j][c][0], a[c]);
+                    if (A < NW) __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            // (a tile lies in one workgroup's units: U is a multiple of 16; rows 4 g .. 4 g + 3 of a lane are those of one or two threads)
-            const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;
-            const uint32_t out_lane = (uint32_t)(g * (4 / PPT) * U + r) * 16u;
-            constexpr uint32_t next = PPT == 4 ? 512u * 8u : (uint32_t)U * 16u;        // from rows 0, 1 to rows 2, 3
-            if (how == kOneXcd) {
-                // the rows of a lane are those of one thread or two; they are in the L2 when the wait ends
+            // a tile's results: [row r][units 4 g ..] of 16 x 16 (it lies in one workgroup's units: U is a multiple of 16)
+            const uint32_t at = (uint32_t)(r * 16 + 4 * g);
+            if constexpr (one_xcd) {                       // they are in the L2 when the wait ends
                 const uint32_t to_slot = (uint32_t)((s + 1) & 1) * (uint32_t)(C::RAW_SLOT * 4);
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) {
                     const int n0 = (wave + 4 * j) * 16;
-                    Rows<PPT>::template store<U>(acc[j], raw, g, r, to_slot + (uint32_t)(((n0 / U) * S + w.m) * C::RB * U + n0 % U * PPT) * 4u);
+                    Vec<4>::store<kToL2>(acc[j], raw, at * 4u, to_slot + (uint32_t)(((n0 / U) * S + w.m) * C::RB * U + n0 % U * 16) * 4u);
                 }
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __builtin_amdgcn_raw_buffer_store_b32(w.tag0 + s + 1, raw, lane < S ? (lane * 4 * S + w.m * 4 + wave) * 4 : (int)kOutOfRange,
                                                       (int)(to_slot + (uint32_t)C::RAW_VALUES * 4u), kToL2);
             } else {
+                const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) {
                     const int n0 = (wave + 4 * j) * 16;
-                    const uint32_t to = out + (uint32_t)((n0 / U) * S * C::RB * U) * 8u + (uint32_t)(n0 % U) * 16u;
-                    put2_<kToMemory>(xch, out_lane, to, acc[j][0], acc[j][1], w.tag0 + s + 1);
-                    put2_<kToMemory>(xch, out_lane, to + next, acc[j][2], acc[j][3], w.tag0 + s + 1);
+                    const uint32_t to = out + (uint32_t)((n0 / U) * S * C::RB * U + n0 % U * 16) * 8u;
+                    put2_<kToMemory>(xch, at * 8u, to, acc[j][0], acc[j][1], w.tag0 + s + 1);
+                    put2_<kToMemory>(xch, at * 8u, to + 16u, acc[j][2], acc[j][3], w.tag0 + s + 1);
                 }
             }
         }
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const uint32_t va = vg[i] == kOutOfRange ? kOutOfRange : vg[i] / (4u / (uint32_t)sizeof(T));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) buf_store_<kPassing>(Elem<T>::from(a4[i][q]), da, va, (m * G4 + q * H) * (uint32_t)sizeof(T));
-        }
-    }
+        for (int q = 0; q < 4; ++q) buf_store8_<kPassing>(op[q], da, vg == kOutOfRange ? kOutOfRange : vg / (4u / (uint32_t)sizeof(T)), (m * G4 + q * H) * (uint32_t)sizeof(T));
+        if constexpr (!last) in = next;
+    };
+    auto pass = [&](auto one_xcd) {
+        frame(0, one_xcd, std::true_type{}, std::false_type{});
+#pragma unroll 1
+        for (int s = 1; s + 1 < Tn; ++s) frame(s, one_xcd, std::false_type{}, std::false_type{});
+        frame(Tn - 1, one_xcd, std::false_type{}, std::true_type{});
+    };
+    if (how == kOneXcd) pass(std::true_type{});
+    else pass(std::false_type{});
     bias_sums_<C>(cd, w, bred, bs, w.m);
 }
 
