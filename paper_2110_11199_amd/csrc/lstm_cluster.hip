@@ -1023,10 +1023,17 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
                     bwd_plain_<T, C>(acc, al, make_buf_((const T*)p.wh + w.li * p.sWi + d * p.sWd, (int64_t)4 * H * H * sizeof(T)), H, w.m, wave, r, g);
                 } else {
                     const char* arow = al + r * C::BWD_PART_ROW + g * 16;
+                    uint4 a[NW][3];
+                    auto read = [&](int c) {
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) a[c][k] = *(const uint4*)(arow + c * 64 + k * C::BWD_PART);
+                    };
+                    read(0);                               // (one chunk ahead of the products: 6 x 320 cells, batch 64 73 -> 71 us a pass)
 #pragma unroll
                     for (int c = 0; c < NW; ++c) {
-                        const uint4 a[3] = {*(const uint4*)(arow + c * 64), *(const uint4*)(arow + c * 64 + C::BWD_PART), *(const uint4*)(arow + c * 64 + 2 * C::BWD_PART)};
-                        mma_parts_<true, C::NT>(acc, a, [&](int j) -> const uint4 (&)[3] { return wf[j][c]; });
+                        if (c + 1 < NW) read(c + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        mma_parts_<true, C::NT>(acc, a[c], [&](int j) -> const uint4 (&)[3] { return wf[j][c]; });
                     }
                 }
             } else {
