@@ -283,7 +283,8 @@ int adpsgd_consensus_static(const float* dev_x, int64_t stride, int32_t L, int64
  * stream at every change of phase (no host synchronisation inside the step).
  * Phases: 0 minibatch staging + bf16 weight copy, 1 time-batched GEMMs,
  * 2 recurrent forward steps, 3 recurrent backward steps, 4 softmax
- * cross-entropy, 5 bias-gradient column sums (those that share a launch with
+ * cross-entropy (in 1 where it shares a launch with the output layer's
+ * product), 5 bias-gradient column sums (those that share a launch with
  * products are in 1), 6 mixing + update.
  * adpsgd_profile waits for the stream, reports the totals over all steps since
  * profiling was switched on or last read, and starts a new total:

@@ -609,15 +609,21 @@ int compute_gradients(adpsgd_handle* h, const float* at, const void* const* batc
     g.B = W(h->ix_wo); g.ldb = F; g.sBi = Pp;
     g.C = h->logits; g.ldc = h->ldl; g.sCi = M * h->ldl;
     g.bias = Bias(h->ix_bo); g.sBiasI = Pp;
-    if (int rc = gemm(h, g, "output GEMM")) return rc;
 
     SoftmaxDesc sm{};
     sm.precision = prec; sm.L = n; sm.lmap = act; sm.rows = M; sm.C = C;
     sm.status = h->status;
     sm.logits = h->logits; sm.ldl = h->ldl; sm.sLi = M * h->ldl; sm.y = h->labels; sm.sYi = M;
     sm.dlogits = h->dlogits; sm.ldd = h->ldd; sm.sDi = M * h->ldd; sm.row_loss = h->row_loss;
-    if (int rc = mark(h, 4, 1)) return rc;
-    HIPCHK(launch_softmax_ce(sm, s), "softmax cross-entropy");
+    g.tile = h->tune_gemm_tile;
+    if (output_small_supported(g, sm)) {
+        if (int rc = mark_gemm(h, g, 1, 0)) return rc;
+        HIPCHK(launch_output_small(g, sm, s), "output layer and softmax cross-entropy");
+    } else {
+        if (int rc = gemm(h, g, "output GEMM")) return rc;
+        if (int rc = mark(h, 4, 1)) return rc;
+        HIPCHK(launch_softmax_ce(sm, s), "softmax cross-entropy");
+    }
 
     // ---- backward: output layer(s) ----
     // dW_o = dlogits' z, db_o and the losses, d(z) = dlogits W_o

@@ -193,6 +193,9 @@ struct SoftmaxDesc {
     float* row_loss;                     // [L][rows]
 };
 hipError_t launch_softmax_ce(const SoftmaxDesc& d, hipStream_t s);
+// The product that gives the logits and launch_softmax_ce in one launch (output_small.hip); the logits are not stored.
+bool output_small_supported(const GemmDesc& g, const SoftmaxDesc& p);
+hipError_t launch_output_small(const GemmDesc& g, const SoftmaxDesc& p, hipStream_t s);
 
 // out[z][n] = sum_m in[z][m][n]   (bias gradients), z = lmap.idx[0..L)
 struct ColsumDesc {

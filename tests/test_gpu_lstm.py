@@ -101,6 +101,15 @@ def test_gradient_with_padded_rows_of_logits(classes, prec):
     _check_gradient(Shape(8, 16, 1, 0, 0, classes, 9, 3), 2, prec)
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("classes", [4, 16, 20, 128, 132, 256, 260, 512])
+@pytest.mark.parametrize("hidden,batch,frames", [(8, 9, 1), (24, 5, 3), (16, 16, 2), (32, 11, 3)])
+def test_gradient_with_the_output_layer_and_softmax_in_one_launch(hidden, batch, frames, classes, prec):
+    # class tiles of 16 over the waves: one, a part of one, whole rounds, one more; 9, 15, 32 and 33 frames of blocks of 16; a contraction of part of a
+    # chunk, of one and a part, of more than are in flight
+    _check_gradient(Shape(8, hidden, 1, 1, 0, classes, batch, frames), 3, prec)
+
+
 @pytest.mark.parametrize("hidden", [64, 100])
 @pytest.mark.parametrize("frames", [2, 3, 4, 6, 7, 8, 9])
 def test_gradient_with_inputs_requested_some_frames_ahead(hidden, frames):
