@@ -737,12 +737,18 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
             const bool small = d.P >= (1 << 16) && d.P < (7 << 16) && d.L >= 8 && d.L * d.P <= (d.P < (1 << 18) ? 1 << 24 : 1 << 23);
             // The delayed mean: segments on small models (us, one walk / two learners / four / two kernels: 12 x 20k 7.6 / 4.5 /
             // 4.7 / 7.3, 16 x 100k 12.3 / 5.6 / 6.1 / 10.5, 64 x 100k 45 / 17.6 / 14.5 / 22, 64 x 250k 55 / 36.7 / 35.2 / 36.9;
-            // 128 x 250k 106 / 90 / 72 / 66) and on the largest of 8 to 11 learners (60M, one walk / two learners / two
-            // kernels: 8 1025 / 931 / 1014, 11 1435 / 1295 / 1376).
-            const bool small_mean = d.P < (1 << 18) && d.L >= 12 && d.L * d.P <= (1 << 24), large_mean = d.P >= (1 << 25) && d.L >= 8;
+            // 128 x 250k 106 / 90 / 72 / 66), for up to 32 learners on all below a million parameters (one walk / two / four: 4 x 300k 5.4 / 4.4 / -, 5 x 200k
+            // 6.7 / 4.5 / 5.1, 8 x 60k 7.4 / 4.9 / 4.9, x 300k 11.1 / 5.9 / 6.7, x 800k 14.9 / 14.0 / 13.9, 12 x 300k 14.4 / 8.3 / 8.4, 24 x 500k 29.1 / 25.5 /
+            // 26.9, 32 x 800k 55.1 / 54.8 / 54.6; in an iteration of a model 8 x 737k 21.6 / 18.8 / 17.8, 11 x 416k 21.4 / 16.4 / 15.1, 24 x 737k 49.6 / 46.4 /
+            // 47.8; beside other work on the device four learners a thread lose what they gain alone) and on large ones of 4 to 11 (4 x 12M 93.9 / 92.1, 8 x 12M 196 / 189, 11 x 12M 284 / 257, 8 x 25M 446 / 403; 8 x 60M 1025 / 931, two
+            // kernels 1014).  Between them one walk, which is the faster while all models fit the memory-side cache (8 x 1.5M 23.2 / 26.1, 8 x 3M 47.5 / 50.6;
+            // of models in their iterations 8 x 2.5M 54.5 / 49.4, 8 x 3.8M 71.4 / 69.4).
+            const bool small_mean = d.P < (1 << 18) && d.L >= 12 && d.L * d.P <= (1 << 24);
+            const bool middle_mean = d.P < (1 << 20) && d.L >= 4 && d.L <= 32, large_mean = d.P >= (1 << 23) && d.L >= 4;       // (12 and more of that size: two kernels)
             const int seg = d.sync_segment >= 0 ? d.sync_segment
                             : d.update_first ? (large || small ? 2 : 0)
-                            : (small_mean && d.L >= 32 ? 4 : small_mean || large_mean ? 2 : 0);
+                            : small_mean && d.L >= 32 ? 4
+                            : small_mean || middle_mean || large_mean ? 2 : 0;
             if (n4 > 0 && seg >= 2 && d.L > seg) {
                 if (d.update_first) launch_mean_seg<true>(a, seg, s);
                 else launch_mean_seg<false>(a, seg, s);
