@@ -1131,7 +1131,8 @@ template <typename T, int S> void launch_cluster_t(ClusterDesc& p, bool backward
 // and of 5 frames: bf16 forward 32 x 512, 64 94 / 107, backward 121 / 103; fp32 forward 32 x 512, 64 200 / 331.
 // Of 388 such pairs the estimates picked the longer way by more than 3 us and 5 per cent for 5, and lost 0.2 ms in all; clusters throughout
 // lose 2.8, frames throughout 34.  The bf16 rows were fitted again when backward partial sums went bare, the fp32 rows and the fp32 figures above
-// were not (16 x 512, batch 32 backward 313 us by the estimate, 275 measured): some fp32 passes whose two ways are close still run frame by frame.  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
+// were not (16 x 512, batch 32 backward 313 us by the estimate, 275 measured): some fp32 passes whose two ways are close still run frame by frame;
+// nor were any when backward frames became 5 to 12 per cent shorter (16-byte accesses) and forward ones up to 10 (settle_).  More rows to a cluster (two and four tiles one after the other) shorten nothing: 32 x 512, 64: 16 -> 15 and 18.
 namespace {
 
 double frames_time(const RecDesc& d, bool backward) {

@@ -136,6 +136,13 @@ def test_global_mean_with_the_learners_in_segments(L, P, seg):
     _run(L, P, S.FIXED_RING, 3, mix=S.MIX_ALL, tau=0, tune=tune)
 
 
+@pytest.mark.parametrize("L,P", [(4, 1003), (5, 3), (7, 65537), (11, 262147), (32, 262145), (4, 1048573), (9, 1048577), (4, 8388611), (33, 300001)])
+def test_global_mean_with_the_learners_in_segments_by_default(L, P):
+    # both ends of the sizes that take two learners to a thread by themselves, odd numbers of learners, P % 4 tails, fewer than four elements
+    print("global mean, segments by default", L, P, flush=True)
+    _run(L, P, S.D1D, 2)
+
+
 @pytest.mark.parametrize("L,P", [(12, 20002), (32, 50725), (128, 131071), (128, 131077)])
 def test_global_mean_of_small_models_of_many_learners_by_default(L, P):
     # segments of two and of four learners; the last two sizes lie on either side of the two-kernel form
