@@ -181,6 +181,23 @@ template <int POLICY = 0> __device__ inline void buf_store8_(u32x2_t v, buf_t x,
     __builtin_amdgcn_raw_buffer_store_b64(v, x, (int)lane_bytes, (int)bytes, POLICY);
 }
 
+// Exchange through memory, backward.  A lane holds four consecutive units of a row, 32 bytes of words, two accesses of 16: as they lie, each would be
+// half of every line it touches, and stores that write through to memory pay for that twice.  So two lanes whose rows differ swap one of their two pairs,
+// and an access covers a row of 16 units, 128 bytes, whole, the next one the other row.  Backward pass of 21 frames, us, half lines / whole (four
+// rows of one unit to a thread and whole lines before): bf16 14 x 360 cells, batch 48 193 / 126 (125), 5 x 640, 80 279 / 176 (178); fp32 5 x 320, 65 154 / 136 (135),
+// 6 x 348, 48 181 / 167, 12 x 384, 40 348 / 327 (324) and, the operand not read ahead of its products there (AHEAD), 164 (166) and 320.
+// rows_out_: (a, b), of units 4 g and 4 g + 2 of row r (lane r + 16 g) -> of units 4 g + 2 (r / 8) of rows r % 8 and r % 8 + 8.
+__device__ inline void rows_out_(float& a, float& b) {
+    const int x = __builtin_bit_cast(int, a), y = __builtin_bit_cast(int, b);
+    a = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false));     // lanes 8 to 15 of 16: that of lane ^ 8
+    b = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false));     // lanes 0 to 7
+}
+// rows_in_: (a, b), of units 4 t + 2 (row % 2) of the even row and of the odd one (lane 16 row + t) -> of units 4 t and 4 t + 2 of the lane's row.
+__device__ inline void rows_in_(float& a, float& b) {
+    const auto v = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    a = __builtin_bit_cast(float, (uint32_t)v[0]); b = __builtin_bit_cast(float, (uint32_t)v[1]);
+}
+
 // A cluster's word: how many of its members have started, 6 bits for each XCD; kClosed and the member it is left to.
 constexpr int kXcds = 8;
 constexpr uint64_t kClosed = 1ull << 63;
@@ -856,6 +873,7 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     const uint32_t vg = ok_c ? (row * G4 + d * 4 * H + cu) * 4u : kOutOfRange, vc = ok_c ? (row * H + cu) * 4u : kOutOfRange;
     const uint32_t vy = ok_c ? (row * DH + d * H + cu) * 4u : kOutOfRange;
     const uint32_t at_values = (uint32_t)(uu / 16 * 256 + crow * 16 + uu % 16);      // of 16 rows of U partial sums
+    const uint32_t at_words = PR == 2 ? at_values : (uint32_t)(uu / 16 * 256 + (crow & ~1) * 16 + uu % 16 + 2 * (crow & 1));   // (rows_in_)
     struct In { V dy, g[4], c; };                          // what a frame reads: dY, the gates, the cell state of the frame handled after it
     auto load_in = [&](int s, In& in) {
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;                    // reverse of the forward order
@@ -968,19 +986,20 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
 #pragma unroll
                     for (int i = 0; i < PR; ++i) dh[i] += v[j][i];
             } else {
-                // partial sums for this workgroup's units: words [member][16 units][row][unit]
+                // partial sums for this workgroup's units: words [member][16 units][row][unit], loaded as rows_in_ says
                 const uint32_t slot = (uint32_t)((s & 1) * C::BWD_SLOT + (int64_t)w.m * S * C::RB * U) * 8u;
                 constexpr int PB = PR * S <= 32 ? PR : 2;            // units gathered together
                 static_assert(PR % PB == 0, "gather blocks");
 #pragma unroll
                 for (int i0 = 0; i0 < PR; i0 += PB) {
                     uint32_t v[PB * S];
-                    ok &= get_<PB * S / 2>(cd, xch, at_values * 8u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U) * 8u + (uint32_t)(i0 / 2 + j / S) * 16u; }, w.tag0 + s, v);
+                    ok &= get_<PB * S / 2>(cd, xch, at_words * 8u, [&](int j) { return slot + (uint32_t)((j % S) * C::RB * U) * 8u + (uint32_t)(i0 / 2 + j / S) * 128u; }, w.tag0 + s, v);
 #pragma unroll
                     for (int i = 0; i < PB; ++i)
 #pragma unroll
                         for (int j = 0; j < S; ++j) dh[i0 + i] += __builtin_bit_cast(float, v[2 * (i / 2 * S + j) + i % 2]);
                 }
+                if constexpr (PR == 4) { rows_in_(dh[0], dh[2]); rows_in_(dh[1], dh[3]); }
             }
             if (!ok) expired = 1;
         }
@@ -1038,22 +1057,23 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
                 }
             } else {
                 const char* arow = al + r * C::BWD_ROW + g * 16;
-                constexpr int A = C::SETTLE_B ? NW : 3;    // chunks that the operand is read ahead
+                constexpr bool AHEAD = sizeof(T) == 2 || one_xcd;      // (rows_out_)
+                constexpr int A = !AHEAD ? 0 : C::SETTLE_B ? NW : 3;    // chunks that the operand is read ahead
                 uint4 a[NW];
 #pragma unroll
                 for (int c = 0; c < NW && c < A; ++c) a[c] = *(const uint4*)(arow + c * 64);
-                __builtin_amdgcn_sched_barrier(0);
+                if (AHEAD) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int c = 0; c < NW; ++c) {
                     if (c + A < NW) a[c + A] = *(const uint4*)(arow + (c + A) * 64);
 #pragma unroll
                     for (int j = 0; j < C::NT; ++j) mma16_<T>(acc[j], wf[j][c][0], a[c]);
-                    if (A < NW) __builtin_amdgcn_sched_barrier(0);
+                    if (AHEAD && A < NW) __builtin_amdgcn_sched_barrier(0);
                 }
             }
             // a tile's results: [row r][units 4 g ..] of 16 x 16 (it lies in one workgroup's units: U is a multiple of 16)
-            const uint32_t at = (uint32_t)(r * 16 + 4 * g);
             if constexpr (one_xcd) {                       // they are in the L2 when the wait ends
+                const uint32_t at = (uint32_t)(r * 16 + 4 * g);
                 const uint32_t to_slot = (uint32_t)((s + 1) & 1) * (uint32_t)(C::RAW_SLOT * 4);
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) {
@@ -1064,13 +1084,15 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
                 __builtin_amdgcn_raw_buffer_store_b32(w.tag0 + s + 1, raw, lane < S ? (lane * 4 * S + w.m * 4 + wave) * 4 : (int)kOutOfRange,
                                                       (int)(to_slot + (uint32_t)C::RAW_VALUES * 4u), kToL2);
             } else {
-                const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u;
+                const uint32_t out = (uint32_t)(((s + 1) & 1) * C::BWD_SLOT + (int64_t)w.m * C::RB * U) * 8u, at_row = (uint32_t)(r % 8 * 16 + 4 * g + r / 8 * 2);
 #pragma unroll
                 for (int j = 0; j < C::NT; ++j) {
                     const int n0 = (wave + 4 * j) * 16;
                     const uint32_t to = out + (uint32_t)((n0 / U) * S * C::RB * U + n0 % U * 16) * 8u;
-                    put2_<kToMemory>(xch, at * 8u, to, acc[j][0], acc[j][1], w.tag0 + s + 1);
-                    put2_<kToMemory>(xch, at * 8u, to + 16u, acc[j][2], acc[j][3], w.tag0 + s + 1);
+                    float v[4] = {acc[j][0], acc[j][1], acc[j][2], acc[j][3]};
+                    rows_out_(v[0], v[2]); rows_out_(v[1], v[3]);
+                    put2_<kToMemory>(xch, at_row * 8u, to, v[0], v[1], w.tag0 + s + 1);
+                    put2_<kToMemory>(xch, at_row * 8u + 8u * 128u, to, v[2], v[3], w.tag0 + s + 1);
                 }
             }
         }

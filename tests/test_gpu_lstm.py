@@ -166,6 +166,30 @@ def test_gradient_on_clusters_that_exchange_through_memory(prec, shape, L, membe
         assert (a == b).all()
 
 
+@pytest.mark.parametrize("shape,L", [(Shape(12, 360, 1, 1, 0, 24, 48, 21), 7), (Shape(12, 640, 1, 0, 0, 24, 80, 21), 5)])
+def test_backward_on_clusters_that_exchange_through_memory_keeps_up_with_forward(shape, L):
+    # Both passes exchange H words a row and member and multiply as much.  Partial sums in whole lines: backward 1.67 and 1.89 times as long as forward; in half
+    # lines 2.55 and 3.0.
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("backward against forward through memory", shape, L, flush=True)
+    eng = _engine(shape, L, S.FIXED_RING, 1)
+    eng.set_params(-1, torch.from_numpy(synth.initial_model(1, eng.P, 0.1)).cuda())
+    b = _to_dev(_batches(shape, L, 0))
+    ratios = []
+    for _ in range(5):
+        eng.step(b, 0.0)
+        Bd.adpsgd_set_profiling(eng.h, 1)
+        for _ in range(10):
+            eng.step(b, 0.0)
+        prof = Bd.adpsgd_profile(eng.h)
+        Bd.adpsgd_set_profiling(eng.h, 0)
+        assert prof["recurrent_fwd"]["launches"] == 10 and prof["recurrent_bwd"]["launches"] == 10
+        ratios.append(prof["recurrent_bwd"]["ms"] / prof["recurrent_fwd"]["ms"])
+    eng.close()
+    assert sorted(ratios)[2] < 2.2, ratios
+
+
 @pytest.mark.parametrize("shape,L", [
     (Shape(12, 20, 1, 0, 132, 4104, 193, 8), 16),  # 272 tiles of 256x256 of dW_o, two rounds with a third empty, beside 208 blocks of rows of dz: launches of their own
     (Shape(12, 20, 1, 0, 132, 8200, 193, 8), 8),   # 264 tiles and 104 blocks: dW_o in 128x256 tiles in the launch of dz
