@@ -67,7 +67,7 @@ template <typename T, int S_> struct Cl {
     static constexpr int FWD_PART_ROW = KP * 2 + 16, BWD_PART_ROW = 4 * U * 2 + 16, FWD_PART = RB * FWD_PART_ROW, BWD_PART = RB * BWD_PART_ROW;
     static constexpr bool PARTS = sizeof(T) == 4 && S <= 10;
     static constexpr int PCW = KP / (32 * KS), PBCH = 4 * U / 32;
-    static constexpr bool SETTLE_F = sizeof(T) == 2 || PARTS, SETTLE_B = PARTS || (sizeof(T) == 2 && S <= 8);   // (settle_)
+    static constexpr bool SETTLE_F = sizeof(T) == 2 || (PARTS && S > 8), SETTLE_B = PARTS || (sizeof(T) == 2 && S <= 8);   // (settle_)
     static constexpr int FWD_BUF = PARTS ? 3 * FWD_PART : RB * FWD_ROW, BWD_BUF = PARTS ? 3 * BWD_PART : RB * BWD_ROW;   // one frame's operand
     static constexpr int W_ROW = KP + 4;                   // words of a row of staged W_h: rows 4 apart lie 16 banks apart
     static constexpr int BCH = 4 * U / KC, NT = KP / 64;                        // backward: k-chunks, 16-column tiles of a wave
@@ -296,7 +296,8 @@ __device__ inline void end_if_(const int& flag) {
 // read as they are (16 registers are left for sums).  Left to itself the compiler spreads W_h over both halves of the register file and copies
 // fragments between them in every frame, 112 copies at 512 cells in bf16, and has no registers to read a frame's operand from the LDS ahead of its products:
 // 8 to 16 reads and waits one after the other.  us of a pass of 21 frames, before / with both: forward bf16 16 x 2 x 512 cells, batch 64 297 / 270, 8 x 2 x 640, 96
-// 333 / 296, fp32 6 x 320, 64 84 / 80; backward 317 / 312, -, 82 / 79.  SETTLE_F, SETTLE_B: where both passes are the faster for it; not
+// 333 / 296, fp32 6 x 320, 64 84 / 80; backward 317 / 312, -, 82 / 79.  SETTLE_F, SETTLE_B: the passes that are the faster for it; not
+// forward at 256 cells in fp32, whose registers suffice and whose launch begins 2.4 us later (8 x 256, batch 32, 5 frames 22.1 / 24.8, 21 frames 63.6 / 66.1), nor
 // backward at 640 cells in bf16 (415 / 426; there the operand is read three chunks ahead, 404), nor with W_h in fp32 (16 x 2 x 512, 16 313 / 328 and 303 / 313).
 __device__ inline void settle_(uint4& w, int i) {
     if (i >= 60) return;
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(256, 1) void rec_forward_cluster_kernel(ClusterDesc
                     for (int c = 0; c < NW; ++c)
 #pragma unroll
                         for (int k = 0; k < 3; ++k) a[c][k] = *(const uint4*)(hrow + c * 64 + k * C::FWD_PART);
-                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (C::SETTLE_F) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int c = 0; c < NW; ++c) mma_parts_<false, 4>(acc, a[c], [&](int q) -> const uint4 (&)[3] { return wf[q][c]; });
                 }
