@@ -51,6 +51,12 @@ class _Colsum(ctypes.Structure):       # adpsgd::ColsumDesc
                 ("L_all", ctypes.c_int), ("active_bits", ctypes.c_uint32 * 4)]
 
 
+class _Softmax(ctypes.Structure):      # adpsgd::SoftmaxDesc
+    _fields_ = [("precision", ctypes.c_int), ("L", ctypes.c_int), ("lmap", ctypes.c_uint8 * 128), ("status", ctypes.c_int64), ("rows", ctypes.c_int64), ("C", ctypes.c_int),
+                ("logits", ctypes.c_int64), ("ldl", ctypes.c_int64), ("sLi", ctypes.c_int64), ("y", ctypes.c_int64), ("sYi", ctypes.c_int64),
+                ("dlogits", ctypes.c_int64), ("ldd", ctypes.c_int64), ("sDi", ctypes.c_int64), ("row_loss", ctypes.c_int64)]
+
+
 class _Products(ctypes.Structure):     # adpsgd::GradProducts
     _fields_ = [("has_dx", ctypes.c_bool), ("has_cs", ctypes.c_bool), ("dx", _Gemm), ("ndw", ctypes.c_int), ("dw", _Gemm * 2), ("cs", _Colsum)]
 
@@ -127,3 +133,18 @@ def test_numbers_of_clusters_that_are_meant_to_exchange_through_memory_do(prec, 
     assert members * units >= shape.hidden and (members - 2) * units < shape.hidden
     one_xcd, anywhere = 256 // 8 // members * 8, 256 // members
     assert -(-clusters // one_xcd) > -(-clusters // anywhere)
+
+
+@pytest.mark.parametrize("precision,classes,width,want", [
+    (Bd.BF16_GEMM, 40, 768, True), (Bd.BF16_GEMM, 4, 768, True), (Bd.BF16_GEMM, 4, 776, False), (Bd.BF16_GEMM, 32, 1024, False), (Bd.BF16_GEMM, 16, 2048, False),
+    (Bd.BF16_GEMM, 4, 8192, False), (Bd.BF16_GEMM, 500, 64, True), (Bd.BF16_GEMM, 512, 72, False), (Bd.FP32, 200, 80, True), (Bd.FP32, 208, 80, False),
+])
+def test_output_layer_and_softmax_share_a_launch_where_w_o_is_small_and_its_rows_are_short(precision, classes, width, want):
+    rows, learners = 336, 2
+    ldd = (classes + 63) // 64 * 64
+    g = _gemm_desc(rows, classes, width, learners, a_kc=1, b_kc=1, precision=precision)
+    g.bias = 64
+    sm = _Softmax(precision=precision, L=learners, rows=rows, C=classes, ldl=ldd, sLi=rows * ldd, ldd=ldd, sDi=rows * ldd)
+    supported = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd22output_small_supportedERKNS_8GemmDescERKNS_11SoftmaxDescE"]
+    supported.restype = ctypes.c_bool
+    assert supported(ctypes.byref(g), ctypes.byref(sm)) == want
