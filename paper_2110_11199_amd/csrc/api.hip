@@ -336,9 +336,12 @@ size_t plan(adpsgd_handle* h, void* base) {
         h->dz = h->Bn ? w.take(L * M * h->Bn * e) : nullptr;
         // Rows of logits and dlogits are whole cache lines apart.  Where they are not, the output layer's stores write most lines in two pieces, and
         // memory takes them at 1.7 TB/s instead of 4.5: 8 x 2016 x 9000 x 256 in bf16 335 us, 8 x 2016 x 9024 128; 16 x 1344 x 9000 x 1024 517.
-        h->ldl = (int)round_up(h->C, 32);
+        // Rows shorter than a line take a power of two of elements, so that none lies in two lines: whole lines of few classes are bytes for nothing (us an
+        // iteration, frames x classes x K x learners, whole lines / so: fp32 1344 x 16 x 2048 x 8 282 / 278, 2688 x 4 x 2048 x 16 847 / 841, bf16 1 per cent).
+        auto row = [&](int line) { int n = 4; while (n < h->C && n < line) n *= 2; return (int)round_up(h->C, n); };
+        h->ldl = row(32);
         h->logits = (float*)w.take(L * M * h->ldl * 4);
-        h->ldd = (int)round_up(h->C, 128 / (int)e);
+        h->ldd = (int)round_up(row(128 / (int)e), 16 / (int)e);
         h->dlogits = w.take(L * M * h->ldd * e);
         h->dy = (float*)w.take(L * M * DH * 4);
         h->da = w.take(L * M * G4 * e);

@@ -112,6 +112,15 @@ def test_learning_rate_helper_matches_the_oracle_and_the_papers_figures():
             Bd.adpsgd_lr_at_epoch(*bad)
 
 
+@pytest.mark.parametrize("precision,logits,dlogits", [(Bd.FP32, 4 * 4, 4 * 4), (Bd.BF16_GEMM, 4 * 4, 8 * 2)])
+def test_rows_of_few_classes_are_no_whole_lines(precision, logits, dlogits):
+    # bytes of a frame's logits and of their gradient: 4 classes against 64, whose rows are whole lines of 128 bytes
+    shape = dict(input_dim=8, hidden=16, layers=1, batch=64, frames=1024, precision=precision)
+    few, many = (Bd.adpsgd_workspace_bytes(Bd.make_config(3, Bd.FIXED_RING, classes=c, **shape)) for c in (4, 64))
+    saved = 3 * 64 * 1024 * (64 * 4 + 64 * (2 if precision else 4) - logits - dlogits)
+    assert saved <= many - few < saved + 3 * 64 * 32 * 16          # (and the models, 1020 parameters apart)
+
+
 def test_create_rejects_a_missing_workspace():
     cfg = Bd.make_config(2, 0, flat_params=8)
     with pytest.raises(Bd.AdpsgdError) as ei:
