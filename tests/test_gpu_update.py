@@ -143,6 +143,15 @@ def test_global_mean_with_the_learners_in_segments_by_default(L, P):
     _run(L, P, S.D1D, 2)
 
 
+@pytest.mark.parametrize("L,P,seg", [(4, 4 * 64 + 1, 2), (7, 4 * 128 + 3, 4), (32, 4 * 32 + 2, 2), (128, 4 * 16 * 5 + 3, 4), (128, 4 * 8 + 1, 2), (5, 7, 2), (4, 4 * 64, 2)])
+def test_means_in_segments_whose_last_elements_are_a_workgroup_of_their_own(L, P, seg):
+    # whole workgroups of 64, 32, 16 and 8 positions and one to three elements more, one position and three elements, and no element more
+    from paper_2110_11199_amd import binding as Bd
+    print("means in segments, last elements", L, P, seg, flush=True)
+    _run(L, P, S.D1D, 3, tune=[(Bd.TUNE_MEAN_CHUNK, 0), (Bd.TUNE_SYNC_SEGMENT, seg)])
+    _run(L, P, S.SDPSGD, 3, tune=[(Bd.TUNE_SYNC_SEGMENT, seg)])
+
+
 @pytest.mark.parametrize("L,P", [(12, 20002), (32, 50725), (128, 131071), (128, 131077)])
 def test_global_mean_of_small_models_of_many_learners_by_default(L, P):
     # segments of two and of four learners; the last two sizes lie on either side of the two-kernel form
