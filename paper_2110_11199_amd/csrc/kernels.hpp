@@ -59,6 +59,7 @@ struct UpdateDesc {
     int64_t mean_elems;        //   chunk of that many elements in two kernels (fewer streams per thread); NULL: one kernel
 };
 hipError_t launch_update(const UpdateDesc& d, hipStream_t s);
+int mean_learners_a_thread(int L, int64_t P, bool update_first, bool shadow);
 hipError_t launch_average(const float* x, int64_t stride, int L, int64_t P, float* out, hipStream_t s);
 // out[0] = sum_i sum_e (x_i[e] - mean_i x_i[e])^2 in fp64; partial: kConsensusBlocks doubles of scratch
 constexpr int kConsensusBlocks = 2048;

@@ -696,6 +696,31 @@ __global__ __launch_bounds__(256) void average_kernel(const float* x, int64_t st
     out[t] = __fmul_rn(s, inv_L);
 }
 
+// Learners that a thread of the mean's single-kernel form owns, 0: all of a position.
+int mean_learners_a_thread(int L, int64_t P, bool update_first, bool shadow) {
+    // Two learners per thread are the measured best on large models (64 x 135M: 5.16 -> 5.48 TB/s, 16 x 145M:
+    // 5.49 -> 5.99; four 5.40 / 5.75, eight 5.34 / 5.67) and on small ones, where few threads walk all learners one
+    // after another and the models of all learners still fit caches (us, one walk -> two learners: 16 x 100k 10.4 -> 6.3,
+    // x 400k 15.8 -> 14.8, x 520k 16.7 -> 18.0; 8 x 400k 8.7 -> 7.4; 5 x 400k 5.8 -> 6.3; 32 x 250k 24.6 -> 19.0, x 400k
+    // 29.1 -> 31.0; 64 x 250k 46.6 -> 40.9, x 400k 57 -> 64; 128 x 100k 78 -> 47, x 250k 90 -> 100).
+    if (update_first) return (P >= (4 << 20) && L >= 4) || (P >= (1 << 16) && P < (7 << 16) && L >= 8 && L * P <= (P < (1 << 18) ? 1 << 24 : 1 << 23)) ? 2 : 0;
+    // The delayed mean: segments on small models (us, one walk / two learners / four / two kernels: 12 x 20k 7.6 / 4.5 /
+    // 4.7 / 7.3, 16 x 100k 12.3 / 5.6 / 6.1 / 10.5, 64 x 100k 45 / 17.6 / 14.5 / 22, 64 x 250k 55 / 36.7 / 35.2 / 36.9;
+    // 128 x 250k 106 / 90 / 72 / 66) and on large ones of 4 to 11 learners (4 x 12M 93.9 / 92.1, 8 x 12M 196 / 189, 11 x 12M 284 / 257, 8 x 25M 446 / 403; 8 x 60M
+    // 1025 / 931, two kernels 1014; 12 and more of that size: two kernels).
+    if (P < (1 << 18) && L >= 12 && L * P <= (1 << 24)) return L >= 32 ? 4 : 2;
+    if (P >= (1 << 23) && L >= 4) return 2;
+    // Between them, up to 32 learners: two as long as few threads are in flight (flat vectors, one walk / two: 4 x 350k 6.2 / 5.0, 6 x 500k 8.9 / 6.8, 8 x 270k 10.0 /
+    // 5.8, x 500k 11.3 / 9.5, 12 x 500k 15.2 / 14.0, 16 x 270k 17.5 / 11.4, 32 x 500k 37.3 / 34.5), then one walk, which is the faster while all models fit the
+    // memory-side cache (10 x 700k 15.1 / 17.2, 16 x 700k 24.4 / 25.7, 24 x 600k 33.8 / 36.1, 32 x 600k 44.3 / 49.0, 8 x 1M 16.6 / 18.6; four learners a thread lie between).
+    // The line is later for few learners (4 x 700k 7.4 / 6.6, 6 x 700k 10.5 / 10.6, 8 x 600k 12.8 / 11.7, x 800k 14.7 / 14.6, x 900k 15.7 / 16.7) and where the bf16 copies are
+    // written too (iterations of a model, difference: 8 x 737k -2.2, 16 x 737k -2.6, x 818k -2.2, 24 x 818k -2.9, 32 x 737k -3.8, x 992k +0.5; in fp32 8 x 737k -3.3, 16 x 737k
+    // +0.1, 32 x 587k +3.2, x 737k +4.2).  Up to 8M one walk: flat vectors 8 x 1.5M 23.2 / 26.1, 8 x 3M 47.5 /
+    // 50.6; in iterations 8 x 2.5M 54.5 / 49.4, 8 x 3.8M 71.4 / 69.4.
+    if (L < 4 || L > 32) return 0;
+    return P < ((L <= 8 || shadow) ? 13 << 16 : 1 << 19) ? 2 : 0;
+}
+
 hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
     if (d.L < 1 || d.L > 128 || d.P < 1) return hipErrorInvalidValue;
     bool vec = ((uintptr_t)d.src % 16 == 0) && ((uintptr_t)d.dst % 16 == 0) && (d.stride % 4 == 0);
@@ -734,27 +759,7 @@ hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {
         } else if (vec) {
             const int64_t n4 = d.P >> 2;
             const unsigned blocks = (unsigned)((n4 > 0 ? n4 : 1) + 255) / 256;
-            // Two learners per thread are the measured best on large models (64 x 135M: 5.16 -> 5.48 TB/s, 16 x 145M:
-            // 5.49 -> 5.99; four 5.40 / 5.75, eight 5.34 / 5.67) and on small ones, where few threads walk all learners one
-            // after another and the models of all learners still fit caches (us, one walk -> two learners: 16 x 100k 10.4 -> 6.3,
-            // x 400k 15.8 -> 14.8, x 520k 16.7 -> 18.0; 8 x 400k 8.7 -> 7.4; 5 x 400k 5.8 -> 6.3; 32 x 250k 24.6 -> 19.0, x 400k
-            // 29.1 -> 31.0; 64 x 250k 46.6 -> 40.9, x 400k 57 -> 64; 128 x 100k 78 -> 47, x 250k 90 -> 100).
-            const bool large = d.P >= (4 << 20) && d.L >= 4;
-            const bool small = d.P >= (1 << 16) && d.P < (7 << 16) && d.L >= 8 && d.L * d.P <= (d.P < (1 << 18) ? 1 << 24 : 1 << 23);
-            // The delayed mean: segments on small models (us, one walk / two learners / four / two kernels: 12 x 20k 7.6 / 4.5 /
-            // 4.7 / 7.3, 16 x 100k 12.3 / 5.6 / 6.1 / 10.5, 64 x 100k 45 / 17.6 / 14.5 / 22, 64 x 250k 55 / 36.7 / 35.2 / 36.9;
-            // 128 x 250k 106 / 90 / 72 / 66), for up to 32 learners on all below a million parameters (one walk / two / four: 4 x 300k 5.4 / 4.4 / -, 5 x 200k
-            // 6.7 / 4.5 / 5.1, 8 x 60k 7.4 / 4.9 / 4.9, x 300k 11.1 / 5.9 / 6.7, x 800k 14.9 / 14.0 / 13.9, 12 x 300k 14.4 / 8.3 / 8.4, 24 x 500k 29.1 / 25.5 /
-            // 26.9, 32 x 800k 55.1 / 54.8 / 54.6; in an iteration of a model 8 x 737k 21.6 / 18.8 / 17.8, 11 x 416k 21.4 / 16.4 / 15.1, 24 x 737k 49.6 / 46.4 /
-            // 47.8; beside other work on the device four learners a thread lose what they gain alone) and on large ones of 4 to 11 (4 x 12M 93.9 / 92.1, 8 x 12M 196 / 189, 11 x 12M 284 / 257, 8 x 25M 446 / 403; 8 x 60M 1025 / 931, two
-            // kernels 1014).  Between them one walk, which is the faster while all models fit the memory-side cache (8 x 1.5M 23.2 / 26.1, 8 x 3M 47.5 / 50.6;
-            // of models in their iterations 8 x 2.5M 54.5 / 49.4, 8 x 3.8M 71.4 / 69.4).
-            const bool small_mean = d.P < (1 << 18) && d.L >= 12 && d.L * d.P <= (1 << 24);
-            const bool middle_mean = d.P < (1 << 20) && d.L >= 4 && d.L <= 32, large_mean = d.P >= (1 << 23) && d.L >= 4;       // (12 and more of that size: two kernels)
-            const int seg = d.sync_segment >= 0 ? d.sync_segment
-                            : d.update_first ? (large || small ? 2 : 0)
-                            : small_mean && d.L >= 32 ? 4
-                            : small_mean || middle_mean || large_mean ? 2 : 0;
+            const int seg = d.sync_segment >= 0 ? d.sync_segment : mean_learners_a_thread(d.L, d.P, d.update_first, d.shadow != nullptr);
             if (n4 > 0 && seg >= 2 && d.L > seg) {
                 if (d.update_first) launch_mean_seg<true>(a, seg, s);
                 else launch_mean_seg<false>(a, seg, s);

@@ -148,3 +148,20 @@ def test_output_layer_and_softmax_share_a_launch_where_w_o_is_small_and_its_rows
     supported = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd22output_small_supportedERKNS_8GemmDescERKNS_11SoftmaxDescE"]
     supported.restype = ctypes.c_bool
     assert supported(ctypes.byref(g), ctypes.byref(sm)) == want
+
+
+@pytest.mark.parametrize("learners,params,copies,want", [
+    (4, 350_000, False, 2), (8, 800_000, False, 2), (8, 900_000, False, 0), (12, 500_000, False, 2), (10, 700_000, False, 0), (16, 700_000, False, 0),
+    (24, 600_000, False, 0), (32, 600_000, False, 0), (24, 1_000_000, False, 0),                   # flat vectors and fp32 models: one walk is the shorter from there
+    (16, 737_000, True, 2), (32, 737_000, True, 2), (16, 1_000_000, True, 0),                      # models with a bf16 copy: later
+    (33, 300_000, False, 0), (3, 300_000, False, 0), (12, 20_000, False, 2), (64, 100_000, False, 4), (4, 8_388_608, False, 2), (8, 3_000_000, False, 0),
+])
+def test_delayed_mean_takes_two_learners_to_a_thread_where_that_is_the_shorter(learners, params, copies, want):
+    rule = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd22mean_learners_a_threadEilbb"]
+    assert rule(learners, ctypes.c_int64(params), ctypes.c_bool(False), ctypes.c_bool(copies)) == want
+
+
+@pytest.mark.parametrize("learners,params,want", [(4, 4 << 20, 2), (3, 4 << 20, 0), (8, 400_000, 2), (8, 7 << 16, 0), (16, 100_000, 2), (7, 100_000, 0), (64, 250_000, 2), (64, 400_000, 0)])
+def test_synchronous_mean_takes_two_learners_to_a_thread_where_that_is_the_shorter(learners, params, want):
+    rule = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd22mean_learners_a_threadEilbb"]
+    assert rule(learners, ctypes.c_int64(params), ctypes.c_bool(True), ctypes.c_bool(False)) == want
