@@ -243,22 +243,19 @@ __device__ inline void all_scalar_(const AllArgs& p, int64_t t) {
 // of the updated models, the synchronous baseline) runs through the segments in learner order, one segment per barrier,
 // through LDS: the same additions in the same order as the single walk, bit-identical results.  Every model of the workgroup's
 // positions has been read before the first result is written (the writes follow the last barrier), so it stays safe in place.
-// The P % 4 last elements, a thread for each that walks all learners, are a workgroup of their own, the first: ahead of the segments of another one the walk
-// adds its whole length to small updates, in the last workgroup to large ones.
-template <int SEG, bool FIRST>
+// The P % 4 last elements take a thread each that walks all learners: in front of the first workgroup's segments (kWithin), or in a workgroup of its own, the
+// first (kOwn), for small updates, to which the walk would add its whole length.
+enum Tail { kNone, kWithin, kOwn };
+template <int SEG, bool FIRST, Tail TAIL>
 __global__ __launch_bounds__(1024) void mean_seg_update_kernel(AllArgs p) {
     __shared__ float4 chain[64];
     const int tx = threadIdx.x, sy = threadIdx.y, nx = blockDim.x, ns = blockDim.y;
-    const int last = (int)(p.P & 3);
-    const int64_t e = ((int64_t)blockIdx.x - (last != 0)) * nx + tx;
-    const bool ok = e < (p.P >> 2);
+    const int64_t e = ((int64_t)blockIdx.x - (TAIL == kOwn)) * nx + tx;
+    const bool ok = (TAIL != kOwn || e >= 0) && e < (p.P >> 2);
     const int j0 = sy * SEG;
-    if (last != 0 && blockIdx.x == 0) {
-        if (sy == 0 && tx < last) {
-            if constexpr (FIRST) sync_scalar_(p, ((p.P >> 2) << 2) + tx);
-            else all_scalar_(p, ((p.P >> 2) << 2) + tx);
-        }
-        return;
+    if (TAIL != kNone && blockIdx.x == 0 && sy == 0 && tx < (p.P & 3)) {
+        if constexpr (FIRST) sync_scalar_(p, ((p.P >> 2) << 2) + tx);
+        else all_scalar_(p, ((p.P >> 2) << 2) + tx);
     }
     float4 u[SEG], g[SEG];
 #pragma unroll
@@ -297,7 +294,11 @@ static void launch_mean_seg_t(const AllArgs& a, hipStream_t s) {
     int nx = 64;
     while (nx * ns > 512 && nx > 8) nx >>= 1;
     const int64_t n4 = a.P >> 2;
-    hipLaunchKernelGGL((mean_seg_update_kernel<SEG, FIRST>), dim3((unsigned)((n4 + nx - 1) / nx + (a.P % 4 != 0))), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
+    const unsigned blocks = (unsigned)((n4 + nx - 1) / nx);
+    // (us, within / own: 64 x 262141 59.3 / 40.5, 64 x 4200001 585 / 592)
+    if (a.P % 4 == 0) hipLaunchKernelGGL((mean_seg_update_kernel<SEG, FIRST, kNone>), dim3(blocks), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
+    else if (a.P < (1 << 20)) hipLaunchKernelGGL((mean_seg_update_kernel<SEG, FIRST, kOwn>), dim3(blocks + 1), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
+    else hipLaunchKernelGGL((mean_seg_update_kernel<SEG, FIRST, kWithin>), dim3(blocks), dim3((unsigned)nx, (unsigned)ns), 0, s, a);
 }
 template <bool FIRST>
 static void launch_mean_seg(const AllArgs& a, int seg, hipStream_t s) {
