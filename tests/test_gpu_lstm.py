@@ -110,6 +110,34 @@ def test_gradient_with_the_output_layer_and_softmax_in_one_launch(hidden, batch,
     _check_gradient(Shape(8, hidden, 1, 1, 0, classes, batch, frames), 3, prec)
 
 
+def _softmax_launches(shape, L, prec, tune=()):
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    eng = _engine(shape, L, S.FIXED_RING, prec)
+    for key, value in tune:
+        eng.tune(key, value)
+    eng.set_params(-1, torch.from_numpy(synth.initial_model(1, eng.P, 0.2)).cuda())
+    b = _to_dev(_batches(shape, L, 0))
+    eng.step(b, 0.0)
+    Bd.adpsgd_set_profiling(eng.h, 1)
+    eng.step(b, 0.0)
+    launches = Bd.adpsgd_profile(eng.h)["softmax_ce"]["launches"]
+    eng.close()
+    return launches
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("tile,classes", [(15, 4), (15, 8), (15, 12), (0, 16), (15, 20), (0, 28), (15, 32), (15, 36), (0, 60), (15, 64), (14, 68), (14, 132), (-1, 516), (-1, 540), (-1, 544), (-1, 548)])
+def test_gradient_with_logits_in_memory(tile, classes, prec):
+    # The output layer's product stores the logits and the softmax reads them (a tile configuration that the caller sets means two launches; from 516
+    # classes x 72 on W_o is past one launch by itself).  Their rows are 4, 8, 16 or 32 elements and multiples of 32 apart, those of their gradient up to 64 (bf16): a few
+    # columns less, none, four more.
+    from paper_2110_11199_amd import binding as Bd
+    shape, tune = Shape(8, 16 if tile >= 0 else 72, 1, 0, 0, classes, 9, 3), [(Bd.TUNE_GEMM_TILE, tile)]
+    assert _softmax_launches(shape, 2, prec, tune) == 1
+    _check_gradient(shape, 2, prec, tune=tune)
+
+
 @pytest.mark.parametrize("hidden", [64, 100])
 @pytest.mark.parametrize("frames", [2, 3, 4, 6, 7, 8, 9])
 def test_gradient_with_inputs_requested_some_frames_ahead(hidden, frames):
