@@ -138,6 +138,16 @@ def test_gradient_with_logits_in_memory(tile, classes, prec):
     _check_gradient(shape, 2, prec, tune=tune)
 
 
+@pytest.mark.parametrize("prec,width,classes", [(1, 88, 128), (1, 104, 260), (1, 120, 256), (1, 88, 340), (1, 96, 340), (1, 768, 40), (1, 392, 20),
+                                                (0, 64, 128), (0, 72, 132), (0, 44, 260), (0, 52, 312), (0, 188, 20)])
+def test_gradient_with_the_output_layer_and_softmax_in_one_launch_over_more_chunks_than_are_in_flight(prec, width, classes):
+    # each number of waves and of class tiles to a wave, a contraction of three chunks and more (32 of k in bf16, 16 in fp32; two are in flight), some ending in part of
+    # one; fp32 up to 192 in one round of tiles
+    shape = Shape(8, 16, 1, 0, width, classes, 11, 3)
+    assert _softmax_launches(shape, 2, prec) == 0
+    _check_gradient(shape, 2, prec)
+
+
 @pytest.mark.parametrize("hidden", [64, 100])
 @pytest.mark.parametrize("frames", [2, 3, 4, 6, 7, 8, 9])
 def test_gradient_with_inputs_requested_some_frames_ahead(hidden, frames):
