@@ -377,6 +377,30 @@ def test_label_out_of_range_is_reported_not_repaired_silently():
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("classes", [20, 1500, 5000, 32772])
+def test_label_out_of_range_is_reported_by_every_kind_of_softmax(classes, prec):
+    # in one launch with the output layer, rows in registers of 256 and of 512 threads, and rows longer than those
+    import torch
+    from paper_2110_11199_amd import binding as Bd
+    print("bad label", classes, prec, flush=True)
+    shape = Shape(8, 32, 1, 0, 0, classes, 3, 2)
+    assert _softmax_launches(shape, 2, prec) == (0 if classes == 20 else 1)
+    for bad in (-1, classes, 1 << 30):
+        eng = _engine(shape, 2, S.FIXED_RING, prec)
+        eng.set_params(-1, torch.from_numpy(synth.initial_model(0, eng.P, 0.1)).cuda())
+        b = _batches(shape, 2, 0)
+        b[1][1].reshape(-1)[:] = classes - 1               # (the largest label is one)
+        eng.step(_to_dev(b), 0.1)
+        eng.status()
+        b[1][1][1, 2] = bad
+        eng.step(_to_dev(b), 0.1)
+        with pytest.raises(Bd.AdpsgdError) as ei:
+            eng.losses()
+        assert ei.value.code == Bd.EINVAL and "label" in str(ei.value)
+        eng.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 def test_delay_by_one_small_model(prec):
     print("d1d small", prec, flush=True)
     # weights U(-0.1, 0.1): with 12 frames per minibatch and weights of 0.3 the bf16 operand rounding
