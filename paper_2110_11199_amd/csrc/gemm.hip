@@ -152,10 +152,12 @@ int gemm_pick_tile(const GemmDesc& d, bool& dma) {
         if (v < 0) {
             const bool mfma = gemm_long_fp32(d);
             v = !dma ? 0 : tile_time(d, 64, 64, mfma ? 14.0 : 12.8, mfma ? 20.0 : 15.5) < tile_time(d, 128, 128, mfma ? 53.0 : 36.0, mfma ? 60.0 : 43.0) ? 15 : 14;
-            // Short contractions are bound by how a tile starts and by its stores.  Where rows of C are not whole 64 bytes the stores of 128x128 tiles take
-            // half as long again; elsewhere those tiles pay once there are a few rounds of them.  us, 128x128 on the bf16 matrix units / 64x64 on fp32
-            // MFMAs: 168x5000x40x12 25 / 19, 1344x3000x64x12 108 / 78, 2000x320x64x6 12.3 / 9.8, 512x1024x40x8 9.1 / 8.6; 1280x1280x80x6 16.3 / 20.4, 3360x1280x80x8
-            // 42 / 59, 672x2048x40x16 26 / 31; and up to 112 terms 128x128 / 64x64, both on the bf16 matrix units: 1344x3000x96x12 112 / 92, 168x5000x96x12 30 / 26.
+            // Short contractions are bound by how a tile starts and by its stores.  Where rows of C are not whole 64 bytes (widths of layers; rows of logits are) the
+            // stores of 128x128 tiles take half as long again: of 1051 products of 20 to 360 columns, K = 40 to 112, eight are more than 5 per cent slower in 64x64 tiles, by up to
+            // 1.5 us (2688x72x80x16 13.0 / 14.3; all 12250 / 8450).  Elsewhere 128x128 tiles pay once there are a few rounds of them.  us, 128x128 on the bf16 matrix units /
+            // 64x64, up to 80 terms on fp32 MFMAs: 168x5000x40x12 20 / 19, 1344x3000x64x12 55 / 81, x80 62 / 90, x96 69 / 92, 5120x200x80x8 17.6 / 23.1, 2000x320x64x6
+            // 12.3 / 9.8, 512x1024x40x8 9.1 / 8.6, 1280x1280x80x6 16.3 / 20.4, 3360x1280x80x8 42 / 59, 672x2048x40x16 26 / 31.  Against 64 bits, of the 2-norm at 64, 80, 96,
+            // 112 terms: 128x128 1.1, 1.25, 1.4, 1.5e-7; 64x64 1.4, 1.6, 0.96, 1.06e-7.  (Gradients of an iteration behind either are as far from it, to 1 per cent.)
             const bool whole = d.ldc % 16 == 0;
             if (dma && d.K <= 80) v = whole && 2.6 * (gemm_tiles(d, 128, 128) + 256) < gemm_tiles(d, 64, 64) + 256 ? 14 : 15;
             else if (dma && d.K <= 112 && !whole) v = 15;

@@ -11,8 +11,12 @@
 // 336x128x256x8 89 / 85, 2688x100x256x16 338 / 304, 336x500x64x8 66.2 / 62.4, 5120x500x64x16 382 / 323; and beyond fp32
 // 640x500x64x8 98.9 / 98.9, bf16 336x500x256x8 92.5 / 94.7, 1344x100x1024x8 490 / 495, 336x500x1024x8 256 / 279.  Few classes are few tiles, for two or one of
 // the waves, and a long row is a long chain, two chunks of it in flight: bf16 1344x32xKx8, K = 640 97.8 / 95.6, 768 99.5 / 98.9, 832 100.7 / 100.8, 896 102.2 / 103.4,
-// 1024 107.1 / 110.3; 1344x16x2048x8 147.5 / 161.7, 1344x4x8192x8 419 / 486, 2688x4x8192x16 1364 / 1583.  fp32 only where the
-// product would run on fp32 MFMAs anyway: a 16x16x4 one rounds a sum half as often as the 32x32x2 ones of the tiles.
+// 1024 107.1 / 110.3; 1344x16x2048x8 147.5 / 161.7, 1344x4x8192x8 419 / 486, 2688x4x8192x16 1364 / 1583.
+//
+// fp32: only contractions short enough for fp32 MFMAs in 64x64 tiles (gemm_plain_fp32), though two launches of the larger of these would multiply on the bf16 matrix
+// units (gemm.hip: rows of logits are whole lines).  A 16x16x4 MFMA rounds a sum half as often as the 32x32x2 ones of the tiles.  Gradients of an iteration against
+// 64 bits, two launches / one, 2-norm of b_o, W_o, b_p: 5120x200x80x8 1.42 / 1.42e-7, 1.27 / 1.27e-6, 1.42 / 1.43e-6, 5120x100x64x8 1.54 / 1.56e-7, 1.26 / 1.26e-6, 0.94 /
+// 0.95e-6, 5120x256x64x8 1.44 / 1.43e-7, 1.29 / 1.29e-6, 1.50 / 1.51e-6.
 #include <algorithm>
 #include "gemm_tile.hpp"
 #include "kernels.hpp"

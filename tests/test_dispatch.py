@@ -90,6 +90,19 @@ def test_fp32_tile_of_short_contractions(M, N, K, groups, want):
         assert pick(ctypes.byref(_gemm_desc(M, N, K, groups, a_kc=kc, b_kc=kc)), ctypes.byref(dma)) == want and dma.value
 
 
+@pytest.mark.parametrize("rows,states,K,learners,want", [
+    (168, 5000, 40, 12, 15), (336, 300, 64, 8, 15), (672, 1000, 64, 8, 15),                        # us, 128x128 / 64x64: 20 / 19; 9.4 / 5.4; 13.1 / 12.6
+    (1344, 3000, 64, 12, 14), (1344, 3000, 96, 12, 14), (5120, 200, 80, 8, 14),                    # 55 / 81, 69 / 92, 18 / 23
+])
+def test_fp32_tile_of_short_output_layers_whose_rows_of_logits_are_whole_lines(rows, states, K, learners, want):
+    dma = ctypes.c_bool()
+    pick = ctypes.CDLL(Bd.LIB_PATH)["_ZN6adpsgd14gemm_pick_tileERKNS_8GemmDescERb"]
+    g = _gemm_desc(rows, states, K, learners, a_kc=1, b_kc=1)
+    g.ldc = (states + 31) // 32 * 32
+    g.sCi = rows * g.ldc
+    assert pick(ctypes.byref(g), ctypes.byref(dma)) == want and dma.value
+
+
 @pytest.mark.parametrize("frames,before,want", [(2016, 1920, 1), (2688, 2560, 2), (2688, 2624, 1), (4200, 4000, 1)])
 def test_fp32_weight_gradients_of_a_layer_share_a_launch_whatever_their_length(frames, before, want):
     # (one that is long and one that is not run on kernels of either kind)
