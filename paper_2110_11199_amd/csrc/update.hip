@@ -715,11 +715,11 @@ int mean_learners_a_thread(int L, int64_t P, bool update_first, bool shadow) {
     // 5.8, x 500k 11.3 / 9.5, 12 x 500k 15.2 / 14.0, 16 x 270k 17.5 / 11.4, 32 x 500k 37.3 / 34.5), then one walk, which is the faster while all models fit the
     // memory-side cache (10 x 700k 15.1 / 17.2, 16 x 700k 24.4 / 25.7, 24 x 600k 33.8 / 36.1, 32 x 600k 44.3 / 49.0, 8 x 1M 16.6 / 18.6; four learners a thread lie between).
     // The line is later for few learners (4 x 700k 7.4 / 6.6, 6 x 700k 10.5 / 10.6, 8 x 600k 12.8 / 11.7, x 800k 14.7 / 14.6, x 900k 15.7 / 16.7) and where the bf16 copies are
-    // written too (iterations of a model, difference: 8 x 737k -2.2, 16 x 737k -2.6, x 818k -2.2, 24 x 818k -2.9, 32 x 737k -3.8, x 992k +0.5; in fp32 8 x 737k -3.3, 16 x 737k
+    // written too (iterations of a model, difference: 8 x 737k -2.2, 16 x 737k -2.6, x 818k -2.2, 24 x 818k -2.9, 32 x 737k -3.8, x 992k +0.5, 5 x 958k -3.2, 8 x 992k -0.3; in fp32 8 x 737k -3.3, 16 x 737k
     // +0.1, 32 x 587k +3.2, x 737k +4.2).  Up to 8M one walk: flat vectors 8 x 1.5M 23.2 / 26.1, 8 x 3M 47.5 /
     // 50.6; in iterations 8 x 2.5M 54.5 / 49.4, 8 x 3.8M 71.4 / 69.4.
     if (L < 4 || L > 32) return 0;
-    return P < ((L <= 8 || shadow) ? 13 << 16 : 1 << 19) ? 2 : 0;
+    return P < (L <= 8 && shadow ? 1 << 20 : L <= 8 || shadow ? 13 << 16 : 1 << 19) ? 2 : 0;
 }
 
 hipError_t launch_update(const UpdateDesc& d, hipStream_t s) {

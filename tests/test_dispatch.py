@@ -166,7 +166,7 @@ def test_output_layer_and_softmax_share_a_launch_where_w_o_is_small_and_its_rows
 @pytest.mark.parametrize("learners,params,copies,want", [
     (4, 350_000, False, 2), (8, 800_000, False, 2), (8, 900_000, False, 0), (12, 500_000, False, 2), (10, 700_000, False, 0), (16, 700_000, False, 0),
     (24, 600_000, False, 0), (32, 600_000, False, 0), (24, 1_000_000, False, 0),                   # flat vectors and fp32 models: one walk is the shorter from there
-    (16, 737_000, True, 2), (32, 737_000, True, 2), (16, 1_000_000, True, 0),                      # models with a bf16 copy: later
+    (16, 737_000, True, 2), (32, 737_000, True, 2), (16, 1_000_000, True, 0), (5, 958_000, True, 2), (8, 1_050_000, True, 0),      # models with a bf16 copy: later
     (33, 300_000, False, 0), (3, 300_000, False, 0), (12, 20_000, False, 2), (64, 100_000, False, 4), (4, 8_388_608, False, 2), (8, 3_000_000, False, 0),
 ])
 def test_delayed_mean_takes_two_learners_to_a_thread_where_that_is_the_shorter(learners, params, copies, want):
