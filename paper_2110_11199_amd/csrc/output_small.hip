@@ -6,12 +6,12 @@
 // logits stay in its accumulators: W_o is the first operand of the MFMAs, so that a lane holds four consecutive classes of one frame.  Maximum and sum
 // go over the lanes of a frame, then over the waves through LDS.
 //
-// What bounds it: reading W_o, 16 bytes of 16 rows to an access.  Taken where W_o is up to 64 KB and its rows up to 1536 bytes: us an iteration, two launches / one
-// (frames x classes x K x learners), fp32 80x100x64x4 67.0 / 63.5, 1280x100x64x16 146 / 126, 1280x256x64x8 126 / 118, 320x500x32x8 74.9 / 72.1, 5120x200x80x8 504 / 472; bf16
+// What bounds it: reading W_o, 16 bytes of 16 rows to an access.  Taken where W_o is up to 64 KB and its rows up to 1536 bytes, 2048 where every workgroup has a compute unit
+// to itself: us an iteration, two launches / one (frames x classes x K x learners), fp32 80x100x64x4 67.0 / 63.5, 1280x100x64x16 146 / 126, 1280x256x64x8 126 / 118, 320x500x32x8 74.9 / 72.1, 5120x200x80x8 504 / 472; bf16
 // 336x128x256x8 89 / 85, 2688x100x256x16 338 / 304, 336x500x64x8 66.2 / 62.4, 5120x500x64x16 382 / 323; and beyond fp32
 // 640x500x64x8 98.9 / 98.9, bf16 336x500x256x8 92.5 / 94.7, 1344x100x1024x8 490 / 495, 336x500x1024x8 256 / 279.  Few classes are few tiles, for two or one of
 // the waves, and a long row is a long chain, two chunks of it in flight: bf16 1344x32xKx8, K = 640 97.8 / 95.6, 768 99.5 / 98.9, 832 100.7 / 100.8, 896 102.2 / 103.4,
-// 1024 107.1 / 110.3; 1344x16x2048x8 147.5 / 161.7, 1344x4x8192x8 419 / 486, 2688x4x8192x16 1364 / 1583.
+// 1024 107.1 / 110.3; 336x32xKx8, 1024 64.9 / 64.0, 80x32xKx4, 1024 52.5 / 52.0; 80x16x2048x4 60.8 / 63.9, 1344x16x2048x8 147.5 / 161.7, 1344x4x8192x8 419 / 486, 2688x4x8192x16 1364 / 1583.
 //
 // fp32: only contractions short enough for fp32 MFMAs in 64x64 tiles (gemm_plain_fp32), though two launches of the larger of these would multiply on the bf16 matrix
 // units (gemm.hip: rows of logits are whole lines).  A 16x16x4 MFMA rounds a sum half as often as the 32x32x2 ones of the tiles.  Gradients of an iteration against
@@ -143,7 +143,8 @@ bool output_small_supported(const GemmDesc& g, const SoftmaxDesc& p) {
     if (g.sAi * esz % 16 != 0 || g.sBi * esz % 16 != 0 || p.sDi * esz % 16 != 0) return false;
     if ((int64_t)g.M * std::max(g.lda, p.ldd) * esz >= (int64_t)kOutOfRange || (int64_t)p.C * g.ldb * esz >= (int64_t)kOutOfRange) return false;     // buffer offsets
     if (!g.precision && !gemm_plain_fp32(g)) return false;
-    return g.K * esz <= 1536 && (int64_t)p.C * g.K * esz <= 65536;
+    if (g.K * esz > ((p.rows + 15) / 16 * p.L <= 256 ? 2048 : 1536)) return false;
+    return (int64_t)p.C * g.K * esz <= 65536;
 }
 
 hipError_t launch_output_small(const GemmDesc& g, const SoftmaxDesc& p, hipStream_t s) {

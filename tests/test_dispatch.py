@@ -148,12 +148,13 @@ def test_numbers_of_clusters_that_are_meant_to_exchange_through_memory_do(prec, 
     assert -(-clusters // one_xcd) > -(-clusters // anywhere)
 
 
-@pytest.mark.parametrize("precision,classes,width,want", [
-    (Bd.BF16_GEMM, 40, 768, True), (Bd.BF16_GEMM, 4, 768, True), (Bd.BF16_GEMM, 4, 776, False), (Bd.BF16_GEMM, 32, 1024, False), (Bd.BF16_GEMM, 16, 2048, False),
-    (Bd.BF16_GEMM, 4, 8192, False), (Bd.BF16_GEMM, 500, 64, True), (Bd.BF16_GEMM, 512, 72, False), (Bd.FP32, 200, 80, True), (Bd.FP32, 208, 80, False),
+@pytest.mark.parametrize("precision,rows,classes,width,want", [
+    (Bd.BF16_GEMM, 4096, 40, 768, True), (Bd.BF16_GEMM, 2049, 4, 768, True), (Bd.BF16_GEMM, 2049, 4, 776, False), (Bd.BF16_GEMM, 2048, 4, 776, True),      # 258 workgroups, 256
+    (Bd.BF16_GEMM, 2048, 32, 1024, True), (Bd.BF16_GEMM, 80, 4, 1032, False), (Bd.BF16_GEMM, 2049, 32, 1024, False), (Bd.BF16_GEMM, 80, 16, 2048, False),
+    (Bd.BF16_GEMM, 336, 4, 8192, False), (Bd.BF16_GEMM, 336, 500, 64, True), (Bd.BF16_GEMM, 336, 512, 72, False), (Bd.FP32, 336, 200, 80, True), (Bd.FP32, 336, 208, 80, False),
 ])
-def test_output_layer_and_softmax_share_a_launch_where_w_o_is_small_and_its_rows_are_short(precision, classes, width, want):
-    rows, learners = 336, 2
+def test_output_layer_and_softmax_share_a_launch_where_w_o_is_small_and_its_rows_are_short(precision, rows, classes, width, want):
+    learners = 2
     ldd = (classes + 63) // 64 * 64
     g = _gemm_desc(rows, classes, width, learners, a_kc=1, b_kc=1, precision=precision)
     g.bias = 64
