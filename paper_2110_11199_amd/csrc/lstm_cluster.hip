@@ -2,8 +2,8 @@
 // hidden sizes above what one compute unit holds (lstm_resident.hip).
 //
 // Frame by frame such a layer costs a launch, W_h from the caches and a latency-bound product per frame: 8-20 us, of which the
-// products are 1-4; here 2.9-4 where all clusters run at once (both sides at the rule below).  Iterations: fp32 8 x 2 x 256 cells 1556 -> 789 us,
-// 6 x 320 2709 -> 1196, bf16 5 x 2 x 360 1316 -> 699.  What is left of a frame: the exchange (0.5-1 us), products of one wave per SIMD, the cells.
+// products are 1-4; here 2.9-4 where all clusters run at once (both sides at the rule below).  Iterations: fp32 8 x 2 x 256 cells 1556 -> 771 us,
+// 6 x 320 2709 -> 1140, bf16 5 x 2 x 360 1316 -> 608.  What is left of a frame: the exchange (0.5-1 us), products of one wave per SIMD, the cells.
 //
 // Here a CLUSTER of S workgroups takes 16 batch rows of one (learner, direction) through all frames (batch rows do not depend
 // on each other: as many clusters as row blocks).  Workgroup m of a cluster owns U hidden units and holds their part of W_h as
@@ -965,7 +965,8 @@ __global__ __launch_bounds__(256, 1) void rec_backward_cluster_kernel(ClusterDes
     // The two ways of the exchange, the first frame and the last each have their own code: where branches meet the compiler waits for all that may be
     // outstanding on either, here inputs of the next frame on their way from memory and the flags just stored (us of a pass of 21 frames, one code for
     // all / this: bf16 16 x 2 x 512, batch 64 306 / 284, 10 x 2 x 360, 50 130 / 119, 32 x 2 x 256, 64 240 / 220, 8 x 2 x 640, 96 417 / 396; fp32 16 x 2 x 256, 32 73 / 69, 16 x 2 x
-    // 512, 16 305 / 278).  Inputs requested earlier, with the partial sums, delay those: 366, 156, 268.
+    // 512, 16 305 / 278).  At 640 cells in bf16 one fragment of W_h is in scratch.  Where it is loaded again behind a frame's barrier, the wait for it is one for the next
+    // frame's inputs: through memory still; on one XCD no more (8 x 2 x 640, 96 382 / 327).  Inputs requested earlier, with the partial sums, delay those: 366, 156, 268.
     auto frame = [&](int s, auto one_xcd_, auto first_, auto last_) {
         constexpr bool one_xcd = decltype(one_xcd_)::value, first = decltype(first_)::value, last = decltype(last_)::value;
         const uint32_t m = (uint32_t)(d == 0 ? Tn - 1 - s : s) * B;
